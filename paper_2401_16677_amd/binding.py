@@ -111,21 +111,31 @@ def problem(M, N, K, tp, rank, tile_m=0, tile_n=0, b_layout=T3_B_NK, lda=None, l
 
 
 def _dptr(t):
-    """Device (or NULL) pointer of a torch tensor / raw int / None."""
-    if t is None:
-        return None
-    if isinstance(t, int):
-        return ctypes.c_void_p(t)
-    return ctypes.c_void_p(t.data_ptr())
+    """Device (or NULL) address of a torch tensor / raw int / None, as the foreign call takes it."""
+    if t is None or isinstance(t, int):
+        return t
+    return t.data_ptr()
+
+
+# torch.cuda.current_stream() builds a Stream object through several layers of Python (4 of the
+# 7.5 us a small call spent on the host); the raw handle of the current device's current stream
+# is one C call.
+_raw_stream = None
 
 
 def _stream(stream):
+    global _raw_stream
     if stream is None:
-        import torch
-        return ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
+        if _raw_stream is None:
+            import torch
+            s = torch.cuda.current_stream().cuda_stream           # initialises the runtime if need be
+            get, dev = torch._C._cuda_getCurrentRawStream, torch._C._cuda_getDevice
+            _raw_stream = lambda: get(dev())                       # noqa: E731
+            return s
+        return _raw_stream()
     if isinstance(stream, int):
-        return ctypes.c_void_p(stream)
-    return ctypes.c_void_p(stream.cuda_stream)
+        return stream
+    return stream.cuda_stream
 
 
 # ------------------------------------------------------------------ host-only entry points
@@ -141,7 +151,7 @@ def t3_chunk_order(tp, rank):
 
 def t3_default_tile(p):
     tm, tn = ctypes.c_int32(), ctypes.c_int32()
-    _check(lib().t3_default_tile(ctypes.byref(p), ctypes.cast(ctypes.pointer(tm), ctypes.c_void_p),
+    _check(lib().t3_default_tile(p, ctypes.cast(ctypes.pointer(tm), ctypes.c_void_p),
                                  ctypes.cast(ctypes.pointer(tn), ctypes.c_void_p)),
            "t3_default_tile")
     return tm.value, tn.value
@@ -157,7 +167,7 @@ def t3_tiles_per_chunk(p):
 
 def t3_tile_of(p, t):
     out = [ctypes.c_int32() for _ in range(4)]
-    _check(lib().t3_tile_of(ctypes.byref(p), t,
+    _check(lib().t3_tile_of(p, t,
                             *[ctypes.cast(ctypes.pointer(o), ctypes.c_void_p) for o in out]),
            "t3_tile_of")
     return tuple(o.value for o in out)
@@ -174,18 +184,18 @@ def t3_track_reset(tp, track, stream=None):
 
 
 def t3_gemm_rs_fused(p, A, B, R, fwd, track, stream=None):
-    _check(lib().t3_gemm_rs_fused(ctypes.byref(p), _dptr(A), _dptr(B), _dptr(R), _dptr(fwd),
+    _check(lib().t3_gemm_rs_fused(p, _dptr(A), _dptr(B), _dptr(R), _dptr(fwd),
                                   _dptr(track), _stream(stream)), "t3_gemm_rs_fused")
 
 
 def t3_gemm_rs_fused_static(p, A, B, R, fwd, track_copy=None, stream=None):
-    _check(lib().t3_gemm_rs_fused_static(ctypes.byref(p), _dptr(A), _dptr(B), _dptr(R), _dptr(fwd),
+    _check(lib().t3_gemm_rs_fused_static(p, _dptr(A), _dptr(B), _dptr(R), _dptr(fwd),
                                          _dptr(track_copy), _stream(stream)),
            "t3_gemm_rs_fused_static")
 
 
 def t3_ag_step(p, step, upstream_R, R, ld_up=None, stream=None):
-    _check(lib().t3_ag_step(ctypes.byref(p), step, _dptr(upstream_R), p.ldr if ld_up is None else ld_up,
+    _check(lib().t3_ag_step(p, step, _dptr(upstream_R), p.ldr if ld_up is None else ld_up,
                             _dptr(R), _stream(stream)), "t3_ag_step")
 
 
@@ -198,22 +208,22 @@ def t3_timeline(stamps):
 
 
 def t3_gemm(p, A, B, C, stream=None):
-    _check(lib().t3_gemm(ctypes.byref(p), _dptr(A), _dptr(B), _dptr(C), _stream(stream)),
+    _check(lib().t3_gemm(p, _dptr(A), _dptr(B), _dptr(C), _stream(stream)),
            "t3_gemm")
 
 
 def t3_rs_reduce(p, C, R, fwd, track, stream=None):
-    _check(lib().t3_rs_reduce(ctypes.byref(p), _dptr(C), _dptr(R), _dptr(fwd), _dptr(track),
+    _check(lib().t3_rs_reduce(p, _dptr(C), _dptr(R), _dptr(fwd), _dptr(track),
                               _stream(stream)), "t3_rs_reduce")
 
 
 def t3_upstream_update(p, incoming, R, track, stream=None):
-    _check(lib().t3_upstream_update(ctypes.byref(p), _dptr(incoming), _dptr(R), _dptr(track),
+    _check(lib().t3_upstream_update(p, _dptr(incoming), _dptr(R), _dptr(track),
                                     _stream(stream)), "t3_upstream_update")
 
 
 def t3_release_chunks(p, R, fwd, track, stream=None):
-    _check(lib().t3_release_chunks(ctypes.byref(p), _dptr(R), _dptr(fwd), _dptr(track),
+    _check(lib().t3_release_chunks(p, _dptr(R), _dptr(fwd), _dptr(track),
                                    _stream(stream)), "t3_release_chunks")
 
 
