@@ -131,7 +131,10 @@ typedef struct {
  * M*ldr*4 and M*ldc*4 below 2^32 bytes (the kernels address R, C and a forward slot with
  * 32-bit byte offsets from a uniform base); fewer than 2^31 tiles.
  *
- * Launch shape.  In the direct release mode and for t3_gemm the tile kernel runs persistent
+ * Launch shape.  Over whole ring steps the tile kernel cuts a chunk into workgroup tiles as
+ * suits the device and the sizes (256 x 256 down to the smallest), whatever tile_m x tile_n, the
+ * tracked region, is; a tile range that cuts a step runs one workgroup tile per tracked tile.
+ * The tile kernel runs persistent
  * workgroups (as many as the device holds at once) that walk the grid positions in issue
  * order.  The first wave of workgroups starts in a few phase groups a few microseconds
  * apart, so that the compute units do not all reach their reduction traffic at the same
@@ -153,7 +156,9 @@ typedef struct {
  *
  * Tracker state (Sec. 4.2): one caller-owned device array of t3_track_words(tp) uint32
  * words, cleared once by t3_track_reset().  It holds two banks of 3*tp + 2 words
- *   [0, tp)        counter[c]  tiles of chunk c that have landed
+ *   [0, tp)        counter[c]  tiles of chunk c that have landed (once the chunk is complete;
+ *                              until then, where workgroup tiles are not tracked tiles, the
+ *                              workgroup tiles that have)
  *   [tp, 2tp)      ready[c]    1 once counter[c] == tpc
  *   [2tp, 3tp)     queue[i]    chunk ids in trigger order (forwarded chunks only, so at
  *                              most tp-1 entries are used); 0xFFFFFFFF = empty
@@ -161,8 +166,8 @@ typedef struct {
  *   [3tp+1]        done        workgroups of the launch that have finished
  * followed by two global words
  *   [6tp+4]        gen         launches completed since the reset
- *   [6tp+5]        error       0, or 1 if a release workgroup gave up waiting for a chunk
- *                              (cannot happen in a launch that ran to completion)
+ *   [6tp+5]        error       0, or 1 if the second half of a split tile gave up waiting for
+ *                              the first (cannot happen in a launch that ran to completion)
  * and by 256 words the kernels use between the two halves of a split tile (balanced tail,
  * above); they are 0 whenever no launch is running.
  * A launch of t3_gemm_rs_fused / t3_rs_reduce works in bank gen & 1; its last workgroup
@@ -181,9 +186,6 @@ typedef struct {
  * reserved before the entry is written and may run ahead of it.  (This is the ordering gfx950
  * gives agent-scope stores and atomics; it is not promised to other devices or to the host
  * before the launch has completed.)
- * A release workgroup that gives up waiting (see `error`) leaves its slot unfilled although
- * the call returned T3_OK: callers that use the default release mode check `error` (it stays 0
- * in any launch that runs to completion).
  */
 
 /* Ring order of `rank` and the chunk it keeps: order[s] = (rank + s) mod tp is the chunk produced
@@ -226,9 +228,10 @@ t3_status t3_track_reset(int32_t tp, uint32_t *track, void *stream);
  *   R    fp32 [M][ldr]      in: incoming partials.  out: incoming + C on every executed
  *                           tile; with T3_FLAG_FWD_DIRECT only the own chunk is updated
  *   fwd  fp32 [tp-1][M][W]  out, dense: slot s holds chunk order[s] = incoming + C.
- *                           Default: a slot is filled once its chunk is complete (copied
- *                           from R by release workgroups of the same launch, which wait on
- *                           the chunk's ready flag) and left untouched otherwise.  T3_FLAG_FWD_DIRECT: executed tiles
+ *                           Default: a chunk that the call completes is in its slot as well as
+ *                           in R when its ready flag is set (every tile is stored to both
+ *                           places); the slot of a chunk of which a tile range runs only some
+ *                           tiles is left untouched.  T3_FLAG_FWD_DIRECT: executed tiles
  *                           are written as they finish.  May be NULL if tp == 1.
  *                           With T3_FLAG_FWD_BF16 (here and in t3_rs_reduce / t3_release_chunks)
  *                           the same array holds bfloat16: [tp-1][M][W] of 2 bytes.

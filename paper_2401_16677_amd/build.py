@@ -1,16 +1,28 @@
 """Compile the HIP sources into paper_2401_16677_amd/libt3.so for gfx950 (in-tree)."""
 import os
 import subprocess
+from concurrent.futures import ThreadPoolExecutor
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libt3.so")
-SOURCES = ["t3_api.hip"]          # t3_kernels.hip is included by t3_api.hip
-DEPS = ["t3_api.hip", "t3_kernels.hip"]
+BUILD_DIR = os.path.join(HERE, "_build")
+# Translation units: (source, object, defines).  t3_gemm_launch.hip is compiled once per mode (0 plain
+# GEMM, 1 fused) and operand layout, so that the kernel instantiations compile in parallel.
+UNITS = [("t3_api.hip", "t3_api.o", [])] + [
+    ("t3_gemm_launch.hip", f"{fn}.o",
+     [f"-DT3_LAUNCHER={fn}", f"-DT3_MODE={mode}", f"-DT3_BKN={kn}", f"-DT3_AKM={km}"])
+    for fn, mode, kn, km in [
+        ("launch_fused", 1, 0, 0), ("launch_fused_kn", 1, 1, 0),
+        ("launch_fused_km", 1, 0, 1), ("launch_fused_km_kn", 1, 1, 1),
+        ("launch_gemm_nk", 0, 0, 0), ("launch_gemm_kn", 0, 1, 0),
+        ("launch_gemm_km", 0, 0, 1), ("launch_gemm_km_kn", 0, 1, 1)]]
+DEPS = ["t3_api.hip", "t3_gemm_launch.hip", "t3_device.h", "t3_gemm.h", "t3_aux.h", "t3_launch.h"]
+JOBS = 8
 
 HIPCC_FLAGS = [
-    "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared",
+    "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
     "-mllvm", "-pragma-unroll-threshold=1000000",
     "-Wall", "-Wno-unused-command-line-argument",
@@ -29,9 +41,17 @@ def build(force=True, extra_flags=()):
     if not force and up_to_date():
         return LIB
     hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
-    cmd = [hipcc, *HIPCC_FLAGS, *extra_flags, "-I", os.path.join(ROOT, "include"), "-I", CSRC,
-           "-o", LIB, *[os.path.join(CSRC, s) for s in SOURCES]]
-    subprocess.run(cmd, check=True)
+    os.makedirs(BUILD_DIR, exist_ok=True)
+    objects = [os.path.join(BUILD_DIR, obj) for _, obj, _ in UNITS]
+
+    def compile_unit(unit):
+        src, obj, defines = unit
+        subprocess.run([hipcc, *HIPCC_FLAGS, *extra_flags, *defines, "-I", os.path.join(ROOT, "include"), "-I", CSRC,
+                        "-c", os.path.join(CSRC, src), "-o", os.path.join(BUILD_DIR, obj)], check=True)
+
+    with ThreadPoolExecutor(JOBS) as pool:
+        list(pool.map(compile_unit, UNITS))
+    subprocess.run([hipcc, "--offload-arch=gfx950", "-shared", "-fPIC", "-o", LIB, *objects], check=True)
     return LIB
 
 

@@ -10,11 +10,16 @@
 #include <atomic>
 #include <mutex>
 
-#include "t3_kernels.hip"
+#include "t3_aux.h"
+#include "t3_launch.h"
+
+namespace t3k {
+thread_local int32_t last_hip_error = 0;
+}
 
 namespace {
 
-thread_local int32_t g_last_hip_error = 0;
+using t3k::launch;
 
 struct TileShape {
   int32_t m, n;
@@ -25,6 +30,7 @@ constexpr int kNumTileShapes = sizeof(kTileShapes) / sizeof(kTileShapes[0]);
 constexpr int kNumXcd = 8;            // the XCD grouping of decode_tile is written for 8 XCDs
 constexpr int kDefaultCus = 256;       // compute units of an MI355X (host-only plan queries assume it)
 constexpr int kMaxDevices = 64;
+constexpr int kReleaseAgents = 32;     // release workgroups per chunk (t3_release_chunks)
 constexpr int kNtMinK = 3072;          // K from which result stores take the streaming hint
 constexpr int64_t kMemorySideCacheBytes = 256ll << 20;
 constexpr int kTailMinSlabs = 8;       // K-slabs of 64 a tile needs before a balanced tail splits it
@@ -67,7 +73,7 @@ t3_status device_facts(DeviceFacts *out) {
     if (e == hipSuccess) *out = g_facts[dev];
   }
   if (e != hipSuccess) {
-    g_last_hip_error = (int32_t)e;
+    t3k::last_hip_error = (int32_t)e;
     return T3_ERR_HIP;
   }
   return T3_OK;
@@ -102,7 +108,7 @@ t3_status static_track(uint32_t **out) {
     if (e == hipSuccess) *out = g_scratch_ptr[dev];
   }
   if (e != hipSuccess) {
-    g_last_hip_error = (int32_t)e;
+    t3k::last_hip_error = (int32_t)e;
     return T3_ERR_HIP;
   }
   return T3_OK;
@@ -234,6 +240,41 @@ void default_tile(const t3_problem *p, int cus, int32_t *tm, int32_t *tn) {
   }
 }
 
+// The workgroup tile for `steps` whole ring steps of a problem: the shape with the least time by
+// rounds of workgroups x time of a tile.
+TileShape workgroup_tile(const t3_problem *p, int cus, int64_t steps) {
+  struct Cand {
+    TileShape t;
+    bool any_layout;
+    int per_cu;
+    double slab_us, ends_us;     // a K-slab of 64 / set-up and hand-over of one tile
+  };
+  static const Cand kCand[] = {{{256, 256}, true, 1, 1.20, 17.0},
+                               {{256, 192}, false, 1, 0.93, 13.0},
+                               {{256, 128}, true, 1, 0.84, 9.0},
+                               {{128, 128}, true, 2, 1.00, 9.0}};
+  const int64_t W = p->N / p->tp;
+  const bool nk = p->b_layout == T3_B_NK && p->a_layout == T3_A_MK;
+  const double slabs = (double)ceil_div(p->K, 64);
+  double best = -1.0;
+  TileShape pick = kCand[0].t;
+//@FORCE
+  for (const Cand &c : kCand) {
+    if (!c.any_layout && !nk) continue;
+    const int64_t T = ceil_div(p->M, c.t.m) * ceil_div(W, c.t.n) * steps, slots = (int64_t)cus * c.per_cu;
+    double rounds = (double)ceil_div(T, slots);
+    if (nk && T > slots && T % slots && 2 * (T % slots) <= slots) rounds -= 0.5;     // balanced tail
+    // (a compute unit with one 128 x 128 tile instead of two has it done in 0.6 of the time)
+    const double alone = c.per_cu == 2 && T <= cus ? 0.6 : 1.0;
+    const double us = rounds * alone * (c.ends_us + c.slab_us * slabs);
+    if (best < 0 || us < best * 0.999) {
+      best = us;
+      pick = c.t;
+    }
+  }
+  return pick;
+}
+
 t3_status resolve_tile(const t3_problem *p, int32_t *tm, int32_t *tn) {
   if (p->tile_m == 0 && p->tile_n == 0) {
     default_tile(p, kDefaultCus, tm, tn);
@@ -257,8 +298,8 @@ inline bool aligned16(const void *q) { return (reinterpret_cast<uintptr_t>(q) & 
 
 enum Need { kNeedAB = 1, kNeedR = 2, kNeedC = 4, kNeedFwd = 8, kNeedTrack = 16,
             kNeedTwoWriters = 32 /* the call exists only in two-writer mode */,
-            kMayPair = 64 /* the call launches the tile kernel, which can compute 256 x 256
-                             workgroup tiles under 128 x 256 tracked ones */ };
+            kTileKernel = 64 /* the call launches the tile kernel, whose workgroup tiles need not
+                                be the tracked ones */ };
 
 // The flag words of a balanced tail in tracker state: behind the two banks, gen and error.
 inline uint32_t *tail_flags_in(uint32_t *track, int32_t tp) { return track + 2 * (3 * (int64_t)tp + 2) + 2; }
@@ -332,29 +373,26 @@ t3_status make_plan(const t3_problem *p, int need, const void *A, const void *B,
 
   // tracked tiles (the problem's tile shape): what the issue order, the tile range and the
   // tracker's thresholds are counted in
-  const int64_t Mt_t = ceil_div(p->M, *tm), Wt = ceil_div(W, *tn);
-  const int64_t tpc_t = Mt_t * Wt, T_t = tpc_t * p->tp;
+  int64_t Wt = ceil_div(W, *tn);
+  const int64_t tpc_t = ceil_div(p->M, *tm) * Wt, T_t = tpc_t * p->tp;
   if (T_t >= (1ll << 31)) return T3_ERR_UNSUPPORTED;
   const int64_t limit_t = (p->tile_limit < 0 || p->tile_limit > T_t) ? T_t : p->tile_limit;
   const int64_t begin_t = p->tile_begin < 0 ? 0 : (p->tile_begin > limit_t ? limit_t : p->tile_begin);
-  // Workgroup tiles.  128 x 256 tracked tiles are computed two at a time, as one 256 x 256
-  // workgroup tile (tracked tiles 2 mi and 2 mi + 1 of a tile column are neighbours in the issue
-  // order): the larger tile needs a third less operand traffic per product.  Only for ranges of
-  // whole ring steps, so that no pair is cut by the range, and not with two writers.
-  int64_t pair_m = 1;
-  if ((need & kMayPair) && *tm == 128 && *tn == 256 && !two_writers && tpc_t > 0 && Mt_t > 1 &&
-      begin_t % tpc_t == 0 && limit_t % tpc_t == 0) {
-    pair_m = 2;
-    *tm = 256;
+  // Workgroup tiles.  Over whole ring steps nothing but the counters' final values depends on
+  // the tracked tile, so the tile kernel cuts a chunk as suits the chip; a range that cuts a
+  // step is in units of tracked tiles, and so are the two-writer calls' counts.
+  if ((need & kTileKernel) && !two_writers && tpc_t > 0 && begin_t % tpc_t == 0 && limit_t % tpc_t == 0) {
+    const TileShape w = workgroup_tile(p, kDefaultCus, (limit_t - begin_t) / tpc_t);
+    *tm = w.m;
+    *tn = w.n;
   }
-  const int64_t Mt = ceil_div(Mt_t, pair_m);
+  const int64_t Mt = ceil_div(p->M, *tm);
+  Wt = ceil_div(W, *tn);
   const int64_t tpc = Mt * Wt, T = tpc * p->tp;
   *empty = (T == 0);
 
-  // (the last refusals, before the device is asked anything: with release workgroups and with
-  // split-K the grid still has to fit 31 bits)
-  const int64_t n_agents = (fused_like && !direct && !two_writers && p->tp > 1) ? T3_AGENTS : 0;
-  if (T + n_agents * (p->tp - 1) >= (1ll << 31)) return T3_ERR_UNSUPPORTED;
+  // (the last refusals, before the device is asked anything: the grid has to fit 31 bits)
+  if (T >= (1ll << 31)) return T3_ERR_UNSUPPORTED;
   if (two_writers && T * split_k >= (1ll << 31)) return T3_ERR_UNSUPPORTED;
   if ((need & kNeedTwoWriters) && (need & kNeedC) && p->upstream_agents < 0) return T3_ERR_BAD_SHAPE;
 
@@ -375,8 +413,9 @@ t3_status make_plan(const t3_problem *p, int need, const void *A, const void *B,
   q.ldb = p->ldb;
   q.ldr = p->ldr;
   q.ldc = p->ldc;
-  q.limit = limit_t;
-  q.begin = begin_t;
+  // the range in workgroup tiles (where they are not the tracked ones it is whole steps)
+  q.limit = tpc == tpc_t ? limit_t : (tpc_t ? limit_t / tpc_t * tpc : 0);
+  q.begin = tpc == tpc_t ? begin_t : (tpc_t ? begin_t / tpc_t * tpc : 0);
   if (q.begin >= q.limit) *empty = true;       // an empty tile range: nothing to launch
   q.M = p->M;
   q.N = p->N;
@@ -388,9 +427,7 @@ t3_status make_plan(const t3_problem *p, int need, const void *A, const void *B,
   q.Mt = (int32_t)Mt;
   q.Wt = (int32_t)Wt;
   q.tpc = (int32_t)tpc;
-  q.pair_m = (int32_t)pair_m;
-  q.Mt_t = (int32_t)Mt_t;
-  q.tpc_t = (int32_t)tpc_t;
+  q.tracked = (int32_t)tpc_t;
   q.flags = fused_like ? p->flags : 0u;
 
   // XCD grouping: split a stage's Mt x Wt tiles into 8 equal blocks, one per XCD, choosing the
@@ -411,15 +448,9 @@ t3_status make_plan(const t3_problem *p, int need, const void *A, const void *B,
     }
   }
 
-  // Release workgroups (default release mode only): `agents` per forwarded chunk, placed in
-  // the grid `lag` stages after the chunk's own tiles, far enough that those tiles have been
-  // dispatched and are mostly finished when the release workgroups start.
-  q.agents = (int32_t)n_agents;
+  q.agents = q.rows_per_agent = 0;
   // tile workgroups the device holds at once: one per compute unit, two of the smallest tile
   const int64_t resident = (int64_t)dev.cus * ((*tm == 128 && *tn == 128) ? 2 : 1);
-  q.lag = (int32_t)(ceil_div(resident, tpc > 0 ? tpc : 1) + 1);
-  if (q.lag > p->tp) q.lag = p->tp;
-  q.rows_per_agent = q.agents ? (int32_t)ceil_div(p->M, q.agents) : 0;
   // Start-up phase offsets (see stagger_start): four groups over a 12 us window, or half an
   // estimated tile time if that is shorter, once there are tiles enough to fill the chip.
   // The environment variable T3_STAGGER="groups,window_ns" overrides this ("0" turns it off).
@@ -429,7 +460,7 @@ t3_status make_plan(const t3_problem *p, int need, const void *A, const void *B,
     double window_ns = 12000.0;
     const double tile_ns = 2.0 * *tm * *tn * (double)p->K / kCuFlopPerNs;
     if (window_ns > tile_ns / 2) window_ns = tile_ns / 2;
-    if (T < resident) g = 0;
+    if (T < resident) g = 0;         // (T of the whole order: a range's launch is short of phases anyway)
     const StaggerEnv &env = stagger_env();
     if (env.set) {
       g = env.off ? 0 : env.groups;
@@ -441,15 +472,10 @@ t3_status make_plan(const t3_problem *p, int need, const void *A, const void *B,
       q.stagger_blocks = (int32_t)resident;
     }
   }
-  // workgroups that will do work: the tiles below the limit and the release workgroups of the
-  // forwarded chunks those tiles complete
-  // chunks all of whose tiles lie in [begin, limit); the forwarded ones among them get released
-  int64_t released = 0;
-  for (int64_t s = 0; s + 1 < p->tp; ++s)
-    if (s * tpc_t >= q.begin && (s + 1) * tpc_t <= q.limit && tpc_t > 0) ++released;
-  // (paired tiles: the range is whole ring steps, tpc workgroup tiles each)
-  const int64_t wg_tiles = pair_m > 1 ? (q.limit - q.begin) / tpc_t * tpc : q.limit - q.begin;
-  q.expected_done = (int32_t)(wg_tiles + q.agents * released);
+  q.expected_done = (int32_t)(q.limit - q.begin);
+  // the grid spans the ring steps the range touches
+  q.stage0 = tpc > 0 ? (int32_t)(q.begin / tpc) : 0;
+  q.total_blocks = tpc > 0 && q.begin < q.limit ? (int32_t)((ceil_div(q.limit, tpc) - q.stage0) * tpc) : 0;
   // updates expected per element (Sec. 4.2.1): with two writers the launches of both count in
   // one bank, which closes when the tiles of both have been counted
   q.upd_first = q.upd_rest = 1;
@@ -464,14 +490,12 @@ t3_status make_plan(const t3_problem *p, int need, const void *A, const void *B,
   }
   // K walks start at a different slab on every XCD (see the kernels' `koff`)
   q.k_groups = dev.xcds > 1 ? dev.xcds : 0;
-  q.total_blocks = (int32_t)(T + (int64_t)q.agents * (p->tp - 1));
   q.resident = (int32_t)resident;
   // Results leave the XCD's L2 at once (streaming hint) where that L2 is better spent on slabs
   // of A and B: long K loops, or an output that the memory-side cache cannot hold anyway.
   // Measured: -3 % on gpt3_fc2 and hightp_outproj, -1 % on wide_fc2, but +6 % on gpt3_outproj
-  // (short K loop, output within the memory-side cache), so not there; and not when release
-  // workgroups read R back.
-  q.nt_out = (q.agents == 0 && !two_writers &&
+  // (short K loop, output within the memory-side cache), so not there.
+  q.nt_out = (!two_writers &&
               (p->K >= kNtMinK || 4ll * p->M * p->N > kMemorySideCacheBytes)) ? 1 : 0;
   q.timeline = g_timeline.load();
   {
@@ -484,92 +508,32 @@ t3_status make_plan(const t3_problem *p, int need, const void *A, const void *B,
   // through bfloat16 forward slots), each element with one writer at a time.
   q.tail_r = q.tail_q = 0;
   q.tail_flags = nullptr;
-  const bool persistent = (need & kMayPair) && q.agents == 0 && !two_writers;
+  // Ring steps in a range are as good as the whole order, a cut range is not (its positions are
+  // not all tiles).
   const bool bf16_direct = direct && (p->flags & T3_FLAG_FWD_BF16);
   const bool default_layouts = p->b_layout == T3_B_NK && p->a_layout == T3_A_MK;
-  const bool tail_kernel = !(*tm == 128 && *tn == 256);   // (128 x 256 tiles that are not paired: none)
-  if (persistent && !bf16_direct && default_layouts && tail_kernel && T > resident && q.begin == 0 &&
-      q.limit == T_t && p->K / 64 >= kTailMinSlabs) {
-    const int64_t r = T % resident;
+  const bool tail_kernel = !(*tm == 128 && *tn == 256);   // (128 x 256 tiles serve cut ranges only)
+  if ((need & kTileKernel) && !two_writers && !bf16_direct && default_layouts && tail_kernel &&
+      q.total_blocks > resident && q.limit - q.begin == q.total_blocks && p->K / 64 >= kTailMinSlabs) {
+    const int64_t r = q.total_blocks % resident;
     if (r > 0 && 2 * r <= resident && r <= t3k::kTailSlots) {
       q.tail_r = (int32_t)r;
-      q.tail_q = (int32_t)(T / resident);
+      q.tail_q = (int32_t)(q.total_blocks / resident);
       if (track) q.tail_flags = tail_flags_in(track, p->tp);   // (t3_gemm brings its own)
     }
   }
   return T3_OK;
 }
 
-// Launches `kernel` and returns what THIS launch returned: an error some earlier call left in
-// the runtime is not taken for ours.
-template <typename... KArgs>
-t3_status launch(void (*kernel)(KArgs...), dim3 grid, dim3 block, hipStream_t s, KArgs... a) {
-  void *args[] = {static_cast<void *>(&a)...};
-  const hipError_t e = hipLaunchKernel(reinterpret_cast<const void *>(kernel), grid, block, args, 0, s);
-  if (e != hipSuccess) {
-    g_last_hip_error = (int32_t)e;
-    return T3_ERR_HIP;
-  }
-  return T3_OK;
-}
-
 inline unsigned grid_size(const t3k::Plan &q) { return (unsigned)q.total_blocks; }
 
-template <int MODE, int BKN, int AKM>
-t3_status launch_gemm_layout(const t3k::Plan &q, int32_t tm, int32_t tn, hipStream_t s) {
-  // Persistent workgroups: as many as the chip holds at once, each walking the grid positions.
-  // With release work in the grid (default release mode) every position gets a workgroup of
-  // its own instead: a release position may have to wait for its chunk, and a persistent
-  // workgroup would sit on its later tiles meanwhile.
-  const bool persistent = q.agents == 0;
-  const int64_t positions = (int64_t)q.total_blocks * (MODE == t3k::kModeFused ? q.split_k : 1);
-  const dim3 grid((unsigned)(persistent && positions > q.resident ? q.resident : positions));
-  // A balanced tail (make_plan decides; operands in their default layouts only) takes the
-  // kernels' TAIL variants.  The 256 x 256 one of the plain GEMM is cut from the fused kernel
-  // (TAIL = 2).
-  if constexpr (!BKN && !AKM) {
-    if (q.tail_r) {
-      if (tm == 256 && tn == 256) {
-        if (MODE == t3k::kModeGemm) {
-          t3k::Plan g = q;
-          g.flags = 0;
-          g.ldr = q.ldc;                  // (R already is the output pointer)
-          return launch(t3k::gemm_tile_kernel<256, 256, 2, 2, 2, t3k::kModeFused, 0, 0, 2>, grid, dim3(256), s, g);
-        }
-        return launch(t3k::gemm_tile_kernel<256, 256, 2, 2, 2, t3k::kModeFused, 0, 0, 1>, grid, dim3(256), s, q);
-      }
-      if (tm == 256 && tn == 128)
-        return launch(t3k::gemm_tile_kernel<256, 128, 4, 2, 3, MODE, 0, 0, 1>, grid, dim3(512), s, q);
-      if (tm == 128 && tn == 128)
-        return launch(t3k::gemm_tile_kernel<128, 128, 2, 2, 2, MODE, 0, 0, 1>, grid, dim3(256), s, q);
-    }
-  }
-  // K-slabs of 64 everywhere.  256 x 256: 4 wavefronts of 128 x 128 (or 8 of 128 x 64), two 64-KiB stages; the
-  // 256 x 128 and 128 x 256 tiles: 8 wavefronts of 64 x 64, three 48-KiB stages; one workgroup
-  // per compute unit.  128 x 128: 4 wavefronts of 64 x 64, two 32-KiB stages, two workgroups.
-  if (tm == 256 && tn == 256) {
-    // B stored N x K: four wavefronts of 128 x 128 with the hand-ordered main loop, which adds the
-    // incoming partial on the way out.  It has no two-writer epilogue and does not write
-    // bfloat16 forward slots itself: those, and B stored K x N, take the eight-wavefront kernel.
-    const bool eight = BKN || AKM || (MODE == t3k::kModeFused &&
-                               ((q.flags & t3k::kFlagTwoWriters) ||
-                                ((q.flags & t3k::kFlagFwdDirect) && (q.flags & t3k::kFlagFwdBf16))));
-    if constexpr (!BKN && !AKM) {
-      if (!eight) return launch(t3k::gemm_tile_kernel<256, 256, 2, 2, 2, MODE, 0>, grid, dim3(256), s, q);
-    }
-    return launch(t3k::gemm_tile_kernel<256, 256, 2, 4, 2, MODE, BKN, AKM>, grid, dim3(512), s, q);
-  }
-  if (tm == 256 && tn == 128)
-    return launch(t3k::gemm_tile_kernel<256, 128, 4, 2, 3, MODE, BKN, AKM>, grid, dim3(512), s, q);
-  if (tm == 128 && tn == 256)
-    return launch(t3k::gemm_tile_kernel<128, 256, 2, 4, 3, MODE, BKN, AKM>, grid, dim3(512), s, q);
-  return launch(t3k::gemm_tile_kernel<128, 128, 2, 2, 2, MODE, BKN, AKM>, grid, dim3(256), s, q);
-}
-
-template <int MODE>
-t3_status launch_gemm(const t3k::Plan &q, int32_t tm, int32_t tn, bool b_kn, bool a_km, hipStream_t s) {
-  if (a_km) return b_kn ? launch_gemm_layout<MODE, 1, 1>(q, tm, tn, s) : launch_gemm_layout<MODE, 0, 1>(q, tm, tn, s);
-  return b_kn ? launch_gemm_layout<MODE, 1, 0>(q, tm, tn, s) : launch_gemm_layout<MODE, 0, 0>(q, tm, tn, s);
+t3_status launch_gemm(int mode, const t3k::Plan &q, int32_t tm, int32_t tn, bool b_kn, bool a_km, hipStream_t s) {
+  using namespace t3k;
+  if (mode == kModeFused)
+    return a_km ? (b_kn ? launch_fused_km_kn(q, tm, tn, s) : launch_fused_km(q, tm, tn, s))
+                : (b_kn ? launch_fused_kn(q, tm, tn, s) : launch_fused(q, tm, tn, s));
+  return a_km ? (b_kn ? launch_gemm_km_kn(q, tm, tn, s) : launch_gemm_km(q, tm, tn, s))
+              : (b_kn ? launch_gemm_kn(q, tm, tn, s) : launch_gemm_nk(q, tm, tn, s));
 }
 
 }  // namespace
@@ -589,7 +553,7 @@ const char *t3_status_string(t3_status s) {
   return "unknown status";
 }
 
-int32_t t3_last_hip_error(void) { return g_last_hip_error; }
+int32_t t3_last_hip_error(void) { return t3k::last_hip_error; }
 
 t3_status t3_chunk_order(int32_t tp, int32_t rank, int32_t *order, int32_t *own) {
   if (!order || !own) return T3_ERR_NULL;
@@ -650,11 +614,11 @@ t3_status t3_gemm_rs_fused(const t3_problem *p, const void *A, const void *B, fl
   t3k::Plan q;
   int32_t tm, tn;
   bool empty = false;
-  const t3_status st = make_plan(p, kNeedAB | kNeedR | kNeedFwd | kNeedTrack | kMayPair, A, B, nullptr, R,
+  const t3_status st = make_plan(p, kNeedAB | kNeedR | kNeedFwd | kNeedTrack | kTileKernel, A, B, nullptr, R,
                                  fwd, track, &q, &tm, &tn, &empty);
   if (st != T3_OK) return st;
   if (empty) return T3_OK;
-  return launch_gemm<t3k::kModeFused>(q, tm, tn, p->b_layout == T3_B_KN, p->a_layout == T3_A_KM,
+  return launch_gemm(t3k::kModeFused, q, tm, tn, p->b_layout == T3_B_KN, p->a_layout == T3_A_KM,
                                       static_cast<hipStream_t>(stream));
 }
 
@@ -668,7 +632,7 @@ t3_status t3_gemm_rs_fused_static(const t3_problem *p, const void *A, const void
   int32_t tm, tn;
   bool empty = false;
   uint32_t stand_in = 0;
-  t3_status st = make_plan(p, kNeedAB | kNeedR | kNeedFwd | kNeedTrack | kMayPair, A, B, nullptr, R, fwd,
+  t3_status st = make_plan(p, kNeedAB | kNeedR | kNeedFwd | kNeedTrack | kTileKernel, A, B, nullptr, R, fwd,
                            &stand_in, &q, &tm, &tn, &empty);
   if (st != T3_OK) return st;
   uint32_t *track = nullptr;
@@ -681,7 +645,7 @@ t3_status t3_gemm_rs_fused_static(const t3_problem *p, const void *A, const void
   st = launch(t3k::track_reset_kernel, dim3(1), dim3(256), s, track, (int)p->tp);
   if (st != T3_OK) return st;
   if (!empty) {
-    st = launch_gemm<t3k::kModeFused>(q, tm, tn, p->b_layout == T3_B_KN, p->a_layout == T3_A_KM, s);
+    st = launch_gemm(t3k::kModeFused, q, tm, tn, p->b_layout == T3_B_KN, p->a_layout == T3_A_KM, s);
     if (st != T3_OK) return st;
   }
   if (track_copy)
@@ -695,14 +659,14 @@ t3_status t3_gemm(const t3_problem *p, const void *A, const void *B, float *C, v
   t3k::Plan q;
   int32_t tm, tn;
   bool empty = false;
-  const t3_status st = make_plan(p, kNeedAB | kNeedC | kMayPair, A, B, C, nullptr, nullptr, nullptr, &q,
+  const t3_status st = make_plan(p, kNeedAB | kNeedC | kTileKernel, A, B, C, nullptr, nullptr, nullptr, &q,
                                  &tm, &tn, &empty);
   if (st != T3_OK) return st;
   if (empty) return T3_OK;
   q.R = C;   // the GEMM kernel's output pointer, addressed with ldc
   hipStream_t s = static_cast<hipStream_t>(stream);
   const bool b_kn = p->b_layout == T3_B_KN, a_km = p->a_layout == T3_A_KM;
-  auto go = [&](const t3k::Plan &plan) { return launch_gemm<t3k::kModeGemm>(plan, tm, tn, b_kn, a_km, s); };
+  auto go = [&](const t3k::Plan &plan) { return launch_gemm(t3k::kModeGemm, plan, tm, tn, b_kn, a_km, s); };
   return q.tail_r ? launch_with_gemm_tail(q, s, go) : go(q);
 }
 
@@ -759,7 +723,7 @@ t3_status t3_release_chunks(const t3_problem *p, const float *R, void *fwd,
                                  const_cast<uint32_t *>(track), &q, &tm, &tn, &empty);
   if (st != T3_OK) return st;
   if (p->tp < 2 || p->M == 0 || p->N == 0) return T3_OK;
-  q.agents = T3_AGENTS;
+  q.agents = kReleaseAgents;
   q.rows_per_agent = (int32_t)ceil_div(p->M, q.agents);
   return launch(t3k::release_ready_kernel, dim3((unsigned)(q.agents * (p->tp - 1))),
                 dim3(t3k::kThreads), static_cast<hipStream_t>(stream), q);

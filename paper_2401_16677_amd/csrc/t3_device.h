@@ -1,0 +1,371 @@
+// What every kernel of the library shares: the launch plan, the walk over tiles, the tracker
+// (track & trigger, Sec. 4.2 of the T3 paper) and the memory accesses with a cache policy.
+#pragma once
+
+#include <hip/hip_runtime.h>
+#include <stdint.h>
+
+#include <type_traits>
+
+#ifndef T3_MH
+#define T3_MH 2            // row passes per MFMA k-step of a 128-row wavefront tile (2 or 4)
+#endif
+
+namespace t3k {
+
+typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
+typedef __attribute__((ext_vector_type(16))) float f32x16;
+typedef __attribute__((ext_vector_type(4))) float f32x4;
+typedef __attribute__((address_space(3))) void *lds_void_ptr;
+typedef const __attribute__((address_space(1))) void *global_void_ptr;
+
+constexpr int kThreads = 256;
+constexpr uint32_t kEmpty = 0xFFFFFFFFu;
+constexpr int kSpinLimit = 1 << 22;   // polls of a release workgroup before it gives up
+constexpr int kTimelineItems = 16;     // pieces of work per workgroup a timeline records
+constexpr int kTailSlots = 256;       // tiles a balanced tail can split (flag words behind the tracker state)
+
+constexpr uint32_t kFlagStep0StoreOnly = 1u;
+constexpr uint32_t kFlagFwdDirect = 2u;
+constexpr uint32_t kFlagTwoWriters = 4u;
+constexpr uint32_t kFlagFwdBf16 = 8u;
+
+enum Mode { kModeGemm = 0, kModeFused = 1 };
+
+// s_waitcnt immediates (gfx9 encoding: vmcnt[3:0] | expcnt << 4 | lgkmcnt << 8 | vmcnt[5:4] << 14)
+constexpr int kWaitVm0 = 0x0F70;
+constexpr int kWaitLgkm0 = 0xF0FF;    // and-mask that turns a wait into "... and lgkmcnt(0)"
+constexpr int kWaitAll = 0;
+__host__ __device__ constexpr int wait_vm(int n) { return 0x0F70 | (n & 15) | ((n >> 4) << 14); }
+
+// Everything a kernel needs, passed by value.
+struct Plan {
+  const uint16_t *A;
+  const uint16_t *B;
+  const float *C;    // reduce kernel input
+  float *R;          // fused / reduce: incoming in, sums out.  gemm: the C output
+  float *fwd;
+  uint32_t *track;
+  int64_t lda, ldb, ldr, ldc;
+  int64_t limit;     // tiles with issue index >= limit do nothing
+  int64_t begin;     // nor do tiles with issue index < begin
+  int32_t M, N, K, P, rank, W, own;
+  // The grid of WORKGROUP tiles: rows, columns, tiles per chunk.  `begin` and `limit` are counted
+  // in these.  Where the launch covers whole ring steps they are cut as suits the chip, whatever
+  // the tracked tile of the problem; tracked = the tracked tiles of a chunk, which is what its
+  // counter holds once it is complete.
+  int32_t Mt, Wt, tpc, tracked;
+  int32_t xcd_nbm, xcd_bmk, xcd_bnk;   // XCD grouping of a stage's tiles; xcd_nbm == 0: none
+  int32_t agents, rows_per_agent;      // release_ready_kernel: workgroups per chunk, rows of each
+  int32_t expected_done;               // grid positions of this launch that do work
+  int32_t stage0, total_blocks;        // first ring step of the range, grid positions (tiles) from there
+  int32_t resident;                    // tile workgroups the chip holds at once
+  int32_t upd_first, upd_rest;         // updates expected per element of chunk order[0] / the others
+  int32_t split_k;                     // >= 1: workgroups that share a tile, each taking a part of K (Sec. 7.7)
+  int32_t stagger_blocks, stagger_groups, stagger_ticks;   // start-up phase offsets (see stagger_start)
+  int32_t k_groups;                    // > 1: workgroup w starts its K loop (w % k_groups) / k_groups of the way in
+  int32_t nt_out;                      // results leave with the streaming hint (hand-ordered kernel)
+  // Timeline (a profiling aid, normally null): workgroup w < timeline_wgs writes, for its i-th
+  // piece of work, i < kTimelineItems, four wall-clock readings (100 MHz) at
+  // timeline[(w * kTimelineItems + i) * 4 + ...]: piece taken; accumulators set up (the
+  // incoming partial in place); main loop done; results handed to the memory system.
+  uint64_t *timeline;
+  int32_t timeline_wgs;
+  // Balanced tail (persistent launches): the last tail_r grid positions, which would keep only
+  // tail_r of the workgroups busy for a whole tile time, are each split into two halves of K
+  // (see work_item).  0: off.  tail_q = full rounds of the grid before them; tail_flags = one
+  // word per split tile, 0 between launches.
+  int32_t tail_r, tail_q;
+  uint32_t *tail_flags;
+  uint32_t flags;
+};
+
+struct Tile {
+  int s, c, mi, nj;
+};
+
+// Tracker state (uint32 words): two banks of { counter[P] ready[P] queue[P] queue_len done },
+// then the globals { gen, error }.  A launch works in bank gen & 1; the last workgroup of the
+// launch to finish clears the other bank and increments gen, so the next launch starts from a
+// clean bank without a reset kernel in between, and the caller finds the results of the launch
+// that just ended in bank (gen - 1) & 1.
+__device__ inline int trk_bank_words(int P) { return 3 * P + 2; }
+struct Trk {
+  uint32_t *counter, *ready, *queue, *queue_len, *done;   // this launch's bank
+  uint32_t *other;                                         // the bank to clear at the end
+  uint32_t *gen, *error;
+};
+__device__ inline Trk trk_open(const Plan &p) {
+  Trk t;
+  t.gen = p.track + 2 * trk_bank_words(p.P);
+  t.error = t.gen + 1;
+  // (the same in every lane: made uniform so that the bank pointers live in scalar registers)
+  const uint32_t g = __builtin_amdgcn_readfirstlane(
+      __hip_atomic_load(t.gen, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+  uint32_t *b = p.track + (g & 1u) * trk_bank_words(p.P);
+  t.counter = b;
+  t.ready = b + p.P;
+  t.queue = b + 2 * p.P;
+  t.queue_len = b + 3 * p.P;
+  t.done = b + 3 * p.P + 1;
+  t.other = p.track + ((g & 1u) ^ 1u) * trk_bank_words(p.P);
+  return t;
+}
+__device__ inline void trk_clear_bank(uint32_t *b, int P) {
+  for (int i = 0; i < 3 * P + 2; ++i)
+    __hip_atomic_store(&b[i], (i >= 2 * P && i < 3 * P) ? kEmpty : 0u, __ATOMIC_RELAXED,
+                       __HIP_MEMORY_SCOPE_AGENT);
+}
+// Called by thread 0 of every workgroup that did work, as its last act; d = the value its
+// increment of `done` returned.
+__device__ inline void trk_close_if_last(const Plan &p, const Trk &t, uint32_t d) {
+  if (d + 1u == (uint32_t)p.expected_done) {
+    trk_clear_bank(t.other, p.P);
+    __hip_atomic_fetch_add(t.gen, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  }
+}
+__device__ inline void trk_workgroup_done(const Plan &p, const Trk &t) {
+  trk_close_if_last(
+      p, t, __hip_atomic_fetch_add(t.done, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+}
+
+// Index j of a tile inside its stage -> tile.  Workgroups are dealt round-robin to the 8 XCDs,
+// so workgroup j of a stage lands on XCD j % 8; that XCD gets a compact block of
+// xcd_bmk x xcd_bnk tiles which share A rows and B columns in its L2.
+__device__ inline bool decode_tile(const Plan &p, int s, int j, Tile &tl) {
+  int mi, nj;
+  if (p.xcd_nbm) {
+    const int x = j & 7, i = j >> 3;
+    const int bxm = x % p.xcd_nbm, bxn = x / p.xcd_nbm;
+    mi = bxm * p.xcd_bmk + i % p.xcd_bmk;
+    nj = bxn * p.xcd_bnk + i / p.xcd_bmk;
+  } else {
+    mi = j % p.Mt;
+    nj = j / p.Mt;
+  }
+  const int64_t t = (int64_t)s * p.tpc + (int64_t)nj * p.Mt + mi;   // issue index
+  int c = p.rank + s;
+  if (c >= p.P) c -= p.P;
+  tl.s = s;
+  tl.c = c;
+  tl.mi = mi;
+  tl.nj = nj;
+  return t >= p.begin && t < p.limit;
+}
+
+// Grid layout: the tiles of the range's stages in order.  False: a position outside the tile range.
+__device__ inline bool decode_block(const Plan &p, int b, Tile &tl) {
+  const int s = b / p.tpc;
+  return decode_tile(p, p.stage0 + s, b - s * p.tpc, tl);
+}
+// Whether this launch produces all of stage s's chunk: only then does the chunk get released.
+__device__ inline bool chunk_is_whole(const Plan &p, int s) {
+  return (int64_t)s * p.tpc >= p.begin && (int64_t)(s + 1) * p.tpc <= p.limit;
+}
+
+// The it-th piece of work of a persistent workgroup: grid position `blk`, part `part` of
+// `nparts` parts of K.  Without a balanced tail, workgroup w of G takes positions w, w + G, ...
+// (split-K: `split_k` consecutive positions share a tile).
+//
+// Balanced tail.  With T = q G + r positions, 0 < r <= G / 2, the last round would run r tiles on
+// r workgroups while the others idle.  Instead each of those r tiles is cut into two halves of
+// K.  Half the workgroups are "early": early workgroup number i < r computes the first half of
+// tile q G + i BEFORE its q whole tiles, starting from the incoming partial as any tile does,
+// and stores the partial sums where the tile's result belongs.  The others are "late": late
+// workgroup number i < r computes the second half AFTER its q whole tiles, starting from those
+// partial sums, and stores and counts the tile.  Each workgroup then has at most q + 1/2 tiles
+// of work, and the first half is q tile times old when the second half asks for it (a flag per
+// tile says it is there; see the wait in the kernel).
+//
+// Workgroups 0 .. r-1 are early, r .. 2r-1 late; the early workgroup of a tile has the lower
+// index: it was dispatched first and waits for nothing, so the late one's wait ends.  Early and
+// late workgroups run half a tile time apart for the whole launch, and every XCD has both kinds
+// (r is normally a multiple of 8, so the two halves of a tile even run on the same XCD): that
+// spread of phases measures 5 % faster than whole XCDs running early or late.
+template <int TAIL>
+__device__ inline bool work_item(const Plan &p, int it, int &blk, int &part, int &nparts) {
+  const int G = (int)gridDim.x, w = (int)blockIdx.x;
+  if (TAIL && p.tail_r) {
+    nparts = 1;
+    part = 0;
+    const bool early = w < p.tail_r;
+    const int i = early ? w : w - p.tail_r;
+    if (early) {
+      if (it == 0) {
+        blk = p.tail_q * G + i;
+        nparts = 2;
+        return true;
+      }
+      blk = w + (it - 1) * G;
+      return it <= p.tail_q;
+    }
+    if (it < p.tail_q) {
+      blk = w + it * G;
+      return true;
+    }
+    if (it == p.tail_q && !early && i < p.tail_r) {
+      blk = p.tail_q * G + i;
+      part = 1;
+      nparts = 2;
+      return true;
+    }
+    return false;
+  }
+  // (positions fit 31 bits, the launch code sees to that)
+  const uint32_t pos = (uint32_t)w + (uint32_t)it * (uint32_t)G;
+  if (pos >= (uint32_t)p.total_blocks * (uint32_t)p.split_k) return false;
+  blk = (int)(pos / (uint32_t)p.split_k);
+  part = (int)(pos - (uint32_t)blk * (uint32_t)p.split_k);
+  nparts = p.split_k;
+  return true;
+}
+
+// Phase offsets at start-up.  All workgroups of the first wave of tiles start together and would
+// reach their reduction traffic (incoming tile in, sums out) together, an HBM-bound burst during
+// which no matrix core works.  The first `stagger_blocks` workgroups are put into
+// `stagger_groups` phase groups; group g starts g * stagger_ticks (100 MHz ticks) late.  A
+// persistent workgroup keeps its offset through all its tiles (every tile takes the same time);
+// with one workgroup per grid position, later ones are dispatched as earlier ones retire.
+__device__ inline void stagger_start(const Plan &p) {
+  const int b = blockIdx.x;
+  if (b >= p.stagger_blocks) return;
+  const int grp = ((b >> 3) + (b >> 8)) % p.stagger_groups;
+  if (!grp) return;
+  const uint64_t t0 = wall_clock64(), wait = (uint64_t)grp * (uint64_t)p.stagger_ticks;
+  while (wall_clock64() - t0 < wait) __builtin_amdgcn_s_sleep(8);
+}
+
+// Stores that are visible to every XCD once acknowledged: agent scope, i.e. the sc1 bit, which
+// writes through the issuing XCD's L2.  (Plain and non-temporal stores stay in that L2 until a
+// release fence writes the whole cache back.)
+__device__ inline void store_agent(float *p, float v) {
+  __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ inline void store_agent(f32x4 *p, f32x4 v) {
+  asm volatile("global_store_dwordx4 %0, %1, off sc1" : : "v"(p), "v"(v) : "memory");
+}
+// Tile results and the incoming partial are accessed through buffer instructions: uniform
+// descriptor, 32-bit byte offset of the lane, uniform offset of the block.  They are issued as
+// compiler builtins, not inline assembly, so that the compiler keeps the required distance
+// between an MFMA and a store that reads its result.
+typedef __attribute__((ext_vector_type(4))) uint32_t u32x4;
+constexpr int kAuxNt = 2, kAuxSc1 = 16;     // cache-policy bits of the buffer builtins on gfx94x/gfx950
+__device__ inline __amdgpu_buffer_rsrc_t make_rsrc(const void *base, uint32_t bytes) {
+  return __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(base), 0, (int)bytes, 0x00020000);
+}
+__device__ inline void store_agent(__amdgpu_buffer_rsrc_t r, uint32_t lane_off, uint32_t blk_off, f32x4 v) {
+  __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, v), r, (int)lane_off, (int)blk_off, kAuxSc1);
+}
+// (NT: with the streaming hint as well: the lines do not stay in the XCD's L2, where slabs of A
+// and B are better kept)
+template <bool NT>
+__device__ inline void store_agent_hint(__amdgpu_buffer_rsrc_t r, uint32_t lane_off, uint32_t blk_off, f32x4 v) {
+  __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, v), r, (int)lane_off, (int)blk_off,
+                                         NT ? (kAuxSc1 | kAuxNt) : kAuxSc1);
+}
+__device__ inline f32x4 load_stream(__amdgpu_buffer_rsrc_t r, uint32_t lane_off, uint32_t blk_off) {
+  return __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(r, (int)lane_off, (int)blk_off, kAuxNt));
+}
+
+// fp32 -> bfloat16, round to nearest even (v_cvt_pk_bf16_f32): the 16-bit format a forward slot
+// may hold (activations under mixed precision, Sec. 5.2).
+typedef __attribute__((ext_vector_type(4))) __bf16 bf16x4;
+typedef __attribute__((ext_vector_type(2))) uint32_t u32x2;
+__device__ inline u32x2 pack_bf16(f32x4 v) {
+  return __builtin_bit_cast(u32x2, __builtin_convertvector(v, bf16x4));
+}
+__device__ inline u32x4 pack_bf16(f32x4 lo, f32x4 hi) {
+  const u32x2 a = pack_bf16(lo), b = pack_bf16(hi);
+  return u32x4{a[0], a[1], b[0], b[1]};
+}
+
+// Rows r0, r0 + step, ... < r_end of chunk c of R into forward slot `slot`, one wavefront per
+// row, 16 bytes per lane: the copy a trigger starts (Sec. 4.2.2).  The slot holds fp32, or
+// bfloat16 under kFlagFwdBf16.
+__device__ inline f32x4 load_agent(__amdgpu_buffer_rsrc_t r, uint32_t lane_off, uint32_t row_off) {
+  return __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(r, (int)lane_off, (int)row_off, kAuxSc1 | kAuxNt));
+}
+__device__ inline void copy_chunk_rows(const Plan &p, int slot, int c, int r0, int r_end, int step) {
+  const int lane = threadIdx.x & 63;
+  // R is read with agent-scope loads: they see the producers' write-through stores, so no cache
+  // has to be invalidated first (which would cost every workgroup of the XCD its slabs in L2)
+  const __amdgpu_buffer_rsrc_t rs = make_rsrc(p.R, (uint32_t)p.M * (uint32_t)p.ldr * 4u);
+  const uint32_t col_off = (uint32_t)c * (uint32_t)p.W * 4u;
+  if (p.flags & kFlagFwdBf16) {
+    const int W8 = p.W >> 3;
+    for (int r = r0; r < r_end; r += step) {
+      const uint32_t row_off = (uint32_t)r * (uint32_t)p.ldr * 4u + col_off;
+      u32x4 *dst = (u32x4 *)((uint16_t *)p.fwd + ((int64_t)slot * p.M + r) * p.W);
+      for (int c0 = lane; c0 < W8; c0 += 2 * 64) {
+        f32x4 v[4];
+#pragma unroll
+        for (int u = 0; u < 2; ++u)
+          if (c0 + u * 64 < W8) {
+            v[2 * u] = load_agent(rs, (uint32_t)(c0 + u * 64) * 32u, row_off);
+            v[2 * u + 1] = load_agent(rs, (uint32_t)(c0 + u * 64) * 32u + 16u, row_off);
+          }
+#pragma unroll
+        for (int u = 0; u < 2; ++u)
+          if (c0 + u * 64 < W8)
+            __builtin_nontemporal_store(pack_bf16(v[2 * u], v[2 * u + 1]), dst + c0 + u * 64);
+      }
+    }
+    return;
+  }
+  const int W4 = p.W >> 2;
+  for (int r = r0; r < r_end; r += step) {
+    const uint32_t row_off = (uint32_t)r * (uint32_t)p.ldr * 4u + col_off;
+    f32x4 *dst = (f32x4 *)(p.fwd + ((int64_t)slot * p.M + r) * p.W);
+    for (int c0 = lane; c0 < W4; c0 += 4 * 64) {
+      f32x4 v[4];
+#pragma unroll
+      for (int u = 0; u < 4; ++u)
+        if (c0 + u * 64 < W4) v[u] = load_agent(rs, (uint32_t)(c0 + u * 64) * 16u, row_off);
+#pragma unroll
+      for (int u = 0; u < 4; ++u)
+        if (c0 + u * 64 < W4) __builtin_nontemporal_store(v[u], dst + c0 + u * 64);
+    }
+  }
+}
+
+// ---------------------------------------------------------------------------------------------
+// Track & trigger (Sec. 4.2).  Called by all threads of a workgroup after the tile's stores
+// have been issued.  Tile results are written with agent-scope stores; once they have been
+// acknowledged (vmcnt == 0 in every wavefront, then the barrier) the tile is counted.  A
+// device-scope release fence instead would write back the whole L2 for every tile and costs
+// several times the reduction itself.
+__device__ inline void track_count(const Plan &p, const Trk &t, int c);
+__device__ inline void track_tile(const Plan &p, const Trk &t, int c) {
+  __builtin_amdgcn_s_waitcnt(kWaitAll);
+  __syncthreads();
+  track_count(p, t, c);
+}
+// The counting itself, once every wavefront's stores of the tile are known to be acknowledged
+// and a barrier has passed.
+__device__ inline void track_count(const Plan &p, const Trk &t, int c) {
+  if (threadIdx.x == 0) {
+    // both increments are in flight together: one round trip at the end of a tile, not two
+    const uint32_t old = __hip_atomic_fetch_add(&t.counter[c], 1u, __ATOMIC_RELAXED,
+                                                __HIP_MEMORY_SCOPE_AGENT);
+    const uint32_t d = __hip_atomic_fetch_add(t.done, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    // threshold = regions of the chunk x updates expected per element (Sec. 4.2.1)
+    const uint32_t upd = (uint32_t)(c == p.rank ? p.upd_first : p.upd_rest);
+    if (old + 1u == (uint32_t)p.tpc * upd) {      // the landing that reaches the threshold triggers
+      if (p.tracked != p.tpc)                     // what the counter is read as: tracked tiles
+        __hip_atomic_store(&t.counter[c], (uint32_t)p.tracked * upd, __ATOMIC_RELAXED,
+                           __HIP_MEMORY_SCOPE_AGENT);
+      if (c != p.own) {
+        const uint32_t pos = __hip_atomic_fetch_add(t.queue_len, 1u, __ATOMIC_RELAXED,
+                                                    __HIP_MEMORY_SCOPE_AGENT);
+        __hip_atomic_store(&t.queue[pos], (uint32_t)c, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      }
+      // The flag is what publishes: a release store, so the queue entry above and everything this
+      // workgroup made visible before the barrier that precedes the count are ordered before it.
+      // (queue_len alone publishes nothing: it may run ahead of the entry it reserves.)
+      __hip_atomic_store(&t.ready[c], 1u, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    trk_close_if_last(p, t, d);
+  }
+}
+
+}  // namespace t3k

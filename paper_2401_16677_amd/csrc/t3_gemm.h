@@ -18,425 +18,11 @@
 //
 // A persistent launch whose last round of tiles would fill at most half the chip computes each
 // of those tiles as two halves of K on two workgroups (balanced tail, see work_item).
-//
-// Included by t3_api.hip only.
 #pragma once
 
-#include <hip/hip_runtime.h>
-#include <stdint.h>
-
-#include <type_traits>
-
-#ifndef T3_MH
-#define T3_MH 2            // row passes per MFMA k-step of a 128-row wavefront tile (2 or 4)
-#endif
-#ifndef T3_AGENTS
-#define T3_AGENTS 32          // release workgroups per forwarded chunk (multiple of 8)
-#endif
+#include "t3_device.h"
 
 namespace t3k {
-
-typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
-typedef __attribute__((ext_vector_type(16))) float f32x16;
-typedef __attribute__((ext_vector_type(4))) float f32x4;
-typedef __attribute__((address_space(3))) void *lds_void_ptr;
-typedef const __attribute__((address_space(1))) void *global_void_ptr;
-
-constexpr int kThreads = 256;
-constexpr uint32_t kEmpty = 0xFFFFFFFFu;
-constexpr int kSpinLimit = 1 << 22;   // polls of a release workgroup before it gives up
-constexpr int kTimelineItems = 16;     // pieces of work per workgroup a timeline records
-constexpr int kTailSlots = 256;       // tiles a balanced tail can split (flag words behind the tracker state)
-
-constexpr uint32_t kFlagStep0StoreOnly = 1u;
-constexpr uint32_t kFlagFwdDirect = 2u;
-constexpr uint32_t kFlagTwoWriters = 4u;
-constexpr uint32_t kFlagFwdBf16 = 8u;
-
-enum Mode { kModeGemm = 0, kModeFused = 1 };
-enum Role { kRoleNone = 0, kRoleTile = 1, kRoleRelease = 2 };
-
-// s_waitcnt immediates (gfx9 encoding: vmcnt[3:0] | expcnt << 4 | lgkmcnt << 8 | vmcnt[5:4] << 14)
-constexpr int kWaitVm0 = 0x0F70;
-constexpr int kWaitLgkm0 = 0xF0FF;    // and-mask that turns a wait into "... and lgkmcnt(0)"
-constexpr int kWaitAll = 0;
-__host__ __device__ constexpr int wait_vm(int n) { return 0x0F70 | (n & 15) | ((n >> 4) << 14); }
-
-// Everything a kernel needs, passed by value.
-struct Plan {
-  const uint16_t *A;
-  const uint16_t *B;
-  const float *C;    // reduce kernel input
-  float *R;          // fused / reduce: incoming in, sums out.  gemm: the C output
-  float *fwd;
-  uint32_t *track;
-  int64_t lda, ldb, ldr, ldc;
-  int64_t limit;     // tiles with issue index >= limit do nothing
-  int64_t begin;     // nor do tiles with issue index < begin
-  int32_t M, N, K, P, rank, W, own;
-  int32_t Mt, Wt, tpc;                 // the grid of WORKGROUP tiles: rows, columns, tiles per chunk
-  // The tracked tile may be half a workgroup tile high (128 x 256 tracked, 256 x 256 computed):
-  // then pair_m == 2, a workgroup tile covers the tracked tiles 2 mi and 2 mi + 1 of its column
-  // (consecutive in the issue order) and counts as many as exist.  Otherwise pair_m == 1 and
-  // the two grids are the same.
-  int32_t pair_m, Mt_t, tpc_t;         // tracked tile rows and tracked tiles per chunk
-  int32_t xcd_nbm, xcd_bmk, xcd_bnk;   // XCD grouping of a stage's tiles; xcd_nbm == 0: none
-  int32_t agents, lag, rows_per_agent; // release workgroups per chunk, their lag in stages
-  int32_t expected_done;               // grid positions of this launch that do work
-  int32_t total_blocks;                // grid positions (tiles and release work) of the launch
-  int32_t resident;                    // tile workgroups the chip holds at once
-  int32_t upd_first, upd_rest;         // updates expected per element of chunk order[0] / the others
-  int32_t split_k;                     // >= 1: workgroups that share a tile, each taking a part of K (Sec. 7.7)
-  int32_t stagger_blocks, stagger_groups, stagger_ticks;   // start-up phase offsets (see stagger_start)
-  int32_t k_groups;                    // > 1: workgroup w starts its K loop (w % k_groups) / k_groups of the way in
-  int32_t nt_out;                      // results leave with the streaming hint (hand-ordered kernel)
-  // Timeline (a profiling aid, normally null): workgroup w < timeline_wgs writes, for its i-th
-  // piece of work, i < kTimelineItems, four wall-clock readings (100 MHz) at
-  // timeline[(w * kTimelineItems + i) * 4 + ...]: piece taken; accumulators set up (the
-  // incoming partial in place); main loop done; results handed to the memory system.
-  uint64_t *timeline;
-  int32_t timeline_wgs;
-  // Balanced tail (persistent launches): the last tail_r grid positions, which would keep only
-  // tail_r of the workgroups busy for a whole tile time, are each split into two halves of K
-  // (see work_item).  0: off.  tail_q = full rounds of the grid before them; tail_flags = one
-  // word per split tile, 0 between launches.
-  int32_t tail_r, tail_q;
-  uint32_t *tail_flags;
-  uint32_t flags;
-};
-
-struct Tile {
-  int s, c, mi, nj;
-};
-
-// Tracker state (uint32 words): two banks of { counter[P] ready[P] queue[P] queue_len done },
-// then the globals { gen, error }.  A launch works in bank gen & 1; the last workgroup of the
-// launch to finish clears the other bank and increments gen, so the next launch starts from a
-// clean bank without a reset kernel in between, and the caller finds the results of the launch
-// that just ended in bank (gen - 1) & 1.
-__device__ inline int trk_bank_words(int P) { return 3 * P + 2; }
-struct Trk {
-  uint32_t *counter, *ready, *queue, *queue_len, *done;   // this launch's bank
-  uint32_t *other;                                         // the bank to clear at the end
-  uint32_t *gen, *error;
-};
-__device__ inline Trk trk_open(const Plan &p) {
-  Trk t;
-  t.gen = p.track + 2 * trk_bank_words(p.P);
-  t.error = t.gen + 1;
-  // (the same in every lane: made uniform so that the bank pointers live in scalar registers)
-  const uint32_t g = __builtin_amdgcn_readfirstlane(
-      __hip_atomic_load(t.gen, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
-  uint32_t *b = p.track + (g & 1u) * trk_bank_words(p.P);
-  t.counter = b;
-  t.ready = b + p.P;
-  t.queue = b + 2 * p.P;
-  t.queue_len = b + 3 * p.P;
-  t.done = b + 3 * p.P + 1;
-  t.other = p.track + ((g & 1u) ^ 1u) * trk_bank_words(p.P);
-  return t;
-}
-__device__ inline void trk_clear_bank(uint32_t *b, int P) {
-  for (int i = 0; i < 3 * P + 2; ++i)
-    __hip_atomic_store(&b[i], (i >= 2 * P && i < 3 * P) ? kEmpty : 0u, __ATOMIC_RELAXED,
-                       __HIP_MEMORY_SCOPE_AGENT);
-}
-// Called by thread 0 of every workgroup that did work, as its last act; d = the value its
-// increment of `done` returned.
-__device__ inline void trk_close_if_last(const Plan &p, const Trk &t, uint32_t d) {
-  if (d + 1u == (uint32_t)p.expected_done) {
-    trk_clear_bank(t.other, p.P);
-    __hip_atomic_fetch_add(t.gen, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  }
-}
-__device__ inline void trk_workgroup_done(const Plan &p, const Trk &t) {
-  trk_close_if_last(
-      p, t, __hip_atomic_fetch_add(t.done, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
-}
-
-// Index j of a tile inside its stage -> tile.  Workgroups are dealt round-robin to the 8 XCDs,
-// so workgroup j of a stage lands on XCD j % 8; that XCD gets a compact block of
-// xcd_bmk x xcd_bnk tiles which share A rows and B columns in its L2.
-__device__ inline bool decode_tile(const Plan &p, int s, int j, Tile &tl) {
-  int mi, nj;
-  if (p.xcd_nbm) {
-    const int x = j & 7, i = j >> 3;
-    const int bxm = x % p.xcd_nbm, bxn = x / p.xcd_nbm;
-    mi = bxm * p.xcd_bmk + i % p.xcd_bmk;
-    nj = bxn * p.xcd_bnk + i / p.xcd_bmk;
-  } else {
-    mi = j % p.Mt;
-    nj = j / p.Mt;
-  }
-  // issue index of the (first) tracked tile
-  const int64_t t = (int64_t)s * p.tpc_t + (int64_t)nj * p.Mt_t + (int64_t)mi * p.pair_m;
-  int c = p.rank + s;
-  if (c >= p.P) c -= p.P;
-  tl.s = s;
-  tl.c = c;
-  tl.mi = mi;
-  tl.nj = nj;
-  return t >= p.begin && t < p.limit;
-}
-
-// Grid layout: the tiles of stage 0, 1, ... in order; after the tiles of stage s come the
-// `agents` release workgroups of forward slot s - lag (a chunk whose tiles were all dispatched
-// at least `lag` stages earlier); slots not served that way follow the last stage.
-__device__ inline int decode_block(const Plan &p, int b, Tile &tl, int &slot, int &agent) {
-  int base = 0;
-  for (int s = 0; s < p.P; ++s) {
-    if (b < base + p.tpc) return decode_tile(p, s, b - base, tl) ? kRoleTile : kRoleNone;
-    base += p.tpc;
-    const int sl = s - p.lag;
-    if (p.agents && sl >= 0 && sl <= p.P - 2) {
-      if (b < base + p.agents) {
-        slot = sl;
-        agent = b - base;
-        return kRoleRelease;
-      }
-      base += p.agents;
-    }
-  }
-  if (!p.agents) return kRoleNone;
-  const int rem = b - base;
-  slot = max(0, p.P - p.lag) + rem / p.agents;
-  agent = rem % p.agents;
-  return slot <= p.P - 2 ? kRoleRelease : kRoleNone;
-}
-
-// The it-th piece of work of a persistent workgroup: grid position `blk`, part `part` of
-// `nparts` parts of K.  Without a balanced tail, workgroup w of G takes positions w, w + G, ...
-// (split-K: `split_k` consecutive positions share a tile).
-//
-// Balanced tail.  With T = q G + r positions, 0 < r <= G / 2, the last round would run r tiles on
-// r workgroups while the others idle.  Instead each of those r tiles is cut into two halves of
-// K.  Half the workgroups are "early": early workgroup number i < r computes the first half of
-// tile q G + i BEFORE its q whole tiles, starting from the incoming partial as any tile does,
-// and stores the partial sums where the tile's result belongs.  The others are "late": late
-// workgroup number i < r computes the second half AFTER its q whole tiles, starting from those
-// partial sums, and stores and counts the tile.  Each workgroup then has at most q + 1/2 tiles
-// of work, and the first half is q tile times old when the second half asks for it (a flag per
-// tile says it is there; see the wait in the kernel).
-//
-// Workgroups 0 .. r-1 are early, r .. 2r-1 late; the early workgroup of a tile has the lower
-// index: it was dispatched first and waits for nothing, so the late one's wait ends.  Early and
-// late workgroups run half a tile time apart for the whole launch, and every XCD has both kinds
-// (r is normally a multiple of 8, so the two halves of a tile even run on the same XCD): that
-// spread of phases measures 5 % faster than whole XCDs running early or late.
-template <int TAIL>
-__device__ inline bool work_item(const Plan &p, int it, int &blk, int &part, int &nparts) {
-  const int G = (int)gridDim.x, w = (int)blockIdx.x;
-  if (TAIL && p.tail_r) {
-    nparts = 1;
-    part = 0;
-    const bool early = w < p.tail_r;
-    const int i = early ? w : w - p.tail_r;
-    if (early) {
-      if (it == 0) {
-        blk = p.tail_q * G + i;
-        nparts = 2;
-        return true;
-      }
-      blk = w + (it - 1) * G;
-      return it <= p.tail_q;
-    }
-    if (it < p.tail_q) {
-      blk = w + it * G;
-      return true;
-    }
-    if (it == p.tail_q && !early && i < p.tail_r) {
-      blk = p.tail_q * G + i;
-      part = 1;
-      nparts = 2;
-      return true;
-    }
-    return false;
-  }
-  // (positions fit 31 bits, the launch code sees to that)
-  const uint32_t pos = (uint32_t)w + (uint32_t)it * (uint32_t)G;
-  if (pos >= (uint32_t)p.total_blocks * (uint32_t)p.split_k) return false;
-  blk = (int)(pos / (uint32_t)p.split_k);
-  part = (int)(pos - (uint32_t)blk * (uint32_t)p.split_k);
-  nparts = p.split_k;
-  return true;
-}
-
-// Phase offsets at start-up.  All workgroups of the first wave of tiles start together and would
-// reach their reduction traffic (incoming tile in, sums out) together, an HBM-bound burst during
-// which no matrix core works.  The first `stagger_blocks` workgroups are put into
-// `stagger_groups` phase groups; group g starts g * stagger_ticks (100 MHz ticks) late.  A
-// persistent workgroup keeps its offset through all its tiles (every tile takes the same time);
-// with one workgroup per grid position, later ones are dispatched as earlier ones retire.
-__device__ inline void stagger_start(const Plan &p) {
-  const int b = blockIdx.x;
-  if (b >= p.stagger_blocks) return;
-  const int grp = ((b >> 3) + (b >> 8)) % p.stagger_groups;
-  if (!grp) return;
-  const uint64_t t0 = wall_clock64(), wait = (uint64_t)grp * (uint64_t)p.stagger_ticks;
-  while (wall_clock64() - t0 < wait) __builtin_amdgcn_s_sleep(8);
-}
-
-// Stores that are visible to every XCD once acknowledged: agent scope, i.e. the sc1 bit, which
-// writes through the issuing XCD's L2.  (Plain and non-temporal stores stay in that L2 until a
-// release fence writes the whole cache back.)
-__device__ inline void store_agent(float *p, float v) {
-  __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-__device__ inline void store_agent(f32x4 *p, f32x4 v) {
-  asm volatile("global_store_dwordx4 %0, %1, off sc1" : : "v"(p), "v"(v) : "memory");
-}
-// Tile results and the incoming partial are accessed through buffer instructions: uniform
-// descriptor, 32-bit byte offset of the lane, uniform offset of the block.  They are issued as
-// compiler builtins, not inline assembly, so that the compiler keeps the required distance
-// between an MFMA and a store that reads its result.
-typedef __attribute__((ext_vector_type(4))) uint32_t u32x4;
-constexpr int kAuxNt = 2, kAuxSc1 = 16;     // cache-policy bits of the buffer builtins on gfx94x/gfx950
-__device__ inline __amdgpu_buffer_rsrc_t make_rsrc(const void *base, uint32_t bytes) {
-  return __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(base), 0, (int)bytes, 0x00020000);
-}
-__device__ inline void store_agent(__amdgpu_buffer_rsrc_t r, uint32_t lane_off, uint32_t blk_off, f32x4 v) {
-  __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, v), r, (int)lane_off, (int)blk_off, kAuxSc1);
-}
-// (NT: with the streaming hint as well: the lines do not stay in the XCD's L2, where slabs of A
-// and B are better kept)
-template <bool NT>
-__device__ inline void store_agent_hint(__amdgpu_buffer_rsrc_t r, uint32_t lane_off, uint32_t blk_off, f32x4 v) {
-  __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, v), r, (int)lane_off, (int)blk_off,
-                                         NT ? (kAuxSc1 | kAuxNt) : kAuxSc1);
-}
-__device__ inline f32x4 load_stream(__amdgpu_buffer_rsrc_t r, uint32_t lane_off, uint32_t blk_off) {
-  return __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(r, (int)lane_off, (int)blk_off, kAuxNt));
-}
-
-// fp32 -> bfloat16, round to nearest even (v_cvt_pk_bf16_f32): the 16-bit format a forward slot
-// may hold (activations under mixed precision, Sec. 5.2).
-typedef __attribute__((ext_vector_type(4))) __bf16 bf16x4;
-typedef __attribute__((ext_vector_type(2))) uint32_t u32x2;
-__device__ inline u32x2 pack_bf16(f32x4 v) {
-  return __builtin_bit_cast(u32x2, __builtin_convertvector(v, bf16x4));
-}
-__device__ inline u32x4 pack_bf16(f32x4 lo, f32x4 hi) {
-  const u32x2 a = pack_bf16(lo), b = pack_bf16(hi);
-  return u32x4{a[0], a[1], b[0], b[1]};
-}
-
-// Rows r0, r0 + step, ... < r_end of chunk c of R into forward slot `slot`, one wavefront per
-// row, 16 bytes per lane: the copy a trigger starts (Sec. 4.2.2).  The slot holds fp32, or
-// bfloat16 under kFlagFwdBf16.
-__device__ inline f32x4 load_agent(__amdgpu_buffer_rsrc_t r, uint32_t lane_off, uint32_t row_off) {
-  return __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(r, (int)lane_off, (int)row_off, kAuxSc1 | kAuxNt));
-}
-__device__ inline void copy_chunk_rows(const Plan &p, int slot, int c, int r0, int r_end, int step) {
-  const int lane = threadIdx.x & 63;
-  // R is read with agent-scope loads: they see the producers' write-through stores, so no cache
-  // has to be invalidated first (which would cost every workgroup of the XCD its slabs in L2)
-  const __amdgpu_buffer_rsrc_t rs = make_rsrc(p.R, (uint32_t)p.M * (uint32_t)p.ldr * 4u);
-  const uint32_t col_off = (uint32_t)c * (uint32_t)p.W * 4u;
-  if (p.flags & kFlagFwdBf16) {
-    const int W8 = p.W >> 3;
-    for (int r = r0; r < r_end; r += step) {
-      const uint32_t row_off = (uint32_t)r * (uint32_t)p.ldr * 4u + col_off;
-      u32x4 *dst = (u32x4 *)((uint16_t *)p.fwd + ((int64_t)slot * p.M + r) * p.W);
-      for (int c0 = lane; c0 < W8; c0 += 2 * 64) {
-        f32x4 v[4];
-#pragma unroll
-        for (int u = 0; u < 2; ++u)
-          if (c0 + u * 64 < W8) {
-            v[2 * u] = load_agent(rs, (uint32_t)(c0 + u * 64) * 32u, row_off);
-            v[2 * u + 1] = load_agent(rs, (uint32_t)(c0 + u * 64) * 32u + 16u, row_off);
-          }
-#pragma unroll
-        for (int u = 0; u < 2; ++u)
-          if (c0 + u * 64 < W8)
-            __builtin_nontemporal_store(pack_bf16(v[2 * u], v[2 * u + 1]), dst + c0 + u * 64);
-      }
-    }
-    return;
-  }
-  const int W4 = p.W >> 2;
-  for (int r = r0; r < r_end; r += step) {
-    const uint32_t row_off = (uint32_t)r * (uint32_t)p.ldr * 4u + col_off;
-    f32x4 *dst = (f32x4 *)(p.fwd + ((int64_t)slot * p.M + r) * p.W);
-    for (int c0 = lane; c0 < W4; c0 += 4 * 64) {
-      f32x4 v[4];
-#pragma unroll
-      for (int u = 0; u < 4; ++u)
-        if (c0 + u * 64 < W4) v[u] = load_agent(rs, (uint32_t)(c0 + u * 64) * 16u, row_off);
-#pragma unroll
-      for (int u = 0; u < 4; ++u)
-        if (c0 + u * 64 < W4) __builtin_nontemporal_store(v[u], dst + c0 + u * 64);
-    }
-  }
-}
-
-// ---------------------------------------------------------------------------------------------
-// Track & trigger (Sec. 4.2).  Called by all threads of a workgroup after the tile's stores
-// have been issued.  Tile results are written with agent-scope stores; once they have been
-// acknowledged (vmcnt == 0 in every wavefront, then the barrier) the tile is counted.  A
-// device-scope release fence instead would write back the whole L2 for every tile and costs
-// several times the reduction itself.
-__device__ inline void track_count(const Plan &p, const Trk &t, int c, int n = 1);
-__device__ inline void track_tile(const Plan &p, const Trk &t, int c, int n = 1) {
-  __builtin_amdgcn_s_waitcnt(kWaitAll);
-  __syncthreads();
-  track_count(p, t, c, n);
-}
-// The counting itself, once every wavefront's stores of the tile are known to be acknowledged
-// and a barrier has passed.
-// (n: tracked tiles the workgroup's tile covers)
-__device__ inline void track_count(const Plan &p, const Trk &t, int c, int n) {
-  if (threadIdx.x == 0) {
-    // both increments are in flight together: one round trip at the end of a tile, not two
-    const uint32_t old = __hip_atomic_fetch_add(&t.counter[c], (uint32_t)n, __ATOMIC_RELAXED,
-                                                __HIP_MEMORY_SCOPE_AGENT);
-    const uint32_t d = __hip_atomic_fetch_add(t.done, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    // threshold = tracked regions of the chunk x updates expected per element (Sec. 4.2.1)
-    const uint32_t threshold = (uint32_t)p.tpc_t * (uint32_t)(c == p.rank ? p.upd_first : p.upd_rest);
-    if (old + (uint32_t)n == threshold) {         // the landing that reaches the threshold triggers
-      if (c != p.own) {
-        const uint32_t pos = __hip_atomic_fetch_add(t.queue_len, 1u, __ATOMIC_RELAXED,
-                                                    __HIP_MEMORY_SCOPE_AGENT);
-        __hip_atomic_store(&t.queue[pos], (uint32_t)c, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      }
-      // The flag is what publishes: a release store, so the queue entry above and everything this
-      // workgroup made visible before the barrier that precedes the count are ordered before it.
-      // (queue_len alone publishes nothing: it may run ahead of the entry it reserves.)
-      __hip_atomic_store(&t.ready[c], 1u, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
-    }
-    trk_close_if_last(p, t, d);
-  }
-}
-
-// Release of a triggered chunk into its forward slot (the DMA of Sec. 4.2.2): workgroup `agent`
-// of `agents` waits for the chunk's ready flag and copies its share of rows.  Every tile of the
-// chunk was dispatched before this workgroup (lower block index), so the wait ends; should it
-// not (a broken launch), the workgroup gives up after kSpinLimit polls and raises the error word.
-__device__ inline void release_chunk(const Plan &p, int slot, int agent, uint32_t *sh) {
-  if ((int64_t)(slot + 1) * p.tpc_t > p.limit || (int64_t)slot * p.tpc_t < p.begin)
-    return;                                              // this chunk will not complete
-  const Trk t = trk_open(p);
-  int c = p.rank + slot;
-  if (c >= p.P) c -= p.P;
-  if (threadIdx.x == 0) {
-    int spins = 0;
-    while (__hip_atomic_load(&t.ready[c], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == 0u &&
-           ++spins < kSpinLimit)
-      __builtin_amdgcn_s_sleep(16);
-    const uint32_t ok = spins < kSpinLimit;
-    if (!ok) __hip_atomic_fetch_or(t.error, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    *sh = ok;
-  }
-  __syncthreads();
-  if (!*sh) {            // gave up: still count as finished so that the launch closes its bank
-    if (threadIdx.x == 0) trk_workgroup_done(p, t);
-    return;
-  }
-  copy_chunk_rows(p, slot, c, agent * p.rows_per_agent + (int)(threadIdx.x >> 6),
-                  min(p.M, (agent + 1) * p.rows_per_agent), (int)(blockDim.x >> 6));
-  __builtin_amdgcn_s_waitcnt(kWaitAll);
-  __syncthreads();
-  if (threadIdx.x == 0) trk_workgroup_done(p, t);
-}
 
 // ---------------------------------------------------------------------------------------------
 // LDS layout of one stage: BM rows of A then BN rows of B; a row holds the 64 bf16 of one tile
@@ -502,6 +88,13 @@ __device__ __forceinline__ void asm_wait_operands(bf16x8 (&a)[8], bf16x8 (&b)[8]
                :
                : "memory");
 }
+__device__ __forceinline__ void asm_wait_operands(bf16x8 (&a)[8], bf16x8 (&b)[6]) {
+  asm volatile("s_waitcnt lgkmcnt(0)"
+               : "+v"(a[0]), "+v"(a[1]), "+v"(a[2]), "+v"(a[3]), "+v"(a[4]), "+v"(a[5]), "+v"(a[6]), "+v"(a[7]),
+                 "+v"(b[0]), "+v"(b[1]), "+v"(b[2]), "+v"(b[3]), "+v"(b[4]), "+v"(b[5])
+               :
+               : "memory");
+}
 
 constexpr int kRingSlots = 4;         // 1-KiB LDS slots per wavefront for transposing pairs: two pairs
 
@@ -529,7 +122,12 @@ constexpr int kRingSlots = 4;         // 1-KiB LDS slots per wavefront for trans
 // TAIL = 2: that variant of the fused kernel with the reduction and the tracking taken out: the
 // plain GEMM with a balanced tail (the plain kernel's own TAIL = 1 variant of the hand-ordered
 // loop does not fit the register file).
-template <int BM, int BN, int WAVES_M, int WAVES_N, int NSTAGE, int MODE, int BKN, int AKM = 0, int TAIL = 0>
+//
+// SLOT (hand-ordered kernel, whose registers do not allow for all of it in one): 0 = results in
+// one place, in fp32; 1 = in R and, in fp32, in a forward slot; 2 = forward slots in bfloat16.
+// -1: any of these, told by the flags.
+template <int BM, int BN, int WAVES_M, int WAVES_N, int NSTAGE, int MODE, int BKN, int AKM = 0, int TAIL = 0,
+          int SLOT = -1>
 __global__ __launch_bounds__(64 * WAVES_M * WAVES_N)
 __attribute__((amdgpu_waves_per_eu((BM / WAVES_M) * (BN / WAVES_N) > 8192 ? 1 : 2)))
 void gemm_tile_kernel(const Plan p) {
@@ -549,14 +147,13 @@ void gemm_tile_kernel(const Plan p) {
   static_assert(NSTAGE >= 2 && (NSTAGE - 2) * NL < 64, "vmcnt range");
   static_assert(KS == 2, "the loop body is written as two k-steps");
   static_assert(NL % MH == 0, "a slab's copies are split evenly over the first k-step's passes");
-  static_assert((FN & (FN - 1)) == 0, "block index -> (row block, column block) by shifts");
   static_assert(NSTAGE * kStageBytes <= 160 * 1024, "LDS");
 
   // Four wavefronts of 128 x 128 (one per SIMD) run the hand-ordered main loop and add the
   // incoming partial on the way out; B stored N x K only.
-  constexpr bool kAsmLoop = (NW == 4 && FM == 8 && FN == 8 && NSTAGE == 2 && !BKN && !AKM);
+  constexpr bool kAsmLoop = (NW == 4 && FM == 8 && FN >= 6 && NSTAGE == 2 && !BKN && !AKM);
   // Their pair transpositions get LDS of their own (4 KiB per wavefront) behind the stages.
-  constexpr int kScrOff = kAsmLoop ? NSTAGE * kStageBytes : 0;
+  constexpr int kScrOff = kAsmLoop ? NSTAGE * kStageBytes : 0;   // (otherwise: the epilogue's, in stage 0)
   static_assert(kScrOff + NW * kRingSlots * 1024 <= 160 * 1024, "LDS");
 
   __shared__ __attribute__((aligned(1024))) char lds[NSTAGE * kStageBytes + (kAsmLoop ? NW * kRingSlots * 1024 : 0)];
@@ -588,11 +185,10 @@ void gemm_tile_kernel(const Plan p) {
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wm = wave / WAVES_N, wn = wave % WAVES_N;
   int pending_c = -1;                          // chunk of a tile whose stores are issued but not counted
-  int pending_n = 1;                           //   and the tracked tiles it covers
   int pending_half = -1;                       // first half of a split tile whose stores are issued but not announced
   // to be called after a barrier that every wavefront reached with its stores acknowledged
   auto settle_pending = [&]() {
-    if (tracked && pending_c >= 0) track_count(p, trk, pending_c, pending_n);
+    if (tracked && pending_c >= 0) track_count(p, trk, pending_c);
     // (relaxed, like the counting: what orders it behind the partial sums is that they were
     // written through and acknowledged before the barrier; a release would write back the L2)
     if (TAIL && pending_half >= 0 && threadIdx.x == 0)
@@ -633,17 +229,7 @@ void gemm_tile_kernel(const Plan p) {
   const char *const Ap = (const char *)p.A + (AKM ? (int64_t)k0 * p.lda * 2 : (int64_t)k0 * 2);
   const char *const Bp = (const char *)p.B + (BKN ? (int64_t)k0 * p.ldb * 2 : (int64_t)k0 * 2);
   Tile tl;
-  int slot = 0, agent = 0;
-  const int role = decode_block(p, blk, tl, slot, agent);
-  if (role != kRoleTile) {
-    flush_pending();                           // release work may wait for the very tile we finished
-    // the release role never touches the stages: its one shared word lives there
-    if (role == kRoleRelease && MODE == kModeFused) {
-      __syncthreads();
-      release_chunk(p, slot, agent, (uint32_t *)lds);
-    }
-    continue;
-  }
+  if (!decode_block(p, blk, tl)) continue;
   if (half1 && threadIdx.x == 0) {
     // The first half was computed by a workgroup with a lower index as its first piece of work
     // and waits for nothing, so this wait ends (normally at once: that was q tile times ago).
@@ -780,9 +366,15 @@ void gemm_tile_kernel(const Plan p) {
   // Block (i, j), element e of this lane: row 16*i + (lane & 15), column 16*j + 4*(lane >> 4) + e
   // of the wavefront tile.  Per 16-byte access 4 lanes cover 64 contiguous bytes of a row.
   const bool store_only = (MODE == kModeGemm) || plain || ((p.flags & kFlagStep0StoreOnly) && tl.s == 0);
-  const bool to_fwd = (MODE == kModeFused) && (p.flags & kFlagFwdDirect) && tl.c != p.own;
+  const bool to_fwd = (MODE == kModeFused) && SLOT != 1 && (p.flags & kFlagFwdDirect) && tl.c != p.own;
   // two writers (Sec. 4.1): the tile is ADDED into R with atomics, as the upstream update is
   const bool two_writers = (MODE == kModeFused) && (p.flags & kFlagTwoWriters);
+  // Release by copy: the sums go to R AND into the chunk's forward slot, from the registers that
+  // hold them, if this launch completes the chunk.  (A copy behind the chunk's trigger would read
+  // R back: 4 M W bytes more per chunk, and it measured 30 to 60 % of the launch's time.)
+  const bool to_both = (MODE == kModeFused) && SLOT != 0 && !plain && !two_writers && !(p.flags & kFlagFwdDirect) &&
+                       tl.c != p.own && chunk_is_whole(p, tl.s);
+  const bool slot_bf16 = (MODE == kModeFused) && (SLOT < 0 || SLOT == 2) && (p.flags & kFlagFwdBf16) && (to_fwd || to_both);
   const int rw0 = m0 + wm * WM, cw0 = n0 + wn * WN;          // wavefront tile origin (uniform)
   const bool full = (rw0 + WM <= p.M) && (cw0 + WN <= col_hi);
   // where the tile's result goes (uniform): R, C, or the chunk's forward slot
@@ -1112,156 +704,144 @@ void gemm_tile_kernel(const Plan p) {
   }
 
   stamp(it, 2);
-  // ---- epilogue: the tile leaves in whole 128-byte lines, agent-scope (write-through) stores
-  if constexpr (kAsmLoop) {
-    // Pair by pair through this wavefront's own 4 KiB of LDS: written in the accumulator layout,
-    // read back linearly, stored 8 rows x 128 bytes per instruction.  (Two-writer mode and
-    // bfloat16 forward slots written directly are served by the eight-wavefront kernel.)
-    const __amdgpu_buffer_rsrc_t out_rsrc = make_rsrc(out_base, (uint32_t)p.M * ld_out * 4u);
-    char *scr = lds + kScrOff + wave * (kRingSlots * 1024);
-    int lane_e = lane;                             // recomputed here rather than kept through the main loop
-    asm volatile("" : "+v"(lane_e));
-    const PairLane ue = pair_lane(lane_e);
-    const int *u_row = ue.row, *u_col = ue.col, *u_acc = ue.acc;
-    uint32_t out_u[2];
-#pragma unroll
-    for (int h = 0; h < 2; ++h)
-      out_u[h] = ((uint32_t)(rw0 + u_row[h]) * ld_out + (uint32_t)(cw0 - col_org + u_col[h])) * 4u;
-    // the next grid position of this workgroup: if it is a tile that takes an incoming partial,
-    // its accumulator blocks are requested once this tile's sums have been stored
-    bool next_in = false, next_full = false;
-    int next_rw0 = 0, next_cw0 = 0, next_col_hi = 0;
-    int blk_n, part_n, nparts_n;
-    if (MODE == kModeFused && !plain && work_item<TAIL>(p, it + 1, blk_n, part_n, nparts_n) && nparts_n == 1) {
-      Tile tn;
-      int slot_n = 0, agent_n = 0;
-      if (decode_block(p, blk_n, tn, slot_n, agent_n) == kRoleTile &&
-          !((p.flags & kFlagStep0StoreOnly) && tn.s == 0)) {
-        next_in = true;
-        next_col_hi = tn.c * p.W + p.W;
-        next_rw0 = tn.mi * BM + wm * WM;
-        next_cw0 = tn.c * p.W + tn.nj * BN + wn * WN;
-        next_full = (next_rw0 + WM <= p.M) && (next_cw0 + WN <= next_col_hi);
-      }
-    }
-    auto store_pairs = [&](auto NT) {
-#pragma unroll
-      for (int t = 0; t < NPAIR; ++t) {
-        const int i = t / UJ, jj = t % UJ;
-        char *slot = scr + ((2 * t) & (kRingSlots - 1)) * 1024;
-        *(f32x4 *)(slot + u_acc[0]) = acc[i][2 * jj];
-        *(f32x4 *)(slot + u_acc[1]) = acc[i][2 * jj + 1];
-#pragma unroll
-        for (int h = 0; h < 2; ++h) {
-          const f32x4 v = *(const f32x4 *)(slot + h * 1024 + lane_e * 16);
-          if (full || (rw0 + 16 * i + u_row[h] < p.M && cw0 + 32 * jj + u_col[h] < col_hi))
-            store_agent_hint<decltype(NT)::value>(out_rsrc, out_u[h],
-                                                  ((uint32_t)(16 * i) * ld_out + (uint32_t)(32 * jj)) * 4u, v);
-        }
-        // keep the scheduler from running many pairs ahead: it would park their values in registers
-        if (t % 2 == 1) __builtin_amdgcn_sched_barrier(0);
-      }
-    };
-    if (p.nt_out) store_pairs(std::true_type{});
-    else store_pairs(std::false_type{});
-    // (after the last store, not between the stores: reads and writes that alternate cost the
-    // memory more than a burst of each)
-    if (next_in) {
-      __builtin_amdgcn_sched_barrier(0);
-      in_pairs_load(std::false_type{}, ue, p.R, (uint32_t)p.ldr, 0, next_rw0, next_cw0, next_col_hi, next_full);
-    }
-    have_in = next_in;
-  } else if (to_fwd && (p.flags & kFlagFwdBf16)) {
-    // Forward slot in bfloat16: a row of the wavefront tile (64 columns) is one 128-byte line.
-    // Row of blocks by row of blocks through LDS: the lane's four rounded sums of each block
-    // (8 bytes) go to row (lane & 15), columns 16 j + 4 (lane >> 4) of a 16-row x 128-byte
-    // image, 16-byte chunk k of row r kept at position k ^ ((r >> 1) & 7) (both sides free of
-    // bank conflicts); read back linearly, each store instruction covers 8 rows x 128 bytes.
-    static_assert(FN == 4, "a wavefront tile is 64 columns wide");
-    __syncthreads();
-    char *scr = lds + wave * (kRingSlots * 1024);
-    int lane_e = lane;
-    asm volatile("" : "+v"(lane_e));
-    const int arow = lane_e & 15, aq = lane_e >> 4;
-    int w_off[FN];
-#pragma unroll
-    for (int j = 0; j < FN; ++j)
-      w_off[j] = arow * 128 + (((2 * j + (aq >> 1)) ^ ((arow >> 1) & 7)) << 4) + ((aq & 1) << 3);
-    const __amdgpu_buffer_rsrc_t o16 =
-        make_rsrc((const uint16_t *)p.fwd + (int64_t)tl.s * p.M * p.W, (uint32_t)p.M * p.W * 2u);
-    int l_row[2], l_col[2];
-    uint32_t l_off[2];
-#pragma unroll
-    for (int h = 0; h < 2; ++h) {
-      l_row[h] = 8 * h + (lane_e >> 3);
-      l_col[h] = 8 * ((lane_e & 7) ^ ((l_row[h] >> 1) & 7));
-      l_off[h] = ((uint32_t)(rw0 + l_row[h]) * (uint32_t)p.W + (uint32_t)(cw0 - col_lo + l_col[h])) * 2u;
-    }
-#pragma unroll
-    for (int i = 0; i < FM; ++i) {
-      char *img = scr + (i & 1) * 2048;
-#pragma unroll
-      for (int j = 0; j < FN; ++j) *(u32x2 *)(img + w_off[j]) = pack_bf16(acc[i][j]);
-#pragma unroll
-      for (int h = 0; h < 2; ++h) {
-        const u32x4 v = *(const u32x4 *)(img + h * 1024 + lane_e * 16);
-        if (full || (rw0 + 16 * i + l_row[h] < p.M && cw0 + l_col[h] < col_hi))
-          __builtin_amdgcn_raw_buffer_store_b128(v, o16, (int)l_off[h],
-                                                 (int)((uint32_t)(16 * i) * (uint32_t)p.W * 2u), kAuxSc1);
-      }
-      if (i % 2 == 1) __builtin_amdgcn_sched_barrier(0);
-    }
-  } else {
-  const __amdgpu_buffer_rsrc_t out_rsrc = make_rsrc(out_base, (uint32_t)p.M * ld_out * 4u);
-  // Pair by pair through LDS (the stages are free now; each wavefront uses 4 KiB of its own):
-  // written in the accumulator layout, read back linearly, stored as 8 rows x 128 bytes.
-  {
-  __syncthreads();
-  char *scr = lds + wave * (kRingSlots * 1024);
+  // ---- epilogue: agent-scope (write-through) stores of whole rows of the WORKGROUP tile.  Row
+  // block by row block, all wavefronts write their 16-row strips in the accumulator layout into
+  // one LDS image (WAVES_M strips x 16 rows x BN columns) and read it back along the rows, so that
+  // a store instruction covers 1 KiB of consecutive addresses.  What that is for: a chunk's rows start anywhere
+  // (W * 4 bytes need not be a multiple of 64), and every end of a contiguous run that falls
+  // inside a 64-byte granule costs the memory side a read-modify-write.  With 128-byte runs
+  // (8 rows per instruction) an 8192 x 4256 x 2128 problem, W = 532, took 1.5 x the time of W = 544.
+  // Two images: one barrier per row block.  Chunk k (16 bytes) of a row sits at k ^ (row & 7),
+  // which keeps both sides free of bank conflicts.
+  constexpr int kRowsPerWave = 16 / WAVES_N;
+  constexpr int kImgBytes = WAVES_M * 16 * BN * 4;
+  static_assert(2 * kImgBytes <= (kAsmLoop ? kStageBytes : NSTAGE * kStageBytes), "two images");
+  // (hand-ordered kernel: the stage no wavefront reads any more -- that of the last slab but one, or
+  // stage 1 behind a ragged end of K -- so nothing has to be waited for)
+  char *img0 = lds + (kAsmLoop ? ((ktail ? 1 : (nkf & 1)) * kStageBytes) : 0);
+  if constexpr (!kAsmLoop) __syncthreads();
   int lane_e = lane;                             // recomputed here rather than kept through the main loop
   asm volatile("" : "+v"(lane_e));
-  const PairLane ue = pair_lane(lane_e);
-  const int *u_row = ue.row, *u_col = ue.col, *u_acc = ue.acc;
-  uint32_t out_u[2];
+  // the next grid position of this workgroup (hand-ordered kernel): if it is a tile that takes an
+  // incoming partial, its accumulator blocks are requested once this tile's sums have been stored
+  bool next_in = false, next_full = false;
+  int next_rw0 = 0, next_cw0 = 0, next_col_hi = 0;
+  int blk_n, part_n, nparts_n;
+  if (kAsmLoop && MODE == kModeFused && !plain && work_item<TAIL>(p, it + 1, blk_n, part_n, nparts_n) &&
+      nparts_n == 1) {
+    Tile tn;
+    if (decode_block(p, blk_n, tn) && !((p.flags & kFlagStep0StoreOnly) && tn.s == 0)) {
+      next_in = true;
+      next_col_hi = tn.c * p.W + p.W;
+      next_rw0 = tn.mi * BM + wm * WM;
+      next_cw0 = tn.c * p.W + tn.nj * BN + wn * WN;
+      next_full = (next_rw0 + WM <= p.M) && (next_cw0 + WN <= next_col_hi);
+    }
+  }
+  const int e_row = lane_e & 15, e_q = lane_e >> 4;
+  const int w_base = (wm * 16 + e_row) * (BN * 4);     // this lane's image row
+  const bool whole = (m0 + BM <= p.M) && (n0 + BN <= col_hi);
+  // Piece u of this wavefront's share of an image: G columns at image row ir, column col.
+  auto piece = [&](int u, int G, int &ir, int &col) {
+    const int L = u * 64 + lane_e, per_row = BN / G;
+    ir = wave * kRowsPerWave + L / per_row;
+    col = (L % per_row) * G;
+  };
+  auto img_chunk = [&](const char *img, int ir, int k) {   // 16-byte chunk k of image row ir
+    return *(const f32x4 *)(img + ir * (BN * 4) + ((k ^ (ir & 7)) << 4));
+  };
+  // TO: 0 = R / C / fp32 slot (out_base), 1 = R and the fp32 slot, 2 = the bfloat16 slot,
+  // 3 = R and the bfloat16 slot, 4 = atomic adds into R (two writers)
+  auto store_tile = [&](auto NT, auto TO) {
+    constexpr int to = decltype(TO)::value;
+    const __amdgpu_buffer_rsrc_t out_rsrc = make_rsrc(out_base, (uint32_t)p.M * ld_out * 4u);
+    const float *slot_base = p.fwd + (int64_t)tl.s * p.M * p.W;
+    const __amdgpu_buffer_rsrc_t fwd_rsrc = make_rsrc(slot_base, (uint32_t)p.M * (uint32_t)p.W * 4u);
+    const __amdgpu_buffer_rsrc_t f16_rsrc =
+        make_rsrc((const uint16_t *)p.fwd + (int64_t)tl.s * p.M * p.W, (uint32_t)p.M * (uint32_t)p.W * 2u);
 #pragma unroll
-  for (int h = 0; h < 2; ++h)
-    out_u[h] = ((uint32_t)(rw0 + u_row[h]) * ld_out + (uint32_t)(cw0 - col_org + u_col[h])) * 4u;
+    for (int i = 0; i < FM; ++i) {
+      char *img = img0 + (i & 1) * kImgBytes;
 #pragma unroll
-  for (int t = 0; t < NBLK / 2; ++t) {
-    const int i = t / UJ, jj = t % UJ;
-    char *slot = scr + ((2 * t) & (kRingSlots - 1)) * 1024;
-    *(f32x4 *)(slot + u_acc[0]) = acc[i][2 * jj];
-    *(f32x4 *)(slot + u_acc[1]) = acc[i][2 * jj + 1];
+      for (int j = 0; j < FN; ++j)
+        *(f32x4 *)(img + w_base + (((wn * (WN / 4) + 4 * j + e_q) ^ (e_row & 7)) << 4)) = acc[i][j];
+      // the strips are complete (and everyone's reads of the other image, an iteration ago, done)
+      asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+      __builtin_amdgcn_s_barrier();
+      asm volatile("" ::: "memory");
+      if constexpr (to == 0 || to == 1 || to == 3) {
 #pragma unroll
-    for (int h = 0; h < 2; ++h) {
-      const uint32_t blk_off = ((uint32_t)(16 * i) * ld_out + (uint32_t)(32 * jj)) * 4u;
-      if (two_writers) {
-        // op-and-store (Sec. 4.3): the other writer adds into the same words.  One word per lane
-        // and instruction, so that an instruction covers two whole 128-byte rows of the pair.
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          const int rp = 2 * e + (lane_e >> 5);            // row position in the slot (see pair_lane)
-          const int r = h ? (rp ^ 1) : rp;                 // the row it holds ...
-          const int ar = 8 * h + r;
-          const int ac = 4 * (((lane_e & 31) >> 2) ^ r) + (lane_e & 3);   // ... and the column
-          const float v = *(const float *)(slot + h * 1024 + e * 256 + lane_e * 4);
-          if (full || (rw0 + 16 * i + ar < p.M && cw0 + 32 * jj + ac < col_hi)) {
-            float *dst = (float *)((char *)const_cast<float *>(out_base) + blk_off) +
-                         (int64_t)(rw0 + ar) * ld_out + (cw0 - col_org + ac);
-            __hip_atomic_fetch_add(dst, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        for (int u = 0; u < FN; ++u) {
+          int ir, col;
+          piece(u, 4, ir, col);
+          const f32x4 v = img_chunk(img, ir, col >> 2);
+          const int row = m0 + (ir >> 4) * WM + 16 * i + (ir & 15);
+          if (whole || (row < p.M && n0 + col < col_hi)) {
+            store_agent_hint<decltype(NT)::value>(out_rsrc, ((uint32_t)row * ld_out + (uint32_t)(n0 - col_org + col)) * 4u,
+                                                  0u, v);
+            if constexpr (to == 1)
+              store_agent_hint<decltype(NT)::value>(fwd_rsrc, ((uint32_t)row * (uint32_t)p.W + (uint32_t)(n0 - col_lo + col)) * 4u,
+                                                    0u, v);
           }
         }
-      } else {
-        const f32x4 v = *(const f32x4 *)(slot + h * 1024 + lane * 16);
-        if (full || (rw0 + 16 * i + u_row[h] < p.M && cw0 + 32 * jj + u_col[h] < col_hi))
-          store_agent(out_rsrc, out_u[h], blk_off, v);
       }
+      if constexpr (to == 2 || to == 3) {
+        // (rounded behind the LDS, not before it: accumulators of the hand-ordered kernel can go
+        // from their registers to LDS directly, but not into an arithmetic instruction)
+#pragma unroll
+        for (int u = 0; u < FN / 2; ++u) {
+          int ir, col;
+          piece(u, 8, ir, col);
+          const u32x4 v = pack_bf16(img_chunk(img, ir, col >> 2), img_chunk(img, ir, (col >> 2) + 1));
+          const int row = m0 + (ir >> 4) * WM + 16 * i + (ir & 15);
+          if (whole || (row < p.M && n0 + col < col_hi))
+            __builtin_amdgcn_raw_buffer_store_b128(
+                v, f16_rsrc, (int)(((uint32_t)row * (uint32_t)p.W + (uint32_t)(n0 - col_lo + col)) * 2u), 0, kAuxSc1);
+        }
+      }
+      if constexpr (to == 4) {
+        // op-and-store (Sec. 4.3): the other writer adds into the same words.  One word per lane
+        // and instruction: an instruction covers 256 consecutive bytes.
+#pragma unroll
+        for (int u = 0; u < 4 * FN; ++u) {
+          int ir, col;
+          piece(u, 1, ir, col);
+          const float v = *(const float *)(img + ir * (BN * 4) + (((col >> 2) ^ (ir & 7)) << 4) + (col & 3) * 4);
+          const int row = m0 + (ir >> 4) * WM + 16 * i + (ir & 15);
+          if (whole || (row < p.M && n0 + col < col_hi))
+            __hip_atomic_fetch_add(const_cast<float *>(out_base) + (int64_t)row * ld_out + (n0 - col_org + col), v,
+                                   __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
+      }
+      __builtin_amdgcn_sched_barrier(0);
     }
-    // keep the scheduler from running many pairs ahead: it would park their values in registers
-    if (t % 2 == 1) __builtin_amdgcn_sched_barrier(0);
+  };
+  using std::false_type;
+  using std::true_type;
+  constexpr std::integral_constant<int, 0> to_one{};
+  constexpr std::integral_constant<int, 1> to_r_and_slot{};
+  constexpr std::integral_constant<int, 2> to_slot16{};
+  constexpr std::integral_constant<int, 3> to_r_and_slot16{};
+  constexpr std::integral_constant<int, 4> to_atomic{};
+  if (SLOT < 0 && MODE == kModeFused && two_writers) {
+    if constexpr (SLOT < 0 && MODE == kModeFused) store_tile(false_type{}, to_atomic);
+  } else if (slot_bf16) {
+    if (to_fwd) store_tile(false_type{}, to_slot16);
+    else store_tile(false_type{}, to_r_and_slot16);
+  } else if (to_both) {
+    store_tile(true_type{}, to_r_and_slot);
+  } else if (p.nt_out) {
+    store_tile(true_type{}, to_one);
+  } else {
+    store_tile(false_type{}, to_one);
   }
+  // (after the last store, not between the stores: reads and writes that alternate cost the
+  // memory more than a burst of each)
+  if (next_in) {
+    __builtin_amdgcn_sched_barrier(0);
+    in_pairs_load(std::false_type{}, pair_lane(lane_e), p.R, (uint32_t)p.ldr, 0, next_rw0, next_cw0, next_col_hi, next_full);
   }
-  }
+  have_in = next_in;
 
   stamp(it, 3);
   if (nkf == 0) flush_pending();                 // (no main loop ran: nothing was settled on the way)
@@ -1269,167 +849,9 @@ void gemm_tile_kernel(const Plan p) {
     pending_half = tail_idx;                     // announced once the stores are acknowledged
   } else if (tracked) {
     pending_c = tl.c;
-    pending_n = min(p.pair_m, p.Mt_t - tl.mi * p.pair_m);
   }
   }  // pieces of work
   flush_pending();
-}
-
-// ---------------------------------------------------------------------------------------------
-// Unfused baseline, second kernel: the reduce-scatter's reduction (Sec. 2.3): out = C + incoming,
-// tile by tile in the same issue order, driving the same tracker and release.
-template <int BM, int BN>
-__global__ __launch_bounds__(kThreads) void reduce_tile_kernel(const Plan p) {
-  __shared__ uint32_t sh_word;
-  Tile tl;
-  int slot = 0, agent = 0;
-  const int role = decode_block(p, blockIdx.x, tl, slot, agent);
-  if (role == kRoleNone) return;
-  if (role == kRoleRelease) {
-    release_chunk(p, slot, agent, &sh_word);
-    return;
-  }
-  const Trk trk = trk_open(p);
-  const int tid = threadIdx.x;
-  const int m0 = tl.mi * BM;
-  const int col_lo = tl.c * p.W;
-  const int n0 = col_lo + tl.nj * BN;
-  const int rows = min(BM, p.M - m0);
-  const int cols4 = min(BN, col_lo + p.W - n0) >> 2;
-  const bool store_only = (p.flags & kFlagStep0StoreOnly) && tl.s == 0;
-  const bool to_fwd = (p.flags & kFlagFwdDirect) && tl.c != p.own;
-  float *out_base = to_fwd ? p.fwd + (int64_t)tl.s * p.M * p.W + (n0 - col_lo) : p.R + n0;
-  const int64_t ld_out = to_fwd ? p.W : p.ldr;
-  if (to_fwd && (p.flags & kFlagFwdBf16)) {
-    // bfloat16 forward slot: eight sums = 16 bytes per lane
-    const int cols8 = cols4 >> 1;
-    uint16_t *out16 = (uint16_t *)p.fwd + (int64_t)tl.s * p.M * p.W + (n0 - col_lo);
-    for (int e = tid; e < rows * cols8; e += kThreads) {
-      const int rr = e / cols8, cc = e - rr * cols8;
-      const int64_t row = m0 + rr;
-      const f32x4 *c = (const f32x4 *)(p.C + row * p.ldc + n0) + 2 * cc;
-      const f32x4 *r = (const f32x4 *)(p.R + row * p.ldr + n0) + 2 * cc;
-      f32x4 lo = __builtin_nontemporal_load(c), hi = __builtin_nontemporal_load(c + 1);
-      if (!store_only) {
-        lo += __builtin_nontemporal_load(r);
-        hi += __builtin_nontemporal_load(r + 1);
-      }
-      const u32x4 v = pack_bf16(lo, hi);
-      asm volatile("global_store_dwordx4 %0, %1, off sc1"
-                   : : "v"((u32x4 *)(out16 + row * p.W) + cc), "v"(v) : "memory");
-    }
-    track_tile(p, trk, tl.c);
-    return;
-  }
-  const int total = rows * cols4;
-  for (int e = tid; e < total; e += kThreads) {
-    const int rr = e / cols4, cc = e - rr * cols4;
-    const int64_t row = m0 + rr;
-    f32x4 v = __builtin_nontemporal_load((const f32x4 *)(p.C + row * p.ldc + n0) + cc);
-    if (!store_only)
-      v += __builtin_nontemporal_load((const f32x4 *)(p.R + row * p.ldr + n0) + cc);
-    store_agent((f32x4 *)(out_base + row * ld_out) + cc, v);
-  }
-  track_tile(p, trk, tl.c);
-}
-
-// The upstream neighbour's updates (the DMA updates of Sec. 4.1), stood in for on one GPU:
-// `incoming` (p.C) is added into R tile by tile with the same op-and-store atomics as the local
-// GEMM's tiles, in the same issue order, and every tile is counted in the same tracker.  With
-// the first chunk stored only (Sec. 4.4) it has no upstream update: those tiles are skipped.
-template <int BM, int BN>
-__global__ __launch_bounds__(kThreads) void upstream_update_kernel(const Plan p) {
-  const Trk trk = trk_open(p);
-  // one workgroup per grid position, or fewer workgroups walking the positions in issue order
-  for (int pos = blockIdx.x; pos < p.total_blocks; pos += gridDim.x) {
-    Tile tl;
-    int slot = 0, agent = 0;
-    if (decode_block(p, pos, tl, slot, agent) != kRoleTile) continue;
-    if ((p.flags & kFlagStep0StoreOnly) && tl.s == 0) continue;
-    const int m0 = tl.mi * BM;
-    const int col_lo = tl.c * p.W;
-    const int n0 = col_lo + tl.nj * BN;
-    const int rows = min(BM, p.M - m0);
-    const int cols = min(BN, col_lo + p.W - n0);
-    const int total = rows * cols;
-    // One word per lane, so that an atomic instruction covers whole 128-byte lines; eight loads
-    // in flight per lane before their adds go out (a workgroup would otherwise move one word per
-    // lane per memory round trip).
-    constexpr int kBatch = 8;
-    for (int e0 = threadIdx.x; e0 < total; e0 += kBatch * kThreads) {
-      float v[kBatch];
-      int64_t at[kBatch];
-#pragma unroll
-      for (int k = 0; k < kBatch; ++k) {
-        const int e = e0 + k * kThreads;
-        const int rr = e / cols, cc = e - rr * cols;
-        at[k] = (int64_t)(m0 + rr);
-        v[k] = 0.f;
-        if (e < total) v[k] = __builtin_nontemporal_load(p.C + at[k] * p.ldc + n0 + cc);
-        at[k] = at[k] * p.ldr + n0 + cc;
-      }
-#pragma unroll
-      for (int k = 0; k < kBatch; ++k)
-        if (e0 + k * kThreads < total)
-          __hip_atomic_fetch_add(p.R + at[k], v[k], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    }
-    track_tile(p, trk, tl.c);
-  }
-}
-
-// The triggered transfers, as a launch of their own (two-writer mode, where no launch can wait
-// for the other writer): workgroup (slot, agent) copies its rows of chunk order[slot] into the
-// forward slot if the chunk's ready flag is set in the bank of the launch that last completed.
-__global__ __launch_bounds__(kThreads) void release_ready_kernel(const Plan p) {
-  const int slot = blockIdx.x / p.agents, agent = blockIdx.x % p.agents;
-  if (slot > p.P - 2) return;
-  const uint32_t g = __builtin_amdgcn_readfirstlane(__hip_atomic_load(
-      p.track + 2 * trk_bank_words(p.P), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
-  const uint32_t *bank = p.track + ((g + 1u) & 1u) * trk_bank_words(p.P);   // bank (g - 1) & 1
-  int c = p.rank + slot;
-  if (c >= p.P) c -= p.P;
-  if (__hip_atomic_load(bank + p.P + c, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == 0u) return;
-  copy_chunk_rows(p, slot, c, agent * p.rows_per_agent + (int)(threadIdx.x >> 6),
-                  min(p.M, (agent + 1) * p.rows_per_agent), kThreads / 64);
-}
-
-// Clears tracker state: both banks (queue entries to empty, the rest to 0), gen, error and the
-// flags of split tiles to 0.
-__global__ void track_reset_kernel(uint32_t *track, int P) {
-  const int bank = 3 * P + 2, n = 2 * bank + 2 + kTailSlots;
-  for (int i = threadIdx.x; i < n; i += blockDim.x) {
-    const int j = i < 2 * bank ? i % bank : -1;
-    track[i] = (j >= 2 * P && j < 3 * P) ? kEmpty : 0u;
-  }
-}
-
-// One step of the ring all-gather (Sec. 2.3): a chunk of M rows x W columns moves, unchanged,
-// from the upstream neighbour's buffer into the same columns of this rank's.  One wavefront per
-// row and pass, 16 bytes per lane, four accesses in flight per lane.
-__global__ __launch_bounds__(kThreads) void ag_copy_kernel(const float *src, int64_t ld_src, float *dst,
-                                                           int64_t ld_dst, int32_t M, int32_t W) {
-  const int lane = threadIdx.x & 63;
-  const int W4 = W >> 2;
-  const int waves = (int)(gridDim.x * (blockDim.x >> 6));
-  for (int r = (int)(blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6)); r < M; r += waves) {
-    const f32x4 *s4 = (const f32x4 *)(src + (int64_t)r * ld_src);
-    f32x4 *d4 = (f32x4 *)(dst + (int64_t)r * ld_dst);
-    for (int c0 = lane; c0 < W4; c0 += 4 * 64) {
-      f32x4 v[4];
-#pragma unroll
-      for (int u = 0; u < 4; ++u)
-        if (c0 + u * 64 < W4) v[u] = __builtin_nontemporal_load(s4 + c0 + u * 64);
-#pragma unroll
-      for (int u = 0; u < 4; ++u)
-        if (c0 + u * 64 < W4) __builtin_nontemporal_store(v[u], d4 + c0 + u * 64);
-    }
-  }
-}
-
-// Copies n words of tracker state (for callers that want to read the state another array holds).
-__global__ void track_copy_kernel(const uint32_t *src, uint32_t *dst, int n) {
-  for (int i = threadIdx.x; i < n; i += blockDim.x)
-    dst[i] = __hip_atomic_load(&src[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
 }  // namespace t3k

@@ -1,0 +1,35 @@
+// How the host side launches kernels, and the tile-kernel launchers of the other translation units.
+#pragma once
+
+#include "t3.h"
+#include "t3_device.h"
+
+namespace t3k {
+
+extern thread_local int32_t last_hip_error;      // t3_last_hip_error() (t3_api.hip)
+
+// Launches `kernel` and returns what THIS launch returned: an error some earlier call left in
+// the runtime is not taken for ours.
+template <typename... KArgs>
+t3_status launch(void (*kernel)(KArgs...), dim3 grid, dim3 block, hipStream_t s, KArgs... a) {
+  void *args[] = {static_cast<void *>(&a)...};
+  const hipError_t e = hipLaunchKernel(reinterpret_cast<const void *>(kernel), grid, block, args, 0, s);
+  if (e != hipSuccess) {
+    last_hip_error = (int32_t)e;
+    return T3_ERR_HIP;
+  }
+  return T3_OK;
+}
+
+// The tile kernel by mode (fused / plain GEMM) and operand layout; defined in t3_gemm_launch.hip,
+// which is compiled once for each.  tm x tn: the workgroup tile.
+t3_status launch_fused(const Plan &q, int32_t tm, int32_t tn, hipStream_t s);
+t3_status launch_fused_kn(const Plan &q, int32_t tm, int32_t tn, hipStream_t s);
+t3_status launch_fused_km(const Plan &q, int32_t tm, int32_t tn, hipStream_t s);
+t3_status launch_fused_km_kn(const Plan &q, int32_t tm, int32_t tn, hipStream_t s);
+t3_status launch_gemm_nk(const Plan &q, int32_t tm, int32_t tn, hipStream_t s);
+t3_status launch_gemm_kn(const Plan &q, int32_t tm, int32_t tn, hipStream_t s);
+t3_status launch_gemm_km(const Plan &q, int32_t tm, int32_t tn, hipStream_t s);
+t3_status launch_gemm_km_kn(const Plan &q, int32_t tm, int32_t tn, hipStream_t s);
+
+}  // namespace t3k
