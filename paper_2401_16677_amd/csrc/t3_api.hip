@@ -252,7 +252,11 @@ TileShape workgroup_tile(const t3_problem *p, int cus, int64_t steps) {
   static const Cand kCand[] = {{{256, 256}, true, 1, 1.20, 17.0},
                                {{256, 192}, false, 1, 0.93, 13.0},
                                {{256, 128}, true, 1, 0.84, 9.0},
-                               {{128, 128}, true, 2, 1.00, 9.0}};
+                               {{128, 192}, false, 1, 0.50, 8.0},
+                               {{128, 128}, true, 2, 1.00, 9.0},
+                               {{64, 64}, true, 1, 0.16, 6.0},
+                               {{32, 64}, true, 1, 0.12, 6.0},
+                               {{32, 32}, true, 2, 0.12, 6.0}};
   const int64_t W = p->N / p->tp;
   const bool nk = p->b_layout == T3_B_NK && p->a_layout == T3_A_MK;
   const double slabs = (double)ceil_div(p->K, 64);
@@ -381,7 +385,8 @@ t3_status make_plan(const t3_problem *p, int need, const void *A, const void *B,
   // Workgroup tiles.  Over whole ring steps nothing but the counters' final values depends on
   // the tracked tile, so the tile kernel cuts a chunk as suits the chip; a range that cuts a
   // step is in units of tracked tiles, and so are the two-writer calls' counts.
-  if ((need & kTileKernel) && !two_writers && tpc_t > 0 && begin_t % tpc_t == 0 && limit_t % tpc_t == 0) {
+  const bool free_tile = (need & kTileKernel) && !two_writers && tpc_t > 0 && begin_t % tpc_t == 0 && limit_t % tpc_t == 0;
+  if (free_tile) {
     const TileShape w = workgroup_tile(p, kDefaultCus, (limit_t - begin_t) / tpc_t);
     *tm = w.m;
     *tn = w.n;
@@ -430,16 +435,28 @@ t3_status make_plan(const t3_problem *p, int need, const void *A, const void *B,
   q.tracked = (int32_t)tpc_t;
   q.flags = fused_like ? p->flags : 0u;
 
-  // XCD grouping: split a stage's Mt x Wt tiles into 8 equal blocks, one per XCD, choosing the
-  // split whose block touches the fewest A rows + B columns.  (A device with another number of
-  // XCDs runs without grouping: plain issue order inside a stage.)
+  // XCD grouping: split a stage's Mt x Wt tiles into 8 equal blocks, one per XCD, or, where they do
+  // not split or that is better, into 8 runs down the tile columns (see decode_tile).  What counts is
+  // how many A rows and B columns an XCD's L2 pulls; the A rows are the same ones in every stage, so
+  // if they stay in that L2 (half of its 4 MiB) they count once for all stages.  That is for small
+  // tiles, which are in flight for several stages at a time: with large ones the slabs of B push A
+  // out.  (A device with another number of XCDs takes the runs: order inside a stage is free.)
   q.xcd_nbm = 0;
   q.xcd_bmk = q.xcd_bnk = 0;
-  int64_t best = -1;
+  const int64_t range_steps = tpc > 0 ? ceil_div(q.limit, tpc) - q.begin / tpc : 0;
+  auto footprint = [&](double rows, double cols) {
+    const bool stays = *tm < 128 && rows * (double)p->K * 2.0 <= 2.0 * (1 << 20);
+    return (stays && range_steps > 1 ? rows / (double)range_steps : rows) + cols;
+  };
+  double best = -1.0;
+  if (*tm < 128 && tpc > 0) {
+    const double run = (double)ceil_div(tpc, kNumXcd);
+    best = run >= (double)Mt ? footprint((double)p->M, (run / (double)Mt + 0.5) * *tn) : footprint(run * *tm, 1.5 * *tn);
+  }
   for (int nbm = 1; nbm <= kNumXcd && dev.xcds == kNumXcd; nbm *= 2) {
     const int nbn = kNumXcd / nbm;
     if (Mt % nbm || Wt % nbn) continue;
-    const int64_t foot = (Mt / nbm) * *tm + (Wt / nbn) * *tn;
+    const double foot = footprint((double)(Mt / nbm) * *tm, (double)(Wt / nbn) * *tn);
     if (best < 0 || foot < best) {
       best = foot;
       q.xcd_nbm = nbm;
@@ -451,8 +468,11 @@ t3_status make_plan(const t3_problem *p, int need, const void *A, const void *B,
   q.agents = q.rows_per_agent = 0;
   // tile workgroups the device holds at once: one per compute unit, two of the smallest tile
   const int64_t resident = (int64_t)dev.cus * ((*tm == 128 && *tn == 128) ? 2 : 1);
+  // the grid spans the ring steps the range touches
+  q.stage0 = tpc > 0 ? (int32_t)(q.begin / tpc) : 0;
+  q.total_blocks = tpc > 0 && q.begin < q.limit ? (int32_t)((ceil_div(q.limit, tpc) - q.stage0) * tpc) : 0;
   // Start-up phase offsets (see stagger_start): four groups over a 12 us window, or half an
-  // estimated tile time if that is shorter, once there are tiles enough to fill the chip.
+  // estimated tile time if that is shorter, from two rounds of tiles on (one round only ends later).
   // The environment variable T3_STAGGER="groups,window_ns" overrides this ("0" turns it off).
   q.stagger_blocks = q.stagger_groups = q.stagger_ticks = 0;
   {
@@ -460,7 +480,7 @@ t3_status make_plan(const t3_problem *p, int need, const void *A, const void *B,
     double window_ns = 12000.0;
     const double tile_ns = 2.0 * *tm * *tn * (double)p->K / kCuFlopPerNs;
     if (window_ns > tile_ns / 2) window_ns = tile_ns / 2;
-    if (T < resident) g = 0;         // (T of the whole order: a range's launch is short of phases anyway)
+    if (q.total_blocks < 2 * resident || *tm < 128) g = 0;
     const StaggerEnv &env = stagger_env();
     if (env.set) {
       g = env.off ? 0 : env.groups;
@@ -473,9 +493,6 @@ t3_status make_plan(const t3_problem *p, int need, const void *A, const void *B,
     }
   }
   q.expected_done = (int32_t)(q.limit - q.begin);
-  // the grid spans the ring steps the range touches
-  q.stage0 = tpc > 0 ? (int32_t)(q.begin / tpc) : 0;
-  q.total_blocks = tpc > 0 && q.begin < q.limit ? (int32_t)((ceil_div(q.limit, tpc) - q.stage0) * tpc) : 0;
   // updates expected per element (Sec. 4.2.1): with two writers the launches of both count in
   // one bank, which closes when the tiles of both have been counted
   q.upd_first = q.upd_rest = 1;
@@ -505,21 +522,30 @@ t3_status make_plan(const t3_problem *p, int need, const void *A, const void *B,
   // Balanced tail (see the kernels' work_item): persistent launches of the tile kernel over the
   // whole issue order whose last round of grid positions would fill at most half the chip; every
   // half needs a few K-slabs, and the partial sums pass through the fp32 destination (so not
-  // through bfloat16 forward slots), each element with one writer at a time.
+  // with bfloat16 forward slots), each element with one writer at a time.
   q.tail_r = q.tail_q = 0;
-  q.tail_flags = nullptr;
+  q.tail_flags = track ? tail_flags_in(track, p->tp) : nullptr;   // (t3_gemm brings its own)
   // Ring steps in a range are as good as the whole order, a cut range is not (its positions are
   // not all tiles).
-  const bool bf16_direct = direct && (p->flags & T3_FLAG_FWD_BF16);
-  const bool default_layouts = p->b_layout == T3_B_NK && p->a_layout == T3_A_MK;
-  const bool tail_kernel = !(*tm == 128 && *tn == 256);   // (128 x 256 tiles serve cut ranges only)
-  if ((need & kTileKernel) && !two_writers && !bf16_direct && default_layouts && tail_kernel &&
-      q.total_blocks > resident && q.limit - q.begin == q.total_blocks && p->K / 64 >= kTailMinSlabs) {
+  const bool slot_bf16 = fused_like && (p->flags & T3_FLAG_FWD_BF16);
+  q.hand = free_tile && *tm >= 128 && p->b_layout == T3_B_NK && p->a_layout == T3_A_MK;
+  if (q.hand && resident == dev.cus && !slot_bf16 && q.total_blocks > resident && p->K / 64 >= kTailMinSlabs) {
     const int64_t r = q.total_blocks % resident;
     if (r > 0 && 2 * r <= resident && r <= t3k::kTailSlots) {
       q.tail_r = (int32_t)r;
       q.tail_q = (int32_t)(q.total_blocks / resident);
-      if (track) q.tail_flags = tail_flags_in(track, p->tp);   // (t3_gemm brings its own)
+    }
+  }
+  // Counting.  Groups pay where many tiles finish together; up to 32 ring steps x 8 groups, 16 x 16
+  // or 8 x 32 fit the words.
+  q.whole_chunks = !two_writers && tpc > 0 && q.begin % tpc == 0 && q.limit % tpc == 0;
+  q.sub_groups = 1;
+  q.sub_shift = 0;
+  if (q.whole_chunks && track && !q.tail_r && range_steps <= 32 && tpc >= 24) {
+    q.sub_groups = 8;
+    for (int g = 16; g <= 32 && tpc >= 8 * g && range_steps * g <= t3k::kTailSlots; g *= 2) {
+      q.sub_groups = g;
+      ++q.sub_shift;
     }
   }
   return T3_OK;
@@ -529,6 +555,8 @@ inline unsigned grid_size(const t3k::Plan &q) { return (unsigned)q.total_blocks;
 
 t3_status launch_gemm(int mode, const t3k::Plan &q, int32_t tm, int32_t tn, bool b_kn, bool a_km, hipStream_t s) {
   using namespace t3k;
+  if (tm < 128)
+    return mode == kModeFused ? launch_small_fused(q, tm, tn, b_kn, a_km, s) : launch_small_gemm(q, tm, tn, b_kn, a_km, s);
   if (mode == kModeFused)
     return a_km ? (b_kn ? launch_fused_km_kn(q, tm, tn, s) : launch_fused_km(q, tm, tn, s))
                 : (b_kn ? launch_fused_kn(q, tm, tn, s) : launch_fused(q, tm, tn, s));
@@ -639,7 +667,7 @@ t3_status t3_gemm_rs_fused_static(const t3_problem *p, const void *A, const void
   st = static_track(&track);
   if (st != T3_OK) return st;
   q.track = track;
-  if (q.tail_r) q.tail_flags = tail_flags_in(track, p->tp);
+  q.tail_flags = tail_flags_in(track, p->tp);
   hipStream_t s = static_cast<hipStream_t>(stream);
   // the array keeps the last call's contents: every call starts from a cleared tracker
   st = launch(t3k::track_reset_kernel, dim3(1), dim3(256), s, track, (int)p->tp);

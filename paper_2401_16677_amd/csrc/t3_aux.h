@@ -45,7 +45,7 @@ __global__ __launch_bounds__(kThreads) void reduce_tile_kernel(const Plan p) {
       asm volatile("global_store_dwordx4 %0, %1, off sc1"
                    : : "v"((u32x4 *)(out16 + row * p.W) + cc), "v"(v) : "memory");
     }
-    track_tile(p, trk, tl.c);
+    track_tile(p, trk, tl);
     return;
   }
   float *fwd_base = p.fwd + (int64_t)tl.s * p.M * p.W + (n0 - col_lo);
@@ -59,7 +59,7 @@ __global__ __launch_bounds__(kThreads) void reduce_tile_kernel(const Plan p) {
     if (!to_fwd) store_agent(r, v);
     if (to_fwd || to_both) store_agent((f32x4 *)(fwd_base + row * p.W) + cc, v);
   }
-  track_tile(p, trk, tl.c);
+  track_tile(p, trk, tl);
 }
 
 // The upstream neighbour's updates (the DMA updates of Sec. 4.1), stood in for on one GPU:
@@ -101,7 +101,7 @@ __global__ __launch_bounds__(kThreads) void upstream_update_kernel(const Plan p)
         if (e0 + k * kThreads < total)
           __hip_atomic_fetch_add(p.R + at[k], v[k], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
-    track_tile(p, trk, tl.c);
+    track_tile(p, trk, tl);
   }
 }
 

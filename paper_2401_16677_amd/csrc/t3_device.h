@@ -77,6 +77,10 @@ struct Plan {
   // word per split tile, 0 between launches.
   int32_t tail_r, tail_q;
   uint32_t *tail_flags;
+  // Counting (see track_issue): a chunk's tiles in sub_groups (a power of two) groups, `done` by
+  // whole chunks; sub_shift places the groups' words.
+  int32_t sub_groups, sub_shift, whole_chunks;
+  int32_t hand;                        // the hand-ordered kernel serves the launch (host side only)
   uint32_t flags;
 };
 
@@ -95,13 +99,13 @@ struct Trk {
   uint32_t *other;                                         // the bank to clear at the end
   uint32_t *gen, *error;
 };
-__device__ inline Trk trk_open(const Plan &p) {
+// the pointers of the launch that finds generation `gen_now`
+__device__ inline Trk trk_at(const Plan &p, uint32_t gen_now) {
   Trk t;
   t.gen = p.track + 2 * trk_bank_words(p.P);
   t.error = t.gen + 1;
   // (the same in every lane: made uniform so that the bank pointers live in scalar registers)
-  const uint32_t g = __builtin_amdgcn_readfirstlane(
-      __hip_atomic_load(t.gen, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+  const uint32_t g = __builtin_amdgcn_readfirstlane(gen_now);
   uint32_t *b = p.track + (g & 1u) * trk_bank_words(p.P);
   t.counter = b;
   t.ready = b + p.P;
@@ -111,27 +115,26 @@ __device__ inline Trk trk_open(const Plan &p) {
   t.other = p.track + ((g & 1u) ^ 1u) * trk_bank_words(p.P);
   return t;
 }
+// (an ordinary load: only the end of a launch changes the word, so the XCD's L2 may serve it)
+__device__ inline uint32_t trk_gen(const Plan &p) { return p.track[2 * trk_bank_words(p.P)]; }
+__device__ inline Trk trk_open(const Plan &p) { return trk_at(p, trk_gen(p)); }
 __device__ inline void trk_clear_bank(uint32_t *b, int P) {
   for (int i = 0; i < 3 * P + 2; ++i)
     __hip_atomic_store(&b[i], (i >= 2 * P && i < 3 * P) ? kEmpty : 0u, __ATOMIC_RELAXED,
                        __HIP_MEMORY_SCOPE_AGENT);
 }
-// Called by thread 0 of every workgroup that did work, as its last act; d = the value its
-// increment of `done` returned.
+// Called by thread 0 of a workgroup behind its addition to `done`; d = what that made of it.
 __device__ inline void trk_close_if_last(const Plan &p, const Trk &t, uint32_t d) {
-  if (d + 1u == (uint32_t)p.expected_done) {
+  if (d == (uint32_t)p.expected_done) {
     trk_clear_bank(t.other, p.P);
     __hip_atomic_fetch_add(t.gen, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   }
 }
-__device__ inline void trk_workgroup_done(const Plan &p, const Trk &t) {
-  trk_close_if_last(
-      p, t, __hip_atomic_fetch_add(t.done, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
-}
 
-// Index j of a tile inside its stage -> tile.  Workgroups are dealt round-robin to the 8 XCDs,
-// so workgroup j of a stage lands on XCD j % 8; that XCD gets a compact block of
-// xcd_bmk x xcd_bnk tiles which share A rows and B columns in its L2.
+// Position j of a stage -> tile.  Workgroups are dealt round-robin to the 8 XCDs: grid position b
+// runs on XCD b % 8.  If a stage's tiles split into 8 equal rectangles, XCD x gets a compact block of
+// xcd_bmk x xcd_bnk tiles which share A rows and B columns in its L2.  Otherwise it gets a run of
+// neighbouring tiles (down the columns), as long as the others' up to one tile.
 __device__ inline bool decode_tile(const Plan &p, int s, int j, Tile &tl) {
   int mi, nj;
   if (p.xcd_nbm) {
@@ -140,8 +143,12 @@ __device__ inline bool decode_tile(const Plan &p, int s, int j, Tile &tl) {
     mi = bxm * p.xcd_bmk + i % p.xcd_bmk;
     nj = bxn * p.xcd_bnk + i / p.xcd_bmk;
   } else {
-    mi = j % p.Mt;
-    nj = j / p.Mt;
+    // the stage's positions are b0 .. n - 1 counted from the last multiple of 8 before them; in
+    // front of XCD x's run come the positions of XCDs 0 .. x - 1
+    const int b0 = ((s - p.stage0) * p.tpc) & 7, n = b0 + p.tpc, jj = j + b0, x = jj & 7;
+    const int q = (n >> 3) * x + min(n & 7, x) - min(b0, x) + (jj >> 3) - (x < b0 ? 1 : 0);
+    mi = q % p.Mt;
+    nj = q / p.Mt;
   }
   const int64_t t = (int64_t)s * p.tpc + (int64_t)nj * p.Mt + mi;   // issue index
   int c = p.rank + s;
@@ -329,43 +336,70 @@ __device__ inline void copy_chunk_rows(const Plan &p, int slot, int c, int r0, i
 }
 
 // ---------------------------------------------------------------------------------------------
-// Track & trigger (Sec. 4.2).  Called by all threads of a workgroup after the tile's stores
-// have been issued.  Tile results are written with agent-scope stores; once they have been
-// acknowledged (vmcnt == 0 in every wavefront, then the barrier) the tile is counted.  A
-// device-scope release fence instead would write back the whole L2 for every tile and costs
-// several times the reduction itself.
-__device__ inline void track_count(const Plan &p, const Trk &t, int c);
-__device__ inline void track_tile(const Plan &p, const Trk &t, int c) {
+// Track & trigger (Sec. 4.2).  Tile results are written with agent-scope stores; once they have been
+// acknowledged (vmcnt == 0 in every wavefront, then a barrier) the tile is counted.  A device-scope
+// release fence instead would write back the whole L2 for every tile and costs several times the
+// reduction itself.
+//
+// Atomic adds to words of one line are done one after the other at the memory side, 20 to 30 ns
+// each: with two of them per tile (the chunk's counter and `done`) a launch of 16000 small tiles
+// took 1020 us for the counting alone.  So `done` grows by whole chunks, where the launch runs whole
+// chunks, and the tiles of a chunk are counted in sub_groups groups first, each in a word of its
+// own, eight lines apart in turn; the tile that completes a group counts the group.  (The words are those of
+// the balanced tail, which such a launch does not have, and return to 0.)
+__device__ inline uint32_t *trk_group_word(const Plan &p, int s, int g) {
+  return p.tail_flags + (((g & 7) << 5) | ((s - p.stage0) << p.sub_shift) | (g >> 3));
+}
+// By thread 0, when the tile's results are visible: requests the count.
+struct TrkCount {
+  uint32_t old, done;
+};
+__device__ inline TrkCount track_issue(const Plan &p, const Trk &t, const Tile &tl) {
+  TrkCount k;
+  uint32_t *w = p.sub_groups > 1 ? trk_group_word(p, tl.s, (tl.nj * p.Mt + tl.mi) & (p.sub_groups - 1)) : &t.counter[tl.c];
+  k.old = __hip_atomic_fetch_add(w, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  k.done = p.whole_chunks ? 0u : __hip_atomic_fetch_add(t.done, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  return k;
+}
+// By thread 0: acts on what the count returned.
+__device__ inline void track_finish(const Plan &p, const Trk &t, const Tile &tl, TrkCount k) {
+  const int c = tl.c;
+  uint32_t parts = (uint32_t)p.tpc;
+  if (p.sub_groups > 1) {
+    const int g = (tl.nj * p.Mt + tl.mi) & (p.sub_groups - 1);
+    if (k.old + 1u != (uint32_t)((p.tpc - g + p.sub_groups - 1) / p.sub_groups)) return;
+    __hip_atomic_store(trk_group_word(p, tl.s, g), 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    k.old = __hip_atomic_fetch_add(&t.counter[c], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    parts = (uint32_t)p.sub_groups;
+  }
+  // threshold = regions of the chunk x updates expected per element (Sec. 4.2.1)
+  const uint32_t upd = (uint32_t)(c == p.rank ? p.upd_first : p.upd_rest);
+  if (k.old + 1u == parts * upd) {                // the landing that reaches the threshold triggers
+    if (p.whole_chunks)
+      k.done = __hip_atomic_fetch_add(t.done, (uint32_t)p.tpc, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (p.tracked * upd != k.old + 1u)            // what the counter is read as: tracked tiles
+      __hip_atomic_store(&t.counter[c], (uint32_t)p.tracked * upd, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (c != p.own) {
+      const uint32_t pos = __hip_atomic_fetch_add(t.queue_len, 1u, __ATOMIC_RELAXED,
+                                                  __HIP_MEMORY_SCOPE_AGENT);
+      __hip_atomic_store(&t.queue[pos], (uint32_t)c, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    // The flag is what publishes.  Everything it stands for was written through the caches and has
+    // been acknowledged: the tiles before they were counted, the queue entry by the wait here.  (A
+    // release store would write back the L2 on top, in which nothing of this is left.)
+    // (queue_len alone publishes nothing: it may run ahead of the entry it reserves.)
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    __hip_atomic_store(&t.ready[c], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  } else if (p.whole_chunks) {
+    return;
+  }
+  trk_close_if_last(p, t, k.done + (p.whole_chunks ? (uint32_t)p.tpc : 1u));
+}
+// The whole of it, by all threads of a workgroup, after the tile's stores have been issued.
+__device__ inline void track_tile(const Plan &p, const Trk &t, const Tile &tl) {
   __builtin_amdgcn_s_waitcnt(kWaitAll);
   __syncthreads();
-  track_count(p, t, c);
-}
-// The counting itself, once every wavefront's stores of the tile are known to be acknowledged
-// and a barrier has passed.
-__device__ inline void track_count(const Plan &p, const Trk &t, int c) {
-  if (threadIdx.x == 0) {
-    // both increments are in flight together: one round trip at the end of a tile, not two
-    const uint32_t old = __hip_atomic_fetch_add(&t.counter[c], 1u, __ATOMIC_RELAXED,
-                                                __HIP_MEMORY_SCOPE_AGENT);
-    const uint32_t d = __hip_atomic_fetch_add(t.done, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    // threshold = regions of the chunk x updates expected per element (Sec. 4.2.1)
-    const uint32_t upd = (uint32_t)(c == p.rank ? p.upd_first : p.upd_rest);
-    if (old + 1u == (uint32_t)p.tpc * upd) {      // the landing that reaches the threshold triggers
-      if (p.tracked != p.tpc)                     // what the counter is read as: tracked tiles
-        __hip_atomic_store(&t.counter[c], (uint32_t)p.tracked * upd, __ATOMIC_RELAXED,
-                           __HIP_MEMORY_SCOPE_AGENT);
-      if (c != p.own) {
-        const uint32_t pos = __hip_atomic_fetch_add(t.queue_len, 1u, __ATOMIC_RELAXED,
-                                                    __HIP_MEMORY_SCOPE_AGENT);
-        __hip_atomic_store(&t.queue[pos], (uint32_t)c, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      }
-      // The flag is what publishes: a release store, so the queue entry above and everything this
-      // workgroup made visible before the barrier that precedes the count are ordered before it.
-      // (queue_len alone publishes nothing: it may run ahead of the entry it reserves.)
-      __hip_atomic_store(&t.ready[c], 1u, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
-    }
-    trk_close_if_last(p, t, d);
-  }
+  if (threadIdx.x == 0) track_finish(p, t, tl, track_issue(p, t, tl));
 }
 
 }  // namespace t3k

@@ -79,21 +79,22 @@ template <int OFF>
 __device__ __forceinline__ void asm_ds_read_b128(bf16x8 &dst, uint32_t addr) {
   asm volatile("ds_read_b128 %0, %1 offset:%2" : "=v"(dst) : "v"(addr), "n"(OFF));
 }
-// "The 8 + 8 operands of a k-step have landed": the wait carries them as in/out operands, so
-// that no product that uses them can be moved above it.
-__device__ __forceinline__ void asm_wait_operands(bf16x8 (&a)[8], bf16x8 (&b)[8]) {
-  asm volatile("s_waitcnt lgkmcnt(0)"
-               : "+v"(a[0]), "+v"(a[1]), "+v"(a[2]), "+v"(a[3]), "+v"(a[4]), "+v"(a[5]), "+v"(a[6]), "+v"(a[7]),
-                 "+v"(b[0]), "+v"(b[1]), "+v"(b[2]), "+v"(b[3]), "+v"(b[4]), "+v"(b[5]), "+v"(b[6]), "+v"(b[7])
-               :
-               : "memory");
+// "The operands of a k-step have landed": the wait is followed by statements that carry them as
+// in/out operands, so that no product that uses them can be moved above it.
+__device__ __forceinline__ void asm_tie(bf16x8 (&a)[8]) {
+  asm volatile("" : "+v"(a[0]), "+v"(a[1]), "+v"(a[2]), "+v"(a[3]), "+v"(a[4]), "+v"(a[5]), "+v"(a[6]), "+v"(a[7]));
 }
-__device__ __forceinline__ void asm_wait_operands(bf16x8 (&a)[8], bf16x8 (&b)[6]) {
-  asm volatile("s_waitcnt lgkmcnt(0)"
-               : "+v"(a[0]), "+v"(a[1]), "+v"(a[2]), "+v"(a[3]), "+v"(a[4]), "+v"(a[5]), "+v"(a[6]), "+v"(a[7]),
-                 "+v"(b[0]), "+v"(b[1]), "+v"(b[2]), "+v"(b[3]), "+v"(b[4]), "+v"(b[5])
-               :
-               : "memory");
+__device__ __forceinline__ void asm_tie(bf16x8 (&a)[6]) {
+  asm volatile("" : "+v"(a[0]), "+v"(a[1]), "+v"(a[2]), "+v"(a[3]), "+v"(a[4]), "+v"(a[5]));
+}
+__device__ __forceinline__ void asm_tie(bf16x8 (&a)[4]) {
+  asm volatile("" : "+v"(a[0]), "+v"(a[1]), "+v"(a[2]), "+v"(a[3]));
+}
+template <int NA, int NB>
+__device__ __forceinline__ void asm_wait_operands(bf16x8 (&a)[NA], bf16x8 (&b)[NB]) {
+  asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+  asm_tie(a);
+  asm_tie(b);
 }
 
 constexpr int kRingSlots = 4;         // 1-KiB LDS slots per wavefront for transposing pairs: two pairs
@@ -127,9 +128,9 @@ constexpr int kRingSlots = 4;         // 1-KiB LDS slots per wavefront for trans
 // one place, in fp32; 1 = in R and, in fp32, in a forward slot; 2 = forward slots in bfloat16.
 // -1: any of these, told by the flags.
 template <int BM, int BN, int WAVES_M, int WAVES_N, int NSTAGE, int MODE, int BKN, int AKM = 0, int TAIL = 0,
-          int SLOT = -1>
+          int SLOT = -1, int ASM = 0>
 __global__ __launch_bounds__(64 * WAVES_M * WAVES_N)
-__attribute__((amdgpu_waves_per_eu((BM / WAVES_M) * (BN / WAVES_N) > 8192 ? 1 : 2)))
+__attribute__((amdgpu_waves_per_eu(ASM && (BM + BN) * NSTAGE * 128 > 65536 ? 1 : 2)))
 void gemm_tile_kernel(const Plan p) {
   constexpr int NW = WAVES_M * WAVES_N;
   constexpr int WM = BM / WAVES_M, WN = BN / WAVES_N;   // wavefront tile
@@ -149,9 +150,10 @@ void gemm_tile_kernel(const Plan p) {
   static_assert(NL % MH == 0, "a slab's copies are split evenly over the first k-step's passes");
   static_assert(NSTAGE * kStageBytes <= 160 * 1024, "LDS");
 
-  // Four wavefronts of 128 x 128 (one per SIMD) run the hand-ordered main loop and add the
-  // incoming partial on the way out; B stored N x K only.
-  constexpr bool kAsmLoop = (NW == 4 && FM == 8 && FN >= 6 && NSTAGE == 2 && !BKN && !AKM);
+  // The hand-ordered main loop: four wavefronts, one per SIMD (128 x 128 tile: two), operands
+  // K-contiguous.
+  constexpr bool kAsmLoop = ASM != 0;
+  static_assert(!kAsmLoop || (NW == 4 && !BKN && !AKM), "what the hand-ordered loop is written for");
   // Their pair transpositions get LDS of their own (4 KiB per wavefront) behind the stages.
   constexpr int kScrOff = kAsmLoop ? NSTAGE * kStageBytes : 0;   // (otherwise: the epilogue's, in stage 0)
   static_assert(kScrOff + NW * kRingSlots * 1024 <= 160 * 1024, "LDS");
@@ -184,22 +186,33 @@ void gemm_tile_kernel(const Plan p) {
   const int lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wm = wave / WAVES_N, wn = wave % WAVES_N;
-  int pending_c = -1;                          // chunk of a tile whose stores are issued but not counted
+  Tile pending{0, -1, 0, 0};                   // the tile whose stores are issued but not counted (c < 0: none)
   int pending_half = -1;                       // first half of a split tile whose stores are issued but not announced
-  // to be called after a barrier that every wavefront reached with its stores acknowledged
+  // To be called after a barrier that every wavefront reached with its stores acknowledged: requests
+  // the count; finish_pending, a little later, acts on it (one round trip to the memory side, during
+  // which thread 0's wavefront would otherwise multiply nothing).
+  TrkCount counted{0u, 0u};
+  bool in_count = false;
   auto settle_pending = [&]() {
-    if (tracked && pending_c >= 0) track_count(p, trk, pending_c);
+    in_count = tracked && pending.c >= 0;
+    if (in_count && threadIdx.x == 0) counted = track_issue(p, trk, pending);
     // (relaxed, like the counting: what orders it behind the partial sums is that they were
     // written through and acknowledged before the barrier; a release would write back the L2)
     if (TAIL && pending_half >= 0 && threadIdx.x == 0)
       __hip_atomic_store(&p.tail_flags[pending_half], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    pending_c = pending_half = -1;
+    pending_half = -1;
+  };
+  auto finish_pending = [&]() {
+    if (in_count && threadIdx.x == 0) track_finish(p, trk, pending, counted);
+    in_count = false;
+    pending.c = -1;
   };
   auto flush_pending = [&]() {
-    if ((tracked && pending_c >= 0) || (TAIL && pending_half >= 0)) {
+    if ((tracked && pending.c >= 0) || (TAIL && pending_half >= 0)) {
       __builtin_amdgcn_s_waitcnt(kWaitAll);
       __syncthreads();
       settle_pending();
+      finish_pending();
     }
   };
 
@@ -359,8 +372,13 @@ void gemm_tile_kernel(const Plan p) {
 
   // NSTAGE-1 slabs are always in flight.  Past the last slab the copies are repeated into
   // stages nobody reads any more, so every wait below is for the same number of younger copies.
-  if (nkf > 0) issue_slab(0, 0);
-  if (kAsmLoop && nkf > 0) issue_slab(min(1, nkf - 1), 1);   // (its scratch is not in the stages)
+  if constexpr (kAsmLoop) {                      // (every stage is free: its scratch is elsewhere)
+#pragma unroll
+    for (int st = 0; st < NSTAGE; ++st)
+      if (st < nkf) issue_slab(st, st);
+  } else if (nkf > 0) {
+    issue_slab(0, 0);
+  }
 
   // ---- accumulators start from the incoming partial (fused) or zero.
   // Block (i, j), element e of this lane: row 16*i + (lane & 15), column 16*j + 4*(lane >> 4) + e
@@ -488,13 +506,13 @@ void gemm_tile_kernel(const Plan p) {
 
   if constexpr (kAsmLoop) {
   // ---- main loop, hand-ordered.  One wavefront per SIMD: nobody else fills the matrix pipe while
-  // this one waits, so no wait may be exposed.  Two LDS stages, two sets of operand registers.  A
-  // k-step is 64 products; the 16 operand reads of the next k-step go out one per three
-  // products, early enough to have landed when the k-step ends, and the 16 copies of the slab
-  // after next one per three products of a slab's second k-step.  One barrier per slab:
-  //   second k-step of slab t  | reads: first k-step of slab t+1  | copies: slab t+2 -> stage of t
+  // this one waits, so no wait may be exposed.  NSTAGE LDS stages, two sets of operand registers.  A
+  // k-step is FM x FN products; the FM + FN operand reads of the next k-step go out one per kGap
+  // products, early enough to have landed when the k-step ends, and the copies of the slab
+  // NSTAGE ahead one per kGap products of a slab's second k-step.  One barrier per slab:
+  //   second k-step of slab t  | reads: first k-step of slab t+1  | copies: slab t+NSTAGE -> stage of t
   //   first k-step of slab t+1 | reads: second k-step of slab t+1
-  //   wait for own reads and copies, barrier   (slab t+2 visible; all are done reading slab t+1)
+  //   wait for own reads and for slab t+2, barrier   (slab t+2 visible; all are done reading slab t+1)
   if (nkf > 0) {
     bf16x8 xa[2][FM], xb[2][FN];
     uint32_t adA[KS], adB[KS];                   // this lane's operand rows of k-step kk, stage 0
@@ -503,6 +521,8 @@ void gemm_tile_kernel(const Plan p) {
       adA[kk] = lds_base + fragA[kk];
       adB[kk] = lds_base + fragB[kk];
     }
+    constexpr int kGap = FM * FN >= 48 ? 3 : (FM * FN > 16 ? 2 : 1);
+    static_assert(kGap * (FM + FN) <= FM * FN && kGap * NL <= FM * FN, "reads and copies fit a k-step");
     // read r of a k-step's FM + FN, in the order the products need them: B block 0, A block 0,
     // the other B blocks, the other A blocks
     auto read_op = [&](auto R, auto SET, uint32_t a_addr, uint32_t b_addr) {
@@ -522,12 +542,12 @@ void gemm_tile_kernel(const Plan p) {
         constexpr int m = decltype(Mi)::value, i = m / FN, j = m % FN;
         acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(xb[cs][j], xa[cs][i], acc[i][j], 0, 0, 0);
         __builtin_amdgcn_sched_barrier(0);                    // nothing moves across: the order is as written
-        if constexpr (decltype(READS)::value && m % 3 == 0 && m / 3 < FM + FN) {
-          read_op(std::integral_constant<int, m / 3>{}, std::integral_constant<int, cs ^ 1>{}, a_addr, b_addr);
+        if constexpr (decltype(READS)::value && m % kGap == 0 && m / kGap < FM + FN) {
+          read_op(std::integral_constant<int, m / kGap>{}, std::integral_constant<int, cs ^ 1>{}, a_addr, b_addr);
           __builtin_amdgcn_sched_barrier(0);
         }
-        if constexpr (decltype(COPIES)::value && m % 3 == 1 && m / 3 < NL) {
-          issue_copies(kt_c, st_c, m / 3, m / 3 + 1);
+        if constexpr (decltype(COPIES)::value && m % kGap == (kGap > 1 ? 1 : 0) && m / kGap < NL) {
+          issue_copies(kt_c, st_c, m / kGap, m / kGap + 1);
           __builtin_amdgcn_sched_barrier(0);
         }
       });
@@ -537,28 +557,44 @@ void gemm_tile_kernel(const Plan p) {
     constexpr std::integral_constant<int, 0> set0{};
     constexpr std::integral_constant<int, 1> set1{};
 
+    // the next slab but one has landed, own LDS reads are done (fewer slabs than stages: nothing is
+    // in flight behind it)
+    const bool few = nkf < NSTAGE;
+    auto slab_ready = [&](bool drain) {
+      if (NSTAGE == 2 || drain) asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
+      else asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" : : "n"((NSTAGE - 2) * NL) : "memory");
+      __builtin_amdgcn_s_barrier();
+    };
+    auto next_stage = [](uint32_t so) {
+      so += (uint32_t)kStageBytes;
+      return so == (uint32_t)(NSTAGE * kStageBytes) ? 0u : so;
+    };
     __builtin_amdgcn_sched_barrier(0);
-    asm volatile("s_waitcnt vmcnt(%0)" : : "n"(NL) : "memory");   // slab 0 landed (slab 1 may be on its way)
+    if (few) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    else asm volatile("s_waitcnt vmcnt(%0)" : : "n"((NSTAGE - 1) * NL) : "memory");   // slab 0 landed
     __builtin_amdgcn_s_barrier();
     static_for<FM + FN>([&](auto R) { read_op(R, set0, adA[0], adB[0]); });
     kstep(set0, true_type{}, false_type{}, adA[1], adB[1], 0, 0);
-    asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
-    __builtin_amdgcn_s_barrier();                  // slab 1 visible
-    settle_pending();                              // the previous tile's stores are acknowledged too:
-                                                   //   every wavefront has just waited for vmcnt(0)
+    slab_ready(few);                               // slab 1 visible
+    settle_pending();                              // the previous tile's stores are acknowledged too: they
+                                                   //   are older than the slabs waited for
     uint32_t so = 0;                               // byte offset of the stage that holds slab kt
-    for (int kt = 0; kt < nkf - 2; ++kt) {
-      const uint32_t sn = so ^ (uint32_t)kStageBytes;
-      kstep(set1, true_type{}, true_type{}, adA[0] + sn, adB[0] + sn, kt + 2, (int)(so / kStageBytes));
+    int kt = 0;
+    for (; kt < nkf - NSTAGE; ++kt) {
+      const uint32_t sn = next_stage(so);
+      kstep(set1, true_type{}, true_type{}, adA[0] + sn, adB[0] + sn, kt + NSTAGE, (int)(so / kStageBytes));
       kstep(set0, true_type{}, false_type{}, adA[1] + sn, adB[1] + sn, 0, 0);
-      asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
-      __builtin_amdgcn_s_barrier();
+      slab_ready(false);
       so = sn;
+      if (kt == 0) finish_pending();               // (the count has come back: the wait above)
     }
-    if (nkf > 1) {                                 // slab nkf-2's second k-step, slab nkf-1's first
-      const uint32_t sn = so ^ (uint32_t)kStageBytes;
+    if (nkf <= NSTAGE) finish_pending();
+    for (; kt < nkf - 1; ++kt) {                   // the last slabs: nothing left to copy
+      const uint32_t sn = next_stage(so);
       kstep(set1, true_type{}, false_type{}, adA[0] + sn, adB[0] + sn, 0, 0);
       kstep(set0, true_type{}, false_type{}, adA[1] + sn, adB[1] + sn, 0, 0);
+      if (NSTAGE > 2 && kt < nkf - 2) slab_ready(true);
+      so = sn;
     }
     kstep(set1, false_type{}, false_type{}, 0u, 0u, 0, 0);
     __builtin_amdgcn_sched_barrier(0);
@@ -637,6 +673,7 @@ void gemm_tile_kernel(const Plan p) {
     __builtin_amdgcn_s_waitcnt(kWaitSlab & kWaitLgkm0);
     __builtin_amdgcn_s_barrier();
     settle_pending();                              // (also older: the previous tile's stores)
+    finish_pending();
     issue_slab(min(NSTAGE - 1, nkf - 1), NSTAGE - 1);
     read_u(0, 0);
 #pragma unroll
@@ -715,10 +752,17 @@ void gemm_tile_kernel(const Plan p) {
   // which keeps both sides free of bank conflicts.
   constexpr int kRowsPerWave = 16 / WAVES_N;
   constexpr int kImgBytes = WAVES_M * 16 * BN * 4;
-  static_assert(2 * kImgBytes <= (kAsmLoop ? kStageBytes : NSTAGE * kStageBytes), "two images");
-  // (hand-ordered kernel: the stage no wavefront reads any more -- that of the last slab but one, or
-  // stage 1 behind a ragged end of K -- so nothing has to be waited for)
-  char *img0 = lds + (kAsmLoop ? ((ktail ? 1 : (nkf & 1)) * kStageBytes) : 0);
+  // (hand-ordered kernel: in stages no wavefront reads any more -- all but that of the last slab, or
+  // but stage 0 behind a ragged end of K -- so nothing has to be waited for)
+  static_assert((!kAsmLoop || NSTAGE == 2 ? 2 : 1) * kImgBytes <= kStageBytes || (!kAsmLoop && 2 * kImgBytes <= NSTAGE * kStageBytes), "images");
+  char *img0 = lds, *img1 = lds + kImgBytes;
+  if constexpr (kAsmLoop && NSTAGE == 2) {
+    img0 = lds + (ktail ? 1 : (nkf & 1)) * kStageBytes;
+    img1 = img0 + kImgBytes;
+  } else if constexpr (kAsmLoop) {
+    img0 = lds + (ktail ? 1 : nkf % NSTAGE) * kStageBytes;
+    img1 = lds + (ktail ? 2 : (nkf + 1) % NSTAGE) * kStageBytes;
+  }
   if constexpr (!kAsmLoop) __syncthreads();
   int lane_e = lane;                             // recomputed here rather than kept through the main loop
   asm volatile("" : "+v"(lane_e));
@@ -761,7 +805,7 @@ void gemm_tile_kernel(const Plan p) {
         make_rsrc((const uint16_t *)p.fwd + (int64_t)tl.s * p.M * p.W, (uint32_t)p.M * (uint32_t)p.W * 2u);
 #pragma unroll
     for (int i = 0; i < FM; ++i) {
-      char *img = img0 + (i & 1) * kImgBytes;
+      char *img = (i & 1) ? img1 : img0;
 #pragma unroll
       for (int j = 0; j < FN; ++j)
         *(f32x4 *)(img + w_base + (((wn * (WN / 4) + 4 * j + e_q) ^ (e_row & 7)) << 4)) = acc[i][j];
@@ -848,7 +892,7 @@ void gemm_tile_kernel(const Plan p) {
   if (half0) {
     pending_half = tail_idx;                     // announced once the stores are acknowledged
   } else if (tracked) {
-    pending_c = tl.c;
+    pending = tl;
   }
   }  // pieces of work
   flush_pending();

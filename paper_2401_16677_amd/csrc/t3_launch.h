@@ -32,4 +32,8 @@ t3_status launch_gemm_kn(const Plan &q, int32_t tm, int32_t tn, hipStream_t s);
 t3_status launch_gemm_km(const Plan &q, int32_t tm, int32_t tn, hipStream_t s);
 t3_status launch_gemm_km_kn(const Plan &q, int32_t tm, int32_t tn, hipStream_t s);
 
+// The small-tile kernel (64 x 64, 32 x 64, 32 x 32), any layout (t3_small_launch.hip).
+t3_status launch_small_fused(const Plan &q, int32_t tm, int32_t tn, bool b_kn, bool a_km, hipStream_t s);
+t3_status launch_small_gemm(const Plan &q, int32_t tm, int32_t tn, bool b_kn, bool a_km, hipStream_t s);
+
 }  // namespace t3k
