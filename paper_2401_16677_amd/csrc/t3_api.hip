@@ -240,40 +240,39 @@ void default_tile(const t3_problem *p, int cus, int32_t *tm, int32_t *tn) {
   }
 }
 
-// The workgroup tile for `steps` whole ring steps of a problem: the shape with the least time by
-// rounds of workgroups x time of a tile.
-TileShape workgroup_tile(const t3_problem *p, int cus, int64_t steps) {
+// Which kernel computes a launch, on which workgroup tile.
+struct Choice {
+  TileShape t;
+  bool wide;
+};
+// For `steps` whole ring steps of a problem: the tile with the least time by rounds of workgroups x
+// time of a tile.  wide_ok: the wide-tile kernel may be used (sizes, see make_plan).
+Choice workgroup_tile(const t3_problem *p, int cus, int64_t steps, bool wide_ok) {
   struct Cand {
     TileShape t;
-    bool any_layout;
-    int per_cu;
-    double slab_us, ends_us;     // a K-slab of 64 / set-up and hand-over of one tile
+    int stages, per_cu;          // LDS stages of the wide-tile kernel (0: small-tile kernel); workgroups per compute unit
+    double slab_us, ends_us;     // a K-slab of 64 / the rest of a tile
   };
-  static const Cand kCand[] = {{{256, 256}, true, 1, 1.20, 17.0},
-                               {{256, 192}, false, 1, 0.93, 13.0},
-                               {{256, 128}, true, 1, 0.84, 9.0},
-                               {{128, 192}, false, 1, 0.50, 8.0},
-                               {{128, 128}, true, 2, 1.00, 9.0},
-                               {{64, 64}, true, 1, 0.16, 6.0},
-                               {{32, 64}, true, 1, 0.12, 6.0},
-                               {{32, 32}, true, 2, 0.12, 6.0}};
+  static const Cand kCand[] = {{{256, 256}, 2, 1, 1.20, 13.0}, {{256, 192}, 2, 1, 0.93, 10.0},
+                               {{256, 128}, 3, 1, 0.70, 9.0},  {{128, 192}, 3, 1, 0.50, 8.0},
+                               {{128, 128}, 2, 2, 0.80, 8.0},  {{64, 64}, 0, 1, 0.16, 6.0},
+                               {{32, 64}, 0, 1, 0.12, 6.0},    {{32, 32}, 0, 2, 0.12, 6.0}};
   const int64_t W = p->N / p->tp;
-  const bool nk = p->b_layout == T3_B_NK && p->a_layout == T3_A_MK;
-  const double slabs = (double)ceil_div(p->K, 64);
+  const int64_t slabs = ceil_div(p->K, 64);
   double best = -1.0;
-  TileShape pick = kCand[0].t;
+  Choice pick{kCand[5].t, false};
 //@FORCE
   for (const Cand &c : kCand) {
-    if (!c.any_layout && !nk) continue;
+    if (c.stages && (!wide_ok || slabs < c.stages)) continue;
     const int64_t T = ceil_div(p->M, c.t.m) * ceil_div(W, c.t.n) * steps, slots = (int64_t)cus * c.per_cu;
     double rounds = (double)ceil_div(T, slots);
-    if (nk && T > slots && T % slots && 2 * (T % slots) <= slots) rounds -= 0.5;     // balanced tail
+    if (c.stages && c.per_cu == 1 && T > slots && T % slots && 2 * (T % slots) <= slots) rounds -= 0.5;   // balanced tail
     // (a compute unit with one 128 x 128 tile instead of two has it done in 0.6 of the time)
     const double alone = c.per_cu == 2 && T <= cus ? 0.6 : 1.0;
-    const double us = rounds * alone * (c.ends_us + c.slab_us * slabs);
+    const double us = rounds * alone * (c.ends_us + c.slab_us * (double)slabs);
     if (best < 0 || us < best * 0.999) {
       best = us;
-      pick = c.t;
+      pick = {c.t, c.stages != 0};
     }
   }
   return pick;
@@ -385,11 +384,19 @@ t3_status make_plan(const t3_problem *p, int need, const void *A, const void *B,
   // Workgroup tiles.  Over whole ring steps nothing but the counters' final values depends on
   // the tracked tile, so the tile kernel cuts a chunk as suits the chip; a range that cuts a
   // step is in units of tracked tiles, and so are the two-writer calls' counts.
+  bool wide = false;
   const bool free_tile = (need & kTileKernel) && !two_writers && tpc_t > 0 && begin_t % tpc_t == 0 && limit_t % tpc_t == 0;
   if (free_tile) {
-    const TileShape w = workgroup_tile(p, kDefaultCus, (limit_t - begin_t) / tpc_t);
-    *tm = w.m;
-    *tn = w.n;
+    // (the wide-tile kernel marks what lies outside by buffer offsets from 2^31 on, so every array it
+    // addresses, counted to the end of its last tile, has to fit 2 GiB)
+    const int64_t kMost = 1ll << 31, ld_out = p->ldr > p->ldc ? p->ldr : p->ldc;
+    const bool fits = (p->a_layout == T3_A_KM ? p->K : p->M) * p->lda * 2 <= kMost &&
+                      (p->b_layout == T3_B_KN ? p->K : p->N) * p->ldb * 2 <= kMost &&
+                      ((int64_t)p->M + 256) * ((need & kNeedC) ? p->ldc : p->ldr) * 4 <= kMost && ld_out >= 0;
+    const Choice w = workgroup_tile(p, kDefaultCus, (limit_t - begin_t) / tpc_t, fits);
+    *tm = w.t.m;
+    *tn = w.t.n;
+    wide = w.wide;
   }
   const int64_t Mt = ceil_div(p->M, *tm);
   Wt = ceil_div(W, *tn);
@@ -528,8 +535,8 @@ t3_status make_plan(const t3_problem *p, int need, const void *A, const void *B,
   // Ring steps in a range are as good as the whole order, a cut range is not (its positions are
   // not all tiles).
   const bool slot_bf16 = fused_like && (p->flags & T3_FLAG_FWD_BF16);
-  q.hand = free_tile && *tm >= 128 && p->b_layout == T3_B_NK && p->a_layout == T3_A_MK;
-  if (q.hand && resident == dev.cus && !slot_bf16 && q.total_blocks > resident && p->K / 64 >= kTailMinSlabs) {
+  q.wide = wide;
+  if (wide && resident == dev.cus && !slot_bf16 && q.total_blocks > resident && p->K / 64 >= kTailMinSlabs) {
     const int64_t r = q.total_blocks % resident;
     if (r > 0 && 2 * r <= resident && r <= t3k::kTailSlots) {
       q.tail_r = (int32_t)r;
@@ -555,6 +562,16 @@ inline unsigned grid_size(const t3k::Plan &q) { return (unsigned)q.total_blocks;
 
 t3_status launch_gemm(int mode, const t3k::Plan &q, int32_t tm, int32_t tn, bool b_kn, bool a_km, hipStream_t s) {
   using namespace t3k;
+  if (q.wide) {
+    Plan g = q;
+    if (mode != kModeFused) {
+      g.track = nullptr;                // the plain GEMM: C through R
+      g.flags = 0;
+      g.ldr = q.ldc;
+    }
+    return a_km ? (b_kn ? launch_wide_km_kn(g, tm, tn, s) : launch_wide_km(g, tm, tn, s))
+                : (b_kn ? launch_wide_kn(g, tm, tn, s) : launch_wide_nk(g, tm, tn, s));
+  }
   if (tm < 128)
     return mode == kModeFused ? launch_small_fused(q, tm, tn, b_kn, a_km, s) : launch_small_gemm(q, tm, tn, b_kn, a_km, s);
   if (mode == kModeFused)

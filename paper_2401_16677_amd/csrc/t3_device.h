@@ -80,7 +80,7 @@ struct Plan {
   // Counting (see track_issue): a chunk's tiles in sub_groups (a power of two) groups, `done` by
   // whole chunks; sub_shift places the groups' words.
   int32_t sub_groups, sub_shift, whole_chunks;
-  int32_t hand;                        // the hand-ordered kernel serves the launch (host side only)
+  int32_t wide;                        // the wide-tile kernel serves the launch (host side only)
   uint32_t flags;
 };
 
@@ -354,10 +354,12 @@ __device__ inline uint32_t *trk_group_word(const Plan &p, int s, int g) {
 struct TrkCount {
   uint32_t old, done;
 };
+__device__ inline uint32_t *track_word(const Plan &p, const Trk &t, const Tile &tl) {     // what counts this tile
+  return p.sub_groups > 1 ? trk_group_word(p, tl.s, (tl.nj * p.Mt + tl.mi) & (p.sub_groups - 1)) : &t.counter[tl.c];
+}
 __device__ inline TrkCount track_issue(const Plan &p, const Trk &t, const Tile &tl) {
   TrkCount k;
-  uint32_t *w = p.sub_groups > 1 ? trk_group_word(p, tl.s, (tl.nj * p.Mt + tl.mi) & (p.sub_groups - 1)) : &t.counter[tl.c];
-  k.old = __hip_atomic_fetch_add(w, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  k.old = __hip_atomic_fetch_add(track_word(p, t, tl), 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   k.done = p.whole_chunks ? 0u : __hip_atomic_fetch_add(t.done, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   return k;
 }

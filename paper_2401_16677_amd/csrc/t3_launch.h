@@ -21,8 +21,9 @@ t3_status launch(void (*kernel)(KArgs...), dim3 grid, dim3 block, hipStream_t s,
   return T3_OK;
 }
 
-// The tile kernel by mode (fused / plain GEMM) and operand layout; defined in t3_gemm_launch.hip,
-// which is compiled once for each.  tm x tn: the workgroup tile.
+// The tile kernel of tile ranges that cut a ring step, of two writers, and of what the others do not take, by
+// mode (fused / plain GEMM) and operand layout; defined in t3_gemm_launch.hip, which is compiled
+// once for each.  tm x tn: the workgroup tile.
 t3_status launch_fused(const Plan &q, int32_t tm, int32_t tn, hipStream_t s);
 t3_status launch_fused_kn(const Plan &q, int32_t tm, int32_t tn, hipStream_t s);
 t3_status launch_fused_km(const Plan &q, int32_t tm, int32_t tn, hipStream_t s);
@@ -31,6 +32,12 @@ t3_status launch_gemm_nk(const Plan &q, int32_t tm, int32_t tn, hipStream_t s);
 t3_status launch_gemm_kn(const Plan &q, int32_t tm, int32_t tn, hipStream_t s);
 t3_status launch_gemm_km(const Plan &q, int32_t tm, int32_t tn, hipStream_t s);
 t3_status launch_gemm_km_kn(const Plan &q, int32_t tm, int32_t tn, hipStream_t s);
+
+// The wide-tile kernel by operand layout (t3_wide_launch.hip); q.track == nullptr: the plain GEMM.
+t3_status launch_wide_nk(const Plan &q, int32_t tm, int32_t tn, hipStream_t s);
+t3_status launch_wide_kn(const Plan &q, int32_t tm, int32_t tn, hipStream_t s);
+t3_status launch_wide_km(const Plan &q, int32_t tm, int32_t tn, hipStream_t s);
+t3_status launch_wide_km_kn(const Plan &q, int32_t tm, int32_t tn, hipStream_t s);
 
 // The small-tile kernel (64 x 64, 32 x 64, 32 x 32), any layout (t3_small_launch.hip).
 t3_status launch_small_fused(const Plan &q, int32_t tm, int32_t tn, bool b_kn, bool a_km, hipStream_t s);

@@ -1,0 +1,560 @@
+// The tile kernel for problems that fill the chip: persistent workgroups of four wavefronts (2 x 2),
+// tiles of 32 FM x 32 FN, v_mfma_f32_16x16x32_bf16 with a hand-ordered main loop, any operand layout.
+//
+// What bounds it.  A 256 x 256 tile is 2048 clocks of products per K-slab of 64; its slab copies
+// come at 64 bytes/clock out of the XCD's L2 and at whatever the memory gives where they miss, and
+// the reduction adds 512 KiB of HBM traffic per tile (incoming partial in, sums out).  One wavefront
+// per SIMD: nobody else fills the matrix pipe while it waits, so everything is arranged for it
+// never to wait:
+//
+//  - The slabs of all the pieces of work of a workgroup are ONE stream of global -> LDS copies, NSTAGE
+//    slabs ahead of the products, across the ends of tiles: while a tile's last slabs are multiplied
+//    and its results leave, the next tile's first slabs arrive.  A tile costs no fill of the pipeline.
+//  - Accumulators start from zero.  The incoming partial (Sec. 4.3) is requested PRE row blocks of it
+//    during the tile's last NSTAGE slabs and the rest right behind them, into registers (operands'
+//    and spare ones), in the layout the results leave in, and is added on the way out.
+//  - Results go row block by row block through an LDS image of its own and leave in whole rows of
+//    the tile.  (A chunk's rows start anywhere; every run of addresses that ends inside a 64-byte
+//    granule costs the memory side a read-modify-write: 8192 x 4256 x 128, chunks of 532 columns,
+//    stored to R and slots took 224 us in 128-byte runs, 134 us in rows, 88 us where 544 columns.)
+//  - The count of a tile is requested when its stores are known to be acknowledged, in the next
+//    tile's main loop, and acted on a slab later.
+//
+// Copies, incoming partial and results are buffer accesses: rows past M, columns past the chunk and
+// K past its end are addresses past the buffer, read as zeros and not written; no access is
+// conditional, so the number of accesses in flight is always known.  (Addresses past the buffer:
+// kOob = 2^31 plus anything, with buffers of at most 2^31 bytes: the host sees to that.)
+//
+// Included by the launch units only.
+#pragma once
+
+#include "t3_gemm.h"
+
+namespace t3k {
+
+constexpr uint32_t kOob = 0x80000000u;
+
+__device__ __forceinline__ void asm_tie(u32x2 (&a)[8]) {
+  asm volatile("" : "+v"(a[0]), "+v"(a[1]), "+v"(a[2]), "+v"(a[3]), "+v"(a[4]), "+v"(a[5]), "+v"(a[6]), "+v"(a[7]));
+}
+__device__ __forceinline__ void asm_tie(u32x2 (&a)[6]) {
+  asm volatile("" : "+v"(a[0]), "+v"(a[1]), "+v"(a[2]), "+v"(a[3]), "+v"(a[4]), "+v"(a[5]));
+}
+__device__ __forceinline__ void asm_tie(u32x2 (&a)[4]) {
+  asm volatile("" : "+v"(a[0]), "+v"(a[1]), "+v"(a[2]), "+v"(a[3]));
+}
+__device__ __forceinline__ void asm_accumulator(f32x4 &v) { asm volatile("" : "+a"(v)); }
+template <int OFF>
+__device__ __forceinline__ void asm_ds_read_tr(u32x2 &dst, uint32_t addr) {
+  asm volatile("ds_read_b64_tr_b16 %0, %1 offset:%2" : "=v"(dst) : "v"(addr), "n"(OFF));
+}
+
+// The operands of one side for a k-step of 32: F blocks of 16 rows, K-contiguous (one 16-byte read
+// each) or transposed (TR: two transposing reads of 8 bytes each).
+template <int F, bool TR>
+struct Operands;
+template <int F>
+struct Operands<F, false> {
+  static constexpr int kReads = F;
+  bf16x8 v[F];
+  __device__ __forceinline__ void tie() { asm_tie(v); }
+  template <int I>
+  __device__ __forceinline__ bf16x8 get() const { return v[I]; }
+};
+template <int F>
+struct Operands<F, true> {
+  static constexpr int kReads = 2 * F;
+  u32x2 lo[F], hi[F];
+  __device__ __forceinline__ void tie() {
+    asm_tie(lo);
+    asm_tie(hi);
+  }
+  template <int I>
+  __device__ __forceinline__ bf16x8 get() const {
+    return __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo[I], hi[I], 0, 1, 2, 3));
+  }
+};
+
+// A piece of work: a tile, or one half of K of it (balanced tail).
+struct Piece {
+  Tile tl;
+  int k0, nf, ns;      // first K-slab, full slabs, slabs with a ragged last one
+  int half, idx;       // 0: whole tile, 1 / 2: first / second half of split tile idx
+};
+__device__ inline bool get_piece(const Plan &p, int it, Piece &w) {
+  int blk, part, nparts;
+  if (!work_item<1>(p, it, blk, part, nparts)) return false;
+  // (the same in every lane: said so, so that it lives in scalar registers)
+  blk = __builtin_amdgcn_readfirstlane(blk);
+  part = __builtin_amdgcn_readfirstlane(part);
+  nparts = __builtin_amdgcn_readfirstlane(nparts);
+  decode_block(p, blk, w.tl);                    // (launches of whole ring steps: every position is a tile)
+  const int slabs = p.K / kBK, per = slabs / nparts;
+  w.k0 = part * per;
+  w.nf = part == nparts - 1 ? slabs - w.k0 : per;
+  w.ns = w.nf + (part == nparts - 1 && p.K % kBK ? 1 : 0);
+  w.half = nparts == 2 ? 1 + part : 0;
+  w.idx = blk - p.tail_q * (int)gridDim.x;
+  return true;
+}
+
+template <int FM, int FN, int NSTAGE, int NIMG, int PRE, int DEPTH, int BKN, int AKM>
+__global__ __launch_bounds__(256)
+__attribute__((amdgpu_waves_per_eu((32 * (FM + FN) * 128 * NSTAGE + NIMG * 4096 * FN) <= 80 * 1024 ? 2 : 1)))
+void wide_tile_kernel(const Plan p) {
+  constexpr int BM = 32 * FM, BN = 32 * FN, WM = 16 * FM, WN = 16 * FN;
+  constexpr int NA = BM / kRPC / 4, NB = BN / kRPC / 4, NL = NA + NB;   // 1-KiB copies per wavefront and slab
+  constexpr int kStageBytes = (BM + BN) * kRowBytes, kBOff = BM * kRowBytes;
+  constexpr int kImgBytes = 2 * 16 * BN * 4, kImgOff = NSTAGE * kStageBytes;
+  static_assert(kImgOff + NIMG * kImgBytes <= 160 * 1024 && (NSTAGE == 2 || NSTAGE == 3), "LDS");
+  constexpr bool kOneWave = kImgOff + NIMG * kImgBytes > 80 * 1024;     // per SIMD: 512 registers
+  static_assert(PRE <= DEPTH && DEPTH <= FM && NL + PRE * FN < 64, "");
+  __shared__ __attribute__((aligned(1024))) char lds[kImgOff + NIMG * kImgBytes];
+
+  const bool tracked = p.track != nullptr;       // (no tracker: the plain GEMM)
+  Trk trk;
+  if (tracked) trk = trk_open(p);
+  if (p.stagger_groups > 1) stagger_start(p);
+
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+  const int wm = wave >> 1, wn = wave & 1;
+  const int ktail = p.K % kBK;
+  const uint32_t lds_base = (uint32_t)(uintptr_t)(lds_void_ptr)lds;
+
+  // ---- tracking, deferred into the next piece's main loop
+  Tile pending{0, -1, 0, 0};
+  int pending_half = -1;
+  // The count's request is inline assembly: the compiler, were it to know of a value on its way into a
+  // register across iterations of the main loop, would wait for every access in flight wherever
+  // paths meet.  It is used behind a wait for younger copies.
+  uint32_t count_old = 0;
+  bool in_count = false;
+  auto settle = [&]() {                          // behind a barrier, stores acknowledged
+    in_count = pending.c >= 0;
+    if (in_count && threadIdx.x == 0) {
+      uint32_t *w = track_word(p, trk, pending);
+      asm volatile("global_atomic_add %0, %1, %2, %3 sc0" : "+v"(count_old) : "v"(0), "v"(1), "s"(w) : "memory");
+    }
+    if (pending_half >= 0 && threadIdx.x == 0)
+      __hip_atomic_store(&p.tail_flags[pending_half], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    pending_half = -1;
+  };
+  auto finish = [&]() {
+    if (in_count && threadIdx.x == 0) {
+      track_finish(p, trk, pending, TrkCount{count_old, 0u});
+      __builtin_amdgcn_s_waitcnt(kWaitVm0);      // (nothing of it in flight where paths meet again)
+    }
+    in_count = false;
+    pending.c = -1;
+  };
+  auto stamp = [&](int it, int k) {
+    if (p.timeline && threadIdx.x == 0 && (int)blockIdx.x < p.timeline_wgs && it < kTimelineItems)
+      p.timeline[((size_t)blockIdx.x * kTimelineItems + it) * 4 + k] = wall_clock64();
+  };
+
+  // ---- the copy stream.  Copy q of a wavefront and operand fills 1 KiB of the operand's region of a
+  // stage: eight rows of 64 K-contiguous bf16, or k-rows of a transposed operand (layouts and
+  // swizzles as in gemm_tile_kernel).  off*: this lane's byte offsets for the stream's current piece.
+  uint32_t offA[NA], offB[NB];
+  auto descriptor = [](const void *base, int64_t bytes) {        // what make_rsrc makes, for inline assembly
+    const uint64_t a = (uint64_t)(uintptr_t)base;
+    return u32x4{(uint32_t)a, (uint32_t)(a >> 32), (uint32_t)bytes, 0x00020000u};
+  };
+  const u32x4 descA = descriptor(p.A, (AKM ? p.K : p.M) * p.lda * 2), descB = descriptor(p.B, (BKN ? p.K : p.N) * p.ldb * 2);
+  constexpr int kARow = BM * 2, kBRow = BN * 2;  // bytes of a k-row of a transposed operand's region
+  auto sw_mask = [](int blocks) { return (blocks % 8 == 0 ? 8 : 4) - 1; };
+  auto k_chunk = [&](int q) { return (lane % kCPR) ^ swz(q * kRPC + lane / kCPR); };   // (K-contiguous) chunk of copy q
+  auto tr_at = [&](int L, int row_bytes, int mask, int &k, int &col) {                 // (transposed) k-row, column
+    const int cp = (L % row_bytes) / 16;
+    k = L / row_bytes;
+    const int sw = ((k & 3) | (((k >> 3) & 1) << 2)) & mask;
+    col = (((cp >> 1) ^ sw) * 2 + (cp & 1)) * 8;
+  };
+  int st_k0 = 0, st_nf = 0, st_koff = 0;         // the stream's piece: first slab, full slabs, where its walk starts
+  auto stream_to = [&](const Piece &w) {
+    const int m0 = w.tl.mi * BM, col_lo = w.tl.c * p.W, col_hi = col_lo + p.W, n0 = col_lo + w.tl.nj * BN;
+#pragma unroll
+    for (int q = 0; q < NA; ++q) {
+      if (AKM) {
+        int k, col;
+        tr_at((wave * NA + q) * 1024 + lane * 16, kARow, sw_mask(BM / 16), k, col);
+        offA[q] = m0 + col < p.M ? (uint32_t)(k * (int)p.lda + m0 + col) * 2u : kOob;
+      } else {
+        const int row = m0 + wave * (BM / 4) + q * kRPC + lane / kCPR;
+        offA[q] = row < p.M ? (uint32_t)(row * (int)p.lda + k_chunk(q) * 8) * 2u : kOob;
+      }
+    }
+#pragma unroll
+    for (int q = 0; q < NB; ++q) {
+      if (BKN) {
+        int k, col;
+        tr_at((wave * NB + q) * 1024 + lane * 16, kBRow, sw_mask(BN / 16), k, col);
+        offB[q] = n0 + col < col_hi ? (uint32_t)(k * (int)p.ldb + n0 + col) * 2u : kOob;
+      } else {
+        const int row = n0 + wave * (BN / 4) + q * kRPC + lane / kCPR;
+        offB[q] = row < col_hi ? (uint32_t)(row * (int)p.ldb + k_chunk(q) * 8) * 2u : kOob;
+      }
+    }
+    st_k0 = w.k0;
+    st_nf = w.nf;
+    // K walks start at another slab on every XCD (p.k_groups of them) and wrap around: the chip reads as many
+    // K ranges at a time instead of one, which spreads the traffic over the memory channels
+    st_koff = p.k_groups > 1 ? (int)(((uint32_t)(blockIdx.x % (uint32_t)p.k_groups) * (uint32_t)w.nf) / (uint32_t)p.k_groups) : 0;
+  };
+  auto stream_ragged = [&]() {                   // the stream's last slab ends with K: nothing behind it
+    if constexpr (!AKM && !BKN) {
+#pragma unroll
+      for (int q = 0; q < NA; ++q) offA[q] = k_chunk(q) * 8 < ktail ? offA[q] : kOob;
+#pragma unroll
+      for (int q = 0; q < NB; ++q) offB[q] = k_chunk(q) * 8 < ktail ? offB[q] : kOob;
+    }
+  };
+  auto stream_end = [&]() {
+#pragma unroll
+    for (int q = 0; q < NA; ++q) offA[q] = kOob;
+#pragma unroll
+    for (int q = 0; q < NB; ++q) offB[q] = kOob;
+  };
+#pragma clang diagnostic push
+#pragma clang diagnostic ignored "-Winline-asm"
+  auto copy_one = [&](auto Q, uint32_t so, uint32_t soffA, uint32_t soffB) {
+    constexpr int q = decltype(Q)::value;
+    constexpr bool a = q < NA;
+    const uint32_t dst = lds_base + so + (a ? wave * (NA * 1024) + q * 1024 : kBOff + wave * (NB * 1024) + (q - NA) * 1024);
+    const uint32_t off = a ? offA[a ? q : 0] : offB[a ? 0 : q - NA], soff = a ? soffA : soffB;
+    const u32x4 desc = a ? descA : descB;
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds"
+                 : : "s"(dst), "v"(off), "s"(desc), "s"(soff) : "memory", "m0");
+  };
+#pragma clang diagnostic pop
+  auto slab_offs = [&](int j, uint32_t &a, uint32_t &b) {          // slab j of the stream's piece
+    int s = j;
+    if (j < st_nf) {
+      s = j + st_koff;
+      if (s >= st_nf) s -= st_nf;
+    }
+    s = __builtin_amdgcn_readfirstlane(s + st_k0);
+    a = (uint32_t)s * (AKM ? (uint32_t)p.lda * (kBK * 2) : (uint32_t)kRowBytes);
+    b = (uint32_t)s * (BKN ? (uint32_t)p.ldb * (kBK * 2) : (uint32_t)kRowBytes);
+  };
+
+  // ---- operand addresses (see gemm_tile_kernel)
+  const int fr = lane & 15, fq = lane >> 4, fs = swz(fr);
+  uint32_t adA[2], adB[2];                       // (K-contiguous) this lane's row of k-step kk
+#pragma unroll
+  for (int kk = 0; kk < 2; ++kk) {
+    const uint32_t pos = ((4 * kk + fq) ^ fs) * 16;
+    adA[kk] = lds_base + (AKM ? (8 * fq + (fr >> 2)) * kARow + (fr & 3) * 8 : (wm * WM + fr) * kRowBytes + pos);
+    adB[kk] = lds_base + kBOff + (BKN ? (8 * fq + (fr >> 2)) * kBRow + (fr & 3) * 8 : (wn * WN + fr) * kRowBytes + pos);
+  }
+  uint32_t colA[AKM ? FM : 1], colB[BKN ? FN : 1];     // (transposed) byte position of block i's 32-byte piece
+  if constexpr (AKM) {
+#pragma unroll
+    for (int i = 0; i < FM; ++i)
+      colA[i] = ((wm * FM + i) ^ (((fr >> 2) | ((fq & 1) << 2)) & sw_mask(BM / 16))) << 5;
+  }
+  if constexpr (BKN) {
+#pragma unroll
+    for (int j = 0; j < FN; ++j)
+      colB[j] = ((wn * FN + j) ^ (((fr >> 2) | ((fq & 1) << 2)) & sw_mask(BN / 16))) << 5;
+  }
+
+  using OpA = Operands<FM, AKM != 0>;
+  using OpB = Operands<FN, BKN != 0>;
+  OpA xa[2];
+  OpB xb[2];
+  constexpr int NR = OpA::kReads + OpB::kReads, RA = AKM ? 2 : 1, RB = BKN ? 2 : 1;
+  constexpr int NP = FM * FN;                    // products of a k-step
+  constexpr int kGap = NP - 6 >= 3 * NR ? 3 : (NP - 6 >= 2 * NR ? 2 : 1);       // one operand read per kGap products,
+  constexpr int kGapC = NP >= 3 * NL ? 3 : (NP >= 2 * NL ? 2 : 1);              //   one copy per kGapC
+  static_assert(kGap * NR <= NP && kGapC * NL <= NP, "reads and copies fit a k-step");
+  // read r of a k-step, in the order the products need them: B block 0, A block 0, the other B
+  // blocks, the other A blocks
+  auto read_a = [&](auto I, auto H, auto SET, auto KK, uint32_t a_addr) {
+    constexpr int i = decltype(I)::value, set = decltype(SET)::value, kk = decltype(KK)::value;
+    if constexpr (!AKM) asm_ds_read_b128<i * 16 * kRowBytes>(xa[set].v[i], a_addr);
+    else if constexpr (decltype(H)::value == 0) asm_ds_read_tr<32 * kk * kARow>(xa[set].lo[i], a_addr + colA[i]);
+    else asm_ds_read_tr<(32 * kk + 4) * kARow>(xa[set].hi[i], a_addr + colA[i]);
+  };
+  auto read_b = [&](auto J, auto H, auto SET, auto KK, uint32_t b_addr) {
+    constexpr int j = decltype(J)::value, set = decltype(SET)::value, kk = decltype(KK)::value;
+    if constexpr (!BKN) asm_ds_read_b128<j * 16 * kRowBytes>(xb[set].v[j], b_addr);
+    else if constexpr (decltype(H)::value == 0) asm_ds_read_tr<32 * kk * kBRow>(xb[set].lo[j], b_addr + colB[j]);
+    else asm_ds_read_tr<(32 * kk + 4) * kBRow>(xb[set].hi[j], b_addr + colB[j]);
+  };
+  auto read_op = [&](auto R, auto SET, auto KK, uint32_t a_addr, uint32_t b_addr) {
+    constexpr int r = decltype(R)::value;
+    if constexpr (r < RB) read_b(std::integral_constant<int, 0>{}, std::integral_constant<int, r>{}, SET, KK, b_addr);
+    else if constexpr (r < RB + RA) read_a(std::integral_constant<int, 0>{}, std::integral_constant<int, r - RB>{}, SET, KK, a_addr);
+    else if constexpr (r < RA + RB * FN)
+      read_b(std::integral_constant<int, (r - RA) / RB>{}, std::integral_constant<int, (r - RA) % RB>{}, SET, KK, b_addr);
+    else
+      read_a(std::integral_constant<int, (r - RB * FN) / RA>{}, std::integral_constant<int, (r - RB * FN) % RA>{}, SET, KK, a_addr);
+  };
+  f32x4 acc[FM][FN];
+#pragma unroll
+  for (int i = 0; i < FM; ++i)
+#pragma unroll
+    for (int j = 0; j < FN; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+  // One k-step: the products of operand set CS, k-step KK's operands of the stage at `sr` into the
+  // other set, and (COPIES) the stream's slab at (ca, cb) into the stage at `sc`.
+  auto kstep = [&](auto CS, auto KK, auto COPIES, uint32_t sr, uint32_t sc, uint32_t ca, uint32_t cb) {
+    constexpr int cs = decltype(CS)::value, kk = decltype(KK)::value;
+    const uint32_t a_addr = adA[AKM ? 0 : kk] + sr, b_addr = adB[BKN ? 0 : kk] + sr;
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");            // this k-step's operands have landed
+    xa[cs].tie();
+    xb[cs].tie();
+    if constexpr (kOneWave) {                    // (accumulators: the accumulation half of the register file)
+#pragma unroll
+      for (int i = 0; i < FM; ++i)
+#pragma unroll
+        for (int j = 0; j < FN; ++j) asm_accumulator(acc[i][j]);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    static_for<NP>([&](auto Mi) {
+      constexpr int m = decltype(Mi)::value, i = m / FN, j = m % FN;
+      acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(xb[cs].template get<j>(), xa[cs].template get<i>(), acc[i][j], 0, 0, 0);
+      __builtin_amdgcn_sched_barrier(0);                          // nothing moves across: the order is as written
+      if constexpr (m % kGap == 0 && m / kGap < NR) {
+        read_op(std::integral_constant<int, m / kGap>{}, std::integral_constant<int, cs ^ 1>{}, KK, a_addr, b_addr);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      if constexpr (decltype(COPIES)::value && m % kGapC == (kGapC > 1 ? 1 : 0) && m / kGapC < NL) {
+        copy_one(std::integral_constant<int, m / kGapC>{}, sc, ca, cb);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    });
+  };
+  using std::false_type;
+  using std::true_type;
+  constexpr std::integral_constant<int, 0> c0{};
+  constexpr std::integral_constant<int, 1> c1{};
+
+  // ---- the way out.  Image of a row block: 2 strips (wm) x 16 rows x BN columns; chunk k (16 bytes) of
+  // image row ir at k ^ (ir & 7) (both sides free of bank conflicts).  Wavefront w reads rows 8 w .. 8 w + 7
+  // in FN accesses of 64 consecutive chunks; access u is at image row ir(u), column col(u) of the tile,
+  // and the rows of access u + UB are those of access u plus RS.
+  constexpr int kRowCh = BN / 4, UB = BN == 192 ? 3 : 1, RS = UB * 64 / kRowCh;
+  static_assert(UB * 64 == RS * kRowCh && FN % UB == 0, "");
+  auto strip_row = [](int ir) { return (ir >> 4) * WM + (ir & 15); };   // image row -> tile row, row block 0
+
+  Piece cur;
+  get_piece(p, 0, cur);                          // (the grid is no larger than the number of pieces)
+  stream_to(cur);
+#pragma unroll
+  for (int j = 0; j < NSTAGE; ++j) {
+    uint32_t a, b;
+    slab_offs(j, a, b);
+    if (ktail && j == cur.ns - 1 && cur.ns > cur.nf) stream_ragged();
+    static_for<NL>([&](auto Q) { copy_one(Q, (uint32_t)(j * kStageBytes), a, b); });
+  }
+  asm volatile("s_waitcnt vmcnt(%0)" : : "n"((NSTAGE - 1) * NL) : "memory");      // slab 0 landed
+  uint32_t so = 0;                               // byte offset of the stage that holds the current slab
+  constexpr int kFinish = 2 * NSTAGE - 1;        // slab before which a count requested before slab NSTAGE has returned
+  auto flush = [&]() {                           // the pending count at once
+    if (pending.c < 0 && pending_half < 0) return;
+    __builtin_amdgcn_s_waitcnt(kWaitAll);
+    __syncthreads();
+    settle();
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    finish();
+  };
+  auto next_stage = [](uint32_t s) {
+    s += (uint32_t)kStageBytes;
+    return s == (uint32_t)(NSTAGE * kStageBytes) ? 0u : s;
+  };
+
+  for (int it = 0;; ++it) {
+    stamp(it, 0);
+    const Tile tl = cur.tl;
+    const int m0 = tl.mi * BM, col_lo = tl.c * p.W, col_hi = col_lo + p.W, n0 = col_lo + tl.nj * BN;
+    const bool direct = (p.flags & kFlagFwdDirect) != 0, bf16 = (p.flags & kFlagFwdBf16) != 0;
+    const bool to_slot = tracked && tl.c != p.own && cur.half != 1 && (direct || chunk_is_whole(p, tl.s));
+    const bool to_r = !tracked || !direct || tl.c == p.own;
+    // where a whole tile's fp32 sums go, or half a tile's (an fp32 slot if not R / C)
+    const bool out_slot = tracked && direct && tl.c != p.own;
+    float *const out_base = out_slot ? p.fwd + (int64_t)tl.s * p.M * p.W : p.R;
+    const uint32_t ld_out = out_slot ? (uint32_t)p.W : (uint32_t)p.ldr;
+    const int col_org = out_slot ? col_lo : 0;
+    const bool has_in = cur.half == 2 || (tracked && !((p.flags & kFlagStep0StoreOnly) && tl.s == 0));
+    // the incoming partial, or the first half's partial sums where the result will go
+    const float *const in_base = cur.half == 2 ? out_base : p.R;
+    const uint32_t ld_in = cur.half == 2 ? ld_out : (uint32_t)p.ldr;
+    const int in_org = cur.half == 2 ? col_org : 0;
+
+    if (cur.ns <= kFinish) flush();              // (too short a K loop to put the count off into)
+    if (cur.half == 2 && threadIdx.x == 0) {
+      // The first half was computed by a workgroup with a lower index as its first piece of work and
+      // waits for nothing, so this wait ends (normally at once).
+      int spins = 0;
+      while (__hip_atomic_load(&p.tail_flags[cur.idx], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == 0u &&
+             ++spins < kSpinLimit)
+        __builtin_amdgcn_s_sleep(16);
+      if (tracked && spins >= kSpinLimit)
+        __hip_atomic_fetch_or(trk.error, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      // (this workgroup is the flag's only reader: cleared for the next launch)
+      __hip_atomic_store(&p.tail_flags[cur.idx], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      __builtin_amdgcn_s_waitcnt(kWaitVm0);
+    }
+    // slab 0 of this piece is in LDS (every wavefront has seen its own copies land); the images are free
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+    stamp(it, 1);
+    static_for<NR>([&](auto R) { read_op(R, c0, c0, adA[0] + so, adB[0] + so); });
+
+    f32x4 in[FM][FN];
+    const __amdgpu_buffer_rsrc_t in_rsrc = make_rsrc(in_base, (uint32_t)p.M * ld_in * 4u);
+    uint32_t in_at[UB];
+    auto load_in = [&](auto I) {                 // row block I of the incoming partial
+      constexpr int i = decltype(I)::value;
+      static_for<FN>([&](auto U) {
+        constexpr int u = decltype(U)::value;
+        in[i][u] = __builtin_bit_cast(
+            f32x4, __builtin_amdgcn_raw_buffer_load_b128(
+                       in_rsrc, (int)(in_at[u % UB] + (uint32_t)(16 * i + (u / UB) * RS) * ld_in * 4u), 0, kAuxSc1 | kAuxNt));
+      });
+    };
+    Piece nxt;
+    bool more = false;
+    // The K loop, cut where something has to be done between two slabs; `wait` is what the barrier
+    // of a slab waits for: 0 = nothing (the first NSTAGE slabs of every piece but the first landed during
+    // the way out, and behind the last slab nothing is needed), 1 = the next slab, 2 = the
+    // next slab with the incoming partial behind it.
+    int kt = 0, cj = NSTAGE;                     // slab multiplied, slab the stream copies next
+    const int k_switch = cur.ns - NSTAGE;        // the stream goes on to the next piece
+    while (kt < cur.ns) {
+      if (kt == NSTAGE) settle();                // (the previous piece's stores are older than slabs waited for)
+      if (kt == kFinish) finish();
+      if (kt == k_switch) {
+        more = get_piece(p, it + 1, nxt);
+        if (more) stream_to(nxt);
+        else stream_end();
+        cj = 0;
+        if (has_in) {
+#pragma unroll
+          for (int u = 0; u < UB; ++u) {
+            const int L = u * 64 + lane, ir = wave * 8 + L / kRowCh, col = (L % kRowCh) * 4;
+            in_at[u] = n0 + col < col_hi ? ((uint32_t)(m0 + strip_row(ir)) * ld_in + (uint32_t)(n0 - in_org + col)) * 4u : kOob;
+          }
+          static_for<PRE>([&](auto I) { load_in(I); });
+        }
+      }
+      // the slab copied next is the last one of the stream's piece, and ragged
+      if (ktail && (kt == k_switch - 1 || (kt == cur.ns - 1 && more && nxt.ns == NSTAGE)) &&
+          (kt < k_switch ? cur.ns > cur.nf : nxt.ns > nxt.nf))
+        stream_ragged();
+      int stop = kt < k_switch - 1 ? k_switch - 1 : (kt < k_switch ? k_switch : (kt < cur.ns - 1 ? cur.ns - 1 : cur.ns));
+      if (kt < NSTAGE - 1 && stop > NSTAGE - 1) stop = NSTAGE - 1;
+      else if (kt < NSTAGE && stop > NSTAGE) stop = NSTAGE;
+      else if (kt < kFinish && stop > kFinish) stop = kFinish;
+      const int wait = kt == cur.ns - 1 || (it > 0 && kt < NSTAGE - 1) ? 0 : (kt >= k_switch && has_in ? 2 : 1);
+      for (; kt < stop; ++kt) {
+        kstep(c0, c1, false_type{}, so, 0u, 0u, 0u);
+        if (wait == 1) asm volatile("s_waitcnt vmcnt(%0)" : : "n"((NSTAGE - 2) * NL) : "memory");
+        else if (wait == 2) asm volatile("s_waitcnt vmcnt(%0)" : : "n"((NSTAGE - 2) * NL + PRE * FN) : "memory");
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");       // own reads of slab kt done
+        __builtin_amdgcn_s_barrier();                            // slab kt + 1 visible, slab kt's stage free
+        asm volatile("" ::: "memory");
+        const uint32_t sn = next_stage(so);
+        uint32_t a, b;
+        slab_offs(cj, a, b);
+        kstep(c1, c0, true_type{}, sn, so, a, b);                // (behind the last slab it reads what nobody uses)
+        ++cj;
+        so = sn;
+      }
+    }
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");            // those reads are over
+    xa[0].tie();
+    xb[0].tie();
+    stamp(it, 2);
+
+    auto zero_in = [&](auto I) {
+#pragma unroll
+      for (int u = 0; u < FN; ++u) in[decltype(I)::value][u] = f32x4{0.f, 0.f, 0.f, 0.f};
+    };
+    if (has_in) {
+      static_for<DEPTH - PRE>([&](auto I) { load_in(std::integral_constant<int, decltype(I)::value + PRE>{}); });
+    } else {
+      static_for<DEPTH>(zero_in);
+    }
+    int lane_e = lane;                           // recomputed here rather than kept through the main loop
+    asm volatile("" : "+v"(lane_e));
+    const int e_row = lane_e & 15, e_q = lane_e >> 4;
+    // TO: 0 = fp32 to R, C or a slot; 1 = R and the fp32 slot; 2 = the bfloat16 slot; 3 = R and the bfloat16 slot
+    auto way_out = [&](auto TO) {
+      constexpr int to = decltype(TO)::value;
+      const __amdgpu_buffer_rsrc_t out_rsrc = make_rsrc(out_base, (uint32_t)p.M * ld_out * 4u);
+      const float *slot = to >= 2 ? (const float *)((const uint16_t *)p.fwd + (int64_t)tl.s * p.M * p.W)
+                                  : p.fwd + (int64_t)tl.s * p.M * p.W;
+      const __amdgpu_buffer_rsrc_t slot_rsrc = make_rsrc(slot, (uint32_t)p.M * (uint32_t)p.W * (to >= 2 ? 2u : 4u));
+      uint32_t out_at[UB], slot_at[UB], img_at[FN];
+#pragma unroll
+      for (int u = 0; u < UB; ++u) {
+        const int L = u * 64 + lane_e, ir = wave * 8 + L / kRowCh, col = (L % kRowCh) * 4, row = m0 + strip_row(ir);
+        const bool ok = n0 + col < col_hi;
+        out_at[u] = ok ? ((uint32_t)row * ld_out + (uint32_t)(n0 - col_org + col)) * 4u : kOob;
+        slot_at[u] = ok ? ((uint32_t)row * (uint32_t)p.W + (uint32_t)(n0 - col_lo + col)) * (to >= 2 ? 2u : 4u) : kOob;
+      }
+#pragma unroll
+      for (int u = 0; u < FN; ++u) {
+        const int L = u * 64 + lane_e, ir = wave * 8 + L / kRowCh;
+        img_at[u] = kImgOff + ir * (BN * 4) + (((L % kRowCh) ^ (ir & 7)) << 4);
+      }
+      static_for<FM>([&](auto I) {
+        constexpr int i = decltype(I)::value;
+        constexpr int img = (i % NIMG) * kImgBytes;
+        if constexpr (NIMG == 1 && i > 0) {      // everyone has read the image
+          asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+          __builtin_amdgcn_s_barrier();
+          asm volatile("" ::: "memory");
+        }
+#pragma unroll
+        for (int j = 0; j < FN; ++j) {
+          *(f32x4 *)(lds + kImgOff + img + (wm * 16 + e_row) * (BN * 4) + (((wn * (WN / 4) + 4 * j + e_q) ^ (e_row & 7)) << 4)) = acc[i][j];
+          acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+        }
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+        __builtin_amdgcn_s_barrier();
+        asm volatile("" ::: "memory");
+        static_for<FN>([&](auto U) {
+          constexpr int u = decltype(U)::value;
+          const f32x4 v = *(const f32x4 *)(lds + img + img_at[u]) + in[i][u];
+          const uint32_t rows = (uint32_t)(16 * i + (u / UB) * RS);
+          if constexpr (to != 2) store_agent_hint<true>(out_rsrc, out_at[u % UB] + rows * ld_out * 4u, 0u, v);
+          if constexpr (to == 1) store_agent_hint<true>(slot_rsrc, slot_at[u % UB] + rows * (uint32_t)p.W * 4u, 0u, v);
+          if constexpr (to >= 2)
+            __builtin_amdgcn_raw_buffer_store_b64(pack_bf16(v), slot_rsrc, (int)(slot_at[u % UB] + rows * (uint32_t)p.W * 2u), 0,
+                                                  kAuxSc1 | kAuxNt);
+        });
+        if constexpr (i + DEPTH < FM) {
+          if (has_in) load_in(std::integral_constant<int, i + DEPTH>{});
+          else zero_in(std::integral_constant<int, i + DEPTH>{});
+        }
+        // The next piece's first NSTAGE slabs were requested before the last of the incoming partial,
+        // so they have landed when that is used; where they were not, this wait makes sure of it.
+        if constexpr (i == 1) {
+          if (!has_in || (PRE == DEPTH && DEPTH == FM)) asm volatile("s_waitcnt vmcnt(%0)" : : "n"(2 * FN * (to == 0 || to == 2 ? 1 : 2)) : "memory");
+        }
+        __builtin_amdgcn_sched_barrier(0);
+      });
+    };
+    if (to_slot && bf16) {
+      if (to_r) way_out(std::integral_constant<int, 3>{});
+      else way_out(std::integral_constant<int, 2>{});
+    } else if (to_slot && to_r) {
+      way_out(c1);
+    } else {
+      way_out(c0);
+    }
+    stamp(it, 3);
+    if (cur.half == 1) pending_half = cur.idx;
+    else if (tracked) pending = tl;
+    if (!more) break;
+    cur = nxt;
+  }
+  flush();
+}
+
+}  // namespace t3k
