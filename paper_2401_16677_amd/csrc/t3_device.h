@@ -64,7 +64,7 @@ struct Plan {
   int32_t split_k;                     // >= 1: workgroups that share a tile, each taking a part of K (Sec. 7.7)
   int32_t stagger_blocks, stagger_groups, stagger_ticks;   // start-up phase offsets (see stagger_start)
   int32_t k_groups;                    // > 1: workgroup w starts its K loop (w % k_groups) / k_groups of the way in
-  int32_t nt_out;                      // results leave with the streaming hint (hand-ordered kernel)
+  int32_t nt_out;                      // results leave with the streaming hint (wide-tile kernel: the plain GEMM's)
   // Timeline (a profiling aid, normally null): workgroup w < timeline_wgs writes, for its i-th
   // piece of work, i < kTimelineItems, four wall-clock readings (100 MHz) at
   // timeline[(w * kTimelineItems + i) * 4 + ...]: piece taken; accumulators set up (the

@@ -142,6 +142,7 @@ void wide_tile_kernel(const Plan p) {
   };
   auto finish = [&]() {
     if (in_count && threadIdx.x == 0) {
+      asm volatile("" : "+v"(count_old) : : "memory");            // (no use of it moves up from here)
       track_finish(p, trk, pending, TrkCount{count_old, 0u});
       __builtin_amdgcn_s_waitcnt(kWaitVm0);      // (nothing of it in flight where paths meet again)
     }
@@ -482,7 +483,7 @@ void wide_tile_kernel(const Plan p) {
     int lane_e = lane;                           // recomputed here rather than kept through the main loop
     asm volatile("" : "+v"(lane_e));
     const int e_row = lane_e & 15, e_q = lane_e >> 4;
-    // TO: 0 = fp32 to R, C or a slot; 1 = R and the fp32 slot; 2 = the bfloat16 slot; 3 = R and the bfloat16 slot
+    // TO: -1 = fp32 to C, kept in the caches; 0 = fp32 to R, C or a slot, streamed; 1 = R and the fp32 slot; 2 = the bfloat16 slot; 3 = R and the bfloat16 slot
     auto way_out = [&](auto TO) {
       constexpr int to = decltype(TO)::value;
       const __amdgpu_buffer_rsrc_t out_rsrc = make_rsrc(out_base, (uint32_t)p.M * ld_out * 4u);
@@ -522,7 +523,7 @@ void wide_tile_kernel(const Plan p) {
           constexpr int u = decltype(U)::value;
           const f32x4 v = *(const f32x4 *)(lds + img + img_at[u]) + in[i][u];
           const uint32_t rows = (uint32_t)(16 * i + (u / UB) * RS);
-          if constexpr (to != 2) store_agent_hint<true>(out_rsrc, out_at[u % UB] + rows * ld_out * 4u, 0u, v);
+          if constexpr (to != 2) store_agent_hint<(to >= 0)>(out_rsrc, out_at[u % UB] + rows * ld_out * 4u, 0u, v);
           if constexpr (to == 1) store_agent_hint<true>(slot_rsrc, slot_at[u % UB] + rows * (uint32_t)p.W * 4u, 0u, v);
           if constexpr (to >= 2)
             __builtin_amdgcn_raw_buffer_store_b64(pack_bf16(v), slot_rsrc, (int)(slot_at[u % UB] + rows * (uint32_t)p.W * 2u), 0,
@@ -535,7 +536,7 @@ void wide_tile_kernel(const Plan p) {
         // The next piece's first NSTAGE slabs were requested before the last of the incoming partial,
         // so they have landed when that is used; where they were not, this wait makes sure of it.
         if constexpr (i == 1) {
-          if (!has_in || (PRE == DEPTH && DEPTH == FM)) asm volatile("s_waitcnt vmcnt(%0)" : : "n"(2 * FN * (to == 0 || to == 2 ? 1 : 2)) : "memory");
+          if (!has_in || (PRE == DEPTH && DEPTH == FM)) asm volatile("s_waitcnt vmcnt(%0)" : : "n"(2 * FN * (to <= 0 || to == 2 ? 1 : 2)) : "memory");
         }
         __builtin_amdgcn_sched_barrier(0);
       });
@@ -545,6 +546,8 @@ void wide_tile_kernel(const Plan p) {
       else way_out(std::integral_constant<int, 2>{});
     } else if (to_slot && to_r) {
       way_out(c1);
+    } else if (!tracked && !p.nt_out) {
+      way_out(std::integral_constant<int, -1>{});
     } else {
       way_out(c0);
     }
