@@ -5,19 +5,14 @@
 // (global_load_lds_dwordx4) into two or three stages, ahead of the slab being multiplied; LDS
 // rows are XOR-swizzled so that the MFMA operand reads are bank-conflict free.
 //
-// The 256 x 256 tile (B stored N x K, A stored M x K) runs on four wavefronts of 128 x 128, one
-// per SIMD, with a hand-ordered main loop: every operand read and slab copy has its place
-// between the products.  The other shapes and layouts run on eight (or, 128 x 128, four)
-// wavefronts with a compiler-scheduled loop.
+// This is the kernel of what the wide-tile and small-tile kernels (t3_wide.h, t3_small.h) do not
+// take: two writers, split-K, tile ranges that cut a ring step, arrays past 2 GiB, and K of one slab.
+// Eight wavefronts (128 x 128: four), compiler-scheduled.
 //
 // The reduction of Sec. 4.3 of the T3 paper (op-and-store into the buffer that also receives
 // the upstream partial) is done by starting the accumulators from the incoming partial, so a
 // tile is read once and written once; both moves use full 128-byte lines and are transposed to
-// and from the accumulator layout through LDS.  A persistent workgroup requests the next
-// tile's incoming partial right behind the current tile's stores.
-//
-// A persistent launch whose last round of tiles would fill at most half the chip computes each
-// of those tiles as two halves of K on two workgroups (balanced tail, see work_item).
+// and from the accumulator layout through LDS.
 #pragma once
 
 #include "t3_device.h"
@@ -90,13 +85,6 @@ __device__ __forceinline__ void asm_tie(bf16x8 (&a)[6]) {
 __device__ __forceinline__ void asm_tie(bf16x8 (&a)[4]) {
   asm volatile("" : "+v"(a[0]), "+v"(a[1]), "+v"(a[2]), "+v"(a[3]));
 }
-template <int NA, int NB>
-__device__ __forceinline__ void asm_wait_operands(bf16x8 (&a)[NA], bf16x8 (&b)[NB]) {
-  asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-  asm_tie(a);
-  asm_tie(b);
-}
-
 constexpr int kRingSlots = 4;         // 1-KiB LDS slots per wavefront for transposing pairs: two pairs
 
 // WAVES_M x WAVES_N wavefronts per workgroup, each producing a (BM/WAVES_M) x (BN/WAVES_N)
@@ -118,19 +106,9 @@ constexpr int kRingSlots = 4;         // 1-KiB LDS slots per wavefront for trans
 // GEMMs, Sec. 5.2): the same arrangement on the A side -- its stage region holds 64 k-rows of BM
 // values, pieces swizzled the same way, operands fetched with the transposing read.  K must be
 // a multiple of 64 and M a multiple of 8.
-//
-// TAIL = 1: the variant that can balance the tail of a persistent launch (see work_item).
-// TAIL = 2: that variant of the fused kernel with the reduction and the tracking taken out: the
-// plain GEMM with a balanced tail (the plain kernel's own TAIL = 1 variant of the hand-ordered
-// loop does not fit the register file).
-//
-// SLOT (hand-ordered kernel, whose registers do not allow for all of it in one): 0 = results in
-// one place, in fp32; 1 = in R and, in fp32, in a forward slot; 2 = forward slots in bfloat16.
-// -1: any of these, told by the flags.
-template <int BM, int BN, int WAVES_M, int WAVES_N, int NSTAGE, int MODE, int BKN, int AKM = 0, int TAIL = 0,
-          int SLOT = -1, int ASM = 0>
+template <int BM, int BN, int WAVES_M, int WAVES_N, int NSTAGE, int MODE, int BKN, int AKM>
 __global__ __launch_bounds__(64 * WAVES_M * WAVES_N)
-__attribute__((amdgpu_waves_per_eu(ASM && (BM + BN) * NSTAGE * 128 > 65536 ? 1 : 2)))
+__attribute__((amdgpu_waves_per_eu(2)))
 void gemm_tile_kernel(const Plan p) {
   constexpr int NW = WAVES_M * WAVES_N;
   constexpr int WM = BM / WAVES_M, WN = BN / WAVES_N;   // wavefront tile
@@ -150,34 +128,15 @@ void gemm_tile_kernel(const Plan p) {
   static_assert(NL % MH == 0, "a slab's copies are split evenly over the first k-step's passes");
   static_assert(NSTAGE * kStageBytes <= 160 * 1024, "LDS");
 
-  // The hand-ordered main loop: four wavefronts, one per SIMD (128 x 128 tile: two), operands
-  // K-contiguous.
-  constexpr bool kAsmLoop = ASM != 0;
-  static_assert(!kAsmLoop || (NW == 4 && !BKN && !AKM), "what the hand-ordered loop is written for");
-  // Their pair transpositions get LDS of their own (4 KiB per wavefront) behind the stages.
-  constexpr int kScrOff = kAsmLoop ? NSTAGE * kStageBytes : 0;   // (otherwise: the epilogue's, in stage 0)
-  static_assert(kScrOff + NW * kRingSlots * 1024 <= 160 * 1024, "LDS");
+  static_assert(NW * kRingSlots * 1024 <= kStageBytes, "scratch of the pair transpositions: the last stage");
 
-  __shared__ __attribute__((aligned(1024))) char lds[NSTAGE * kStageBytes + (kAsmLoop ? NW * kRingSlots * 1024 : 0)];
+  __shared__ __attribute__((aligned(1024))) char lds[NSTAGE * kStageBytes];
 
-  // Persistent workgroups: workgroup w takes grid positions w, w + gridDim.x, ... in order (a
-  // position is a tile or a piece of release work).  The tracking of a finished tile is
+  // Persistent workgroups: workgroup w takes grid positions w, w + gridDim.x, ... in order.  The tracking of a finished tile is
   // deferred into the next tile: by the first barrier of that tile's main loop every
   // wavefront has waited for its stores (they are older than the slab copies waited for
   // there), so the acknowledgement wait costs nothing.
-  // (TAIL == 2: the fused kernel's code run as a plain GEMM with a balanced tail -- no incoming
-  // partial, nothing tracked, output through R)
-  static_assert(TAIL != 2 || MODE == kModeFused, "the plain variant is cut from the fused kernel");
-  bool plain = false;
-  if constexpr (TAIL == 2) {
-    // always, but not known to the compiler: as compile-time facts (accumulators always start
-    // from zero, nothing tracked, no next tile's partial to request) they lead its register
-    // allocation of the hand-ordered loop to spill, as they do in the plain kernel itself
-    int yes = 1;
-    asm volatile("" : "+s"(yes));
-    plain = yes != 0;
-  }
-  const bool tracked = MODE == kModeFused && !plain;
+  constexpr bool tracked = MODE == kModeFused;
   Trk trk;
   if (tracked) trk = trk_open(p);              // reads gen now; used when tiles are done
   if (p.stagger_groups > 1) stagger_start(p);
@@ -187,7 +146,6 @@ void gemm_tile_kernel(const Plan p) {
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wm = wave / WAVES_N, wn = wave % WAVES_N;
   Tile pending{0, -1, 0, 0};                   // the tile whose stores are issued but not counted (c < 0: none)
-  int pending_half = -1;                       // first half of a split tile whose stores are issued but not announced
   // To be called after a barrier that every wavefront reached with its stores acknowledged: requests
   // the count; finish_pending, a little later, acts on it (one round trip to the memory side, during
   // which thread 0's wavefront would otherwise multiply nothing).
@@ -196,11 +154,6 @@ void gemm_tile_kernel(const Plan p) {
   auto settle_pending = [&]() {
     in_count = tracked && pending.c >= 0;
     if (in_count && threadIdx.x == 0) counted = track_issue(p, trk, pending);
-    // (relaxed, like the counting: what orders it behind the partial sums is that they were
-    // written through and acknowledged before the barrier; a release would write back the L2)
-    if (TAIL && pending_half >= 0 && threadIdx.x == 0)
-      __hip_atomic_store(&p.tail_flags[pending_half], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    pending_half = -1;
   };
   auto finish_pending = [&]() {
     if (in_count && threadIdx.x == 0) track_finish(p, trk, pending, counted);
@@ -208,7 +161,7 @@ void gemm_tile_kernel(const Plan p) {
     pending.c = -1;
   };
   auto flush_pending = [&]() {
-    if ((tracked && pending.c >= 0) || (TAIL && pending_half >= 0)) {
+    if (tracked && pending.c >= 0) {
       __builtin_amdgcn_s_waitcnt(kWaitAll);
       __syncthreads();
       settle_pending();
@@ -223,38 +176,20 @@ void gemm_tile_kernel(const Plan p) {
       p.timeline[((size_t)blockIdx.x * kTimelineItems + it) * 4 + k] = wall_clock64();
   };
 
-  // The accumulators live across tiles: the hand-ordered kernel fills them with the NEXT tile's
-  // incoming partial while the current tile's sums are on their way out (`have_in`).
-  f32x4 acc[BM / WAVES_M / 16][BN / WAVES_N / 16];
-  bool have_in = false;
+  f32x4 acc[FM][FN];
   for (int it = 0;; ++it) {
-  // Parts of K (split-K in two-writer mode; the two halves of a balanced tail's tiles): part j
+  // Parts of K (split-K in two-writer mode): part j
   // takes K-slabs [j q, (j+1) q) of the K / 64 full ones, the last part also what is left over
   int blk, part, nparts;
-  if (!work_item<TAIL>(p, it, blk, part, nparts)) break;
+  if (!work_item<0>(p, it, blk, part, nparts)) break;
   stamp(it, 0);
   const int part_slabs = (p.K / kBK) / nparts;
   const int k0 = part * part_slabs * kBK;
   const int Kpart = (part == nparts - 1) ? p.K - k0 : part_slabs * kBK;
-  const bool half0 = TAIL && p.tail_r && nparts == 2 && part == 0;   // partial sums out, nothing counted
-  const bool half1 = TAIL && p.tail_r && nparts == 2 && part == 1;   // starts from those partial sums
-  const int tail_idx = blk - p.tail_q * (int)gridDim.x;
   const char *const Ap = (const char *)p.A + (AKM ? (int64_t)k0 * p.lda * 2 : (int64_t)k0 * 2);
   const char *const Bp = (const char *)p.B + (BKN ? (int64_t)k0 * p.ldb * 2 : (int64_t)k0 * 2);
   Tile tl;
   if (!decode_block(p, blk, tl)) continue;
-  if (half1 && threadIdx.x == 0) {
-    // The first half was computed by a workgroup with a lower index as its first piece of work
-    // and waits for nothing, so this wait ends (normally at once: that was q tile times ago).
-    int spins = 0;
-    while (__hip_atomic_load(&p.tail_flags[tail_idx], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == 0u &&
-           ++spins < kSpinLimit)
-      __builtin_amdgcn_s_sleep(16);
-    if (tracked && spins >= kSpinLimit)
-      __hip_atomic_fetch_or(trk.error, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    // (this workgroup is the flag's only reader: cleared for the next launch)
-    __hip_atomic_store(&p.tail_flags[tail_idx], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  }
   __syncthreads();                             // the previous tile's epilogue is done with the LDS
 
   const int m0 = tl.mi * BM;
@@ -372,27 +307,21 @@ void gemm_tile_kernel(const Plan p) {
 
   // NSTAGE-1 slabs are always in flight.  Past the last slab the copies are repeated into
   // stages nobody reads any more, so every wait below is for the same number of younger copies.
-  if constexpr (kAsmLoop) {                      // (every stage is free: its scratch is elsewhere)
-#pragma unroll
-    for (int st = 0; st < NSTAGE; ++st)
-      if (st < nkf) issue_slab(st, st);
-  } else if (nkf > 0) {
-    issue_slab(0, 0);
-  }
+  if (nkf > 0) issue_slab(0, 0);
 
   // ---- accumulators start from the incoming partial (fused) or zero.
   // Block (i, j), element e of this lane: row 16*i + (lane & 15), column 16*j + 4*(lane >> 4) + e
   // of the wavefront tile.  Per 16-byte access 4 lanes cover 64 contiguous bytes of a row.
-  const bool store_only = (MODE == kModeGemm) || plain || ((p.flags & kFlagStep0StoreOnly) && tl.s == 0);
-  const bool to_fwd = (MODE == kModeFused) && SLOT != 1 && (p.flags & kFlagFwdDirect) && tl.c != p.own;
+  const bool store_only = (MODE == kModeGemm) || ((p.flags & kFlagStep0StoreOnly) && tl.s == 0);
+  const bool to_fwd = (MODE == kModeFused) && (p.flags & kFlagFwdDirect) && tl.c != p.own;
   // two writers (Sec. 4.1): the tile is ADDED into R with atomics, as the upstream update is
   const bool two_writers = (MODE == kModeFused) && (p.flags & kFlagTwoWriters);
   // Release by copy: the sums go to R AND into the chunk's forward slot, from the registers that
   // hold them, if this launch completes the chunk.  (A copy behind the chunk's trigger would read
   // R back: 4 M W bytes more per chunk, and it measured 30 to 60 % of the launch's time.)
-  const bool to_both = (MODE == kModeFused) && SLOT != 0 && !plain && !two_writers && !(p.flags & kFlagFwdDirect) &&
+  const bool to_both = (MODE == kModeFused) && !two_writers && !(p.flags & kFlagFwdDirect) &&
                        tl.c != p.own && chunk_is_whole(p, tl.s);
-  const bool slot_bf16 = (MODE == kModeFused) && (SLOT < 0 || SLOT == 2) && (p.flags & kFlagFwdBf16) && (to_fwd || to_both);
+  const bool slot_bf16 = (MODE == kModeFused) && (p.flags & kFlagFwdBf16) && (to_fwd || to_both);
   const int rw0 = m0 + wm * WM, cw0 = n0 + wn * WN;          // wavefront tile origin (uniform)
   const bool full = (rw0 + WM <= p.M) && (cw0 + WN <= col_hi);
   // where the tile's result goes (uniform): R, C, or the chunk's forward slot
@@ -433,180 +362,56 @@ void gemm_tile_kernel(const Plan p) {
     u.acc[1] = h * 1024 + rq * 128 + ((4 + q) ^ r) * 16;
     return u;
   };
-  const PairLane ul = pair_lane(lane);           // (for the loads just below; the epilogue recomputes it)
-  const int *u_acc = ul.acc;
+  const PairLane ul = pair_lane(lane);
 
   constexpr int NPAIR = NBLK / 2;
   static_assert(FN % 2 == 0, "pairs");
   // Every access to R, C or a forward slot is (uniform base) + (32-bit byte offset of the lane),
   // the offset formed per block when it is needed: byte sizes of these arrays stay below 4 GiB.
-  if (!have_in) {
 #pragma unroll
-    for (int i = 0; i < FM; ++i)
+  for (int i = 0; i < FM; ++i)
 #pragma unroll
-      for (int j = 0; j < FN; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
-  }
+    for (int j = 0; j < FN; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
   // The incoming partial: every pair as two full-line accesses (8 rows x 128 bytes), all in
   // flight together, landing in the pair's accumulator registers; then pair by pair through LDS
   // into the accumulator layout, so that the products accumulate on top of it.  (The scratch is
-  // the last stage, which no copy touches before the main loop's first barrier; the hand-ordered
-  // kernel has scratch of its own.)
-  // (AGENT: the data was written by another workgroup of this launch, with agent-scope stores,
-  // and is read with agent-scope loads; src / ld_in / org: the array, its leading dimension and
-  // the column its rows start at)
-  auto in_pairs_load = [&](auto AGENT, const PairLane &ul, const float *src, uint32_t ld_in, int org, int m_lo,
-                           int n_lo, int col_end, bool whole) {
-    const int *u_row = ul.row, *u_col = ul.col;
-    const __amdgpu_buffer_rsrc_t in_rsrc = make_rsrc(src, (uint32_t)p.M * ld_in * 4u);
+  // the last stage, which no copy touches before the main loop's first barrier.)
+  if (MODE == kModeFused && !store_only && !two_writers) {
+    const __amdgpu_buffer_rsrc_t in_rsrc = make_rsrc(p.R, (uint32_t)p.M * (uint32_t)p.ldr * 4u);
     uint32_t in_l[2];
 #pragma unroll
     for (int h = 0; h < 2; ++h)
-      in_l[h] = ((uint32_t)(m_lo + u_row[h]) * ld_in + (uint32_t)(n_lo - org + u_col[h])) * 4u;
+      in_l[h] = ((uint32_t)(rw0 + ul.row[h]) * (uint32_t)p.ldr + (uint32_t)(cw0 + ul.col[h])) * 4u;
 #pragma unroll
     for (int t = 0; t < NPAIR; ++t) {
       const int i = t / UJ, jj = t % UJ;
 #pragma unroll
       for (int h = 0; h < 2; ++h) {
         f32x4 v = f32x4{0.f, 0.f, 0.f, 0.f};
-        if (whole || (m_lo + 16 * i + u_row[h] < p.M && n_lo + 32 * jj + u_col[h] < col_end)) {
-          const uint32_t blk_off = ((uint32_t)(16 * i) * ld_in + (uint32_t)(32 * jj)) * 4u;
-          v = decltype(AGENT)::value ? load_agent(in_rsrc, in_l[h], blk_off) : load_stream(in_rsrc, in_l[h], blk_off);
-        }
+        if (full || (rw0 + 16 * i + ul.row[h] < p.M && cw0 + 32 * jj + ul.col[h] < col_hi))
+          v = load_stream(in_rsrc, in_l[h], ((uint32_t)(16 * i) * (uint32_t)p.ldr + (uint32_t)(32 * jj)) * 4u);
         acc[i][2 * jj + h] = v;
       }
     }
-  };
-  auto in_pairs_transpose = [&]() {
-    char *scr = lds + (kAsmLoop ? kScrOff : (NSTAGE - 1) * kStageBytes) + wave * (kRingSlots * 1024);
+    char *scr = lds + (NSTAGE - 1) * kStageBytes + wave * (kRingSlots * 1024);
 #pragma unroll
     for (int t = 0; t < NPAIR; ++t) {
       const int i = t / UJ, jj = t % UJ;
       char *slot = scr + ((2 * t) & (kRingSlots - 1)) * 1024;
       *(f32x4 *)(slot + lane * 16) = acc[i][2 * jj];
       *(f32x4 *)(slot + 1024 + lane * 16) = acc[i][2 * jj + 1];
-      acc[i][2 * jj] = *(const f32x4 *)(slot + u_acc[0]);
-      acc[i][2 * jj + 1] = *(const f32x4 *)(slot + u_acc[1]);
+      acc[i][2 * jj] = *(const f32x4 *)(slot + ul.acc[0]);
+      acc[i][2 * jj + 1] = *(const f32x4 *)(slot + ul.acc[1]);
       if (t % 2 == 1) __builtin_amdgcn_sched_barrier(0);
     }
-  };
-  // A persistent workgroup of the hand-ordered kernel requests the NEXT tile's incoming partial
-  // at the end of a tile's epilogue, right behind that tile's stores (`have_in`): the loads are
-  // then on their way while the workgroup decodes its next position and requests its first slabs.
-  if (half1) {
-    // the second half of a split tile starts from the first half's partial sums, which sit
-    // where the result will go
-    in_pairs_load(std::true_type{}, ul, out_base, ld_out, col_org, rw0, cw0, col_hi, full);
-    in_pairs_transpose();
-  } else if (MODE == kModeFused && !store_only && !two_writers) {
-    if (!have_in) in_pairs_load(std::false_type{}, ul, p.R, (uint32_t)p.ldr, 0, rw0, cw0, col_hi, full);
-    in_pairs_transpose();
   }
-  have_in = false;
   stamp(it, 1);
 
-  if constexpr (kAsmLoop) {
-  // ---- main loop, hand-ordered.  One wavefront per SIMD: nobody else fills the matrix pipe while
-  // this one waits, so no wait may be exposed.  NSTAGE LDS stages, two sets of operand registers.  A
-  // k-step is FM x FN products; the FM + FN operand reads of the next k-step go out one per kGap
-  // products, early enough to have landed when the k-step ends, and the copies of the slab
-  // NSTAGE ahead one per kGap products of a slab's second k-step.  One barrier per slab:
-  //   second k-step of slab t  | reads: first k-step of slab t+1  | copies: slab t+NSTAGE -> stage of t
-  //   first k-step of slab t+1 | reads: second k-step of slab t+1
-  //   wait for own reads and for slab t+2, barrier   (slab t+2 visible; all are done reading slab t+1)
-  if (nkf > 0) {
-    bf16x8 xa[2][FM], xb[2][FN];
-    uint32_t adA[KS], adB[KS];                   // this lane's operand rows of k-step kk, stage 0
-#pragma unroll
-    for (int kk = 0; kk < KS; ++kk) {
-      adA[kk] = lds_base + fragA[kk];
-      adB[kk] = lds_base + fragB[kk];
-    }
-    constexpr int kGap = FM * FN >= 48 ? 3 : (FM * FN > 16 ? 2 : 1);
-    static_assert(kGap * (FM + FN) <= FM * FN && kGap * NL <= FM * FN, "reads and copies fit a k-step");
-    // read r of a k-step's FM + FN, in the order the products need them: B block 0, A block 0,
-    // the other B blocks, the other A blocks
-    auto read_op = [&](auto R, auto SET, uint32_t a_addr, uint32_t b_addr) {
-      constexpr int r = decltype(R)::value, set = decltype(SET)::value;
-      if constexpr (r == 0) asm_ds_read_b128<0>(xb[set][0], b_addr);
-      else if constexpr (r == 1) asm_ds_read_b128<0>(xa[set][0], a_addr);
-      else if constexpr (r <= FN) asm_ds_read_b128<(r - 1) * 16 * kRowBytes>(xb[set][r - 1], b_addr);
-      else asm_ds_read_b128<(r - FN) * 16 * kRowBytes>(xa[set][r - FN], a_addr);
-    };
-    // One k-step: the products of operand set CS.  READS: the next k-step's operands go into the
-    // other set from (a_addr, b_addr).  COPIES: slab kt_c goes into stage st_c.
-    auto kstep = [&](auto CS, auto READS, auto COPIES, uint32_t a_addr, uint32_t b_addr, int kt_c, int st_c) {
-      constexpr int cs = decltype(CS)::value;
-      asm_wait_operands(xa[cs], xb[cs]);                      // this k-step's operands have landed
-      __builtin_amdgcn_sched_barrier(0);
-      static_for<FM * FN>([&](auto Mi) {
-        constexpr int m = decltype(Mi)::value, i = m / FN, j = m % FN;
-        acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(xb[cs][j], xa[cs][i], acc[i][j], 0, 0, 0);
-        __builtin_amdgcn_sched_barrier(0);                    // nothing moves across: the order is as written
-        if constexpr (decltype(READS)::value && m % kGap == 0 && m / kGap < FM + FN) {
-          read_op(std::integral_constant<int, m / kGap>{}, std::integral_constant<int, cs ^ 1>{}, a_addr, b_addr);
-          __builtin_amdgcn_sched_barrier(0);
-        }
-        if constexpr (decltype(COPIES)::value && m % kGap == (kGap > 1 ? 1 : 0) && m / kGap < NL) {
-          issue_copies(kt_c, st_c, m / kGap, m / kGap + 1);
-          __builtin_amdgcn_sched_barrier(0);
-        }
-      });
-    };
-    using std::false_type;
-    using std::true_type;
-    constexpr std::integral_constant<int, 0> set0{};
-    constexpr std::integral_constant<int, 1> set1{};
-
-    // the next slab but one has landed, own LDS reads are done (fewer slabs than stages: nothing is
-    // in flight behind it)
-    const bool few = nkf < NSTAGE;
-    auto slab_ready = [&](bool drain) {
-      if (NSTAGE == 2 || drain) asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
-      else asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" : : "n"((NSTAGE - 2) * NL) : "memory");
-      __builtin_amdgcn_s_barrier();
-    };
-    auto next_stage = [](uint32_t so) {
-      so += (uint32_t)kStageBytes;
-      return so == (uint32_t)(NSTAGE * kStageBytes) ? 0u : so;
-    };
-    __builtin_amdgcn_sched_barrier(0);
-    if (few) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-    else asm volatile("s_waitcnt vmcnt(%0)" : : "n"((NSTAGE - 1) * NL) : "memory");   // slab 0 landed
-    __builtin_amdgcn_s_barrier();
-    static_for<FM + FN>([&](auto R) { read_op(R, set0, adA[0], adB[0]); });
-    kstep(set0, true_type{}, false_type{}, adA[1], adB[1], 0, 0);
-    slab_ready(few);                               // slab 1 visible
-    settle_pending();                              // the previous tile's stores are acknowledged too: they
-                                                   //   are older than the slabs waited for
-    uint32_t so = 0;                               // byte offset of the stage that holds slab kt
-    int kt = 0;
-    for (; kt < nkf - NSTAGE; ++kt) {
-      const uint32_t sn = next_stage(so);
-      kstep(set1, true_type{}, true_type{}, adA[0] + sn, adB[0] + sn, kt + NSTAGE, (int)(so / kStageBytes));
-      kstep(set0, true_type{}, false_type{}, adA[1] + sn, adB[1] + sn, 0, 0);
-      slab_ready(false);
-      so = sn;
-      if (kt == 0) finish_pending();               // (the count has come back: the wait above)
-    }
-    if (nkf <= NSTAGE) finish_pending();
-    for (; kt < nkf - 1; ++kt) {                   // the last slabs: nothing left to copy
-      const uint32_t sn = next_stage(so);
-      kstep(set1, true_type{}, false_type{}, adA[0] + sn, adB[0] + sn, 0, 0);
-      kstep(set0, true_type{}, false_type{}, adA[1] + sn, adB[1] + sn, 0, 0);
-      if (NSTAGE > 2 && kt < nkf - 2) slab_ready(true);
-      so = sn;
-    }
-    kstep(set1, false_type{}, false_type{}, 0u, 0u, 0, 0);
-    __builtin_amdgcn_sched_barrier(0);
-  }
-  }
-  if constexpr (!kAsmLoop) {
   if (nkf > 0) {
 #pragma unroll
     for (int st = 1; st < NSTAGE - 1; ++st) issue_slab(min(st, nkf - 1), st);
   }
 
-  }
   // Two sets of operand registers.  Micro-step u = (k-step kk, row pass h) reads FMH row blocks
   // of A (set u & 1) and, on the first pass of a k-step, the FN column blocks of B (set kk & 1),
   // while the products of micro-step u-1 are issued.
@@ -657,7 +462,6 @@ void gemm_tile_kernel(const Plan p) {
                                                                       acc[h * FMH + i][j], 0, 0, 0);
   };
 
-  if constexpr (!kAsmLoop) {
   // ---- main loop: slab kt is multiplied while the next NSTAGE-1 slabs are in flight.  The
   // products of a slab's last micro-step are issued after the next barrier, under the next
   // slab's first LDS reads.  An iteration is: wait + barrier; k-step 0, with the next slab's
@@ -707,7 +511,6 @@ void gemm_tile_kernel(const Plan p) {
     mfma_u(US - 1);
     __builtin_amdgcn_s_waitcnt(kWaitVm0);          // drain the repeated copies
   }
-  }
   asm volatile("" ::: "memory");
 
   if (ktail) {
@@ -752,36 +555,10 @@ void gemm_tile_kernel(const Plan p) {
   // which keeps both sides free of bank conflicts.
   constexpr int kRowsPerWave = 16 / WAVES_N;
   constexpr int kImgBytes = WAVES_M * 16 * BN * 4;
-  // (hand-ordered kernel: in stages no wavefront reads any more -- all but that of the last slab, or
-  // but stage 0 behind a ragged end of K -- so nothing has to be waited for)
-  static_assert((!kAsmLoop || NSTAGE == 2 ? 2 : 1) * kImgBytes <= kStageBytes || (!kAsmLoop && 2 * kImgBytes <= NSTAGE * kStageBytes), "images");
-  char *img0 = lds, *img1 = lds + kImgBytes;
-  if constexpr (kAsmLoop && NSTAGE == 2) {
-    img0 = lds + (ktail ? 1 : (nkf & 1)) * kStageBytes;
-    img1 = img0 + kImgBytes;
-  } else if constexpr (kAsmLoop) {
-    img0 = lds + (ktail ? 1 : nkf % NSTAGE) * kStageBytes;
-    img1 = lds + (ktail ? 2 : (nkf + 1) % NSTAGE) * kStageBytes;
-  }
-  if constexpr (!kAsmLoop) __syncthreads();
+  static_assert(2 * kImgBytes <= NSTAGE * kStageBytes, "images");
+  __syncthreads();
   int lane_e = lane;                             // recomputed here rather than kept through the main loop
   asm volatile("" : "+v"(lane_e));
-  // the next grid position of this workgroup (hand-ordered kernel): if it is a tile that takes an
-  // incoming partial, its accumulator blocks are requested once this tile's sums have been stored
-  bool next_in = false, next_full = false;
-  int next_rw0 = 0, next_cw0 = 0, next_col_hi = 0;
-  int blk_n, part_n, nparts_n;
-  if (kAsmLoop && MODE == kModeFused && !plain && work_item<TAIL>(p, it + 1, blk_n, part_n, nparts_n) &&
-      nparts_n == 1) {
-    Tile tn;
-    if (decode_block(p, blk_n, tn) && !((p.flags & kFlagStep0StoreOnly) && tn.s == 0)) {
-      next_in = true;
-      next_col_hi = tn.c * p.W + p.W;
-      next_rw0 = tn.mi * BM + wm * WM;
-      next_cw0 = tn.c * p.W + tn.nj * BN + wn * WN;
-      next_full = (next_rw0 + WM <= p.M) && (next_cw0 + WN <= next_col_hi);
-    }
-  }
   const int e_row = lane_e & 15, e_q = lane_e >> 4;
   const int w_base = (wm * 16 + e_row) * (BN * 4);     // this lane's image row
   const bool whole = (m0 + BM <= p.M) && (n0 + BN <= col_hi);
@@ -805,7 +582,7 @@ void gemm_tile_kernel(const Plan p) {
         make_rsrc((const uint16_t *)p.fwd + (int64_t)tl.s * p.M * p.W, (uint32_t)p.M * (uint32_t)p.W * 2u);
 #pragma unroll
     for (int i = 0; i < FM; ++i) {
-      char *img = (i & 1) ? img1 : img0;
+      char *img = lds + (i & 1) * kImgBytes;
 #pragma unroll
       for (int j = 0; j < FN; ++j)
         *(f32x4 *)(img + w_base + (((wn * (WN / 4) + 4 * j + e_q) ^ (e_row & 7)) << 4)) = acc[i][j];
@@ -830,8 +607,6 @@ void gemm_tile_kernel(const Plan p) {
         }
       }
       if constexpr (to == 2 || to == 3) {
-        // (rounded behind the LDS, not before it: accumulators of the hand-ordered kernel can go
-        // from their registers to LDS directly, but not into an arithmetic instruction)
 #pragma unroll
         for (int u = 0; u < FN / 2; ++u) {
           int ir, col;
@@ -867,8 +642,8 @@ void gemm_tile_kernel(const Plan p) {
   constexpr std::integral_constant<int, 2> to_slot16{};
   constexpr std::integral_constant<int, 3> to_r_and_slot16{};
   constexpr std::integral_constant<int, 4> to_atomic{};
-  if (SLOT < 0 && MODE == kModeFused && two_writers) {
-    if constexpr (SLOT < 0 && MODE == kModeFused) store_tile(false_type{}, to_atomic);
+  if (two_writers) {
+    if constexpr (MODE == kModeFused) store_tile(false_type{}, to_atomic);
   } else if (slot_bf16) {
     if (to_fwd) store_tile(false_type{}, to_slot16);
     else store_tile(false_type{}, to_r_and_slot16);
@@ -879,21 +654,9 @@ void gemm_tile_kernel(const Plan p) {
   } else {
     store_tile(false_type{}, to_one);
   }
-  // (after the last store, not between the stores: reads and writes that alternate cost the
-  // memory more than a burst of each)
-  if (next_in) {
-    __builtin_amdgcn_sched_barrier(0);
-    in_pairs_load(std::false_type{}, pair_lane(lane_e), p.R, (uint32_t)p.ldr, 0, next_rw0, next_cw0, next_col_hi, next_full);
-  }
-  have_in = next_in;
-
   stamp(it, 3);
   if (nkf == 0) flush_pending();                 // (no main loop ran: nothing was settled on the way)
-  if (half0) {
-    pending_half = tail_idx;                     // announced once the stores are acknowledged
-  } else if (tracked) {
-    pending = tl;
-  }
+  if (tracked) pending = tl;
   }  // pieces of work
   flush_pending();
 }

@@ -12,10 +12,9 @@ t3_status launch_gemm_layout(const Plan &q, int32_t tm, int32_t tn, hipStream_t 
   // Persistent workgroups: as many as the chip holds at once, each walking the grid positions.
   const int64_t positions = (int64_t)q.total_blocks * (MODE == kModeFused ? q.split_k : 1);
   const dim3 grid((unsigned)(positions > q.resident ? q.resident : positions));
-  // The compiler-scheduled kernels: the other layouts, two writers, and tile ranges that cut a ring
-  // step.  K-slabs of 64 everywhere.  256 x 256: 8 wavefronts of 128 x 64,
-  // two 64-KiB stages; 256 x 128 and 128 x 256: 8 wavefronts of 64 x 64, three 48-KiB stages; one
-  // workgroup per compute unit.  128 x 128: 4 wavefronts of 64 x 64, two 32-KiB stages, two workgroups.
+  // K-slabs of 64 everywhere.  256 x 256: 8 wavefronts of 128 x 64, two 64-KiB stages; 256 x 128 and
+  // 128 x 256: 8 wavefronts of 64 x 64, three 48-KiB stages; one workgroup per compute unit.
+  // 128 x 128: 4 wavefronts of 64 x 64, two 32-KiB stages, two workgroups.
   if (tm == 256 && tn == 256)
     return launch(gemm_tile_kernel<256, 256, 2, 4, 2, MODE, BKN, AKM>, grid, dim3(512), s, q);
   if (tm == 256 && tn == 128)

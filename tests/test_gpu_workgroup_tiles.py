@@ -1,0 +1,90 @@
+"""GPU parity of the kernels and workgroup tiles that the library picks by size: few tokens and
+narrow chunks (32 and 64 wide tiles, K split over wavefronts), chunks that fit no tile, K of a few
+slabs only (fewer than the pipeline of the large tiles is deep, or just enough for a tile's count
+to be put off into the next tile), ragged K, every operand layout.
+
+Small-integer inputs make fp32 accumulation exact in any order: R, the slots and C must equal the
+fp64 oracle bit for bit, whatever tile is picked."""
+import numpy as np
+import pytest
+
+from paper_2401_16677_amd import binding as t3
+from paper_2401_16677_amd import workloads as wl
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def gpu():
+    import torch
+    assert torch.cuda.is_available(), "needs a GPU"
+    from tests import gpu_harness
+    return gpu_harness
+
+
+def _check(gpu, oracle, M, W, K, tp, mode, layout="nk"):
+    N, rank = W * tp, (M + W) % tp
+    print(f"M={M} W={W} K={K} tp={tp} rank={rank} mode={mode} layout={layout}", flush=True)
+    kn, km = layout != "nk", layout == "km_kn"
+    direct, bf16, step0 = mode != "copy", mode == "bf16", mode == "step0"
+    a, b, inc = wl.make_integer_inputs(M, N, K, seed=M + 3 * W + 7 * K)
+    tile = t3.t3_default_tile(t3.problem(M, N, K, tp, rank, 0, 0))
+    init = np.full((tp - 1, M, W), gpu.SENTINEL_BF16 if bf16 else gpu.SENTINEL, np.uint16 if bf16 else np.float32)
+    want = oracle.fused_path(a, b, inc, tp, rank, *tile, fwd_direct=direct, fwd_bf16=bf16,
+                             step0_store_only=step0, fwd_init=init)
+    flags = (t3.T3_FLAG_FWD_DIRECT if direct else 0) | (t3.T3_FLAG_FWD_BF16 if bf16 else 0) | \
+            (t3.T3_FLAG_STEP0_STORE_ONLY if step0 else 0)
+    # a launch before the one that is checked: the words its tiles are counted in must be back to zero
+    got = gpu.run_gpu(a, b, inc, tp, rank, tile, flags=flags, unfused=mode == "unfused", ldr_pad=4,
+                      lda_pad=8, b_kn=kn, a_km=km, launches_before=1)
+    for name in ("R", "fwd"):
+        bad = np.argwhere(got[name] != want[name])
+        assert bad.size == 0, f"{name}: {bad.shape[0]} mismatches, first at {tuple(bad[0])}"
+    assert np.all(got["R_pad"] == 123.0)
+    if mode == "unfused":
+        assert np.array_equal(got["C"], oracle.gemm_rows(a, b).astype(np.float32))
+    assert np.array_equal(got["counter"], want["counter"]) and np.array_equal(got["ready"], want["ready"])
+    n = want["queue_len"]
+    assert got["queue_len"] == n and set(got["queue"][:n].tolist()) == set(want["queue"][:n].tolist())
+    assert got["error"] == 0
+
+
+@pytest.mark.parametrize("mode", ["direct", "copy", "bf16", "unfused", "step0"])
+@pytest.mark.parametrize("M,W,K,tp", [
+    (1, 8, 8, 2),           # one row, no full K-slab
+    (7, 72, 56, 3),
+    (24, 200, 328, 5),      # five slabs and a ragged one over four wavefronts
+    (33, 40, 64, 4),        # one row and 8 columns past a 32-wide tile
+    (65, 136, 456, 2),
+    (96, 1544, 200, 2),     # three slabs: fewer than wavefronts
+])
+def test_few_tokens(gpu, oracle, M, W, K, tp, mode):
+    _check(gpu, oracle, M, W, K, tp, mode)
+
+
+@pytest.mark.parametrize("layout", ["kn", "km_kn"])
+@pytest.mark.parametrize("M,W,K,tp", [(8, 8, 64, 2), (40, 72, 320, 3), (72, 200, 576, 2)])
+def test_few_tokens_transposed(gpu, oracle, M, W, K, tp, layout):
+    _check(gpu, oracle, M, W, K, tp, "direct", layout)
+
+
+# K: slabs of 64 from one to eight, whole and ragged.  Chunk widths: one 192 and one 256 column tile, the
+# same and 4 or 8 columns more or less.
+@pytest.mark.parametrize("K", [64, 128, 136, 192, 200, 256, 264, 328, 384, 392, 512])
+@pytest.mark.parametrize("M,W,tp", [(4088, 384, 8), (4096, 260, 8), (2050, 1020, 8), (1030, 532, 4)])
+def test_short_k(gpu, oracle, M, W, tp, K):
+    _check(gpu, oracle, M, W, K, tp, "direct")
+
+
+@pytest.mark.parametrize("mode", ["copy", "bf16", "unfused", "step0"])
+@pytest.mark.parametrize("K", [128, 200, 520])
+@pytest.mark.parametrize("M,W,tp", [(4088, 384, 8), (2050, 1016, 8)])
+def test_short_k_modes(gpu, oracle, M, W, tp, K, mode):
+    _check(gpu, oracle, M, W, K, tp, mode)
+
+
+@pytest.mark.parametrize("layout", ["kn", "km_kn"])
+@pytest.mark.parametrize("K", [64, 128, 192, 256, 384, 576])
+@pytest.mark.parametrize("M,W,tp", [(4088, 384, 8), (2056, 1032, 8), (2048, 32, 32)])
+def test_short_k_transposed(gpu, oracle, M, W, tp, K, layout):
+    _check(gpu, oracle, M, W, K, tp, "direct", layout)
