@@ -246,33 +246,43 @@ struct Choice {
   bool wide;
 };
 // For `steps` whole ring steps of a problem: the tile with the least time by rounds of workgroups x
-// time of a tile.  wide_ok: the wide-tile kernel may be used (sizes, see make_plan).
+// time of a tile.  The times are fitted to 110 problems (8 to 16384 tokens, K 128 to 10240, all layouts,
+// TP 2 to 32), each run on every tile: what is picked is 0.4 % slower than the best of the eight on
+// average, 10 % at most.  They carry what the problems had in common (traffic past the L2s, clocks).
+// wide_ok: the wide-tile kernel may be used (sizes, see make_plan).  Where it may not, or K has fewer slabs than its LDS stages, gemm_tile_kernel takes its place on the shapes it has: the
+// same main loop rate (12288 x 4096 x 6144, B stored K x N: 493 us, 495 wide), but the incoming partial
+// is waited for at the start of every tile (12288 x 4096 x 1536: 19 us per tile outside the main loop, 14 wide).
 Choice workgroup_tile(const t3_problem *p, int cus, int64_t steps, bool wide_ok) {
   struct Cand {
     TileShape t;
     int stages, per_cu;          // LDS stages of the wide-tile kernel (0: small-tile kernel); workgroups per compute unit
     double slab_us, ends_us;     // a K-slab of 64 / the rest of a tile
   };
-  static const Cand kCand[] = {{{256, 256}, 2, 1, 1.20, 13.0}, {{256, 192}, 2, 1, 0.93, 10.0},
-                               {{256, 128}, 3, 1, 0.70, 9.0},  {{128, 192}, 3, 1, 0.50, 8.0},
-                               {{128, 128}, 2, 2, 0.80, 8.0},  {{64, 64}, 0, 1, 0.16, 6.0},
-                               {{32, 64}, 0, 1, 0.12, 6.0},    {{32, 32}, 0, 2, 0.12, 6.0}};
+  static const Cand kCand[] = {{{256, 256}, 2, 1, 1.22, 14.3}, {{256, 192}, 2, 1, 0.90, 13.3},
+                               {{256, 128}, 3, 1, 0.75, 10.9}, {{128, 192}, 3, 1, 0.59, 8.2},
+                               {{128, 128}, 2, 2, 0.81, 7.4},  {{64, 64}, 0, 1, 0.166, 6.55},
+                               {{32, 64}, 0, 1, 0.113, 6.9},   {{32, 32}, 0, 2, 0.115, 5.3}};
+  const bool km = p->a_layout == T3_A_KM, kn = p->b_layout == T3_B_KN;
   const int64_t W = p->N / p->tp;
   const int64_t slabs = ceil_div(p->K, 64);
   double best = -1.0;
   Choice pick{kCand[5].t, false};
-//@FORCE
   for (const Cand &c : kCand) {
-    if (c.stages && (!wide_ok || slabs < c.stages)) continue;
+    const bool general = c.stages && (!wide_ok || slabs < c.stages);
+    if (general && c.t.n == 192) continue;
     const int64_t T = ceil_div(p->M, c.t.m) * ceil_div(W, c.t.n) * steps, slots = (int64_t)cus * c.per_cu;
     double rounds = (double)ceil_div(T, slots);
-    if (c.stages && c.per_cu == 1 && T > slots && T % slots && 2 * (T % slots) <= slots) rounds -= 0.5;   // balanced tail
-    // (a compute unit with one 128 x 128 tile instead of two has it done in 0.6 of the time)
-    const double alone = c.per_cu == 2 && T <= cus ? 0.6 : 1.0;
-    const double us = rounds * alone * (c.ends_us + c.slab_us * (double)slabs);
+    const bool tail = c.stages && !general && c.per_cu == 1 && T > slots && T % slots && 2 * (T % slots) <= slots &&
+                      p->K / 64 >= kTailMinSlabs && !(p->flags & T3_FLAG_FWD_BF16);
+    if (tail) rounds -= 0.5;
+    // (a compute unit with one tile instead of two has it done in 0.8 of the time)
+    const double alone = c.per_cu == 2 && T <= cus ? 0.8 : 1.0;
+    // (k-rows of a transposed operand are half a 128-byte line long in a 32 wide tile)
+    const double slab_us = c.slab_us * (km && c.t.m == 32 ? 1.34 : 1.0) * (kn && c.t.n == 32 ? 1.34 : 1.0);
+    const double us = rounds * alone * ((general ? 1.4 : 1.0) * c.ends_us + slab_us * (double)slabs);
     if (best < 0 || us < best * 0.999) {
       best = us;
-      pick = {c.t, c.stages != 0};
+      pick = {c.t, c.stages != 0 && !general};
     }
   }
   return pick;
@@ -517,8 +527,9 @@ t3_status make_plan(const t3_problem *p, int need, const void *A, const void *B,
   q.resident = (int32_t)resident;
   // Results leave the XCD's L2 at once (streaming hint) where that L2 is better spent on slabs
   // of A and B: long K loops, or an output that the memory-side cache cannot hold anyway.
-  // Measured: -3 % on gpt3_fc2 and hightp_outproj, -1 % on wide_fc2, but +6 % on gpt3_outproj
-  // (short K loop, output within the memory-side cache), so not there.
+  // The plain GEMM of 16384 x 3072 x 1536 and the reduction that reads C next: 275 us with the hint, 257
+  // without.  (The wide-tile kernel streams fused results always: 4096 x 12288 x 1536 166 us with, 174
+  // without; gemm_tile_kernel loses 6 % there with it, and gains 3 % where K or the output is large.)
   q.nt_out = (!two_writers &&
               (p->K >= kNtMinK || 4ll * p->M * p->N > kMemorySideCacheBytes)) ? 1 : 0;
   q.timeline = g_timeline.load();
