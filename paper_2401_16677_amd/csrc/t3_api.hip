@@ -214,10 +214,10 @@ bool tile_supported(int32_t tm, int32_t tn) {
 }
 
 void default_tile(const t3_problem *p, int cus, int32_t *tm, int32_t *tn) {
-  // Cheapest shape by (work padded up to whole tiles) x (how much slower than the 256 x 256
-  // tile the shape's main loop runs per product, measured) x (how far the tiles fall short of
-  // filling the chip's `cus` compute units).  128 x 256 tiles are computed in pairs, as 256 x 256
-  // workgroup tiles: they cost what those cost, padding of M to 256 rows included.
+  // The TRACKED tile of a caller who names none (workgroup tiles are workgroup_tile's).  A caller
+  // sizes counters by it, so the rule stays as it is: cheapest shape by (work padded up to whole
+  // tiles) x (cost per product relative to 256 x 256) x (how far the tiles fall short of filling `cus`
+  // compute units), 128 x 256 counted in pairs.
   static const double kSlower[kNumTileShapes] = {1.0, 1.21, 1.0, 1.28};
   const int64_t W = p->N / p->tp;
   double best = -1.0;
@@ -399,10 +399,10 @@ t3_status make_plan(const t3_problem *p, int need, const void *A, const void *B,
   if (free_tile) {
     // (the wide-tile kernel marks what lies outside by buffer offsets from 2^31 on, so every array it
     // addresses, counted to the end of its last tile, has to fit 2 GiB)
-    const int64_t kMost = 1ll << 31, ld_out = p->ldr > p->ldc ? p->ldr : p->ldc;
+    const int64_t kMost = 1ll << 31;
     const bool fits = (p->a_layout == T3_A_KM ? p->K : p->M) * p->lda * 2 <= kMost &&
                       (p->b_layout == T3_B_KN ? p->K : p->N) * p->ldb * 2 <= kMost &&
-                      ((int64_t)p->M + 256) * ((need & kNeedC) ? p->ldc : p->ldr) * 4 <= kMost && ld_out >= 0;
+                      ((int64_t)p->M + 256) * ((need & kNeedC) ? p->ldc : p->ldr) * 4 <= kMost;
     const Choice w = workgroup_tile(p, kDefaultCus, (limit_t - begin_t) / tpc_t, fits);
     *tm = w.t.m;
     *tn = w.t.n;

@@ -14,14 +14,13 @@
 namespace t3k {
 
 typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
-typedef __attribute__((ext_vector_type(16))) float f32x16;
 typedef __attribute__((ext_vector_type(4))) float f32x4;
 typedef __attribute__((address_space(3))) void *lds_void_ptr;
 typedef const __attribute__((address_space(1))) void *global_void_ptr;
 
 constexpr int kThreads = 256;
 constexpr uint32_t kEmpty = 0xFFFFFFFFu;
-constexpr int kSpinLimit = 1 << 22;   // polls of a release workgroup before it gives up
+constexpr int kSpinLimit = 1 << 22;   // polls for the other half of a split tile before the wait gives up
 constexpr int kTimelineItems = 16;     // pieces of work per workgroup a timeline records
 constexpr int kTailSlots = 256;       // tiles a balanced tail can split (flag words behind the tracker state)
 
