@@ -30,8 +30,8 @@ CONFIGS = ["tiny_outproj", "gpt3_outproj", "gpt3_fc2", "wide_fc2", "hightp_outpr
 # rocprofv3 --pmc FETCH_SIZE / WRITE_SIZE summaries under profiles/ (each scaled by the same
 # counter's reading of a plain copy; the file says how).  Not measured in this run.  Keyed by
 # (workload, release); a workload is listed only while the kernel is the one that was profiled.
-PROFILED_TRAFFIC_BYTES = {("gpt3_outproj", "direct"): 630.8e6, ("gpt3_fc2", "direct"): 1314.0e6,
-                          ("wide_fc2", "direct"): 2492.1e6, ("hightp_outproj", "direct"): 1737.4e6}
+PROFILED_TRAFFIC_BYTES = {("gpt3_outproj", "direct"): 636.5e6, ("gpt3_fc2", "direct"): 1321.3e6,
+                          ("wide_fc2", "direct"): 2488.7e6, ("hightp_outproj", "direct"): 1982.5e6}
 PROFILED_TRAFFIC_SOURCE = "profiles/fused_gemm_rs_<workload>_hbm_traffic.txt (transcribed, not measured in this run)"
 
 
@@ -141,10 +141,9 @@ def timeline_report(b, direct, torch, t3):
         lines += ["", "fused minus plain GEMM, per piece (set-up / main loop / hand-over / whole): " +
                   "; ".join(f"{a[0] - c[0]:+.1f} / {a[1] - c[1]:+.1f} / {a[2] - c[2]:+.1f} / {a[3] - c[3]:+.1f}"
                             for a, c in zip(f, g))]
-    lines += ["", "set-up = piece taken -> accumulators hold the incoming partial (fused) or zeros (plain); for tiles after a",
-              "workgroup's first the incoming partial was requested at the end of the previous piece's hand-over, so part of",
-              "its flight time shows there.  main loop = the K loop.  hand-over = results through LDS into write-through stores",
-              "(+ the request for the next tile's incoming partial); their acknowledgement overlaps the next piece."]
+    lines += ["", "set-up = piece taken -> first slab in LDS.  main loop = the K loop; the incoming partial is requested and the next",
+              "piece's slabs are copied during its last slabs.  hand-over = results through LDS, the incoming partial added, into",
+              "write-through stores; their acknowledgement overlaps the next piece."]
     return "\n".join(lines)
 
 
@@ -275,7 +274,7 @@ class Bench:
         if traffic is not None:
             roof["traffic_source"] = PROFILED_TRAFFIC_SOURCE.replace("<workload>", w.name)
         tile = (w.tile_m, w.tile_n) if w.tile_m else self.t3.t3_default_tile(self.problem(direct))
-        roof.update(kernel="gemm_tile_kernel<%d,%d,fused>" % tuple(tile), kernel_ms_avg=k_avg,
+        roof.update(kernel="t3_gemm_rs_fused, tracked tile %dx%d" % tuple(tile), kernel_ms_avg=k_avg,
                     kernel_ms_min=k_ms[0], kernel_ms_median=k_ms[len(k_ms) // 2],
                     algorithmic_bytes=bytes_alg, flop=w.flop)
         tflops = w.flop / t_fused / 1e12
