@@ -288,6 +288,22 @@ Choice workgroup_tile(const t3_problem *p, int cus, int64_t steps, bool wide_ok)
   return pick;
 }
 
+// Workgroup tile of the reduction over whole ring steps: columns of a chunk in equal parts of at most
+// 256 (1 KiB runs), cut at whole 128-byte lines; rows so that a workgroup of 256 lanes has one batch of
+// four 16-byte pieces per lane, or half and a quarter of one where that leaves compute units idle.  (Two, four
+// and eight batches per workgroup, GEMM and reduction of 2343 x 17664 x 384: 191, 200 and 197 us, one 188;
+// of 2048 x 4096 x 512: 42, 47 and 47, one 40.)
+TileShape reduce_tile(const t3_problem *p, int cus, int64_t steps) {
+  const int64_t W = p->N / p->tp, parts = ceil_div(W, 256);
+  const int64_t tn = ceil_div(ceil_div(W, parts), 32) * 32, width = tn < W ? tn : W;
+  int64_t tm = 1;
+  for (int64_t batch = t3k::kReduceBatch; batch >= t3k::kReduceBatch / 4; batch /= 2) {
+    tm = batch * t3k::kThreads * 4 / width;
+    if (ceil_div(p->M, tm) * ceil_div(W, tn) * steps >= 2 * cus) break;
+  }
+  return {(int32_t)tm, (int32_t)tn};
+}
+
 t3_status resolve_tile(const t3_problem *p, int32_t *tm, int32_t *tn) {
   if (p->tile_m == 0 && p->tile_n == 0) {
     default_tile(p, kDefaultCus, tm, tn);
@@ -312,7 +328,8 @@ inline bool aligned16(const void *q) { return (reinterpret_cast<uintptr_t>(q) & 
 enum Need { kNeedAB = 1, kNeedR = 2, kNeedC = 4, kNeedFwd = 8, kNeedTrack = 16,
             kNeedTwoWriters = 32 /* the call exists only in two-writer mode */,
             kTileKernel = 64 /* the call launches the tile kernel, whose workgroup tiles need not
-                                be the tracked ones */ };
+                                be the tracked ones */,
+            kReduceKernel = 128 /* the call launches the reduction, likewise */ };
 
 // The flag words of a balanced tail in tracker state: behind the two banks, gen and error.
 inline uint32_t *tail_flags_in(uint32_t *track, int32_t tp) { return track + 2 * (3 * (int64_t)tp + 2) + 2; }
@@ -395,8 +412,12 @@ t3_status make_plan(const t3_problem *p, int need, const void *A, const void *B,
   // the tracked tile, so the tile kernel cuts a chunk as suits the chip; a range that cuts a
   // step is in units of tracked tiles, and so are the two-writer calls' counts.
   bool wide = false;
-  const bool free_tile = (need & kTileKernel) && !two_writers && tpc_t > 0 && begin_t % tpc_t == 0 && limit_t % tpc_t == 0;
-  if (free_tile) {
+  const bool free_tile = (need & (kTileKernel | kReduceKernel)) && !two_writers && tpc_t > 0 && begin_t % tpc_t == 0 && limit_t % tpc_t == 0;
+  if (free_tile && (need & kReduceKernel)) {
+    const TileShape t = reduce_tile(p, kDefaultCus, (limit_t - begin_t) / tpc_t);
+    *tm = t.m;
+    *tn = t.n;
+  } else if (free_tile) {
     // (the wide-tile kernel marks what lies outside by buffer offsets from 2^31 on, so every array it
     // addresses, counted to the end of its last tile, has to fit 2 GiB)
     const int64_t kMost = 1ll << 31;
@@ -449,6 +470,8 @@ t3_status make_plan(const t3_problem *p, int need, const void *A, const void *B,
   q.Mt = (int32_t)Mt;
   q.Wt = (int32_t)Wt;
   q.tpc = (int32_t)tpc;
+  q.tile_m = *tm;
+  q.tile_n = *tn;
   q.tracked = (int32_t)tpc_t;
   q.flags = fused_like ? p->flags : 0u;
 
@@ -731,19 +754,11 @@ t3_status t3_rs_reduce(const t3_problem *p, const float *C, float *R, void *fwd,
   t3k::Plan q;
   int32_t tm, tn;
   bool empty = false;
-  const t3_status st = make_plan(p, kNeedC | kNeedR | kNeedFwd | kNeedTrack, nullptr, nullptr, C,
+  const t3_status st = make_plan(p, kNeedC | kNeedR | kNeedFwd | kNeedTrack | kReduceKernel, nullptr, nullptr, C,
                                  R, fwd, track, &q, &tm, &tn, &empty);
   if (st != T3_OK) return st;
   if (empty) return T3_OK;
-  const dim3 grid(grid_size(q)), block(t3k::kThreads);
-  hipStream_t s = static_cast<hipStream_t>(stream);
-  if (tm == 256 && tn == 256)
-    return launch(t3k::reduce_tile_kernel<256, 256>, grid, block, s, q);
-  else if (tm == 256 && tn == 128)
-    return launch(t3k::reduce_tile_kernel<256, 128>, grid, block, s, q);
-  else if (tm == 128 && tn == 256)
-    return launch(t3k::reduce_tile_kernel<128, 256>, grid, block, s, q);
-  return launch(t3k::reduce_tile_kernel<128, 128>, grid, block, s, q);
+  return launch(t3k::reduce_tile_kernel, dim3(grid_size(q)), dim3(t3k::kThreads), static_cast<hipStream_t>(stream), q);
 }
 
 t3_status t3_upstream_update(const t3_problem *p, const float *incoming, float *R,

@@ -9,56 +9,84 @@ namespace t3k {
 // ---------------------------------------------------------------------------------------------
 // Unfused baseline, second kernel: the reduce-scatter's reduction (Sec. 2.3): out = C + incoming,
 // tile by tile in the same issue order, driving the same tracker and release.
-template <int BM, int BN>
+//
+// Memory bound, and on problems that do not fill the chip bound by the round trips a wavefront makes
+// one after the other.  So a lane requests four 16-byte pieces of C and of R each before it adds any,
+// its row and column move on by a step instead of a division, and the tile (p.tile_m x p.tile_n,
+// reduce_tile in t3_api.hip) is cut to what there is to do.
+// One piece at a time on tiles of 128 x 128 (before), two, four and eight in flight, in us: 1148 x 4096 23.6,
+// 14.8, 15.2, 17.5; 2048 x 4096 40.5, 21.5, 22.3, 23.2; 2343 x 17664 131.7, 114.9, 115.9, 120.6.
+// Sums leave with the streaming hint, or they push out of the memory-side cache what the next GEMM and
+// reduction read there: GEMM and reduction of 2343 x 17664 x 384 173.6 with it, 188.8 without; of
+// 16384 x 3072 x 1536 267 and 272.
+constexpr int kReduceBatch = 4;      // 16-byte pieces of each operand a lane has in flight
+// The tile's sums, V x 4 columns per piece (V = 2: sums leave as bfloat16, 16 bytes of eight).
+template <int V>
+__device__ inline void reduce_tile(const Plan &p, const Tile &tl, bool store_only, bool to_r, bool to_slot) {
+  constexpr int U = kReduceBatch / V;
+  const int m0 = tl.mi * p.tile_m, nc = tl.nj * p.tile_n;              // nc: column within the chunk
+  const int rows = min(p.tile_m, p.M - m0), cols = min(p.tile_n, p.W - nc) / (4 * V);
+  const int total = rows * cols, n0 = tl.c * p.W + nc;
+  const uint32_t ldc = (uint32_t)p.ldc * 4u, ldr = (uint32_t)p.ldr * 4u, lds = (uint32_t)p.W * (V == 2 ? 2u : 4u);
+  const __amdgpu_buffer_rsrc_t c_rsrc = make_rsrc(p.C, (uint32_t)p.M * ldc), r_rsrc = make_rsrc(p.R, (uint32_t)p.M * ldr);
+  // (no slot where nothing is forwarded: the descriptor is not used then)
+  const __amdgpu_buffer_rsrc_t s_rsrc =
+      make_rsrc((const char *)p.fwd + (to_slot ? (int64_t)tl.s * p.M * lds : 0), (uint32_t)p.M * lds);
+  int row = (int)threadIdx.x / cols, cc = (int)threadIdx.x - row * cols;
+  const int row_step = kThreads / cols, cc_step = kThreads - row_step * cols;
+  for (int e0 = 0; e0 < total; e0 += U * kThreads) {
+    uint32_t at_r[U], at_s[U];
+    f32x4 c[U][V], r[U][V];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const uint32_t m = (uint32_t)(m0 + row), col = (uint32_t)(n0 + cc * 4 * V) * 4u, at_c = m * ldc + col;
+      at_r[u] = m * ldr + col;
+      at_s[u] = m * lds + (uint32_t)(nc + cc * 4 * V) * (V == 2 ? 2u : 4u);
+      if (e0 + u * kThreads + (int)threadIdx.x < total) {
+#pragma unroll
+        for (int v = 0; v < V; ++v) {
+          c[u][v] = load_stream(c_rsrc, at_c + 16u * v, 0u);
+          r[u][v] = store_only ? f32x4{0.f, 0.f, 0.f, 0.f} : load_stream(r_rsrc, at_r[u] + 16u * v, 0u);
+        }
+      }
+      row += row_step;
+      cc += cc_step;
+      if (cc >= cols) {
+        cc -= cols;
+        ++row;
+      }
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      if (e0 + u * kThreads + (int)threadIdx.x >= total) continue;
+      if (!store_only) {
+#pragma unroll
+        for (int v = 0; v < V; ++v) c[u][v] += r[u][v];
+      }
+      if (to_r) {
+#pragma unroll
+        for (int v = 0; v < V; ++v) store_agent_hint<true>(r_rsrc, at_r[u] + 16u * v, 0u, c[u][v]);
+      }
+      if (to_slot) {
+        if constexpr (V == 2)
+          __builtin_amdgcn_raw_buffer_store_b128(pack_bf16(c[u][0], c[u][1]), s_rsrc, (int)at_s[u], 0, kAuxSc1 | kAuxNt);
+        else
+          store_agent_hint<true>(s_rsrc, at_s[u], 0u, c[u][0]);
+      }
+    }
+  }
+}
 __global__ __launch_bounds__(kThreads) void reduce_tile_kernel(const Plan p) {
   Tile tl;
   if (!decode_block(p, blockIdx.x, tl)) return;
   const Trk trk = trk_open(p);
-  const int tid = threadIdx.x;
-  const int m0 = tl.mi * BM;
-  const int col_lo = tl.c * p.W;
-  const int n0 = col_lo + tl.nj * BN;
-  const int rows = min(BM, p.M - m0);
-  const int cols4 = min(BN, col_lo + p.W - n0) >> 2;
   const bool store_only = (p.flags & kFlagStep0StoreOnly) && tl.s == 0;
-  const bool to_fwd = (p.flags & kFlagFwdDirect) && tl.c != p.own;
-  const bool to_both = !(p.flags & kFlagFwdDirect) && tl.c != p.own && chunk_is_whole(p, tl.s);
-  if ((to_fwd || to_both) && (p.flags & kFlagFwdBf16)) {
-    // bfloat16 forward slot: eight sums = 16 bytes per lane
-    const int cols8 = cols4 >> 1;
-    uint16_t *out16 = (uint16_t *)p.fwd + (int64_t)tl.s * p.M * p.W + (n0 - col_lo);
-    for (int e = tid; e < rows * cols8; e += kThreads) {
-      const int rr = e / cols8, cc = e - rr * cols8;
-      const int64_t row = m0 + rr;
-      const f32x4 *c = (const f32x4 *)(p.C + row * p.ldc + n0) + 2 * cc;
-      f32x4 *r = (f32x4 *)(p.R + row * p.ldr + n0) + 2 * cc;
-      f32x4 lo = __builtin_nontemporal_load(c), hi = __builtin_nontemporal_load(c + 1);
-      if (!store_only) {
-        lo += __builtin_nontemporal_load(r);
-        hi += __builtin_nontemporal_load(r + 1);
-      }
-      if (to_both) {
-        store_agent(r, lo);
-        store_agent(r + 1, hi);
-      }
-      const u32x4 v = pack_bf16(lo, hi);
-      asm volatile("global_store_dwordx4 %0, %1, off sc1"
-                   : : "v"((u32x4 *)(out16 + row * p.W) + cc), "v"(v) : "memory");
-    }
-    track_tile(p, trk, tl);
-    return;
-  }
-  float *fwd_base = p.fwd + (int64_t)tl.s * p.M * p.W + (n0 - col_lo);
-  const int total = rows * cols4;
-  for (int e = tid; e < total; e += kThreads) {
-    const int rr = e / cols4, cc = e - rr * cols4;
-    const int64_t row = m0 + rr;
-    f32x4 *r = (f32x4 *)(p.R + row * p.ldr + n0) + cc;
-    f32x4 v = __builtin_nontemporal_load((const f32x4 *)(p.C + row * p.ldc + n0) + cc);
-    if (!store_only) v += __builtin_nontemporal_load(r);
-    if (!to_fwd) store_agent(r, v);
-    if (to_fwd || to_both) store_agent((f32x4 *)(fwd_base + row * p.W) + cc, v);
-  }
+  const bool direct = p.flags & kFlagFwdDirect, forwarded = tl.c != p.own;
+  const bool to_slot = forwarded && (direct || chunk_is_whole(p, tl.s)), to_r = !(forwarded && direct);
+  if (to_slot && (p.flags & kFlagFwdBf16))
+    reduce_tile<2>(p, tl, store_only, to_r, true);
+  else
+    reduce_tile<1>(p, tl, store_only, to_r, to_slot);
   track_tile(p, trk, tl);
 }
 

@@ -54,6 +54,7 @@ struct Plan {
   // the tracked tile of the problem; tracked = the tracked tiles of a chunk, which is what its
   // counter holds once it is complete.
   int32_t Mt, Wt, tpc, tracked;
+  int32_t tile_m, tile_n;              // the workgroup tile, for the reduction kernel
   int32_t xcd_nbm, xcd_bmk, xcd_bnk;   // XCD grouping of a stage's tiles; xcd_nbm == 0: none
   int32_t agents, rows_per_agent;      // release_ready_kernel: workgroups per chunk, rows of each
   int32_t expected_done;               // grid positions of this launch that do work

@@ -22,7 +22,7 @@ def gpu():
     return gpu_harness
 
 
-def _check(gpu, oracle, M, W, K, tp, mode, layout="nk"):
+def _check(gpu, oracle, M, W, K, tp, mode, layout="nk", unfused=False):
     N, rank = W * tp, (M + W) % tp
     print(f"M={M} W={W} K={K} tp={tp} rank={rank} mode={mode} layout={layout}", flush=True)
     kn, km = layout != "nk", layout == "km_kn"
@@ -35,7 +35,7 @@ def _check(gpu, oracle, M, W, K, tp, mode, layout="nk"):
     flags = (t3.T3_FLAG_FWD_DIRECT if direct else 0) | (t3.T3_FLAG_FWD_BF16 if bf16 else 0) | \
             (t3.T3_FLAG_STEP0_STORE_ONLY if step0 else 0)
     # a launch before the one that is checked: the words its tiles are counted in must be back to zero
-    got = gpu.run_gpu(a, b, inc, tp, rank, tile, flags=flags, unfused=mode == "unfused", ldr_pad=4,
+    got = gpu.run_gpu(a, b, inc, tp, rank, tile, flags=flags, unfused=unfused or mode == "unfused", ldr_pad=4,
                       lda_pad=8, b_kn=kn, a_km=km, launches_before=1)
     for name in ("R", "fwd"):
         bad = np.argwhere(got[name] != want[name])
@@ -88,3 +88,16 @@ def test_short_k_modes(gpu, oracle, M, W, tp, K, mode):
 @pytest.mark.parametrize("M,W,tp", [(4088, 384, 8), (2056, 1032, 8), (2048, 32, 32)])
 def test_short_k_transposed(gpu, oracle, M, W, tp, K, layout):
     _check(gpu, oracle, M, W, K, tp, "direct", layout)
+
+
+# The reduction's own tiles: parts of a chunk of 256 columns or fewer, few and many rows per workgroup, the
+# last ones ragged, chunks narrower than a wavefront's 16-byte pieces.
+@pytest.mark.parametrize("mode", ["direct", "copy", "bf16", "step0"])
+@pytest.mark.parametrize("M,W,tp", [(1, 8, 2), (5, 264, 3), (1148, 512, 8), (2051, 8, 2), (4097, 536, 4)])
+def test_reduction(gpu, oracle, M, W, tp, mode):
+    _check(gpu, oracle, M, W, 64, tp, mode, unfused=True)
+
+
+@pytest.mark.parametrize("M,W,tp", [(3, 4, 2), (2500, 532, 4), (600, 20, 40)])
+def test_reduction_fp32_columns(gpu, oracle, M, W, tp):
+    _check(gpu, oracle, M, W, 64, tp, "unfused")
