@@ -372,6 +372,8 @@ __device__ inline void track_finish(const Plan &p, const Trk &t, const Tile &tl,
     if (k.old + 1u != (uint32_t)((p.tpc - g + p.sub_groups - 1) / p.sub_groups)) return;
     __hip_atomic_store(trk_group_word(p, tl.s, g), 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     k.old = __hip_atomic_fetch_add(&t.counter[c], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    // (waited for here: where the paths meet again the compiler would have every tile wait for it)
+    __builtin_amdgcn_s_waitcnt(kWaitVm0);
     parts = (uint32_t)p.sub_groups;
   }
   // threshold = regions of the chunk x updates expected per element (Sec. 4.2.1)

@@ -17,7 +17,7 @@
 //    the tile.  (A chunk's rows start anywhere; every run of addresses that ends inside a 64-byte
 //    granule costs the memory side a read-modify-write: 8192 x 4256 x 128, chunks of 532 columns,
 //    stored to R and slots took 224 us in 128-byte runs, 134 us in rows, 88 us where 544 columns.)
-//  - The count of a tile is requested when its stores are known to be acknowledged, in the next
+//  - The count of a tile is asked for when its stores are known to be acknowledged, in the next
 //    tile's main loop, and acted on a slab later.
 //
 // Copies, incoming partial and results are buffer accesses: rows past M, columns past the chunk and
@@ -125,28 +125,22 @@ void wide_tile_kernel(const Plan p) {
   // ---- tracking, deferred into the next piece's main loop
   Tile pending{0, -1, 0, 0};
   int pending_half = -1;
-  // The count's request is inline assembly: the compiler, were it to know of a value on its way into a
-  // register across iterations of the main loop, would wait for every access in flight wherever
-  // paths meet.  It is used behind a wait for younger copies.
-  uint32_t count_old = 0;
-  bool in_count = false;
-  auto settle = [&]() {                          // behind a barrier, stores acknowledged
-    in_count = pending.c >= 0;
-    if (in_count && threadIdx.x == 0) {
-      uint32_t *w = track_word(p, trk, pending);
-      asm volatile("global_atomic_add %0, %1, %2, %3 sc0" : "+v"(count_old) : "v"(0), "v"(1), "s"(w) : "memory");
-    }
+  // The count is an atomic the compiler knows of: the register is its to keep, the wait its to make.  (Out of
+  // inline assembly the value would be taken as there at once, and could be copied before it is.)  Every
+  // lane asks, thread 0's address alone lies inside the tracker state: behind a branch there would be paths on which
+  // nobody waits for the value, and the compiler would wait for every copy in flight where those meet the main loop.
+  const __amdgpu_buffer_rsrc_t trk_rsrc = make_rsrc(p.track, tracked ? (uint32_t)(2 * trk_bank_words(p.P) + 2 + kTailSlots) * 4u : 0u);
+  uint32_t count_old = 0u;
+  auto ask_count = [&]() {                       // behind a barrier, stores acknowledged
     if (pending_half >= 0 && threadIdx.x == 0)
       __hip_atomic_store(&p.tail_flags[pending_half], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     pending_half = -1;
+    const bool ask = pending.c >= 0 && threadIdx.x == 0;
+    const uint32_t at = pending.c >= 0 ? (uint32_t)(track_word(p, trk, pending) - p.track) * 4u : 0u;
+    return (uint32_t)__builtin_amdgcn_raw_ptr_buffer_atomic_add_i32(1, trk_rsrc, (int)(ask ? at : kOob), 0, 0);
   };
-  auto finish = [&]() {
-    if (in_count && threadIdx.x == 0) {
-      asm volatile("" : "+v"(count_old) : : "memory");            // (no use of it moves up from here)
-      track_finish(p, trk, pending, TrkCount{count_old, 0u});
-      __builtin_amdgcn_s_waitcnt(kWaitVm0);      // (nothing of it in flight where paths meet again)
-    }
-    in_count = false;
+  auto act_on_count = [&](uint32_t old) {
+    if (pending.c >= 0 && threadIdx.x == 0) track_finish(p, trk, pending, TrkCount{old, 0u});
     pending.c = -1;
   };
   auto stamp = [&](int it, int k) {
@@ -352,14 +346,13 @@ void wide_tile_kernel(const Plan p) {
   }
   asm volatile("s_waitcnt vmcnt(%0)" : : "n"((NSTAGE - 1) * NL) : "memory");      // slab 0 landed
   uint32_t so = 0;                               // byte offset of the stage that holds the current slab
-  constexpr int kFinish = 2 * NSTAGE - 1;        // slab before which a count requested before slab NSTAGE has returned
   auto flush = [&]() {                           // the pending count at once
     if (pending.c < 0 && pending_half < 0) return;
     __builtin_amdgcn_s_waitcnt(kWaitAll);
     __syncthreads();
-    settle();
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-    finish();
+    const uint32_t old = ask_count();
+    __builtin_amdgcn_s_waitcnt(kWaitVm0);        // (in every wavefront: nothing is on its way where paths meet)
+    act_on_count(old);
   };
   auto next_stage = [](uint32_t s) {
     s += (uint32_t)kStageBytes;
@@ -384,7 +377,7 @@ void wide_tile_kernel(const Plan p) {
     const uint32_t ld_in = cur.half == 2 ? ld_out : (uint32_t)p.ldr;
     const int in_org = cur.half == 2 ? col_org : 0;
 
-    if (cur.ns <= kFinish) flush();              // (too short a K loop to put the count off into)
+    if (cur.ns <= NSTAGE) flush();               // (too short a K loop to put the count off into)
     if (cur.half == 2 && threadIdx.x == 0) {
       // The first half was computed by a workgroup with a lower index as its first piece of work and
       // waits for nothing, so this wait ends (normally at once).
@@ -425,9 +418,8 @@ void wide_tile_kernel(const Plan p) {
     // next slab with the incoming partial behind it.
     int kt = 0, cj = NSTAGE;                     // slab multiplied, slab the stream copies next
     const int k_switch = cur.ns - NSTAGE;        // the stream goes on to the next piece
-    while (kt < cur.ns) {
-      if (kt == NSTAGE) settle();                // (the previous piece's stores are older than slabs waited for)
-      if (kt == kFinish) finish();
+    int count_slab = pending.c >= 0 || pending_half >= 0 ? NSTAGE - 1 : -1;
+    auto before_slab = [&]() {
       if (kt == k_switch) {
         more = get_piece(p, it + 1, nxt);
         if (more) stream_to(nxt);
@@ -446,10 +438,11 @@ void wide_tile_kernel(const Plan p) {
       if (ktail && (kt == k_switch - 1 || (kt == cur.ns - 1 && more && nxt.ns == NSTAGE)) &&
           (kt < k_switch ? cur.ns > cur.nf : nxt.ns > nxt.nf))
         stream_ragged();
+    };
+    while (kt < cur.ns) {
+      before_slab();
       int stop = kt < k_switch - 1 ? k_switch - 1 : (kt < k_switch ? k_switch : (kt < cur.ns - 1 ? cur.ns - 1 : cur.ns));
       if (kt < NSTAGE - 1 && stop > NSTAGE - 1) stop = NSTAGE - 1;
-      else if (kt < NSTAGE && stop > NSTAGE) stop = NSTAGE;
-      else if (kt < kFinish && stop > kFinish) stop = kFinish;
       const int wait = kt == cur.ns - 1 || (it > 0 && kt < NSTAGE - 1) ? 0 : (kt >= k_switch && has_in ? 2 : 1);
       for (; kt < stop; ++kt) {
         kstep(c0, c1, false_type{}, so, 0u, 0u, 0u);
@@ -458,6 +451,14 @@ void wide_tile_kernel(const Plan p) {
         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");       // own reads of slab kt done
         __builtin_amdgcn_s_barrier();                            // slab kt + 1 visible, slab kt's stage free
         asm volatile("" ::: "memory");
+        if (kt == count_slab) {
+          if (kt == NSTAGE - 1) {
+            count_old = ask_count();
+            count_slab = NSTAGE;
+          } else {
+            act_on_count(count_old);
+          }
+        }
         const uint32_t sn = next_stage(so);
         uint32_t a, b;
         slab_offs(cj, a, b);

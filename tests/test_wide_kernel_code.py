@@ -1,0 +1,141 @@
+"""The hand-ordered kernel's compiled code: what inline assembly has requested into registers is not
+touched before it is waited for.
+
+The compiler takes the output of an inline-assembly load as written at once.  It may then copy,
+spill or reuse the register while the data is still on its way (it does, where the K loop's body appears
+twice).  So the LDS reads of the main loop are followed here through the control flow of every
+instantiation, from the read to the wait behind it, and loads or returning atomics from global memory,
+whose waits depend on how many copies are in flight, are not written as inline assembly at all."""
+import os
+import re
+import subprocess
+from concurrent.futures import ThreadPoolExecutor
+
+import pytest
+
+from paper_2401_16677_amd import build as hip_build
+
+LAYOUTS = [u for u in hip_build.UNITS if u[0] == "t3_wide_launch.hip"]
+
+
+@pytest.fixture(scope="module")
+def code(tmp_path_factory):
+    """unit -> {kernel: lines} of the device assembly."""
+    out = tmp_path_factory.mktemp("asm")
+
+    def compile_unit(unit):
+        src, obj, defines = unit
+        path = os.path.join(out, obj + ".asm")
+        flags = [f for f in hip_build.HIPCC_FLAGS if f != "-Wall"]
+        subprocess.run([os.environ.get("HIPCC", "/opt/rocm/bin/hipcc"), *flags, "-w", *defines, "-I",
+                        os.path.join(hip_build.ROOT, "include"), "-I", hip_build.CSRC, "--cuda-device-only", "-S",
+                        os.path.join(hip_build.CSRC, src), "-o", path], check=True, stderr=subprocess.DEVNULL)
+        with open(path) as f:
+            text = f.read()
+        starts = [m for m in re.finditer(r"^(_ZN\S+wide_tile_kernel\S+):", text, re.M)]
+        return {m.group(1): text[m.end():text.index(".Lfunc_end", m.end())].split("\n") for m in starts}
+
+    with ThreadPoolExecutor(4) as pool:
+        return dict(zip([u[1] for u in LAYOUTS], pool.map(compile_unit, LAYOUTS)))
+
+
+def _registers(text):
+    """Vector registers an operand list names: v5, v[4:7], a3, a[0:3]."""
+    regs = set()
+    for kind, lo, hi, one in re.findall(r"\b([va])(?:\[(\d+):(\d+)\]|(\d+))", text):
+        if one:
+            regs.add((kind, int(one)))
+        else:
+            regs.update((kind, i) for i in range(int(lo), int(hi) + 1))
+    return regs
+
+
+def _blocks(lines):
+    """[(instructions, successors)], an instruction being (text, in inline assembly)."""
+    blocks, labels, cur, asm = [], {}, [], False
+
+    def close():
+        nonlocal cur
+        blocks.append(cur)
+        cur = []
+
+    for line in lines:
+        label = re.match(r"^(\.LBB\w+):", line)
+        if label:
+            close()
+            labels[label.group(1)] = len(blocks)
+            continue
+        if "#ASMSTART" in line or "#ASMEND" in line:
+            asm = "#ASMSTART" in line
+            continue
+        text = line.split(";")[0].strip()
+        if not text or text.startswith("."):
+            continue
+        cur.append((text, asm))
+        if re.match(r"s_c?branch|s_endpgm", text):
+            close()
+    close()
+    result = []
+    for i, b in enumerate(blocks):
+        succ, last = [], b[-1][0] if b else ""
+        if last.startswith("s_branch"):
+            succ = [labels[last.split()[1]]]
+        elif last.startswith("s_cbranch"):
+            succ = [labels[last.split()[1]], i + 1]
+        elif not last.startswith("s_endpgm"):
+            succ = [i + 1]
+        result.append((b, [s for s in succ if s < len(blocks)]))
+    return result
+
+
+def _touched_in_flight(lines):
+    """Instructions that name a register an inline-assembly LDS read may still be on its way to."""
+    blocks = _blocks(lines)
+    entry = [set() for _ in blocks]
+    todo, faults, reads = list(range(len(blocks))), set(), 0
+    while todo:
+        i = todo.pop()
+        pending = set(entry[i])
+        for text, asm in blocks[i][0]:
+            if text.startswith("s_waitcnt") and "lgkmcnt(0)" in text:
+                pending.clear()
+                continue
+            op, _, rest = text.partition(" ")
+            if _registers(rest) & pending:
+                faults.add(text)
+            if asm and op.startswith("ds_read"):
+                pending |= _registers(rest.split(",")[0])
+        for s in blocks[i][1]:
+            if not pending <= entry[s]:
+                entry[s] |= pending
+                todo.append(s)
+    reads = sum(asm and t.startswith("ds_read") for b, _ in blocks for t, asm in b)
+    return faults, reads
+
+
+def test_checker_sees_a_copy_of_a_register_in_flight():
+    loop = [".LBB0_1:", "\t;;#ASMSTART", "\tds_read_b128 v[4:7], v0 offset:16", "\t;;#ASMEND", "{}",
+            "\ts_cbranch_scc1 .LBB0_1", "\ts_waitcnt lgkmcnt(0)", "\tv_mov_b32_e32 v1, v4", "\ts_endpgm"]
+    good = [line.format("\tv_mov_b32_e32 v1, v3") for line in loop]
+    bad = [line.format("\tv_accvgpr_write_b32 a2, v6") for line in loop]
+    # (a second pass through the loop asks for the same registers again: in the kernel a wait lies between)
+    assert _touched_in_flight(good[:5] + good[6:])[0] == set()
+    assert "v_accvgpr_write_b32 a2, v6" in _touched_in_flight(bad)[0]
+
+
+@pytest.mark.parametrize("unit", [u[1] for u in LAYOUTS])
+def test_no_register_in_flight_is_touched(code, unit):
+    assert len(code[unit]) == 5                       # the five tiles
+    for kernel, lines in code[unit].items():
+        faults, reads = _touched_in_flight(lines)
+        assert reads >= 24, kernel                    # (the smallest tile's two k-steps and the first one's)
+        assert not faults, (kernel, sorted(faults)[:5])
+
+
+@pytest.mark.parametrize("unit", [u[1] for u in LAYOUTS])
+def test_no_global_load_to_a_register_in_inline_assembly(code, unit):
+    for kernel, lines in code[unit].items():
+        for block, _ in _blocks(lines):
+            for text, asm in block:
+                if asm and re.match(r"(global|buffer|flat|scratch)_(load|atomic)", text):
+                    assert re.search(r"\blds\b", text) or text.split()[0].startswith("global_load_lds"), (kernel, text)
