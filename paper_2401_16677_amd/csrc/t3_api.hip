@@ -11,6 +11,7 @@
 #include <mutex>
 
 #include "t3_aux.h"
+#include "t3_choice.h"
 #include "t3_launch.h"
 
 namespace t3k {
@@ -19,11 +20,10 @@ thread_local int32_t last_hip_error = 0;
 
 namespace {
 
+using t3k::ceil_div;
 using t3k::launch;
+using t3k::TileShape;
 
-struct TileShape {
-  int32_t m, n;
-};
 // preference order of t3_default_tile
 constexpr TileShape kTileShapes[] = {{256, 256}, {256, 128}, {128, 256}, {128, 128}};
 constexpr int kNumTileShapes = sizeof(kTileShapes) / sizeof(kTileShapes[0]);
@@ -33,12 +33,9 @@ constexpr int kMaxDevices = 64;
 constexpr int kReleaseAgents = 32;     // release workgroups per chunk (t3_release_chunks)
 constexpr int kNtMinK = 3072;          // K from which result stores take the streaming hint
 constexpr int64_t kMemorySideCacheBytes = 256ll << 20;
-constexpr int kTailMinSlabs = 8;       // K-slabs of 64 a tile needs before a balanced tail splits it
 // Matrix rate of one compute unit the start-up offsets are sized with: 4096 flop/clock at a
 // sustained ~1.5 GHz under load, in flop per nanosecond.
 constexpr double kCuFlopPerNs = 6.25e3;
-
-inline int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
 
 // What the launch plan needs to know of the device it launches on, read from the runtime once
 // per device (hardware attributes only; they never change while the process lives).
@@ -240,70 +237,6 @@ void default_tile(const t3_problem *p, int cus, int32_t *tm, int32_t *tn) {
   }
 }
 
-// Which kernel computes a launch, on which workgroup tile.
-struct Choice {
-  TileShape t;
-  bool wide;
-};
-// For `steps` whole ring steps of a problem: the tile with the least time by rounds of workgroups x
-// time of a tile.  The times are fitted to 110 problems (8 to 16384 tokens, K 128 to 10240, all layouts,
-// TP 2 to 32), each run on every tile: what is picked is 0.4 % slower than the best of the eight on
-// average, 10 % at most.  They carry what the problems had in common (traffic past the L2s, clocks).
-// wide_ok: the wide-tile kernel may be used (sizes, see make_plan).  Where it may not, or K has fewer slabs than its LDS stages, gemm_tile_kernel takes its place on the shapes it has: the
-// same main loop rate (12288 x 4096 x 6144, B stored K x N: 493 us, 495 wide), but the incoming partial
-// is waited for at the start of every tile (12288 x 4096 x 1536: 19 us per tile outside the main loop, 14 wide).
-Choice workgroup_tile(const t3_problem *p, int cus, int64_t steps, bool wide_ok) {
-  struct Cand {
-    TileShape t;
-    int stages, per_cu;          // LDS stages of the wide-tile kernel (0: small-tile kernel); workgroups per compute unit
-    double slab_us, ends_us;     // a K-slab of 64 / the rest of a tile
-  };
-  static const Cand kCand[] = {{{256, 256}, 2, 1, 1.22, 14.3}, {{256, 192}, 2, 1, 0.90, 13.3},
-                               {{256, 128}, 3, 1, 0.75, 10.9}, {{128, 192}, 3, 1, 0.59, 8.2},
-                               {{128, 128}, 2, 2, 0.81, 7.4},  {{64, 64}, 0, 1, 0.166, 6.55},
-                               {{32, 64}, 0, 1, 0.113, 6.9},   {{32, 32}, 0, 2, 0.115, 5.3}};
-  const bool km = p->a_layout == T3_A_KM, kn = p->b_layout == T3_B_KN;
-  const int64_t W = p->N / p->tp;
-  const int64_t slabs = ceil_div(p->K, 64);
-  double best = -1.0;
-  Choice pick{kCand[5].t, false};
-  for (const Cand &c : kCand) {
-    const bool general = c.stages && (!wide_ok || slabs < c.stages);
-    if (general && c.t.n == 192) continue;
-    const int64_t T = ceil_div(p->M, c.t.m) * ceil_div(W, c.t.n) * steps, slots = (int64_t)cus * c.per_cu;
-    double rounds = (double)ceil_div(T, slots);
-    const bool tail = c.stages && !general && c.per_cu == 1 && T > slots && T % slots && 2 * (T % slots) <= slots &&
-                      p->K / 64 >= kTailMinSlabs && !(p->flags & T3_FLAG_FWD_BF16);
-    if (tail) rounds -= 0.5;
-    // (a compute unit with one tile instead of two has it done in 0.8 of the time)
-    const double alone = c.per_cu == 2 && T <= cus ? 0.8 : 1.0;
-    // (k-rows of a transposed operand are half a 128-byte line long in a 32 wide tile)
-    const double slab_us = c.slab_us * (km && c.t.m == 32 ? 1.34 : 1.0) * (kn && c.t.n == 32 ? 1.34 : 1.0);
-    const double us = rounds * alone * ((general ? 1.4 : 1.0) * c.ends_us + slab_us * (double)slabs);
-    if (best < 0 || us < best * 0.999) {
-      best = us;
-      pick = {c.t, c.stages != 0 && !general};
-    }
-  }
-  return pick;
-}
-
-// Workgroup tile of the reduction over whole ring steps: columns of a chunk in equal parts of at most
-// 256 (1 KiB runs), cut at whole 128-byte lines; rows so that a workgroup of 256 lanes has one batch of
-// four 16-byte pieces per lane, or half and a quarter of one where that leaves compute units idle.  (Two, four
-// and eight batches per workgroup, GEMM and reduction of 2343 x 17664 x 384: 191, 200 and 197 us, one 188;
-// of 2048 x 4096 x 512: 42, 47 and 47, one 40.)
-TileShape reduce_tile(const t3_problem *p, int cus, int64_t steps) {
-  const int64_t W = p->N / p->tp, parts = ceil_div(W, 256);
-  const int64_t tn = ceil_div(ceil_div(W, parts), 32) * 32, width = tn < W ? tn : W;
-  int64_t tm = 1;
-  for (int64_t batch = t3k::kReduceBatch; batch >= t3k::kReduceBatch / 4; batch /= 2) {
-    tm = batch * t3k::kThreads * 4 / width;
-    if (ceil_div(p->M, tm) * ceil_div(W, tn) * steps >= 2 * cus) break;
-  }
-  return {(int32_t)tm, (int32_t)tn};
-}
-
 t3_status resolve_tile(const t3_problem *p, int32_t *tm, int32_t *tn) {
   if (p->tile_m == 0 && p->tile_n == 0) {
     default_tile(p, kDefaultCus, tm, tn);
@@ -326,16 +259,13 @@ static_assert(T3_TIMELINE_ITEMS == t3k::kTimelineItems, "timeline layout of the 
 inline bool aligned16(const void *q) { return (reinterpret_cast<uintptr_t>(q) & 15u) == 0; }
 
 enum Need { kNeedAB = 1, kNeedR = 2, kNeedC = 4, kNeedFwd = 8, kNeedTrack = 16,
-            kNeedTwoWriters = 32 /* the call exists only in two-writer mode */,
-            kTileKernel = 64 /* the call launches the tile kernel, whose workgroup tiles need not
-                                be the tracked ones */,
-            kReduceKernel = 128 /* the call launches the reduction, likewise */ };
+            kNeedTwoWriters = 32 /* the call exists only in two-writer mode */ };
 
 // The flag words of a balanced tail in tracker state: behind the two banks, gen and error.
 inline uint32_t *tail_flags_in(uint32_t *track, int32_t tp) { return track + 2 * (3 * (int64_t)tp + 2) + 2; }
 
 // Validates everything and fills the plan.  *empty is set when there is nothing to launch.
-t3_status make_plan(const t3_problem *p, int need, const void *A, const void *B, const float *C,
+t3_status make_plan(const t3_problem *p, t3k::Call call, int need, const void *A, const void *B, const float *C,
                     float *R, void *fwd, uint32_t *track, t3k::Plan *plan, int32_t *tm,
                     int32_t *tn, bool *empty) {
   t3_status st = check_shape(p);
@@ -401,49 +331,24 @@ t3_status make_plan(const t3_problem *p, int need, const void *A, const void *B,
   // bfloat16 forward slots move 8 elements per 16-byte access
   if ((need & kNeedFwd) && fused_like && (p->flags & T3_FLAG_FWD_BF16) && W % 8) return T3_ERR_ALIGN;
 
-  // tracked tiles (the problem's tile shape): what the issue order, the tile range and the
-  // tracker's thresholds are counted in
-  int64_t Wt = ceil_div(W, *tn);
-  const int64_t tpc_t = ceil_div(p->M, *tm) * Wt, T_t = tpc_t * p->tp;
+  // (the last refusals, before the device is asked anything: tracked tiles, which the issue order, the tile
+  // range and the tracker's thresholds are counted in, fit 31 bits, with split-K in as many parts too; the workgroup tiles
+  // of arrays below 4 GiB always do)
+  const int64_t T_t = ceil_div(p->M, *tm) * ceil_div(W, *tn) * p->tp;
   if (T_t >= (1ll << 31)) return T3_ERR_UNSUPPORTED;
-  const int64_t limit_t = (p->tile_limit < 0 || p->tile_limit > T_t) ? T_t : p->tile_limit;
-  const int64_t begin_t = p->tile_begin < 0 ? 0 : (p->tile_begin > limit_t ? limit_t : p->tile_begin);
-  // Workgroup tiles.  Over whole ring steps nothing but the counters' final values depends on
-  // the tracked tile, so the tile kernel cuts a chunk as suits the chip; a range that cuts a
-  // step is in units of tracked tiles, and so are the two-writer calls' counts.
-  bool wide = false;
-  const bool free_tile = (need & (kTileKernel | kReduceKernel)) && !two_writers && tpc_t > 0 && begin_t % tpc_t == 0 && limit_t % tpc_t == 0;
-  if (free_tile && (need & kReduceKernel)) {
-    const TileShape t = reduce_tile(p, kDefaultCus, (limit_t - begin_t) / tpc_t);
-    *tm = t.m;
-    *tn = t.n;
-  } else if (free_tile) {
-    // (the wide-tile kernel marks what lies outside by buffer offsets from 2^31 on, so every array it
-    // addresses, counted to the end of its last tile, has to fit 2 GiB)
-    const int64_t kMost = 1ll << 31;
-    const bool fits = (p->a_layout == T3_A_KM ? p->K : p->M) * p->lda * 2 <= kMost &&
-                      (p->b_layout == T3_B_KN ? p->K : p->N) * p->ldb * 2 <= kMost &&
-                      ((int64_t)p->M + 256) * ((need & kNeedC) ? p->ldc : p->ldr) * 4 <= kMost;
-    const Choice w = workgroup_tile(p, kDefaultCus, (limit_t - begin_t) / tpc_t, fits);
-    *tm = w.t.m;
-    *tn = w.t.n;
-    wide = w.wide;
-  }
-  const int64_t Mt = ceil_div(p->M, *tm);
-  Wt = ceil_div(W, *tn);
-  const int64_t tpc = Mt * Wt, T = tpc * p->tp;
-  *empty = (T == 0);
-
-  // (the last refusals, before the device is asked anything: the grid has to fit 31 bits)
-  if (T >= (1ll << 31)) return T3_ERR_UNSUPPORTED;
-  if (two_writers && T * split_k >= (1ll << 31)) return T3_ERR_UNSUPPORTED;
+  if (two_writers && T_t * split_k >= (1ll << 31)) return T3_ERR_UNSUPPORTED;
   if ((need & kNeedTwoWriters) && (need & kNeedC) && p->upstream_agents < 0) return T3_ERR_BAD_SHAPE;
 
   DeviceFacts dev{kDefaultCus, kNumXcd};
-  if (!*empty) {                                 // (nothing is launched otherwise: no device needed)
+  if (T_t) {                                     // (nothing is launched otherwise: no device needed)
     st = device_facts(&dev);
     if (st != T3_OK) return st;
   }
+  const t3k::LaunchShape shape = t3k::launch_shape(p, call, {*tm, *tn}, dev.cus);
+  *tm = shape.tile.m;
+  *tn = shape.tile.n;
+  const int64_t Mt = shape.Mt, Wt = shape.Wt, tpc = shape.tpc;
+  *empty = shape.begin >= shape.limit;           // (no tiles, or an empty range of them)
 
   t3k::Plan &q = *plan;
   q.A = static_cast<const uint16_t *>(A);
@@ -456,10 +361,8 @@ t3_status make_plan(const t3_problem *p, int need, const void *A, const void *B,
   q.ldb = p->ldb;
   q.ldr = p->ldr;
   q.ldc = p->ldc;
-  // the range in workgroup tiles (where they are not the tracked ones it is whole steps)
-  q.limit = tpc == tpc_t ? limit_t : (tpc_t ? limit_t / tpc_t * tpc : 0);
-  q.begin = tpc == tpc_t ? begin_t : (tpc_t ? begin_t / tpc_t * tpc : 0);
-  if (q.begin >= q.limit) *empty = true;       // an empty tile range: nothing to launch
+  q.limit = shape.limit;
+  q.begin = shape.begin;
   q.M = p->M;
   q.N = p->N;
   q.K = p->K;
@@ -472,7 +375,7 @@ t3_status make_plan(const t3_problem *p, int need, const void *A, const void *B,
   q.tpc = (int32_t)tpc;
   q.tile_m = *tm;
   q.tile_n = *tn;
-  q.tracked = (int32_t)tpc_t;
+  q.tracked = (int32_t)shape.tracked_tpc;
   q.flags = fused_like ? p->flags : 0u;
 
   // XCD grouping: split a stage's Mt x Wt tiles into 8 equal blocks, one per XCD, or, where they do
@@ -506,11 +409,9 @@ t3_status make_plan(const t3_problem *p, int need, const void *A, const void *B,
   }
 
   q.agents = q.rows_per_agent = 0;
-  // tile workgroups the device holds at once: one per compute unit, two of the smallest tile
-  const int64_t resident = (int64_t)dev.cus * ((*tm == 128 && *tn == 128) ? 2 : 1);
-  // the grid spans the ring steps the range touches
-  q.stage0 = tpc > 0 ? (int32_t)(q.begin / tpc) : 0;
-  q.total_blocks = tpc > 0 && q.begin < q.limit ? (int32_t)((ceil_div(q.limit, tpc) - q.stage0) * tpc) : 0;
+  const int64_t resident = shape.resident;
+  q.stage0 = (int32_t)shape.stage0;
+  q.total_blocks = (int32_t)shape.total_blocks;
   // Start-up phase offsets (see stagger_start): four groups over a 12 us window, or half an
   // estimated tile time if that is shorter, from two rounds of tiles on (one round only ends later).
   // The environment variable T3_STAGGER="groups,window_ns" overrides this ("0" turns it off).
@@ -560,23 +461,10 @@ t3_status make_plan(const t3_problem *p, int need, const void *A, const void *B,
     const int64_t wgs = g_timeline_wgs.load();
     q.timeline_wgs = (int32_t)(wgs > (1ll << 30) ? (1ll << 30) : wgs);
   }
-  // Balanced tail (see the kernels' work_item): persistent launches of the tile kernel over the
-  // whole issue order whose last round of grid positions would fill at most half the chip; every
-  // half needs a few K-slabs, and the partial sums pass through the fp32 destination (so not
-  // with bfloat16 forward slots), each element with one writer at a time.
-  q.tail_r = q.tail_q = 0;
+  q.wide = shape.kernel == t3k::kWideTile;
+  q.tail_r = (int32_t)shape.tail_r;
+  q.tail_q = (int32_t)shape.tail_q;
   q.tail_flags = track ? tail_flags_in(track, p->tp) : nullptr;   // (t3_gemm brings its own)
-  // Ring steps in a range are as good as the whole order, a cut range is not (its positions are
-  // not all tiles).
-  const bool slot_bf16 = fused_like && (p->flags & T3_FLAG_FWD_BF16);
-  q.wide = wide;
-  if (wide && resident == dev.cus && !slot_bf16 && q.total_blocks > resident && p->K / 64 >= kTailMinSlabs) {
-    const int64_t r = q.total_blocks % resident;
-    if (r > 0 && 2 * r <= resident && r <= t3k::kTailSlots) {
-      q.tail_r = (int32_t)r;
-      q.tail_q = (int32_t)(q.total_blocks / resident);
-    }
-  }
   // Counting.  Groups pay where many tiles finish together; up to 32 ring steps x 8 groups, 16 x 16
   // or 8 x 32 fit the words.
   q.whole_chunks = !two_writers && tpc > 0 && q.begin % tpc == 0 && q.limit % tpc == 0;
@@ -693,7 +581,7 @@ t3_status t3_gemm_rs_fused(const t3_problem *p, const void *A, const void *B, fl
   t3k::Plan q;
   int32_t tm, tn;
   bool empty = false;
-  const t3_status st = make_plan(p, kNeedAB | kNeedR | kNeedFwd | kNeedTrack | kTileKernel, A, B, nullptr, R,
+  const t3_status st = make_plan(p, t3k::kCallFused, kNeedAB | kNeedR | kNeedFwd | kNeedTrack, A, B, nullptr, R,
                                  fwd, track, &q, &tm, &tn, &empty);
   if (st != T3_OK) return st;
   if (empty) return T3_OK;
@@ -711,7 +599,7 @@ t3_status t3_gemm_rs_fused_static(const t3_problem *p, const void *A, const void
   int32_t tm, tn;
   bool empty = false;
   uint32_t stand_in = 0;
-  t3_status st = make_plan(p, kNeedAB | kNeedR | kNeedFwd | kNeedTrack | kTileKernel, A, B, nullptr, R, fwd,
+  t3_status st = make_plan(p, t3k::kCallFused, kNeedAB | kNeedR | kNeedFwd | kNeedTrack, A, B, nullptr, R, fwd,
                            &stand_in, &q, &tm, &tn, &empty);
   if (st != T3_OK) return st;
   uint32_t *track = nullptr;
@@ -738,7 +626,7 @@ t3_status t3_gemm(const t3_problem *p, const void *A, const void *B, float *C, v
   t3k::Plan q;
   int32_t tm, tn;
   bool empty = false;
-  const t3_status st = make_plan(p, kNeedAB | kNeedC | kTileKernel, A, B, C, nullptr, nullptr, nullptr, &q,
+  const t3_status st = make_plan(p, t3k::kCallGemm, kNeedAB | kNeedC, A, B, C, nullptr, nullptr, nullptr, &q,
                                  &tm, &tn, &empty);
   if (st != T3_OK) return st;
   if (empty) return T3_OK;
@@ -754,7 +642,7 @@ t3_status t3_rs_reduce(const t3_problem *p, const float *C, float *R, void *fwd,
   t3k::Plan q;
   int32_t tm, tn;
   bool empty = false;
-  const t3_status st = make_plan(p, kNeedC | kNeedR | kNeedFwd | kNeedTrack | kReduceKernel, nullptr, nullptr, C,
+  const t3_status st = make_plan(p, t3k::kCallReduce, kNeedC | kNeedR | kNeedFwd | kNeedTrack, nullptr, nullptr, C,
                                  R, fwd, track, &q, &tm, &tn, &empty);
   if (st != T3_OK) return st;
   if (empty) return T3_OK;
@@ -766,7 +654,7 @@ t3_status t3_upstream_update(const t3_problem *p, const float *incoming, float *
   t3k::Plan q;
   int32_t tm, tn;
   bool empty = false;
-  const t3_status st = make_plan(p, kNeedC | kNeedR | kNeedTrack | kNeedTwoWriters, nullptr, nullptr,
+  const t3_status st = make_plan(p, t3k::kCallOther, kNeedC | kNeedR | kNeedTrack | kNeedTwoWriters, nullptr, nullptr,
                                  incoming, R, nullptr, track, &q, &tm, &tn, &empty);
   if (st != T3_OK) return st;
   if (empty) return T3_OK;
@@ -789,7 +677,7 @@ t3_status t3_release_chunks(const t3_problem *p, const float *R, void *fwd,
   t3k::Plan q;
   int32_t tm, tn;
   bool empty = false;
-  const t3_status st = make_plan(p, kNeedR | kNeedFwd | kNeedTrack | kNeedTwoWriters, nullptr,
+  const t3_status st = make_plan(p, t3k::kCallOther, kNeedR | kNeedFwd | kNeedTrack | kNeedTwoWriters, nullptr,
                                  nullptr, nullptr, const_cast<float *>(R), fwd,
                                  const_cast<uint32_t *>(track), &q, &tm, &tn, &empty);
   if (st != T3_OK) return st;

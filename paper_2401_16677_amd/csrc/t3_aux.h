@@ -13,13 +13,13 @@ namespace t3k {
 // Memory bound, and on problems that do not fill the chip bound by the round trips a wavefront makes
 // one after the other.  So a lane requests four 16-byte pieces of C and of R each before it adds any,
 // its row and column move on by a step instead of a division, and the tile (p.tile_m x p.tile_n,
-// reduce_tile in t3_api.hip) is cut to what there is to do.
+// reduce_tile_shape in t3_choice.h) is cut to what there is to do.
 // One piece at a time on tiles of 128 x 128 (before), two, four and eight in flight, in us: 1148 x 4096 23.6,
 // 14.8, 15.2, 17.5; 2048 x 4096 40.5, 21.5, 22.3, 23.2; 2343 x 17664 131.7, 114.9, 115.9, 120.6.
 // Sums leave with the streaming hint, or they push out of the memory-side cache what the next GEMM and
 // reduction read there: GEMM and reduction of 2343 x 17664 x 384 173.6 with it, 188.8 without; of
 // 16384 x 3072 x 1536 267 and 272.
-constexpr int kReduceBatch = 4;      // 16-byte pieces of each operand a lane has in flight
+static_assert(kReduceThreads == kThreads, "");
 // The tile's sums, V x 4 columns per piece (V = 2: sums leave as bfloat16, 16 bytes of eight).
 template <int V>
 __device__ inline void reduce_tile(const Plan &p, const Tile &tl, bool store_only, bool to_r, bool to_slot) {

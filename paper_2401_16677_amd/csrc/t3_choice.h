@@ -1,0 +1,157 @@
+// Which kernel serves a launch, on which workgroup tile, and how the tiles fall to the workgroups.  Plain
+// C++ without HIP: the library's host side and the tests share it.
+#pragma once
+
+#include <stdint.h>
+
+#include "t3.h"
+
+namespace t3k {
+
+inline int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
+
+struct TileShape {
+  int32_t m, n;
+};
+
+enum Call { kCallFused, kCallGemm, kCallReduce, kCallOther };
+enum Kernel { kGeneralTile, kWideTile, kSmallTile, kReduction };   // t3_gemm.h, t3_wide.h, t3_small.h, t3_aux.h
+
+constexpr int kTailMinSlabs = 8;      // K-slabs of 64 a tile needs before a balanced tail splits it
+constexpr int kTailSlots = 256;       // tiles a balanced tail can split (flag words behind the tracker state)
+constexpr int kReduceThreads = 256;   // threads of a reduction workgroup
+constexpr int kReduceBatch = 4;       // 16-byte pieces of each operand such a thread has in flight
+
+struct Choice {
+  Kernel kernel;
+  TileShape tile;
+};
+
+// For `steps` whole ring steps of a problem: the tile with the least time by rounds of workgroups x
+// time of a tile.  The times are fitted to 110 problems (8 to 16384 tokens, K 128 to 10240, all layouts,
+// TP 2 to 32), each run on every tile: what is picked is 0.4 % slower than the best of the eight on
+// average, 10 % at most.  They carry what the problems had in common (traffic past the L2s, clocks).
+// wide_ok: the wide-tile kernel may be used (sizes, see wide_fits).  Where it may not, or K has fewer slabs than its LDS stages, gemm_tile_kernel takes its place on the shapes it has: the
+// same main loop rate (12288 x 4096 x 6144, B stored K x N: 493 us, 495 wide), but the incoming partial
+// is waited for at the start of every tile (12288 x 4096 x 1536: 19 us per tile outside the main loop, 14 wide).
+inline Choice workgroup_tile(const t3_problem *p, int cus, int64_t steps, bool wide_ok) {
+  struct Cand {
+    TileShape t;
+    int stages, per_cu;          // LDS stages of the wide-tile kernel (0: small-tile kernel); workgroups per compute unit
+    double slab_us, ends_us;     // a K-slab of 64 / the rest of a tile
+  };
+  static const Cand kCand[] = {{{256, 256}, 2, 1, 1.22, 14.3}, {{256, 192}, 2, 1, 0.90, 13.3},
+                               {{256, 128}, 3, 1, 0.75, 10.9}, {{128, 192}, 3, 1, 0.59, 8.2},
+                               {{128, 128}, 2, 2, 0.81, 7.4},  {{64, 64}, 0, 1, 0.166, 6.55},
+                               {{32, 64}, 0, 1, 0.113, 6.9},   {{32, 32}, 0, 2, 0.115, 5.3}};
+  const bool km = p->a_layout == T3_A_KM, kn = p->b_layout == T3_B_KN;
+  const int64_t W = p->N / p->tp;
+  const int64_t slabs = ceil_div(p->K, 64);
+  double best = -1.0;
+  Choice pick{kSmallTile, kCand[5].t};
+  for (const Cand &c : kCand) {
+    const bool general = c.stages && (!wide_ok || slabs < c.stages);
+    if (general && c.t.n == 192) continue;
+    const int64_t T = ceil_div(p->M, c.t.m) * ceil_div(W, c.t.n) * steps, slots = (int64_t)cus * c.per_cu;
+    double rounds = (double)ceil_div(T, slots);
+    const bool tail = c.stages && !general && c.per_cu == 1 && T > slots && T % slots && 2 * (T % slots) <= slots &&
+                      p->K / 64 >= kTailMinSlabs && !(p->flags & T3_FLAG_FWD_BF16);
+    if (tail) rounds -= 0.5;
+    // (a compute unit with one tile instead of two has it done in 0.8 of the time)
+    const double alone = c.per_cu == 2 && T <= cus ? 0.8 : 1.0;
+    // (k-rows of a transposed operand are half a 128-byte line long in a 32 wide tile)
+    const double slab_us = c.slab_us * (km && c.t.m == 32 ? 1.34 : 1.0) * (kn && c.t.n == 32 ? 1.34 : 1.0);
+    const double us = rounds * alone * ((general ? 1.4 : 1.0) * c.ends_us + slab_us * (double)slabs);
+    if (best < 0 || us < best * 0.999) {
+      best = us;
+      pick = {!c.stages ? kSmallTile : (general ? kGeneralTile : kWideTile), c.t};
+    }
+  }
+  return pick;
+}
+
+// Workgroup tile of the reduction over whole ring steps: columns of a chunk in equal parts of at most
+// 256 (1 KiB runs), cut at whole 128-byte lines; rows so that a workgroup of 256 lanes has one batch of
+// four 16-byte pieces per lane, or half and a quarter of one where that leaves compute units idle.  (Two, four
+// and eight batches per workgroup, GEMM and reduction of 2343 x 17664 x 384: 191, 200 and 197 us, one 188;
+// of 2048 x 4096 x 512: 42, 47 and 47, one 40.)
+inline TileShape reduce_tile_shape(const t3_problem *p, int cus, int64_t steps) {
+  const int64_t W = p->N / p->tp, parts = ceil_div(W, 256);
+  const int64_t tn = ceil_div(ceil_div(W, parts), 32) * 32, width = tn < W ? tn : W;
+  int64_t tm = 1;
+  for (int64_t batch = kReduceBatch; batch >= kReduceBatch / 4; batch /= 2) {
+    tm = batch * kReduceThreads * 4 / width;
+    if (ceil_div(p->M, tm) * ceil_div(W, tn) * steps >= 2 * cus) break;
+  }
+  return {(int32_t)tm, (int32_t)tn};
+}
+
+// The wide-tile kernel marks what lies outside by buffer offsets from 2^31 on, so every array it
+// addresses, counted to the end of its last tile, has to fit 2 GiB.
+inline bool wide_fits(const t3_problem *p, int64_t ld_out) {
+  const int64_t kMost = 1ll << 31;
+  return (p->a_layout == T3_A_KM ? p->K : p->M) * p->lda * 2 <= kMost &&
+         (p->b_layout == T3_B_KN ? p->K : p->N) * p->ldb * 2 <= kMost && ((int64_t)p->M + 256) * ld_out * 4 <= kMost;
+}
+
+// What a call over a tile range launches.  `tracked`: the problem's tile, which the range is counted in.
+struct LaunchShape {
+  Kernel kernel;
+  TileShape tile;                // the workgroup tile
+  int64_t tracked_tpc;           // tracked tiles of a chunk
+  int64_t Mt, Wt, tpc;           // workgroup tiles: rows, columns, tiles of a chunk
+  int64_t begin, limit;          // the range in workgroup tiles
+  int64_t stage0, total_blocks;  // the ring steps it touches: the first, grid positions from there
+  int64_t resident;              // workgroups of this tile the device holds at once
+  int64_t tail_r, tail_q;        // balanced tail: tiles split, full rounds before them (0: none)
+};
+inline LaunchShape launch_shape(const t3_problem *p, Call call, TileShape tracked, int cus) {
+  LaunchShape s{};
+  const bool two_writers = (call == kCallFused || call == kCallOther) && (p->flags & T3_FLAG_TWO_WRITERS);
+  const int64_t W = p->N / p->tp;
+  s.tracked_tpc = ceil_div(p->M, tracked.m) * ceil_div(W, tracked.n);
+  const int64_t T = s.tracked_tpc * p->tp;
+  s.limit = (p->tile_limit < 0 || p->tile_limit > T) ? T : p->tile_limit;
+  s.begin = p->tile_begin < 0 ? 0 : (p->tile_begin > s.limit ? s.limit : p->tile_begin);
+  s.kernel = call == kCallReduce ? kReduction : kGeneralTile;
+  s.tile = tracked;
+  // Over whole ring steps nothing but the counters' final values depends on the tracked tile, so a
+  // chunk is cut as suits the chip; a range that cuts a step is in units of tracked tiles, and so are the
+  // two-writer calls' counts.
+  if (T && !two_writers && call != kCallOther && s.begin % s.tracked_tpc == 0 && s.limit % s.tracked_tpc == 0) {
+    const int64_t steps = (s.limit - s.begin) / s.tracked_tpc;
+    if (call == kCallReduce) {
+      s.tile = reduce_tile_shape(p, cus, steps);
+    } else {
+      const Choice c = workgroup_tile(p, cus, steps, wide_fits(p, call == kCallGemm ? p->ldc : p->ldr));
+      s.kernel = c.kernel;
+      s.tile = c.tile;
+    }
+  }
+  s.Mt = ceil_div(p->M, s.tile.m);
+  s.Wt = ceil_div(W, s.tile.n);
+  s.tpc = s.Mt * s.Wt;
+  // (where workgroup tiles are not the tracked ones the range is whole steps)
+  if (s.tpc != s.tracked_tpc && s.tracked_tpc) {
+    s.limit = s.limit / s.tracked_tpc * s.tpc;
+    s.begin = s.begin / s.tracked_tpc * s.tpc;
+  }
+  s.stage0 = s.tpc > 0 ? s.begin / s.tpc : 0;
+  s.total_blocks = s.tpc > 0 && s.begin < s.limit ? (ceil_div(s.limit, s.tpc) - s.stage0) * s.tpc : 0;
+  // one workgroup per compute unit, two of the smallest of the large tiles
+  s.resident = (int64_t)cus * (s.tile.m == 128 && s.tile.n == 128 ? 2 : 1);
+  // Balanced tail (see the kernels' work_item): launches of the wide-tile kernel whose last round of
+  // grid positions would fill at most half the chip; every half needs a few K-slabs, and the partial sums pass
+  // through the fp32 destination (so not with bfloat16 forward slots), each element with one writer at a time.
+  const bool slot_bf16 = call == kCallFused && (p->flags & T3_FLAG_FWD_BF16);
+  if (s.kernel == kWideTile && s.resident == cus && !slot_bf16 && s.total_blocks > s.resident && p->K / 64 >= kTailMinSlabs) {
+    const int64_t r = s.total_blocks % s.resident;
+    if (r > 0 && 2 * r <= s.resident && r <= kTailSlots) {
+      s.tail_r = r;
+      s.tail_q = s.total_blocks / s.resident;
+    }
+  }
+  return s;
+}
+
+}  // namespace t3k

@@ -7,6 +7,8 @@
 
 #include <type_traits>
 
+#include "t3_choice.h"
+
 #ifndef T3_MH
 #define T3_MH 2            // row passes per MFMA k-step of a 128-row wavefront tile (2 or 4)
 #endif
@@ -22,7 +24,6 @@ constexpr int kThreads = 256;
 constexpr uint32_t kEmpty = 0xFFFFFFFFu;
 constexpr int kSpinLimit = 1 << 22;   // polls for the other half of a split tile before the wait gives up
 constexpr int kTimelineItems = 16;     // pieces of work per workgroup a timeline records
-constexpr int kTailSlots = 256;       // tiles a balanced tail can split (flag words behind the tracker state)
 
 constexpr uint32_t kFlagStep0StoreOnly = 1u;
 constexpr uint32_t kFlagFwdDirect = 2u;

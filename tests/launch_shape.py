@@ -1,0 +1,45 @@
+"""What a call of the library launches (kernel, workgroup tile, balanced tail), asked of the header that
+decides it; no GPU needed.  The decision is compiled from csrc/t3_choice.h as the library's is."""
+import ctypes
+import os
+import subprocess
+import tempfile
+from typing import NamedTuple
+
+from paper_2401_16677_amd import binding as t3
+from paper_2401_16677_amd import build as hip_build
+
+GENERAL, WIDE, SMALL, REDUCTION = range(4)
+FUSED, GEMM, REDUCE = range(3)
+CUS = 256
+
+
+class Shape(NamedTuple):
+    kernel: int
+    tile_m: int
+    tile_n: int
+    tpc: int
+    begin: int
+    limit: int
+    blocks: int
+    resident: int
+    tail_r: int
+    tail_q: int
+
+
+_lib = None
+
+
+def launch_shape(p, call=FUSED, cus=CUS):
+    global _lib
+    if _lib is None:
+        with tempfile.TemporaryDirectory() as d:
+            so = os.path.join(d, "kernel_choice.so")
+            subprocess.run(["g++", "-O1", "-std=c++17", "-Wall", "-Werror", "-shared", "-fPIC", "-I",
+                            os.path.join(hip_build.ROOT, "include"), "-I", hip_build.CSRC,
+                            os.path.join(hip_build.ROOT, "tests", "kernel_choice.cpp"), "-o", so], check=True)
+            _lib = ctypes.CDLL(so)
+    tracked = (p.tile_m, p.tile_n) if p.tile_m else t3.t3_default_tile(p)
+    out = (ctypes.c_int64 * 10)()
+    _lib.launch_shape(ctypes.byref(p), call, *tracked, cus, out)
+    return Shape(*out)

@@ -1,0 +1,82 @@
+"""CPU-only checks of which kernel serves a call, on which workgroup tile (csrc/t3_choice.h)."""
+import numpy as np
+import pytest
+
+from paper_2401_16677_amd import binding as t3
+from tests.launch_shape import FUSED, GEMM, GENERAL, REDUCE, REDUCTION, SMALL, WIDE, launch_shape
+
+
+def _problem(M, W, K, tp, layout="nk", **kw):
+    return t3.problem(M, W * tp, K, tp, 0, b_layout=t3.T3_B_KN if "kn" in layout else t3.T3_B_NK,
+                      a_layout=t3.T3_A_KM if "km" in layout else t3.T3_A_MK, **kw)
+
+
+@pytest.mark.parametrize("call", [FUSED, GEMM, REDUCE])
+def test_tile_and_tail_follow_the_device(call):
+    """The tile is chosen, and the workgroups and the balanced tail counted, for the compute units there are."""
+    p = _problem(2048, 2560, 10240, 8)
+    whole, half = launch_shape(p, call, 256), launch_shape(p, call, 128)
+    assert whole.resident == 256 and half.resident == 128
+    if call == REDUCE:
+        assert whole.kernel == half.kernel == REDUCTION
+        few = _problem(64, 256, 64, 8)
+        assert launch_shape(few, REDUCE, 16).tile_m > launch_shape(few, REDUCE, 256).tile_m
+    else:
+        assert (whole.kernel, whole.tile_m, whole.tile_n, whole.tail_r, whole.tail_q) == (WIDE, 256, 256, 128, 2)
+        assert (half.tail_r, half.tail_q) == (0, 0) and half.blocks == 640      # five whole rounds
+        # a problem of one round on 256 units is several on 64, and takes larger tiles there
+        few = _problem(1024, 512, 1536, 8)
+        a, b = launch_shape(few, call, 256), launch_shape(few, call, 64)
+        assert a.tile_m * a.tile_n < b.tile_m * b.tile_n
+
+
+def test_random_problems_are_covered_once():
+    """Workgroup tiles of a random problem: the range covers whole steps of the tracked one, the
+    balanced tail splits what the last round leaves, and ranges that cut a step stay in tracked tiles."""
+    rng = np.random.default_rng(5)
+    for _ in range(400):
+        tp = int(rng.choice([1, 2, 3, 8, 16, 32]))
+        layout = str(rng.choice(["nk", "kn", "km_kn"]))
+        M, W = int(rng.integers(1, 700)) * 8, int(rng.integers(1, 200)) * 8
+        K = int(rng.integers(1, 40)) * 64 if layout != "nk" else int(rng.integers(1, 300)) * 8
+        p = _problem(M, W, K, tp, layout)
+        tpc = t3.t3_tiles_per_chunk(p)
+        lo = int(rng.integers(0, tp))
+        hi = int(rng.integers(lo + 1, tp + 1))
+        cut = bool(rng.integers(0, 2)) and tpc > 1
+        p = _problem(M, W, K, tp, layout, tile_begin=lo * tpc + cut, tile_limit=hi * tpc)
+        for call in (FUSED, GEMM, REDUCE):
+            s = launch_shape(p, call)
+            Mt, Wt = -(-M // s.tile_m), -(-W // s.tile_n)
+            assert s.tpc == Mt * Wt
+            if cut:
+                assert (s.tile_m, s.tile_n) == t3.t3_default_tile(p) and (s.begin, s.limit) == (lo * tpc + 1, hi * tpc)
+            else:
+                assert (s.begin, s.limit) == (lo * s.tpc, hi * s.tpc) and s.blocks == (hi - lo) * s.tpc
+            if s.tail_r:
+                assert s.kernel == WIDE and s.tail_q * s.resident + s.tail_r == s.blocks and 2 * s.tail_r <= s.resident
+
+
+# One problem for every kernel and workgroup tile there is.
+@pytest.mark.parametrize("M,W,K,tp,layout,want", [
+    (4096, 1536, 1536, 8, "nk", (WIDE, 256, 256)),
+    (1536, 1536, 4096, 8, "km_kn", (WIDE, 256, 192)),
+    (512, 512, 4096, 32, "nk", (WIDE, 256, 128)),
+    (4096, 1536, 1536, 1, "nk", (WIDE, 128, 192)),
+    (2048, 512, 1536, 8, "nk", (WIDE, 128, 128)),
+    (64, 384, 128, 32, "nk", (SMALL, 64, 64)),
+    (8, 384, 4096, 32, "kn", (SMALL, 32, 64)),
+    (256, 256, 256, 4, "nk", (SMALL, 32, 32)),
+])
+def test_every_tile_has_a_problem(M, W, K, tp, layout, want):
+    s = launch_shape(_problem(M, W, K, tp, layout))
+    assert (s.kernel, s.tile_m, s.tile_n) == want
+
+
+def test_general_kernel():
+    p = _problem(4096, 1536, 1536, 8, tile_m=256, tile_n=256, tile_begin=1)
+    assert launch_shape(p).kernel == GENERAL                     # a range that cuts a step
+    p = _problem(4096, 1536, 1536, 8, tile_m=128, tile_n=128, flags=t3.T3_FLAG_TWO_WRITERS)
+    s = launch_shape(p)
+    assert (s.kernel, s.tile_m, s.tile_n) == (GENERAL, 128, 128)
+    assert launch_shape(p, GEMM).kernel == WIDE                  # (the plain GEMM has no second writer)
