@@ -86,12 +86,13 @@ inline TileShape reduce_tile_shape(const t3_problem *p, int cus, int64_t steps) 
   return {(int32_t)tm, (int32_t)tn};
 }
 
-// The wide-tile kernel marks what lies outside by buffer offsets from 2^31 on, so every array it
-// addresses, counted to the end of its last tile, has to fit 2 GiB.
+// The wide-tile kernel's offsets count from where a tile starts, and what lies outside is marked by their top
+// bit: the rows of a tile (256 at most) have to fit 2 GiB, of a transposed operand the whole array.  (65536 x 12288
+// x 1536, R of 3 GiB: 2518 us here, 2744 by gemm_tile_kernel.)
 inline bool wide_fits(const t3_problem *p, int64_t ld_out) {
-  const int64_t kMost = 1ll << 31;
-  return (p->a_layout == T3_A_KM ? p->K : p->M) * p->lda * 2 <= kMost &&
-         (p->b_layout == T3_B_KN ? p->K : p->N) * p->ldb * 2 <= kMost && ((int64_t)p->M + 256) * ld_out * 4 <= kMost;
+  const int64_t kMost = 1ll << 31, rows = 256;
+  return (p->a_layout == T3_A_KM ? p->K : rows) * p->lda * 2 <= kMost &&
+         (p->b_layout == T3_B_KN ? p->K : rows) * p->ldb * 2 <= kMost && rows * ld_out * 4 <= kMost;
 }
 
 // What a call over a tile range launches.  `tracked`: the problem's tile, which the range is counted in.

@@ -20,10 +20,10 @@
 //  - The count of a tile is asked for when its stores are known to be acknowledged, in the next
 //    tile's main loop, and acted on a slab later.
 //
-// Copies, incoming partial and results are buffer accesses: rows past M, columns past the chunk and
-// K past its end are addresses past the buffer, read as zeros and not written; no access is
-// conditional, so the number of accesses in flight is always known.  (Addresses past the buffer:
-// kOob = 2^31 plus anything, with buffers of at most 2^31 bytes: the host sees to that.)
+// Copies, incoming partial and results are buffer accesses of buffers that start where the tile does: rows
+// past M, columns past the chunk and K past its end are addresses past the buffer, read as zeros and not
+// written; no access is conditional, so the number of accesses in flight is always known.  (Addresses past the
+// buffer: behind its last row, or kOob = 2^31 plus anything, with buffers of at most 2^31 bytes: the host sees to that.)
 //
 // Included by the launch units only.
 #pragma once
@@ -150,13 +150,11 @@ void wide_tile_kernel(const Plan p) {
 
   // ---- the copy stream.  Copy q of a wavefront and operand fills 1 KiB of the operand's region of a
   // stage: eight rows of 64 K-contiguous bf16, or k-rows of a transposed operand (layouts and
-  // swizzles as in gemm_tile_kernel).  off*: this lane's byte offsets for the stream's current piece.
+  // swizzles as in gemm_tile_kernel).  off*: this lane's byte offsets from where the tile starts in the
+  // operand, which is where the piece's descriptor points: from one piece to the next only the descriptors
+  // change, in scalar registers (and, transposed, which columns lie outside), and a K-contiguous operand may be of
+  // any size.
   uint32_t offA[NA], offB[NB];
-  auto descriptor = [](const void *base, int64_t bytes) {        // what make_rsrc makes, for inline assembly
-    const uint64_t a = (uint64_t)(uintptr_t)base;
-    return u32x4{(uint32_t)a, (uint32_t)(a >> 32), (uint32_t)bytes, 0x00020000u};
-  };
-  const u32x4 descA = descriptor(p.A, (AKM ? p.K : p.M) * p.lda * 2), descB = descriptor(p.B, (BKN ? p.K : p.N) * p.ldb * 2);
   constexpr int kARow = BM * 2, kBRow = BN * 2;  // bytes of a k-row of a transposed operand's region
   auto sw_mask = [](int blocks) { return (blocks % 8 == 0 ? 8 : 4) - 1; };
   auto k_chunk = [&](int q) { return (lane % kCPR) ^ swz(q * kRPC + lane / kCPR); };   // (K-contiguous) chunk of copy q
@@ -166,30 +164,59 @@ void wide_tile_kernel(const Plan p) {
     const int sw = ((k & 3) | (((k >> 3) & 1) << 2)) & mask;
     col = (((cp >> 1) ^ sw) * 2 + (cp & 1)) * 8;
   };
+#pragma unroll
+  for (int q = 0; q < NA; ++q) {
+    if (AKM) {
+      int k, col;
+      tr_at((wave * NA + q) * 1024 + lane * 16, kARow, sw_mask(BM / 16), k, col);
+      offA[q] = (uint32_t)(k * (int)p.lda + col) * 2u;
+    } else {
+      offA[q] = (uint32_t)((wave * (BM / 4) + q * kRPC + lane / kCPR) * (int)p.lda + k_chunk(q) * 8) * 2u;
+    }
+  }
+#pragma unroll
+  for (int q = 0; q < NB; ++q) {
+    if (BKN) {
+      int k, col;
+      tr_at((wave * NB + q) * 1024 + lane * 16, kBRow, sw_mask(BN / 16), k, col);
+      offB[q] = (uint32_t)(k * (int)p.ldb + col) * 2u;
+    } else {
+      offB[q] = (uint32_t)((wave * (BN / 4) + q * kRPC + lane / kCPR) * (int)p.ldb + k_chunk(q) * 8) * 2u;
+    }
+  }
+  auto descriptor = [](const void *base, int64_t bytes) {        // what make_rsrc makes, for inline assembly
+    const uint64_t a = (uint64_t)(uintptr_t)base;
+    return u32x4{(uint32_t)a, (uint32_t)(a >> 32), (uint32_t)bytes, 0x00020000u};
+  };
+  u32x4 descA, descB;
+  // Which of a lane's copies lie outside in the piece's last slab (K-contiguous, ragged K) or throughout (transposed,
+  // columns past the tile's end): their offsets get the top bit, the others lose it.
+  auto mark = [](uint32_t off, bool outside) { return outside ? off | kOob : off & ~kOob; };
+  bool markedA = false, markedB = false;         // some have it
   int st_k0 = 0, st_nf = 0, st_koff = 0;         // the stream's piece: first slab, full slabs, where its walk starts
   auto stream_to = [&](const Piece &w) {
-    const int m0 = w.tl.mi * BM, col_lo = w.tl.c * p.W, col_hi = col_lo + p.W, n0 = col_lo + w.tl.nj * BN;
+    const int m0 = w.tl.mi * BM, n0 = w.tl.c * p.W + w.tl.nj * BN;
+    const int rows = min(BM, p.M - m0), cols = min(BN, p.W - w.tl.nj * BN);
+    descA = AKM ? descriptor(p.A + m0, (p.K * p.lda - m0) * 2) : descriptor(p.A + m0 * p.lda, rows * p.lda * 2);
+    descB = BKN ? descriptor(p.B + n0, (p.K * p.ldb - n0) * 2) : descriptor(p.B + n0 * p.ldb, cols * p.ldb * 2);
+    const bool cutA = AKM && rows < BM, cutB = BKN && cols < BN;
+    if (cutA || markedA) {
 #pragma unroll
-    for (int q = 0; q < NA; ++q) {
-      if (AKM) {
-        int k, col;
-        tr_at((wave * NA + q) * 1024 + lane * 16, kARow, sw_mask(BM / 16), k, col);
-        offA[q] = m0 + col < p.M ? (uint32_t)(k * (int)p.lda + m0 + col) * 2u : kOob;
-      } else {
-        const int row = m0 + wave * (BM / 4) + q * kRPC + lane / kCPR;
-        offA[q] = row < p.M ? (uint32_t)(row * (int)p.lda + k_chunk(q) * 8) * 2u : kOob;
+      for (int q = 0; q < NA; ++q) {
+        int k, col = 0;
+        if (AKM) tr_at((wave * NA + q) * 1024 + lane * 16, kARow, sw_mask(BM / 16), k, col);
+        offA[q] = mark(offA[q], AKM && col >= rows);
       }
+      markedA = cutA;
     }
+    if (cutB || markedB) {
 #pragma unroll
-    for (int q = 0; q < NB; ++q) {
-      if (BKN) {
-        int k, col;
-        tr_at((wave * NB + q) * 1024 + lane * 16, kBRow, sw_mask(BN / 16), k, col);
-        offB[q] = n0 + col < col_hi ? (uint32_t)(k * (int)p.ldb + n0 + col) * 2u : kOob;
-      } else {
-        const int row = n0 + wave * (BN / 4) + q * kRPC + lane / kCPR;
-        offB[q] = row < col_hi ? (uint32_t)(row * (int)p.ldb + k_chunk(q) * 8) * 2u : kOob;
+      for (int q = 0; q < NB; ++q) {
+        int k, col = 0;
+        if (BKN) tr_at((wave * NB + q) * 1024 + lane * 16, kBRow, sw_mask(BN / 16), k, col);
+        offB[q] = mark(offB[q], BKN && col >= cols);
       }
+      markedB = cutB;
     }
     st_k0 = w.k0;
     st_nf = w.nf;
@@ -200,17 +227,13 @@ void wide_tile_kernel(const Plan p) {
   auto stream_ragged = [&]() {                   // the stream's last slab ends with K: nothing behind it
     if constexpr (!AKM && !BKN) {
 #pragma unroll
-      for (int q = 0; q < NA; ++q) offA[q] = k_chunk(q) * 8 < ktail ? offA[q] : kOob;
+      for (int q = 0; q < NA; ++q) offA[q] = mark(offA[q], k_chunk(q) * 8 >= ktail);
 #pragma unroll
-      for (int q = 0; q < NB; ++q) offB[q] = k_chunk(q) * 8 < ktail ? offB[q] : kOob;
+      for (int q = 0; q < NB; ++q) offB[q] = mark(offB[q], k_chunk(q) * 8 >= ktail);
+      markedA = markedB = true;
     }
   };
-  auto stream_end = [&]() {
-#pragma unroll
-    for (int q = 0; q < NA; ++q) offA[q] = kOob;
-#pragma unroll
-    for (int q = 0; q < NB; ++q) offB[q] = kOob;
-  };
+  auto stream_end = [&]() { descA[2] = descB[2] = 0u; };          // (buffers of no bytes)
 #pragma clang diagnostic push
 #pragma clang diagnostic ignored "-Winline-asm"
   auto copy_one = [&](auto Q, uint32_t so, uint32_t soffA, uint32_t soffB) {
@@ -362,20 +385,22 @@ void wide_tile_kernel(const Plan p) {
   for (int it = 0;; ++it) {
     stamp(it, 0);
     const Tile tl = cur.tl;
-    const int m0 = tl.mi * BM, col_lo = tl.c * p.W, col_hi = col_lo + p.W, n0 = col_lo + tl.nj * BN;
+    const int m0 = tl.mi * BM, n0 = tl.c * p.W + tl.nj * BN;
+    const uint32_t rows_in = (uint32_t)min(BM, p.M - m0);         // rows and columns of the tile inside the chunk
+    const int cols_in = min(BN, p.W - tl.nj * BN);
     const bool direct = (p.flags & kFlagFwdDirect) != 0, bf16 = (p.flags & kFlagFwdBf16) != 0;
     const bool to_slot = tracked && tl.c != p.own && cur.half != 1 && (direct || chunk_is_whole(p, tl.s));
     const bool to_r = !tracked || !direct || tl.c == p.own;
     // where a whole tile's fp32 sums go, or half a tile's (an fp32 slot if not R / C)
     const bool out_slot = tracked && direct && tl.c != p.own;
-    float *const out_base = out_slot ? p.fwd + (int64_t)tl.s * p.M * p.W : p.R;
+    float *const slot_at0 = p.fwd + (((int64_t)tl.s * p.M + m0) * p.W + tl.nj * BN);      // the tile's first element in each
+    float *const r_at0 = p.R + (m0 * p.ldr + n0);
+    float *const out_base = out_slot ? slot_at0 : r_at0;
     const uint32_t ld_out = out_slot ? (uint32_t)p.W : (uint32_t)p.ldr;
-    const int col_org = out_slot ? col_lo : 0;
     const bool has_in = cur.half == 2 || (tracked && !((p.flags & kFlagStep0StoreOnly) && tl.s == 0));
     // the incoming partial, or the first half's partial sums where the result will go
-    const float *const in_base = cur.half == 2 ? out_base : p.R;
+    const float *const in_base = cur.half == 2 ? out_base : r_at0;
     const uint32_t ld_in = cur.half == 2 ? ld_out : (uint32_t)p.ldr;
-    const int in_org = cur.half == 2 ? col_org : 0;
 
     if (cur.ns <= NSTAGE) flush();               // (too short a K loop to put the count off into)
     if (cur.half == 2 && threadIdx.x == 0) {
@@ -399,7 +424,7 @@ void wide_tile_kernel(const Plan p) {
     static_for<NR>([&](auto R) { read_op(R, c0, c0, adA[0] + so, adB[0] + so); });
 
     f32x4 in[FM][FN];
-    const __amdgpu_buffer_rsrc_t in_rsrc = make_rsrc(in_base, (uint32_t)p.M * ld_in * 4u);
+    const __amdgpu_buffer_rsrc_t in_rsrc = make_rsrc(in_base, rows_in * ld_in * 4u);
     uint32_t in_at[UB];
     auto load_in = [&](auto I) {                 // row block I of the incoming partial
       constexpr int i = decltype(I)::value;
@@ -429,7 +454,7 @@ void wide_tile_kernel(const Plan p) {
 #pragma unroll
           for (int u = 0; u < UB; ++u) {
             const int L = u * 64 + lane, ir = wave * 8 + L / kRowCh, col = (L % kRowCh) * 4;
-            in_at[u] = n0 + col < col_hi ? ((uint32_t)(m0 + strip_row(ir)) * ld_in + (uint32_t)(n0 - in_org + col)) * 4u : kOob;
+            in_at[u] = col < cols_in ? ((uint32_t)strip_row(ir) * ld_in + (uint32_t)col) * 4u : kOob;
           }
           static_for<PRE>([&](auto I) { load_in(I); });
         }
@@ -487,17 +512,15 @@ void wide_tile_kernel(const Plan p) {
     // TO: -1 = fp32 to C, kept in the caches; 0 = fp32 to R, C or a slot, streamed; 1 = R and the fp32 slot; 2 = the bfloat16 slot; 3 = R and the bfloat16 slot
     auto way_out = [&](auto TO) {
       constexpr int to = decltype(TO)::value;
-      const __amdgpu_buffer_rsrc_t out_rsrc = make_rsrc(out_base, (uint32_t)p.M * ld_out * 4u);
-      const float *slot = to >= 2 ? (const float *)((const uint16_t *)p.fwd + (int64_t)tl.s * p.M * p.W)
-                                  : p.fwd + (int64_t)tl.s * p.M * p.W;
-      const __amdgpu_buffer_rsrc_t slot_rsrc = make_rsrc(slot, (uint32_t)p.M * (uint32_t)p.W * (to >= 2 ? 2u : 4u));
+      const __amdgpu_buffer_rsrc_t out_rsrc = make_rsrc(out_base, rows_in * ld_out * 4u);
+      const void *slot = to >= 2 ? (const void *)((const uint16_t *)p.fwd + (slot_at0 - p.fwd)) : (const void *)slot_at0;
+      const __amdgpu_buffer_rsrc_t slot_rsrc = make_rsrc(slot, rows_in * (uint32_t)p.W * (to >= 2 ? 2u : 4u));
       uint32_t out_at[UB], slot_at[UB], img_at[FN];
 #pragma unroll
       for (int u = 0; u < UB; ++u) {
-        const int L = u * 64 + lane_e, ir = wave * 8 + L / kRowCh, col = (L % kRowCh) * 4, row = m0 + strip_row(ir);
-        const bool ok = n0 + col < col_hi;
-        out_at[u] = ok ? ((uint32_t)row * ld_out + (uint32_t)(n0 - col_org + col)) * 4u : kOob;
-        slot_at[u] = ok ? ((uint32_t)row * (uint32_t)p.W + (uint32_t)(n0 - col_lo + col)) * (to >= 2 ? 2u : 4u) : kOob;
+        const int L = u * 64 + lane_e, ir = wave * 8 + L / kRowCh, col = (L % kRowCh) * 4, row = strip_row(ir);
+        out_at[u] = col < cols_in ? ((uint32_t)row * ld_out + (uint32_t)col) * 4u : kOob;
+        slot_at[u] = col < cols_in ? ((uint32_t)row * (uint32_t)p.W + (uint32_t)col) * (to >= 2 ? 2u : 4u) : kOob;
       }
 #pragma unroll
       for (int u = 0; u < FN; ++u) {

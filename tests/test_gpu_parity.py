@@ -862,13 +862,14 @@ def test_plain_c_client_of_the_abi(gpu, flags):
     assert r.returncode == 0 and " 0 mismatches" in r.stdout
 
 
-def test_largest_supported_buffers(gpu, oracle):
+@pytest.mark.parametrize("K", [64, 136])       # one K-slab: gemm_tile_kernel; two and a ragged one: the wide-tile kernel
+def test_largest_supported_buffers(gpu, oracle, K):
     """R, C and the forward slot just below the documented 4 GiB limit (the kernels address them
     with 32-bit byte offsets): M = 32768, N = 32760, so the last element sits at byte offset
     4,293,918,716.  Integer inputs given by a formula; rows sampled from both ends and the
     middle are compared bit for bit, fused and unfused, and the size one step further is refused."""
     import torch
-    M, N, K, tp, rank, tile = 32768, 32760, 64, 2, 1, (256, 256)
+    M, N, tp, rank, tile = 32768, 32760, 2, 1, (256, 256)
     assert M * N * 4 < 2 ** 32 < (M + 16) * N * 4
     W = N // tp
     a = wl.make_integer_inputs(M, 8, K, seed=1700)[0]          # (the generator's own incoming

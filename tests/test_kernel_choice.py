@@ -80,3 +80,17 @@ def test_general_kernel():
     s = launch_shape(p)
     assert (s.kernel, s.tile_m, s.tile_n) == (GENERAL, 128, 128)
     assert launch_shape(p, GEMM).kernel == WIDE                  # (the plain GEMM has no second writer)
+
+
+@pytest.mark.parametrize("M,W,K,tp,layout,wide", [
+    (160000, 512, 8192, 4, "nk", True),          # A of 2.4 GiB
+    (512, 16384, 10240, 8, "nk", True),          # B of 2.5 GiB
+    (65536, 1536, 1536, 8, "nk", True),          # R of 3 GiB
+    (65536, 1536, 1536, 8, "km_kn", True),       # R of 3 GiB, operands small
+    (512, 16384, 10240, 8, "kn", False),         # B of 2.5 GiB, stored K x N
+    (163840, 512, 8192, 4, "km", False),         # A of 2.5 GiB, stored K x M
+])
+def test_arrays_of_more_than_2_gib(M, W, K, tp, layout, wide):
+    """Only a transposed operand past 2 GiB keeps a problem from the wide-tile kernel."""
+    for call in (FUSED, GEMM):
+        assert (launch_shape(_problem(M, W, K, tp, layout), call).kernel == WIDE) == wide
