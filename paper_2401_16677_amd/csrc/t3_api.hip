@@ -408,6 +408,10 @@ t3_status make_plan(const t3_problem *p, t3k::Call call, int need, const void *A
     }
   }
 
+  // (an empty problem has no tiles to divide by)
+  q.by_tpc = t3k::fast_div((uint32_t)(tpc > 0 ? tpc : 1));
+  q.by_column = t3k::fast_div((uint32_t)(tpc == 0 ? 1 : (q.xcd_nbm ? q.xcd_bmk : Mt)));
+
   q.agents = q.rows_per_agent = 0;
   const int64_t resident = shape.resident;
   q.stage0 = (int32_t)shape.stage0;
@@ -448,6 +452,7 @@ t3_status make_plan(const t3_problem *p, t3k::Call call, int need, const void *A
   }
   // K walks start at a different slab on every XCD (see the kernels' `koff`)
   q.k_groups = dev.xcds > 1 ? dev.xcds : 0;
+  q.by_groups = t3k::fast_div((uint32_t)(q.k_groups > 1 ? q.k_groups : 1));
   q.resident = (int32_t)resident;
   // Results leave the XCD's L2 at once (streaming hint) where that L2 is better spent on slabs
   // of A and B: long K loops, or an output that the memory-side cache cannot hold anyway.
@@ -485,14 +490,13 @@ inline unsigned grid_size(const t3k::Plan &q) { return (unsigned)q.total_blocks;
 t3_status launch_gemm(int mode, const t3k::Plan &q, int32_t tm, int32_t tn, bool b_kn, bool a_km, hipStream_t s) {
   using namespace t3k;
   if (q.wide) {
+    if (mode == kModeFused)
+      return a_km ? (b_kn ? launch_wide_fused_km_kn(q, tm, tn, s) : launch_wide_fused_km(q, tm, tn, s))
+                  : (b_kn ? launch_wide_fused_kn(q, tm, tn, s) : launch_wide_fused(q, tm, tn, s));
     Plan g = q;
-    if (mode != kModeFused) {
-      g.track = nullptr;                // the plain GEMM: C through R
-      g.flags = 0;
-      g.ldr = q.ldc;
-    }
-    return a_km ? (b_kn ? launch_wide_km_kn(g, tm, tn, s) : launch_wide_km(g, tm, tn, s))
-                : (b_kn ? launch_wide_kn(g, tm, tn, s) : launch_wide_nk(g, tm, tn, s));
+    g.ldr = q.ldc;                      // C through R
+    return a_km ? (b_kn ? launch_wide_gemm_km_kn(g, tm, tn, s) : launch_wide_gemm_km(g, tm, tn, s))
+                : (b_kn ? launch_wide_gemm_kn(g, tm, tn, s) : launch_wide_gemm_nk(g, tm, tn, s));
   }
   if (tm < 128)
     return mode == kModeFused ? launch_small_fused(q, tm, tn, b_kn, a_km, s) : launch_small_gemm(q, tm, tn, b_kn, a_km, s);

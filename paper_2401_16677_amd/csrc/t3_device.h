@@ -8,6 +8,7 @@
 #include <type_traits>
 
 #include "t3_choice.h"
+#include "t3_div.h"
 
 #ifndef T3_MH
 #define T3_MH 2            // row passes per MFMA k-step of a 128-row wavefront tile (2 or 4)
@@ -57,6 +58,7 @@ struct Plan {
   int32_t Mt, Wt, tpc, tracked;
   int32_t tile_m, tile_n;              // the workgroup tile, for the reduction kernel
   int32_t xcd_nbm, xcd_bmk, xcd_bnk;   // XCD grouping of a stage's tiles; xcd_nbm == 0: none
+  FastDiv by_tpc, by_column;           // by tpc; by xcd_bmk, or Mt without grouping
   int32_t agents, rows_per_agent;      // release_ready_kernel: workgroups per chunk, rows of each
   int32_t expected_done;               // grid positions of this launch that do work
   int32_t stage0, total_blocks;        // first ring step of the range, grid positions (tiles) from there
@@ -64,6 +66,7 @@ struct Plan {
   int32_t upd_first, upd_rest;         // updates expected per element of chunk order[0] / the others
   int32_t split_k;                     // >= 1: workgroups that share a tile, each taking a part of K (Sec. 7.7)
   int32_t stagger_blocks, stagger_groups, stagger_ticks;   // start-up phase offsets (see stagger_start)
+  FastDiv by_groups;                   // by k_groups
   int32_t k_groups;                    // > 1: workgroup w starts its K loop (w % k_groups) / k_groups of the way in
   int32_t nt_out;                      // results leave with the streaming hint (wide-tile kernel: the plain GEMM's)
   // Timeline (a profiling aid, normally null): workgroup w < timeline_wgs writes, for its i-th
@@ -119,16 +122,42 @@ __device__ inline Trk trk_at(const Plan &p, uint32_t gen_now) {
 // (an ordinary load: only the end of a launch changes the word, so the XCD's L2 may serve it)
 __device__ inline uint32_t trk_gen(const Plan &p) { return p.track[2 * trk_bank_words(p.P)]; }
 __device__ inline Trk trk_open(const Plan &p) { return trk_at(p, trk_gen(p)); }
-__device__ inline void trk_clear_bank(uint32_t *b, int P) {
-  for (int i = 0; i < 3 * P + 2; ++i)
-    __hip_atomic_store(&b[i], (i >= 2 * P && i < 3 * P) ? kEmpty : 0u, __ATOMIC_RELAXED,
-                       __HIP_MEMORY_SCOPE_AGENT);
+// Who acts on the tracker's words: one thread, behind a branch of its own ...
+struct TrkThread {
+  __device__ uint32_t add(uint32_t *w, uint32_t v) const {
+    return __hip_atomic_fetch_add(w, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  }
+  __device__ void put(uint32_t *w, uint32_t v) const {
+    __hip_atomic_store(w, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  }
+};
+// ... or a wavefront as one: every lane issues the access, lane 0's address alone lies inside the array.  Without
+// a branch that differs between lanes the compiler keeps rare code out of the way of the loop it stands in (such
+// branches have it lay out everything around them as one structured region, the loop's normal path last).
+constexpr uint32_t kOob = 0x80000000u;  // an offset past every buffer
+struct TrkWave {
+  __amdgpu_buffer_rsrc_t words;
+  uint32_t *base;
+  uint32_t lane_at;                     // lane 0: 0, the others: kOob
+  __device__ uint32_t ask(uint32_t *w, uint32_t v) const {       // (lane 0 has the answer)
+    return (uint32_t)__builtin_amdgcn_raw_ptr_buffer_atomic_add_i32((int)v, words, (int)lane_at, (int)at(w), 0);
+  }
+  __device__ uint32_t add(uint32_t *w, uint32_t v) const { return __builtin_amdgcn_readfirstlane(ask(w, v)); }
+  __device__ void put(uint32_t *w, uint32_t v) const {
+    __builtin_amdgcn_raw_buffer_store_b32(v, words, (int)lane_at, (int)at(w), 16 /* sc1 */);
+  }
+  __device__ uint32_t at(uint32_t *w) const { return (uint32_t)(w - base) * 4u; }
+};
+template <typename Who>
+__device__ inline void trk_clear_bank(uint32_t *b, int P, const Who &who) {
+  for (int i = 0; i < 3 * P + 2; ++i) who.put(&b[i], (i >= 2 * P && i < 3 * P) ? kEmpty : 0u);
 }
-// Called by thread 0 of a workgroup behind its addition to `done`; d = what that made of it.
-__device__ inline void trk_close_if_last(const Plan &p, const Trk &t, uint32_t d) {
+// Called behind a workgroup's addition to `done`; d = what that made of it.
+template <typename Who>
+__device__ inline void trk_close_if_last(const Plan &p, const Trk &t, uint32_t d, const Who &who) {
   if (d == (uint32_t)p.expected_done) {
-    trk_clear_bank(t.other, p.P);
-    __hip_atomic_fetch_add(t.gen, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    trk_clear_bank(t.other, p.P, who);
+    who.add(t.gen, 1u);
   }
 }
 
@@ -140,16 +169,17 @@ __device__ inline bool decode_tile(const Plan &p, int s, int j, Tile &tl) {
   int mi, nj;
   if (p.xcd_nbm) {
     const int x = j & 7, i = j >> 3;
-    const int bxm = x % p.xcd_nbm, bxn = x / p.xcd_nbm;
-    mi = bxm * p.xcd_bmk + i % p.xcd_bmk;
-    nj = bxn * p.xcd_bnk + i / p.xcd_bmk;
+    const int bxm = x & (p.xcd_nbm - 1), bxn = x >> (31 - __builtin_clz(p.xcd_nbm));   // (a power of two)
+    const int col = (int)div_by((uint32_t)i, p.by_column);
+    mi = bxm * p.xcd_bmk + i - col * p.xcd_bmk;
+    nj = bxn * p.xcd_bnk + col;
   } else {
     // the stage's positions are b0 .. n - 1 counted from the last multiple of 8 before them; in
     // front of XCD x's run come the positions of XCDs 0 .. x - 1
     const int b0 = ((s - p.stage0) * p.tpc) & 7, n = b0 + p.tpc, jj = j + b0, x = jj & 7;
     const int q = (n >> 3) * x + min(n & 7, x) - min(b0, x) + (jj >> 3) - (x < b0 ? 1 : 0);
-    mi = q % p.Mt;
-    nj = q / p.Mt;
+    nj = (int)div_by((uint32_t)q, p.by_column);
+    mi = q - nj * p.Mt;
   }
   const int64_t t = (int64_t)s * p.tpc + (int64_t)nj * p.Mt + mi;   // issue index
   int c = p.rank + s;
@@ -163,7 +193,7 @@ __device__ inline bool decode_tile(const Plan &p, int s, int j, Tile &tl) {
 
 // Grid layout: the tiles of the range's stages in order.  False: a position outside the tile range.
 __device__ inline bool decode_block(const Plan &p, int b, Tile &tl) {
-  const int s = b / p.tpc;
+  const int s = (int)div_by((uint32_t)b, p.by_tpc);
   return decode_tile(p, p.stage0 + s, b - s * p.tpc, tl);
 }
 // Whether this launch produces all of stage s's chunk: only then does the chunk get released.
@@ -221,6 +251,12 @@ __device__ inline bool work_item(const Plan &p, int it, int &blk, int &part, int
   }
   // (positions fit 31 bits, the launch code sees to that)
   const uint32_t pos = (uint32_t)w + (uint32_t)it * (uint32_t)G;
+  if (TAIL || p.split_k == 1) {                  // (a kernel with a balanced tail has no split-K)
+    blk = (int)pos;
+    part = 0;
+    nparts = 1;
+    return pos < (uint32_t)p.total_blocks;
+  }
   if (pos >= (uint32_t)p.total_blocks * (uint32_t)p.split_k) return false;
   blk = (int)(pos / (uint32_t)p.split_k);
   part = (int)(pos - (uint32_t)blk * (uint32_t)p.split_k);
@@ -364,47 +400,41 @@ __device__ inline TrkCount track_issue(const Plan &p, const Trk &t, const Tile &
   k.done = p.whole_chunks ? 0u : __hip_atomic_fetch_add(t.done, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   return k;
 }
-// By thread 0: acts on what the count returned.
-__device__ inline void track_finish(const Plan &p, const Trk &t, const Tile &tl, TrkCount k) {
+// Acts on what the count returned.
+template <typename Who>
+__device__ inline void track_finish(const Plan &p, const Trk &t, const Tile &tl, TrkCount k, const Who &who) {
   const int c = tl.c;
   uint32_t parts = (uint32_t)p.tpc;
   if (p.sub_groups > 1) {
     const int g = (tl.nj * p.Mt + tl.mi) & (p.sub_groups - 1);
-    if (k.old + 1u != (uint32_t)((p.tpc - g + p.sub_groups - 1) / p.sub_groups)) return;
-    __hip_atomic_store(trk_group_word(p, tl.s, g), 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    k.old = __hip_atomic_fetch_add(&t.counter[c], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    // (waited for here: where the paths meet again the compiler would have every tile wait for it)
-    __builtin_amdgcn_s_waitcnt(kWaitVm0);
+    if (k.old + 1u != (uint32_t)(p.tpc - g + p.sub_groups - 1) >> (31 - __builtin_clz(p.sub_groups))) return;
+    who.put(trk_group_word(p, tl.s, g), 0u);
+    k.old = who.add(&t.counter[c], 1u);
     parts = (uint32_t)p.sub_groups;
   }
   // threshold = regions of the chunk x updates expected per element (Sec. 4.2.1)
   const uint32_t upd = (uint32_t)(c == p.rank ? p.upd_first : p.upd_rest);
   if (k.old + 1u == parts * upd) {                // the landing that reaches the threshold triggers
-    if (p.whole_chunks)
-      k.done = __hip_atomic_fetch_add(t.done, (uint32_t)p.tpc, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (p.whole_chunks) k.done = who.add(t.done, (uint32_t)p.tpc);
     if (p.tracked * upd != k.old + 1u)            // what the counter is read as: tracked tiles
-      __hip_atomic_store(&t.counter[c], (uint32_t)p.tracked * upd, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    if (c != p.own) {
-      const uint32_t pos = __hip_atomic_fetch_add(t.queue_len, 1u, __ATOMIC_RELAXED,
-                                                  __HIP_MEMORY_SCOPE_AGENT);
-      __hip_atomic_store(&t.queue[pos], (uint32_t)c, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    }
+      who.put(&t.counter[c], (uint32_t)p.tracked * upd);
+    if (c != p.own) who.put(&t.queue[who.add(t.queue_len, 1u)], (uint32_t)c);
     // The flag is what publishes.  Everything it stands for was written through the caches and has
     // been acknowledged: the tiles before they were counted, the queue entry by the wait here.  (A
     // release store would write back the L2 on top, in which nothing of this is left.)
     // (queue_len alone publishes nothing: it may run ahead of the entry it reserves.)
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-    __hip_atomic_store(&t.ready[c], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    who.put(&t.ready[c], 1u);
   } else if (p.whole_chunks) {
     return;
   }
-  trk_close_if_last(p, t, k.done + (p.whole_chunks ? (uint32_t)p.tpc : 1u));
+  trk_close_if_last(p, t, k.done + (p.whole_chunks ? (uint32_t)p.tpc : 1u), who);
 }
 // The whole of it, by all threads of a workgroup, after the tile's stores have been issued.
 __device__ inline void track_tile(const Plan &p, const Trk &t, const Tile &tl) {
   __builtin_amdgcn_s_waitcnt(kWaitAll);
   __syncthreads();
-  if (threadIdx.x == 0) track_finish(p, t, tl, track_issue(p, t, tl));
+  if (threadIdx.x == 0) track_finish(p, t, tl, track_issue(p, t, tl), TrkThread{});
 }
 
 }  // namespace t3k

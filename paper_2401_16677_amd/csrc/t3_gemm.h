@@ -156,7 +156,7 @@ void gemm_tile_kernel(const Plan p) {
     if (in_count && threadIdx.x == 0) counted = track_issue(p, trk, pending);
   };
   auto finish_pending = [&]() {
-    if (in_count && threadIdx.x == 0) track_finish(p, trk, pending, counted);
+    if (in_count && threadIdx.x == 0) track_finish(p, trk, pending, counted, TrkThread{});
     in_count = false;
     pending.c = -1;
   };

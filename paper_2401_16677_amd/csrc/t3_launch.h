@@ -33,11 +33,15 @@ t3_status launch_gemm_kn(const Plan &q, int32_t tm, int32_t tn, hipStream_t s);
 t3_status launch_gemm_km(const Plan &q, int32_t tm, int32_t tn, hipStream_t s);
 t3_status launch_gemm_km_kn(const Plan &q, int32_t tm, int32_t tn, hipStream_t s);
 
-// The wide-tile kernel by operand layout (t3_wide_launch.hip); q.track == nullptr: the plain GEMM.
-t3_status launch_wide_nk(const Plan &q, int32_t tm, int32_t tn, hipStream_t s);
-t3_status launch_wide_kn(const Plan &q, int32_t tm, int32_t tn, hipStream_t s);
-t3_status launch_wide_km(const Plan &q, int32_t tm, int32_t tn, hipStream_t s);
-t3_status launch_wide_km_kn(const Plan &q, int32_t tm, int32_t tn, hipStream_t s);
+// The wide-tile kernel by mode and operand layout (t3_wide_launch.hip).  The plain GEMM's C goes through q.R, q.ldr.
+t3_status launch_wide_fused(const Plan &q, int32_t tm, int32_t tn, hipStream_t s);
+t3_status launch_wide_fused_kn(const Plan &q, int32_t tm, int32_t tn, hipStream_t s);
+t3_status launch_wide_fused_km(const Plan &q, int32_t tm, int32_t tn, hipStream_t s);
+t3_status launch_wide_fused_km_kn(const Plan &q, int32_t tm, int32_t tn, hipStream_t s);
+t3_status launch_wide_gemm_nk(const Plan &q, int32_t tm, int32_t tn, hipStream_t s);
+t3_status launch_wide_gemm_kn(const Plan &q, int32_t tm, int32_t tn, hipStream_t s);
+t3_status launch_wide_gemm_km(const Plan &q, int32_t tm, int32_t tn, hipStream_t s);
+t3_status launch_wide_gemm_km_kn(const Plan &q, int32_t tm, int32_t tn, hipStream_t s);
 
 // The small-tile kernel (64 x 64, 32 x 64, 32 x 32), any layout (t3_small_launch.hip).
 t3_status launch_small_fused(const Plan &q, int32_t tm, int32_t tn, bool b_kn, bool a_km, hipStream_t s);

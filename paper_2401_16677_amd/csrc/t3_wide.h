@@ -17,6 +17,8 @@
 //    the tile.  (A chunk's rows start anywhere; every run of addresses that ends inside a 64-byte
 //    granule costs the memory side a read-modify-write: 8192 x 4256 x 128, chunks of 532 columns,
 //    stored to R and slots took 224 us in 128-byte runs, 134 us in rows, 88 us where 544 columns.)
+//  - The plain GEMM is an instantiation of its own, whose whole tiles have nothing to add: requested or
+//    cleared registers for it are known to the compiler as accesses to wait for where the way out begins.
 //  - The count of a tile is asked for when its stores are known to be acknowledged, in the next
 //    tile's main loop, and acted on a slab later.
 //
@@ -31,8 +33,6 @@
 #include "t3_gemm.h"
 
 namespace t3k {
-
-constexpr uint32_t kOob = 0x80000000u;
 
 __device__ __forceinline__ void asm_tie(u32x2 (&a)[8]) {
   asm volatile("" : "+v"(a[0]), "+v"(a[1]), "+v"(a[2]), "+v"(a[3]), "+v"(a[4]), "+v"(a[5]), "+v"(a[6]), "+v"(a[7]));
@@ -84,13 +84,9 @@ struct Piece {
 __device__ inline bool get_piece(const Plan &p, int it, Piece &w) {
   int blk, part, nparts;
   if (!work_item<1>(p, it, blk, part, nparts)) return false;
-  // (the same in every lane: said so, so that it lives in scalar registers)
-  blk = __builtin_amdgcn_readfirstlane(blk);
-  part = __builtin_amdgcn_readfirstlane(part);
-  nparts = __builtin_amdgcn_readfirstlane(nparts);
   decode_block(p, blk, w.tl);                    // (launches of whole ring steps: every position is a tile)
-  const int slabs = p.K / kBK, per = slabs / nparts;
-  w.k0 = part * per;
+  const int slabs = p.K / kBK, per = nparts == 2 ? slabs >> 1 : slabs;
+  w.k0 = part ? per : 0;
   w.nf = part == nparts - 1 ? slabs - w.k0 : per;
   w.ns = w.nf + (part == nparts - 1 && p.K % kBK ? 1 : 0);
   w.half = nparts == 2 ? 1 + part : 0;
@@ -98,7 +94,7 @@ __device__ inline bool get_piece(const Plan &p, int it, Piece &w) {
   return true;
 }
 
-template <int FM, int FN, int NSTAGE, int NIMG, int PRE, int DEPTH, int BKN, int AKM>
+template <int FM, int FN, int NSTAGE, int NIMG, int PRE, int DEPTH, int MODE, int BKN, int AKM>
 __global__ __launch_bounds__(256)
 __attribute__((amdgpu_waves_per_eu((32 * (FM + FN) * 128 * NSTAGE + NIMG * 4096 * FN) <= 80 * 1024 ? 2 : 1)))
 void wide_tile_kernel(const Plan p) {
@@ -111,7 +107,7 @@ void wide_tile_kernel(const Plan p) {
   static_assert(PRE <= DEPTH && DEPTH <= FM && NL + PRE * FN < 64, "");
   __shared__ __attribute__((aligned(1024))) char lds[kImgOff + NIMG * kImgBytes];
 
-  const bool tracked = p.track != nullptr;       // (no tracker: the plain GEMM)
+  constexpr bool tracked = MODE == kModeFused;
   Trk trk;
   if (tracked) trk = trk_open(p);
   if (p.stagger_groups > 1) stagger_start(p);
@@ -126,21 +122,18 @@ void wide_tile_kernel(const Plan p) {
   Tile pending{0, -1, 0, 0};
   int pending_half = -1;
   // The count is an atomic the compiler knows of: the register is its to keep, the wait its to make.  (Out of
-  // inline assembly the value would be taken as there at once, and could be copied before it is.)  Every
-  // lane asks, thread 0's address alone lies inside the tracker state: behind a branch there would be paths on which
-  // nobody waits for the value, and the compiler would wait for every copy in flight where those meet the main loop.
-  const __amdgpu_buffer_rsrc_t trk_rsrc = make_rsrc(p.track, tracked ? (uint32_t)(2 * trk_bank_words(p.P) + 2 + kTailSlots) * 4u : 0u);
+  // inline assembly the value would be taken as there at once, and could be copied before it is.)
+  const uint32_t lane_at = threadIdx.x == 0 ? 0u : kOob;
+  const TrkWave who{make_rsrc(p.track, tracked ? (uint32_t)(2 * trk_bank_words(p.P) + 2 + kTailSlots) * 4u : 0u), p.track, lane_at};
   uint32_t count_old = 0u;
   auto ask_count = [&]() {                       // behind a barrier, stores acknowledged
-    if (pending_half >= 0 && threadIdx.x == 0)
-      __hip_atomic_store(&p.tail_flags[pending_half], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (pending_half >= 0) TrkWave{make_rsrc(p.tail_flags, kTailSlots * 4u), p.tail_flags, lane_at}.put(p.tail_flags + pending_half, 1u);
     pending_half = -1;
-    const bool ask = pending.c >= 0 && threadIdx.x == 0;
-    const uint32_t at = pending.c >= 0 ? (uint32_t)(track_word(p, trk, pending) - p.track) * 4u : 0u;
-    return (uint32_t)__builtin_amdgcn_raw_ptr_buffer_atomic_add_i32(1, trk_rsrc, (int)(ask ? at : kOob), 0, 0);
+    count_old = pending.c >= 0 ? who.ask(track_word(p, trk, pending), 1u) : 0u;
   };
-  auto act_on_count = [&](uint32_t old) {
-    if (pending.c >= 0 && threadIdx.x == 0) track_finish(p, trk, pending, TrkCount{old, 0u});
+  auto act_on_count = [&]() {
+    if (pending.c >= 0 && wave == 0)
+      track_finish(p, trk, pending, TrkCount{(uint32_t)__builtin_amdgcn_readfirstlane(count_old), 0u}, who);
     pending.c = -1;
   };
   auto stamp = [&](int it, int k) {
@@ -218,11 +211,13 @@ void wide_tile_kernel(const Plan p) {
       }
       markedB = cutB;
     }
-    st_k0 = w.k0;
-    st_nf = w.nf;
+    // (the same in every lane: said so, so that a slab's addresses are formed in scalar registers)
+    st_k0 = __builtin_amdgcn_readfirstlane(w.k0);
+    st_nf = __builtin_amdgcn_readfirstlane(w.nf);
     // K walks start at another slab on every XCD (p.k_groups of them) and wrap around: the chip reads as many
     // K ranges at a time instead of one, which spreads the traffic over the memory channels
-    st_koff = p.k_groups > 1 ? (int)(((uint32_t)(blockIdx.x % (uint32_t)p.k_groups) * (uint32_t)w.nf) / (uint32_t)p.k_groups) : 0;
+    st_koff = p.k_groups > 1 ? (int)div_by((blockIdx.x % (uint32_t)p.k_groups) * (uint32_t)w.nf, p.by_groups) : 0;
+    st_koff = __builtin_amdgcn_readfirstlane(st_koff);
   };
   auto stream_ragged = [&]() {                   // the stream's last slab ends with K: nothing behind it
     if constexpr (!AKM && !BKN) {
@@ -252,7 +247,7 @@ void wide_tile_kernel(const Plan p) {
       s = j + st_koff;
       if (s >= st_nf) s -= st_nf;
     }
-    s = __builtin_amdgcn_readfirstlane(s + st_k0);
+    s += st_k0;
     a = (uint32_t)s * (AKM ? (uint32_t)p.lda * (kBK * 2) : (uint32_t)kRowBytes);
     b = (uint32_t)s * (BKN ? (uint32_t)p.ldb * (kBK * 2) : (uint32_t)kRowBytes);
   };
@@ -311,19 +306,16 @@ void wide_tile_kernel(const Plan p) {
       read_a(std::integral_constant<int, (r - RB * FN) / RA>{}, std::integral_constant<int, (r - RB * FN) % RA>{}, SET, KK, a_addr);
   };
   f32x4 acc[FM][FN];
-#pragma unroll
-  for (int i = 0; i < FM; ++i)
-#pragma unroll
-    for (int j = 0; j < FN; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
-  // One k-step: the products of operand set CS, k-step KK's operands of the stage at `sr` into the
-  // other set, and (COPIES) the stream's slab at (ca, cb) into the stage at `sc`.
-  auto kstep = [&](auto CS, auto KK, auto COPIES, uint32_t sr, uint32_t sc, uint32_t ca, uint32_t cb) {
+  // One k-step: the products of operand set CS, (READS) k-step KK's operands of the stage at `sr` into the
+  // other set, and (COPIES) the stream's slab at (ca, cb) into the stage at `sc`.  `under`: what else is to
+  // be done under the products.
+  auto kstep = [&](auto FIRST, auto CS, auto KK, auto READS, auto COPIES, uint32_t sr, uint32_t sc, uint32_t ca, uint32_t cb, auto under) {
     constexpr int cs = decltype(CS)::value, kk = decltype(KK)::value;
-    const uint32_t a_addr = adA[AKM ? 0 : kk] + sr, b_addr = adB[BKN ? 0 : kk] + sr;
+    uint32_t a_addr = 0, b_addr = 0;
     asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");            // this k-step's operands have landed
     xa[cs].tie();
     xb[cs].tie();
-    if constexpr (kOneWave) {                    // (accumulators: the accumulation half of the register file)
+    if constexpr (kOneWave && !decltype(FIRST)::value) {                    // (accumulators: the accumulation half of the register file)
 #pragma unroll
       for (int i = 0; i < FM; ++i)
 #pragma unroll
@@ -332,9 +324,17 @@ void wide_tile_kernel(const Plan p) {
     __builtin_amdgcn_sched_barrier(0);
     static_for<NP>([&](auto Mi) {
       constexpr int m = decltype(Mi)::value, i = m / FN, j = m % FN;
-      acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(xb[cs].template get<j>(), xa[cs].template get<i>(), acc[i][j], 0, 0, 0);
+      acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(xb[cs].template get<j>(), xa[cs].template get<i>(), decltype(FIRST)::value ? f32x4{0.f, 0.f, 0.f, 0.f} : acc[i][j], 0, 0, 0);
       __builtin_amdgcn_sched_barrier(0);                          // nothing moves across: the order is as written
-      if constexpr (m % kGap == 0 && m / kGap < NR) {
+      if constexpr (m == 0) {
+        a_addr = adA[AKM ? 0 : kk] + sr;
+        b_addr = adB[BKN ? 0 : kk] + sr;
+      }
+      if constexpr (m == 4) {
+        under();
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      if constexpr (decltype(READS)::value && m % kGap == 0 && m / kGap < NR) {
         read_op(std::integral_constant<int, m / kGap>{}, std::integral_constant<int, cs ^ 1>{}, KK, a_addr, b_addr);
         __builtin_amdgcn_sched_barrier(0);
       }
@@ -373,9 +373,9 @@ void wide_tile_kernel(const Plan p) {
     if (pending.c < 0 && pending_half < 0) return;
     __builtin_amdgcn_s_waitcnt(kWaitAll);
     __syncthreads();
-    const uint32_t old = ask_count();
+    ask_count();
     __builtin_amdgcn_s_waitcnt(kWaitVm0);        // (in every wavefront: nothing is on its way where paths meet)
-    act_on_count(old);
+    act_on_count();
   };
   auto next_stage = [](uint32_t s) {
     s += (uint32_t)kStageBytes;
@@ -435,27 +435,58 @@ void wide_tile_kernel(const Plan p) {
                        in_rsrc, (int)(in_at[u % UB] + (uint32_t)(16 * i + (u / UB) * RS) * ld_in * 4u), 0, kAuxSc1 | kAuxNt));
       });
     };
+    auto in_here = [&]() {
+#pragma unroll
+      for (int u = 0; u < UB; ++u) {
+        const int L = u * 64 + lane, ir = wave * 8 + L / kRowCh, col = (L % kRowCh) * 4;
+        in_at[u] = col < cols_in ? ((uint32_t)strip_row(ir) * ld_in + (uint32_t)col) * 4u : kOob;
+      }
+    };
     Piece nxt;
     bool more = false;
-    // The K loop, cut where something has to be done between two slabs; `wait` is what the barrier
-    // of a slab waits for: 0 = nothing (the first NSTAGE slabs of every piece but the first landed during
-    // the way out, and behind the last slab nothing is needed), 1 = the next slab, 2 = the
-    // next slab with the incoming partial behind it.
+    // The K loop.  A slab is two k-steps with a barrier between them, behind which the slab's stage is free and
+    // the next slab visible; the loop runs from barrier to barrier and is left where something has to be done behind
+    // one (the count, the stream's last slab, its next piece).  One wavefront per SIMD: what stands between two
+    // products in the loop is time the matrix cores idle, so a barrier's wait is one test away, the addresses of the
+    // copies behind it are formed under the products before it, everything rare is outside, and the first k-step,
+    // ahead of the loop, starts the sums from a constant zero instead of 256 cleared registers.  (With all of it in the
+    // loop, and one kernel for both modes: plain GEMM 4096 x 12288 x 1536 132.0 us, now 126.5; 16384 x 3072 x 1536
+    // 141.6, 131.7; 4096 x 12288 x 6144 422.4, 415.1; fused 452.5, 444.6.)
     int kt = 0, cj = NSTAGE;                     // slab multiplied, slab the stream copies next
     const int k_switch = cur.ns - NSTAGE;        // the stream goes on to the next piece
-    int count_slab = pending.c >= 0 || pending_half >= 0 ? NSTAGE - 1 : -1;
-    auto before_slab = [&]() {
+    const bool counting = pending.c >= 0 || pending_half >= 0;
+    uint32_t sn, ca, cb;                         // the next slab's stage, where the slab copied next lies
+    auto first_half = [&](auto FIRST) {
+      kstep(FIRST, c0, c1, true_type{}, false_type{}, so, 0u, 0u, 0u, [&]() {
+        sn = next_stage(so);
+        slab_offs(cj, ca, cb);
+        asm volatile("" : "+s"(sn), "+s"(ca), "+s"(cb));
+      });
+    };
+    // What the barrier waits for, beside this wavefront's own reads of the slab: kNext = the next slab's copies;
+    // kNextIn = the same with the incoming partial requested behind them; kLanded = nothing (the first slabs of every
+    // piece but the first landed during the way out, and behind the last slab nothing is needed).
+    enum { kNext, kNextIn, kLanded };
+    auto sync = [&](int kind) {
+      if (kind == kNext) asm volatile("s_waitcnt vmcnt(%0)" : : "n"((NSTAGE - 2) * NL) : "memory");
+      else if (NSTAGE > 2 && kind == kNextIn) asm volatile("s_waitcnt vmcnt(%0)" : : "n"((NSTAGE - 2) * NL + PRE * FN) : "memory");
+      asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+      __builtin_amdgcn_s_barrier();
+      asm volatile("" ::: "memory");
+    };
+    first_half(true_type{});
+    sync(it > 0 || cur.ns == 1 ? kLanded : kNext);
+    for (;;) {                                   // behind the barrier of slab kt
+      if (kt == NSTAGE - 1 && counting && kt < cur.ns - 1) ask_count();          // (the previous piece's stores are older
+      if (kt == NSTAGE && counting) act_on_count();                              //   than copies that have been waited for)
       if (kt == k_switch) {
         more = get_piece(p, it + 1, nxt);
         if (more) stream_to(nxt);
         else stream_end();
         cj = 0;
-        if (has_in) {
-#pragma unroll
-          for (int u = 0; u < UB; ++u) {
-            const int L = u * 64 + lane, ir = wave * 8 + L / kRowCh, col = (L % kRowCh) * 4;
-            in_at[u] = col < cols_in ? ((uint32_t)strip_row(ir) * ld_in + (uint32_t)col) * 4u : kOob;
-          }
+        slab_offs(cj, ca, cb);
+        if (tracked && has_in) {
+          in_here();
           static_for<PRE>([&](auto I) { load_in(I); });
         }
       }
@@ -463,55 +494,47 @@ void wide_tile_kernel(const Plan p) {
       if (ktail && (kt == k_switch - 1 || (kt == cur.ns - 1 && more && nxt.ns == NSTAGE)) &&
           (kt < k_switch ? cur.ns > cur.nf : nxt.ns > nxt.nf))
         stream_ragged();
-    };
-    while (kt < cur.ns) {
-      before_slab();
-      int stop = kt < k_switch - 1 ? k_switch - 1 : (kt < k_switch ? k_switch : (kt < cur.ns - 1 ? cur.ns - 1 : cur.ns));
-      if (kt < NSTAGE - 1 && stop > NSTAGE - 1) stop = NSTAGE - 1;
-      const int wait = kt == cur.ns - 1 || (it > 0 && kt < NSTAGE - 1) ? 0 : (kt >= k_switch && has_in ? 2 : 1);
-      for (; kt < stop; ++kt) {
-        kstep(c0, c1, false_type{}, so, 0u, 0u, 0u);
-        if (wait == 1) asm volatile("s_waitcnt vmcnt(%0)" : : "n"((NSTAGE - 2) * NL) : "memory");
-        else if (wait == 2) asm volatile("s_waitcnt vmcnt(%0)" : : "n"((NSTAGE - 2) * NL + PRE * FN) : "memory");
-        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");       // own reads of slab kt done
-        __builtin_amdgcn_s_barrier();                            // slab kt + 1 visible, slab kt's stage free
-        asm volatile("" ::: "memory");
-        if (kt == count_slab) {
-          if (kt == NSTAGE - 1) {
-            count_old = ask_count();
-            count_slab = NSTAGE;
-          } else {
-            act_on_count(count_old);
-          }
-        }
-        const uint32_t sn = next_stage(so);
-        uint32_t a, b;
-        slab_offs(cj, a, b);
-        kstep(c1, c0, true_type{}, sn, so, a, b);                // (behind the last slab it reads what nobody uses)
+      // the next barrier something is to be done behind, or whose wait is another one
+      int stop = kt < k_switch - 1 ? k_switch - 1 : (kt < k_switch ? k_switch : (kt < cur.ns - 2 ? cur.ns - 2 : cur.ns - 1));
+      if (kt < NSTAGE) stop = min(stop, kt + 1);
+      const int kind = kt + 1 == cur.ns - 1 || (it > 0 && kt + 1 < NSTAGE - 1) ? kLanded : (kt >= k_switch && tracked && has_in ? kNextIn : kNext);
+      do {
+        kstep(false_type{}, c1, c0, true_type{}, true_type{}, sn, so, ca, cb, []() {});     // (behind the last slab it reads what nobody uses)
         ++cj;
         so = sn;
-      }
+        ++kt;
+        // (the first k-step's wait, ahead of the branch: whatever the compiler keeps in registers along the way out of
+        // the loop is not in those that reads are on their way to)
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+        xa[0].tie();
+        xb[0].tie();
+        if (kt == cur.ns) break;
+        first_half(false_type{});
+        sync(kind);
+      } while (kt < stop);
+      if (kt == cur.ns) break;
     }
-    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");            // those reads are over
-    xa[0].tie();
-    xb[0].tie();
     stamp(it, 2);
 
     auto zero_in = [&](auto I) {
 #pragma unroll
       for (int u = 0; u < FN; ++u) in[decltype(I)::value][u] = f32x4{0.f, 0.f, 0.f, 0.f};
     };
-    if (has_in) {
-      static_for<DEPTH - PRE>([&](auto I) { load_in(std::integral_constant<int, decltype(I)::value + PRE>{}); });
-    } else {
-      static_for<DEPTH>(zero_in);
-    }
     int lane_e = lane;                           // recomputed here rather than kept through the main loop
     asm volatile("" : "+v"(lane_e));
     const int e_row = lane_e & 15, e_q = lane_e >> 4;
     // TO: -1 = fp32 to C, kept in the caches; 0 = fp32 to R, C or a slot, streamed; 1 = R and the fp32 slot; 2 = the bfloat16 slot; 3 = R and the bfloat16 slot
-    auto way_out = [&](auto TO) {
+    // ADD: there is something to add
+    auto way_out = [&](auto TO, auto ADD) {
       constexpr int to = decltype(TO)::value;
+      constexpr bool add = decltype(ADD)::value;
+      if constexpr (add && tracked) {
+        if (has_in) static_for<DEPTH - PRE>([&](auto I) { load_in(std::integral_constant<int, decltype(I)::value + PRE>{}); });
+        else static_for<DEPTH>(zero_in);
+      } else if constexpr (add) {
+        in_here();
+        static_for<DEPTH>(load_in);
+      }
       const __amdgpu_buffer_rsrc_t out_rsrc = make_rsrc(out_base, rows_in * ld_out * 4u);
       const void *slot = to >= 2 ? (const void *)((const uint16_t *)p.fwd + (slot_at0 - p.fwd)) : (const void *)slot_at0;
       const __amdgpu_buffer_rsrc_t slot_rsrc = make_rsrc(slot, rows_in * (uint32_t)p.W * (to >= 2 ? 2u : 4u));
@@ -538,14 +561,14 @@ void wide_tile_kernel(const Plan p) {
 #pragma unroll
         for (int j = 0; j < FN; ++j) {
           *(f32x4 *)(lds + kImgOff + img + (wm * 16 + e_row) * (BN * 4) + (((wn * (WN / 4) + 4 * j + e_q) ^ (e_row & 7)) << 4)) = acc[i][j];
-          acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
         }
         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
         __builtin_amdgcn_s_barrier();
         asm volatile("" ::: "memory");
         static_for<FN>([&](auto U) {
           constexpr int u = decltype(U)::value;
-          const f32x4 v = *(const f32x4 *)(lds + img + img_at[u]) + in[i][u];
+          f32x4 v = *(const f32x4 *)(lds + img + img_at[u]);
+          if constexpr (add) v += in[i][u];
           const uint32_t rows = (uint32_t)(16 * i + (u / UB) * RS);
           if constexpr (to != 2) store_agent_hint<(to >= 0)>(out_rsrc, out_at[u % UB] + rows * ld_out * 4u, 0u, v);
           if constexpr (to == 1) store_agent_hint<true>(slot_rsrc, slot_at[u % UB] + rows * (uint32_t)p.W * 4u, 0u, v);
@@ -553,27 +576,33 @@ void wide_tile_kernel(const Plan p) {
             __builtin_amdgcn_raw_buffer_store_b64(pack_bf16(v), slot_rsrc, (int)(slot_at[u % UB] + rows * (uint32_t)p.W * 2u), 0,
                                                   kAuxSc1 | kAuxNt);
         });
-        if constexpr (i + DEPTH < FM) {
-          if (has_in) load_in(std::integral_constant<int, i + DEPTH>{});
+        if constexpr (add && i + DEPTH < FM) {
+          if (!tracked || has_in) load_in(std::integral_constant<int, i + DEPTH>{});
           else zero_in(std::integral_constant<int, i + DEPTH>{});
         }
         // The next piece's first NSTAGE slabs were requested before the last of the incoming partial,
         // so they have landed when that is used; where they were not, this wait makes sure of it.
         if constexpr (i == 1) {
-          if (!has_in || (PRE == DEPTH && DEPTH == FM)) asm volatile("s_waitcnt vmcnt(%0)" : : "n"(2 * FN * (to <= 0 || to == 2 ? 1 : 2)) : "memory");
+          if (!add || !has_in || (PRE == DEPTH && DEPTH == FM)) asm volatile("s_waitcnt vmcnt(%0)" : : "n"(2 * FN * (to <= 0 || to == 2 ? 1 : 2)) : "memory");
         }
         __builtin_amdgcn_sched_barrier(0);
       });
     };
-    if (to_slot && bf16) {
-      if (to_r) way_out(std::integral_constant<int, 3>{});
-      else way_out(std::integral_constant<int, 2>{});
-    } else if (to_slot && to_r) {
-      way_out(c1);
-    } else if (!tracked && !p.nt_out) {
-      way_out(std::integral_constant<int, -1>{});
+    constexpr std::integral_constant<int, -1> keep{};
+    if constexpr (tracked) {
+      if (to_slot && bf16) {
+        if (to_r) way_out(std::integral_constant<int, 3>{}, true_type{});
+        else way_out(std::integral_constant<int, 2>{}, true_type{});
+      } else if (to_slot && to_r) {
+        way_out(c1, true_type{});
+      } else {
+        way_out(c0, true_type{});
+      }
+    } else if (cur.half == 2) {
+      way_out(keep, true_type{});
     } else {
-      way_out(c0);
+      if (p.nt_out) way_out(c0, false_type{});
+      else way_out(keep, false_type{});
     }
     stamp(it, 3);
     if (cur.half == 1) pending_half = cur.idx;

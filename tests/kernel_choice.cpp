@@ -1,8 +1,13 @@
-// t3_choice.h for the tests: what a call launches on a device of so many compute units.
+// t3_choice.h and t3_div.h for the tests: what a call launches on a device of so many compute units; n / d.
 #include "t3_choice.h"
+#include "t3_div.h"
 
 extern "C" void launch_shape(const t3_problem *p, int call, int tracked_m, int tracked_n, int cus, int64_t *out) {
   const t3k::LaunchShape s = t3k::launch_shape(p, static_cast<t3k::Call>(call), {tracked_m, tracked_n}, cus);
   const int64_t v[] = {s.kernel, s.tile.m, s.tile.n, s.tpc, s.begin, s.limit, s.total_blocks, s.resident, s.tail_r, s.tail_q};
   for (int i = 0; i < 10; ++i) out[i] = v[i];
+}
+
+extern "C" void divide(const uint32_t *n, const uint32_t *d, uint32_t *out, int count) {
+  for (int i = 0; i < count; ++i) out[i] = t3k::div_by(n[i], t3k::fast_div(d[i]));
 }

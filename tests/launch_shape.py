@@ -30,7 +30,7 @@ class Shape(NamedTuple):
 _lib = None
 
 
-def launch_shape(p, call=FUSED, cus=CUS):
+def lib():
     global _lib
     if _lib is None:
         with tempfile.TemporaryDirectory() as d:
@@ -39,7 +39,11 @@ def launch_shape(p, call=FUSED, cus=CUS):
                             os.path.join(hip_build.ROOT, "include"), "-I", hip_build.CSRC,
                             os.path.join(hip_build.ROOT, "tests", "kernel_choice.cpp"), "-o", so], check=True)
             _lib = ctypes.CDLL(so)
+    return _lib
+
+
+def launch_shape(p, call=FUSED, cus=CUS):
     tracked = (p.tile_m, p.tile_n) if p.tile_m else t3.t3_default_tile(p)
     out = (ctypes.c_int64 * 10)()
-    _lib.launch_shape(ctypes.byref(p), call, *tracked, cus, out)
+    lib().launch_shape(ctypes.byref(p), call, *tracked, cus, out)
     return Shape(*out)

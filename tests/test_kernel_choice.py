@@ -1,8 +1,11 @@
 """CPU-only checks of which kernel serves a call, on which workgroup tile (csrc/t3_choice.h)."""
+import ctypes
+
 import numpy as np
 import pytest
 
 from paper_2401_16677_amd import binding as t3
+from tests.launch_shape import lib as choice_lib
 from tests.launch_shape import FUSED, GEMM, GENERAL, REDUCE, REDUCTION, SMALL, WIDE, launch_shape
 
 
@@ -94,3 +97,16 @@ def test_arrays_of_more_than_2_gib(M, W, K, tp, layout, wide):
     """Only a transposed operand past 2 GiB keeps a problem from the wide-tile kernel."""
     for call in (FUSED, GEMM):
         assert (launch_shape(_problem(M, W, K, tp, layout), call).kernel == WIDE) == wide
+
+
+def test_division_without_dividing():
+    """Numbers below 2^31 by 1 .. 2^31 - 1: edges of every power of two and of the quotients, and random ones."""
+    rng = np.random.default_rng(9)
+    near = np.unique(np.clip((2 ** np.arange(31, dtype=np.int64))[:, None] + np.arange(-3, 4), 1, 2 ** 31 - 1))
+    d = np.concatenate([np.repeat(near, 40), rng.integers(1, 2 ** 31, 20000), rng.integers(1, 3000, 20000)])
+    n = rng.integers(0, 2 ** 31, d.size)
+    n[::3] = np.clip(n[::3] // d[::3] * d[::3] - rng.integers(0, 2, n[::3].size), 0, 2 ** 31 - 1)
+    n[:near.size] = 2 ** 31 - 1
+    u32 = [np.ascontiguousarray(x, dtype=np.uint32) for x in (n, d, np.zeros(d.size))]
+    choice_lib().divide(*[x.ctypes.data_as(ctypes.c_void_p) for x in u32], d.size)
+    assert np.array_equal(u32[2], n // d)

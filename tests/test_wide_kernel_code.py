@@ -1,5 +1,5 @@
 """The hand-ordered kernel's compiled code: what inline assembly has requested into registers is not
-touched before it is waited for.
+touched before it is waited for, and the main loop holds nothing that keeps the matrix cores waiting.
 
 The compiler takes the output of an inline-assembly load as written at once.  It may then copy,
 spill or reuse the register while the data is still on its way (it does, where the K loop's body appears
@@ -139,3 +139,24 @@ def test_no_global_load_to_a_register_in_inline_assembly(code, unit):
             for text, asm in block:
                 if asm and re.match(r"(global|buffer|flat|scratch)_(load|atomic)", text):
                     assert re.search(r"\blds\b", text) or text.split()[0].startswith("global_load_lds"), (kernel, text)
+
+
+@pytest.mark.parametrize("unit", [u[1] for u in LAYOUTS])
+def test_nothing_stands_between_the_products(code, unit):
+    """One wavefront per SIMD: what the compiler puts between two products is time the matrix cores idle.
+    No register is spilled to memory; where products are, the compiler waits for no memory access (its own
+    accesses are on their way to registers the loop does not use); behind the barrier of a slab the first product
+    follows at once, its addresses formed before."""
+    for kernel, lines in code[unit].items():
+        blocks = _blocks(lines)
+        halves = 0
+        for block, _ in blocks:
+            assert not any(t.startswith("scratch_") for t, _ in block), kernel
+            products = [i for i, (t, _) in enumerate(block) if t.startswith("v_mfma")]
+            if len(products) < 8:
+                continue
+            assert not any(t.startswith("s_waitcnt") and "vmcnt" in t for t, asm in block if not asm), kernel
+            if any(re.search(r"\blds\b", t) for t, _ in block):       # the half of a slab that copies: behind the barrier
+                halves += 1
+                assert products[0] <= 4, (kernel, block[:products[0]])
+        assert halves == 1, kernel
