@@ -650,7 +650,10 @@ t3_status t3_rs_reduce(const t3_problem *p, const float *C, float *R, void *fwd,
                                  R, fwd, track, &q, &tm, &tn, &empty);
   if (st != T3_OK) return st;
   if (empty) return T3_OK;
-  return launch(t3k::reduce_tile_kernel, dim3(grid_size(q)), dim3(t3k::kThreads), static_cast<hipStream_t>(stream), q);
+  const int64_t W = p->N / p->tp, elements = (int64_t)(tm < p->M ? tm : p->M) * (tn < W ? tn : W);
+  const bool one = elements <= 4 * t3k::kReduceBatch * t3k::kReduceThreads;
+  return launch(one ? t3k::reduce_tile_kernel<true> : t3k::reduce_tile_kernel<false>, dim3(grid_size(q)), dim3(t3k::kThreads),
+                static_cast<hipStream_t>(stream), q);
 }
 
 t3_status t3_upstream_update(const t3_problem *p, const float *incoming, float *R,

@@ -16,39 +16,48 @@ namespace t3k {
 // reduce_tile_shape in t3_choice.h) is cut to what there is to do.
 // One piece at a time on tiles of 128 x 128 (before), two, four and eight in flight, in us: 1148 x 4096 23.6,
 // 14.8, 15.2, 17.5; 2048 x 4096 40.5, 21.5, 22.3, 23.2; 2343 x 17664 131.7, 114.9, 115.9, 120.6.
+// A range that cuts a ring step keeps the tracked tile, many batches per lane: the next batch is requested before
+// the sums of this one leave, or it would wait, in order, for their acknowledgement (1024 x 4096 in 256 x 256 tiles,
+// the range from the 7th to the 20th: 38.1 us where it waited, 13.2 now; 184 x 9672 19.8, 9.5; 4096 x 12288 125.6, 115.6).
 // Sums leave with the streaming hint, or they push out of the memory-side cache what the next GEMM and
-// reduction read there: GEMM and reduction of 2343 x 17664 x 384 173.6 with it, 188.8 without; of
-// 16384 x 3072 x 1536 267 and 272.
+// reduction read there: GEMM and reduction of 4096 x 12288 x 1536 219 us with it, 229 without; of 16384 x 3072 x 1536
+// 235 and 242; of 2343 x 17664 x 384 135 and 132.  (A reduction repeated on its own buffers, with no GEMM between,
+// is the other way round: 4096 x 12288 109 and 95.)
 static_assert(kReduceThreads == kThreads, "");
-// The tile's sums, V x 4 columns per piece (V = 2: sums leave as bfloat16, 16 bytes of eight).
-template <int V>
-__device__ inline void reduce_tile(const Plan &p, const Tile &tl, bool store_only, bool to_r, bool to_slot) {
-  constexpr int U = kReduceBatch / V;
+constexpr uint32_t kPastAll = 0xFFFFFFF0u;      // an offset past every array below 4 GiB
+// The tile's sums, V x 4 columns per piece (V = 2: sums leave as bfloat16, 16 bytes of eight).  Pieces past the tile's end
+// are addresses past the array: no access is conditional, and the compiler knows how many are in flight.  ONE: a
+// batch per lane is all there is (50 registers a lane instead of 90: three wavefronts more per SIMD).
+template <int V, bool TO_R, bool TO_SLOT, bool ONE>
+__device__ inline void reduce_tile(const Plan &p, const Tile &tl, bool store_only) {
+  constexpr int U = kReduceBatch / V, kStep = U * kThreads;
   const int m0 = tl.mi * p.tile_m, nc = tl.nj * p.tile_n;              // nc: column within the chunk
   const int rows = min(p.tile_m, p.M - m0), cols = min(p.tile_n, p.W - nc) / (4 * V);
   const int total = rows * cols, n0 = tl.c * p.W + nc;
   const uint32_t ldc = (uint32_t)p.ldc * 4u, ldr = (uint32_t)p.ldr * 4u, lds = (uint32_t)p.W * (V == 2 ? 2u : 4u);
   const __amdgpu_buffer_rsrc_t c_rsrc = make_rsrc(p.C, (uint32_t)p.M * ldc), r_rsrc = make_rsrc(p.R, (uint32_t)p.M * ldr);
-  // (no slot where nothing is forwarded: the descriptor is not used then)
-  const __amdgpu_buffer_rsrc_t s_rsrc =
-      make_rsrc((const char *)p.fwd + (to_slot ? (int64_t)tl.s * p.M * lds : 0), (uint32_t)p.M * lds);
-  int row = (int)threadIdx.x / cols, cc = (int)threadIdx.x - row * cols;
+  const __amdgpu_buffer_rsrc_t in_rsrc = make_rsrc(p.R, store_only ? 0u : (uint32_t)p.M * ldr);    // (no bytes: zeros)
+  const __amdgpu_buffer_rsrc_t s_rsrc = make_rsrc((const char *)p.fwd + (TO_SLOT ? (int64_t)tl.s * p.M * lds : 0), (uint32_t)p.M * lds);
+  int row = (int)threadIdx.x / cols, cc = (int)threadIdx.x - row * cols, e = (int)threadIdx.x;
   const int row_step = kThreads / cols, cc_step = kThreads - row_step * cols;
-  for (int e0 = 0; e0 < total; e0 += U * kThreads) {
+  struct Batch {
     uint32_t at_r[U], at_s[U];
     f32x4 c[U][V], r[U][V];
+  };
+  auto request = [&](Batch &b) {
 #pragma unroll
     for (int u = 0; u < U; ++u) {
-      const uint32_t m = (uint32_t)(m0 + row), col = (uint32_t)(n0 + cc * 4 * V) * 4u, at_c = m * ldc + col;
-      at_r[u] = m * ldr + col;
-      at_s[u] = m * lds + (uint32_t)(nc + cc * 4 * V) * (V == 2 ? 2u : 4u);
-      if (e0 + u * kThreads + (int)threadIdx.x < total) {
+      const uint32_t m = (uint32_t)(m0 + row), col = (uint32_t)(n0 + cc * 4 * V) * 4u;
+      const bool in = e < total;
+      const uint32_t at_c = in ? m * ldc + col : kPastAll;
+      b.at_r[u] = in ? m * ldr + col : kPastAll;
+      b.at_s[u] = in ? m * lds + (uint32_t)(nc + cc * 4 * V) * (V == 2 ? 2u : 4u) : kPastAll;
 #pragma unroll
-        for (int v = 0; v < V; ++v) {
-          c[u][v] = load_stream(c_rsrc, at_c + 16u * v, 0u);
-          r[u][v] = store_only ? f32x4{0.f, 0.f, 0.f, 0.f} : load_stream(r_rsrc, at_r[u] + 16u * v, 0u);
-        }
+      for (int v = 0; v < V; ++v) {
+        b.c[u][v] = load_stream(c_rsrc, in ? at_c + 16u * v : kPastAll, 0u);
+        b.r[u][v] = load_stream(in_rsrc, in ? b.at_r[u] + 16u * v : kPastAll, 0u);
       }
+      e += kThreads;
       row += row_step;
       cc += cc_step;
       if (cc >= cols) {
@@ -56,37 +65,57 @@ __device__ inline void reduce_tile(const Plan &p, const Tile &tl, bool store_onl
         ++row;
       }
     }
+  };
+  auto finish = [&](Batch &b) {
 #pragma unroll
     for (int u = 0; u < U; ++u) {
-      if (e0 + u * kThreads + (int)threadIdx.x >= total) continue;
-      if (!store_only) {
 #pragma unroll
-        for (int v = 0; v < V; ++v) c[u][v] += r[u][v];
+      for (int v = 0; v < V; ++v) {
+        if (!store_only) b.c[u][v] += b.r[u][v];
+        if (TO_R) store_agent_hint<true>(r_rsrc, b.at_r[u] == kPastAll ? kPastAll : b.at_r[u] + 16u * v, 0u, b.c[u][v]);
       }
-      if (to_r) {
-#pragma unroll
-        for (int v = 0; v < V; ++v) store_agent_hint<true>(r_rsrc, at_r[u] + 16u * v, 0u, c[u][v]);
-      }
-      if (to_slot) {
-        if constexpr (V == 2)
-          __builtin_amdgcn_raw_buffer_store_b128(pack_bf16(c[u][0], c[u][1]), s_rsrc, (int)at_s[u], 0, kAuxSc1 | kAuxNt);
-        else
-          store_agent_hint<true>(s_rsrc, at_s[u], 0u, c[u][0]);
-      }
+      if constexpr (TO_SLOT && V == 2)
+        __builtin_amdgcn_raw_buffer_store_b128(pack_bf16(b.c[u][0], b.c[u][1]), s_rsrc, (int)b.at_s[u], 0, kAuxSc1 | kAuxNt);
+      else if constexpr (TO_SLOT)
+        store_agent_hint<true>(s_rsrc, b.at_s[u], 0u, b.c[u][0]);
     }
+  };
+  Batch a, b;
+  request(a);
+  if constexpr (ONE) {
+    finish(a);
+    return;
   }
+  for (int left = total - kStep; left > 0; left -= kStep) {
+    request(b);
+    finish(a);
+    left -= kStep;
+    if (left <= 0) {
+      finish(b);
+      return;
+    }
+    request(a);
+    finish(b);
+  }
+  finish(a);
 }
+template <bool ONE>
 __global__ __launch_bounds__(kThreads) void reduce_tile_kernel(const Plan p) {
   Tile tl;
   if (!decode_block(p, blockIdx.x, tl)) return;
   const Trk trk = trk_open(p);
   const bool store_only = (p.flags & kFlagStep0StoreOnly) && tl.s == 0;
-  const bool direct = p.flags & kFlagFwdDirect, forwarded = tl.c != p.own;
+  const bool direct = p.flags & kFlagFwdDirect, forwarded = tl.c != p.own, bf16 = p.flags & kFlagFwdBf16;
   const bool to_slot = forwarded && (direct || chunk_is_whole(p, tl.s)), to_r = !(forwarded && direct);
-  if (to_slot && (p.flags & kFlagFwdBf16))
-    reduce_tile<2>(p, tl, store_only, to_r, true);
-  else
-    reduce_tile<1>(p, tl, store_only, to_r, to_slot);
+  if (to_slot && bf16) {
+    if (to_r) reduce_tile<2, true, true, ONE>(p, tl, store_only);
+    else reduce_tile<2, false, true, ONE>(p, tl, store_only);
+  } else if (to_slot) {
+    if (to_r) reduce_tile<1, true, true, ONE>(p, tl, store_only);
+    else reduce_tile<1, false, true, ONE>(p, tl, store_only);
+  } else {
+    reduce_tile<1, true, false, ONE>(p, tl, store_only);
+  }
   track_tile(p, trk, tl);
 }
 

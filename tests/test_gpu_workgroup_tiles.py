@@ -22,21 +22,21 @@ def gpu():
     return gpu_harness
 
 
-def _check(gpu, oracle, M, W, K, tp, mode, layout="nk", unfused=False):
+def _check(gpu, oracle, M, W, K, tp, mode, layout="nk", unfused=False, tile=None, begin=0, limit=-1):
     N, rank = W * tp, (M + W) % tp
     print(f"M={M} W={W} K={K} tp={tp} rank={rank} mode={mode} layout={layout}", flush=True)
     kn, km = layout != "nk", layout == "km_kn"
     direct, bf16, step0 = mode != "copy", mode == "bf16", mode == "step0"
     a, b, inc = wl.make_integer_inputs(M, N, K, seed=M + 3 * W + 7 * K)
-    tile = t3.t3_default_tile(t3.problem(M, N, K, tp, rank, 0, 0))
+    tile = tile or t3.t3_default_tile(t3.problem(M, N, K, tp, rank, 0, 0))
     init = np.full((tp - 1, M, W), gpu.SENTINEL_BF16 if bf16 else gpu.SENTINEL, np.uint16 if bf16 else np.float32)
     want = oracle.fused_path(a, b, inc, tp, rank, *tile, fwd_direct=direct, fwd_bf16=bf16,
-                             step0_store_only=step0, fwd_init=init)
+                             step0_store_only=step0, fwd_init=init, tile_begin=begin, tile_limit=limit)
     flags = (t3.T3_FLAG_FWD_DIRECT if direct else 0) | (t3.T3_FLAG_FWD_BF16 if bf16 else 0) | \
             (t3.T3_FLAG_STEP0_STORE_ONLY if step0 else 0)
     # a launch before the one that is checked: the words its tiles are counted in must be back to zero
     got = gpu.run_gpu(a, b, inc, tp, rank, tile, flags=flags, unfused=unfused or mode == "unfused", ldr_pad=4,
-                      lda_pad=8, b_kn=kn, a_km=km, launches_before=1)
+                      lda_pad=8, b_kn=kn, a_km=km, launches_before=1, tile_begin=begin, tile_limit=limit)
     for name in ("R", "fwd"):
         bad = np.argwhere(got[name] != want[name])
         assert bad.size == 0, f"{name}: {bad.shape[0]} mismatches, first at {tuple(bad[0])}"
@@ -101,3 +101,18 @@ def test_reduction(gpu, oracle, M, W, tp, mode):
 @pytest.mark.parametrize("M,W,tp", [(3, 4, 2), (2500, 532, 4), (600, 20, 40)])
 def test_reduction_fp32_columns(gpu, oracle, M, W, tp):
     _check(gpu, oracle, M, W, 64, tp, "unfused")
+
+
+# A range that cuts a ring step keeps the tracked tile: several batches of 1024 pieces of 16 bytes, the next one requested
+# while one leaves.  Rows and columns of the last tiles: less than one batch, one to sixteen, whole and with a remainder.
+@pytest.mark.parametrize("mode", ["direct", "copy", "bf16", "step0"])
+@pytest.mark.parametrize("M,W,tp,tile", [
+    (300, 264, 3, (128, 128)),       # 4 batches; 44 rows, 8 columns: one, ragged
+    (261, 512, 2, (256, 256)),       # 16 batches; 5 rows: less than one
+    (96, 384, 3, (256, 128)),        # 3 batches
+    (1024, 536, 4, (128, 256)),      # 8 batches; 24 columns: one, ragged
+])
+def test_reduction_of_a_cut_range(gpu, oracle, M, W, tp, tile, mode):
+    tpc = t3.t3_tiles_per_chunk(t3.problem(M, W * tp, 64, tp, 0, *tile))
+    for begin, limit in ((1, tpc * tp), (0, tpc * tp - 1)):
+        _check(gpu, oracle, M, W, 64, tp, mode, unfused=True, tile=tile, begin=begin, limit=limit)
