@@ -122,10 +122,13 @@ __device__ inline Trk trk_at(const Plan &p, uint32_t gen_now) {
 // (an ordinary load: only the end of a launch changes the word, so the XCD's L2 may serve it)
 __device__ inline uint32_t trk_gen(const Plan &p) { return p.track[2 * trk_bank_words(p.P)]; }
 __device__ inline Trk trk_open(const Plan &p) { return trk_at(p, trk_gen(p)); }
-// Who acts on the tracker's words: one thread, behind a branch of its own ...
+// Who acts on the tracker's words: one thread, behind a branch of its own (an answer is waited for in there: where
+// the paths meet again there is none on its way) ...
 struct TrkThread {
   __device__ uint32_t add(uint32_t *w, uint32_t v) const {
-    return __hip_atomic_fetch_add(w, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    const uint32_t old = __hip_atomic_fetch_add(w, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __builtin_amdgcn_s_waitcnt(kWaitVm0);
+    return old;
   }
   __device__ void put(uint32_t *w, uint32_t v) const {
     __hip_atomic_store(w, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -398,6 +401,7 @@ __device__ inline TrkCount track_issue(const Plan &p, const Trk &t, const Tile &
   TrkCount k;
   k.old = __hip_atomic_fetch_add(track_word(p, t, tl), 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   k.done = p.whole_chunks ? 0u : __hip_atomic_fetch_add(t.done, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  __builtin_amdgcn_s_waitcnt(kWaitVm0);          // (see TrkThread)
   return k;
 }
 // Acts on what the count returned.

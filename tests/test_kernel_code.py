@@ -1,11 +1,12 @@
-"""The hand-ordered kernel's compiled code: what inline assembly has requested into registers is not
+"""The compiled code of the product kernels.  The hand-ordered one: what inline assembly has requested into registers is not
 touched before it is waited for, and the main loop holds nothing that keeps the matrix cores waiting.
 
 The compiler takes the output of an inline-assembly load as written at once.  It may then copy,
 spill or reuse the register while the data is still on its way (it does, where the K loop's body appears
 twice).  So the LDS reads of the main loop are followed here through the control flow of every
 instantiation, from the read to the wait behind it, and loads or returning atomics from global memory,
-whose waits depend on how many copies are in flight, are not written as inline assembly at all."""
+whose waits depend on how many copies are in flight, are not written as inline assembly at all.  The general
+kernel's main loop waits for global memory once a slab."""
 import os
 import re
 import subprocess
@@ -16,12 +17,11 @@ import pytest
 from paper_2401_16677_amd import build as hip_build
 
 LAYOUTS = [u for u in hip_build.UNITS if u[0] == "t3_wide_launch.hip"]
+GENERAL = [u for u in hip_build.UNITS if u[0] == "t3_gemm_launch.hip"]
 
 
-@pytest.fixture(scope="module")
-def code(tmp_path_factory):
+def _compile(out, units, kernel):
     """unit -> {kernel: lines} of the device assembly."""
-    out = tmp_path_factory.mktemp("asm")
 
     def compile_unit(unit):
         src, obj, defines = unit
@@ -32,11 +32,21 @@ def code(tmp_path_factory):
                         os.path.join(hip_build.CSRC, src), "-o", path], check=True, stderr=subprocess.DEVNULL)
         with open(path) as f:
             text = f.read()
-        starts = [m for m in re.finditer(r"^(_ZN\S+wide_tile_kernel\S+):", text, re.M)]
+        starts = [m for m in re.finditer(r"^(_ZN\S+%s\S+):" % kernel, text, re.M)]
         return {m.group(1): text[m.end():text.index(".Lfunc_end", m.end())].split("\n") for m in starts}
 
     with ThreadPoolExecutor(4) as pool:
-        return dict(zip([u[1] for u in LAYOUTS], pool.map(compile_unit, LAYOUTS)))
+        return dict(zip([u[1] for u in units], pool.map(compile_unit, units)))
+
+
+@pytest.fixture(scope="module")
+def code(tmp_path_factory):
+    return _compile(tmp_path_factory.mktemp("asm"), LAYOUTS, "wide_tile_kernel")
+
+
+@pytest.fixture(scope="module")
+def general(tmp_path_factory):
+    return _compile(tmp_path_factory.mktemp("asm"), GENERAL, "gemm_tile_kernel")
 
 
 def _registers(text):
@@ -160,3 +170,18 @@ def test_nothing_stands_between_the_products(code, unit):
                 halves += 1
                 assert products[0] <= 4, (kernel, block[:products[0]])
         assert halves == 1, kernel
+
+
+@pytest.mark.parametrize("unit", [u[1] for u in GENERAL])
+def test_general_main_loop_waits_once_a_slab(general, unit):
+    """The loop over the slabs is one block that branches to itself.  Its copies stay in flight from one pass to the
+    next: the only wait that names them is the one before the barrier, with the LDS accesses.  (A second one is what
+    the compiler adds where an answer from memory, asked for behind an earlier branch, may still be on its way.)"""
+    for kernel, lines in general[unit].items():
+        loops = 0
+        for i, (block, succ) in enumerate(_blocks(lines)):
+            if i in succ and sum(t.startswith("v_mfma") for t, _ in block) >= 32:
+                loops += 1
+                waits = [t for t, _ in block if t.startswith("s_waitcnt") and "vmcnt" in t]
+                assert len(waits) == 1 and "lgkmcnt(0)" in waits[0], (kernel, waits)
+        assert loops == 1, kernel
