@@ -119,19 +119,26 @@ def _dptr(t):
 
 # torch.cuda.current_stream() builds a Stream object through several layers of Python (4 of the
 # 7.5 us a small call spent on the host); the raw handle of the current device's current stream
-# is one C call.
+# is one C call.  Those two calls are torch's own, not its public interface: where either is
+# missing, the public one serves.
 _raw_stream = None
+
+
+def _stream_getter():
+    import torch
+    get = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+    dev = getattr(torch._C, "_cuda_getDevice", None)
+    if get is None or dev is None:
+        return lambda: torch.cuda.current_stream().cuda_stream
+    torch.cuda.current_stream()                                    # initialises the runtime if need be
+    return lambda: get(dev())
 
 
 def _stream(stream):
     global _raw_stream
     if stream is None:
         if _raw_stream is None:
-            import torch
-            s = torch.cuda.current_stream().cuda_stream           # initialises the runtime if need be
-            get, dev = torch._C._cuda_getCurrentRawStream, torch._C._cuda_getDevice
-            _raw_stream = lambda: get(dev())                       # noqa: E731
-            return s
+            _raw_stream = _stream_getter()
         return _raw_stream()
     if isinstance(stream, int):
         return stream

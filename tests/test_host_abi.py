@@ -187,6 +187,28 @@ def test_bad_arguments_are_refused_before_any_launch():
         t3.t3_chunk_order(4, 5)
 
 
+@pytest.mark.parametrize("missing", [(), ("_cuda_getCurrentRawStream",), ("_cuda_getDevice",),
+                                     ("_cuda_getCurrentRawStream", "_cuda_getDevice")])
+def test_current_stream_without_the_private_calls(monkeypatch, missing):
+    """The current stream's handle is the public interface's where torch lacks its two internal calls, and
+    follows the current stream from call to call."""
+    torch = pytest.importorskip("torch")
+    now = [0x1230]
+    private = {"_cuda_getCurrentRawStream": lambda dev: now[0] + dev, "_cuda_getDevice": lambda: 0}
+    for name, call in private.items():
+        if name in missing:
+            monkeypatch.delattr(torch._C, name, raising=False)
+        else:
+            monkeypatch.setattr(torch._C, name, call, raising=False)
+    monkeypatch.setattr(torch.cuda, "current_stream",
+                        lambda: type("Stream", (), {"cuda_stream": now[0]})())
+    monkeypatch.setattr(t3, "_raw_stream", None)
+    assert t3._stream(None) == 0x1230
+    now[0] = 0x4560
+    assert t3._stream(None) == 0x4560
+    assert t3._stream(7) == 7
+
+
 def test_header_compiles_as_c11_and_a_c_client_links():
     """include/t3.h is a C header: tests/c_abi_client.c is compiled with gcc -std=c11 -Wall
     -Werror against it and linked with the built library (running it needs a GPU)."""
