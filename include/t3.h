@@ -131,45 +131,52 @@ typedef struct {
  * M*ldr*4 and M*ldc*4 below 2^32 bytes (the kernels address R, C and a forward slot with
  * 32-bit byte offsets from a uniform base); fewer than 2^31 tiles.
  *
- * Launch shape.  Over whole ring steps the tile kernel cuts a chunk into workgroup tiles as
- * suits the device and the sizes (256 x 256 down to the smallest), whatever tile_m x tile_n, the
- * tracked region, is; a tile range that cuts a step runs one workgroup tile per tracked tile.
- * The tile kernel runs persistent
- * workgroups (as many as the device holds at once) that walk the grid positions in issue
- * order.  The first wave of workgroups starts in a few phase groups a few microseconds
+ * Launch shape.  Over whole ring steps a chunk is cut into workgroup tiles as suits the device's
+ * compute units and the sizes (256 x 256 down to 32 x 32), whatever tile_m x tile_n, the
+ * tracked region, is; a tile range that cuts a step, and every two-writer call, runs one workgroup
+ * tile per tracked tile.  Workgroup tiles of 128 rows and more are walked in issue order by
+ * persistent workgroups, as many as the device holds at once; smaller ones have a workgroup
+ * each.  The first wave of persistent workgroups starts in a few phase groups a few microseconds
  * apart, so that the compute units do not all reach their reduction traffic at the same
  * moment; the environment variable T3_STAGGER="groups,window_ns" (read once, at the first
  * launch of the process) overrides the default (4 groups over 12 us), T3_STAGGER=0 turns it
- * off.  Results do not depend on it.  The number of persistent workgroups follows the
- * device's compute-unit count; the XCD grouping is applied on devices with 8 XCDs.
- * Balanced tail: when the tiles of such a launch do not fill a whole number of rounds of the
- * persistent workgroups and the last round would occupy at most half of them, each tile of
- * that round is computed as two halves of K by two workgroups, the first at the start of the
+ * off.  Results do not depend on it.  The XCD grouping is applied on devices with 8 XCDs.
+ * Balanced tail: when the workgroup tiles of a launch over whole ring steps do not fill a whole
+ * number of rounds of the persistent workgroups and the last round would occupy at most half of
+ * them, each tile of that round is computed as two halves of K by two workgroups, the first at the start of the
  * launch and the second at its end, the partial sums passing through the place the result
  * goes to (R, C or the fp32 forward slot); the tile is counted when the second half has
  * stored it.  Tiles and counters are the same as without it, and so are the results up to
  * the order in which the K-slabs are added in fp32 (the partial sums are stored and reloaded
- * as they are; the order differs between workgroups anyway).  It applies to whole-problem
- * launches (no tile range) with A and B in their default layouts and K >= 512, not to
- * bfloat16 forward slots written directly, and for t3_gemm not while its stream is being
- * captured into a graph.
+ * as they are; the order differs between workgroups anyway).  It applies to all layouts of A and
+ * B, where the hand-ordered kernel serves the launch with one workgroup per compute unit (all its
+ * workgroup tiles but 128 x 128) and K >= 512; not to bfloat16 forward slots, and for t3_gemm not
+ * while its stream is being captured into a graph.
  *
  * Tracker state (Sec. 4.2): one caller-owned device array of t3_track_words(tp) uint32
  * words, cleared once by t3_track_reset().  It holds two banks of 3*tp + 2 words
- *   [0, tp)        counter[c]  tiles of chunk c that have landed (once the chunk is complete;
- *                              until then, where workgroup tiles are not tracked tiles, the
- *                              workgroup tiles that have)
+ *   [0, tp)        counter[c]  tiles of chunk c that have landed, once the launch has completed.
+ *                              While it runs over whole ring steps it counts what the kernel
+ *                              does: workgroup tiles, or groups of them; it is set to the
+ *                              tracked tiles when the chunk is complete
  *   [tp, 2tp)      ready[c]    1 once counter[c] == tpc
  *   [2tp, 3tp)     queue[i]    chunk ids in trigger order (forwarded chunks only, so at
  *                              most tp-1 entries are used); 0xFFFFFFFF = empty
  *   [3tp]          queue_len
- *   [3tp+1]        done        workgroups of the launch that have finished
+ *   [3tp+1]        done        workgroup tiles of the launch that have been counted, added a
+ *                              whole chunk at a time in a launch over whole ring steps
  * followed by two global words
  *   [6tp+4]        gen         launches completed since the reset
  *   [6tp+5]        error       0, or 1 if the second half of a split tile gave up waiting for
- *                              the first (cannot happen in a launch that ran to completion)
+ *                              the first.  The first halves are taken before anything that
+ *                              could wait for them, so this does not happen while all of a
+ *                              launch's workgroups run; if it is 1 the results of a launch
+ *                              since the reset are not to be used.  Launches that must be known
+ *                              good check it once they have completed.  (t3_gemm has no
+ *                              tracker to report it in.)
  * and by 256 words the kernels use between the two halves of a split tile (balanced tail,
- * above); they are 0 whenever no launch is running.
+ * above) or, in a launch without one, to count the tiles of a chunk in groups; they are 0 whenever
+ * no launch is running.
  * A launch of t3_gemm_rs_fused / t3_rs_reduce works in bank gen & 1; its last workgroup
  * clears the other bank and increments gen.  So consecutive launches need no reset in
  * between, and after a launch has completed its results are in bank (gen - 1) & 1.  A
@@ -180,8 +187,9 @@ typedef struct {
  * the order in which chunks actually completed on the device.
  * Publication: ready[c] is THE flag.  A tile's results are written with device-scope
  * write-through stores and are acknowledged before the tile is counted; the count that
- * completes a chunk writes its queue entry and then sets ready[c] with a device-scope release
- * store.  A consumer on the same device that observes ready[c] == 1 with an acquiring load may
+ * completes a chunk writes its queue entry, waits until that is acknowledged too, and then sets
+ * ready[c] with a device-scope relaxed store (a release store would write back the XCD's L2, in
+ * which nothing of the chunk is left).  A consumer on the same device that observes ready[c] == 1 with an acquiring load may
  * read chunk c and will find c in the queue.  queue_len by itself publishes nothing: it is
  * reserved before the entry is written and may run ahead of it.  (This is the ordering gfx950
  * gives agent-scope stores and atomics; it is not promised to other devices or to the host
@@ -219,9 +227,9 @@ t3_status t3_track_reset(int32_t tp, uint32_t *track, void *stream);
 /*
  * The fused path (Sec. 4.1): C = A.B is produced tile by tile in issue order and never
  * stored on its own; each tile's epilogue forms incoming + C from R (Sec. 4.3's
- * op-and-store, done by the compute units), then bumps the chunk's counter; the tile
- * that completes a chunk marks it ready and, for forwarded chunks, appends it to the
- * trigger queue, which releases the chunk into its forward slot (Sec. 4.2.2).
+ * op-and-store, done by the compute units) and stores it to R, to the chunk's forward slot or
+ * to both, then the tile is counted; the count that completes a chunk appends it, if it is
+ * forwarded, to the trigger queue and marks it ready: its slot is written by then (Sec. 4.2.2).
  *
  *   A    bf16, see a_layout read
  *   B    bf16, see b_layout read
@@ -322,18 +330,22 @@ t3_status t3_ag_step(const t3_problem *p, int32_t step, const float *upstream_R,
 /*
  * Where a launch's time goes (a measuring aid for Sec. 4.1's overlap: how much of a tile's time
  * is reduction traffic and how much is matrix work).  While `stamps` is set, every launch of
- * the tile kernel (t3_gemm_rs_fused, t3_gemm_rs_fused_static, t3_gemm), from any thread,
+ * the tile kernels (t3_gemm_rs_fused, t3_gemm_rs_fused_static, t3_gemm), from any thread,
  * records for workgroup w and its i-th piece of work (a tile, or half of one in a balanced
  * tail), i < T3_TIMELINE_ITEMS, four readings of the device's 100 MHz wall clock at
  * stamps[(w * T3_TIMELINE_ITEMS + i) * 4 + 0 .. 3]:
  *   0  the piece was taken
- *   1  the accumulators are set up: the incoming partial has arrived and is in place
- *   2  the main loop (and a ragged end of K) is done
+ *   1  the main loop can start: its first slabs are in LDS and, in a launch over part of a ring
+ *      step and in one the hand-ordered kernel does not serve, the incoming partial has arrived
+ *      and is in place
+ *   2  the main loop (and a ragged end of K) is done; the hand-ordered kernel has requested the
+ *      first rows of the incoming partial in its last slabs
  *   3  the results have been handed to the memory system (they are acknowledged later, while
- *      the next piece starts) and the next tile's incoming partial has been requested
- * Workgroups w >= words / (4 * T3_TIMELINE_ITEMS) record nothing, nor do the kernels that serve
- * 256 x 256 tiles with B stored K x N, A stored K x M, two writers or bfloat16 slots written
- * directly.  Entries a launch does not
+ *      the next piece starts); the hand-ordered kernel has added the incoming partial on the
+ *      way, and has the next piece's first slabs in LDS
+ * Workgroups w >= words / (4 * T3_TIMELINE_ITEMS) record nothing, nor do launches on workgroup
+ * tiles of less than 128 rows, nor launches on 256 x 256 tiles that the hand-ordered kernel does
+ * not serve.  Entries a launch does not
  * write keep what they held.  stamps: device memory, 8-byte aligned, that stays valid until
  * the launches that were issued while it was set have finished; NULL switches recording off.
  * Later launches overwrite earlier ones.
