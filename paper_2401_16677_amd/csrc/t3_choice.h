@@ -52,6 +52,9 @@ inline Choice workgroup_tile(const t3_problem *p, int cus, int64_t steps, bool w
   for (const Cand &c : kCand) {
     const bool general = c.stages && (!wide_ok || slabs < c.stages);
     if (general && c.t.n == 192) continue;
+    // (32 x 64 is for k-rows of B of a whole 128-byte line; with B K-contiguous two 32 x 32 workgroups take its place
+    // at the same time per slab, and start and end sooner)
+    if (c.t.m == 32 && c.t.n == 64 && !kn) continue;
     const int64_t T = ceil_div(p->M, c.t.m) * ceil_div(W, c.t.n) * steps, slots = (int64_t)cus * c.per_cu;
     double rounds = (double)ceil_div(T, slots);
     const bool tail = c.stages && !general && c.per_cu == 1 && T > slots && T % slots && 2 * (T % slots) <= slots &&

@@ -19,7 +19,6 @@ namespace t3k {
 typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
 typedef __attribute__((ext_vector_type(4))) float f32x4;
 typedef __attribute__((address_space(3))) void *lds_void_ptr;
-typedef const __attribute__((address_space(1))) void *global_void_ptr;
 
 constexpr int kThreads = 256;
 constexpr uint32_t kEmpty = 0xFFFFFFFFu;
@@ -285,12 +284,6 @@ __device__ inline void stagger_start(const Plan &p) {
 // Stores that are visible to every XCD once acknowledged: agent scope, i.e. the sc1 bit, which
 // writes through the issuing XCD's L2.  (Plain and non-temporal stores stay in that L2 until a
 // release fence writes the whole cache back.)
-__device__ inline void store_agent(float *p, float v) {
-  __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-__device__ inline void store_agent(f32x4 *p, f32x4 v) {
-  asm volatile("global_store_dwordx4 %0, %1, off sc1" : : "v"(p), "v"(v) : "memory");
-}
 // Tile results and the incoming partial are accessed through buffer instructions: uniform
 // descriptor, 32-bit byte offset of the lane, uniform offset of the block.  They are issued as
 // compiler builtins, not inline assembly, so that the compiler keeps the required distance

@@ -6,23 +6,25 @@
 namespace t3k {
 namespace {
 
-template <int BM, int BN, int NST>
+template <int BM, int BN, int NST, bool NK = true>
 t3_status launch_small(const Plan &q, bool b_kn, bool a_km, hipStream_t s) {
   const dim3 grid((unsigned)q.total_blocks), block(256);
-  if (a_km)
-    return b_kn ? launch(small_tile_kernel<BM, BN, 4, NST, T3_MODE, 1, 1>, grid, block, s, q)
-                : launch(small_tile_kernel<BM, BN, 4, NST, T3_MODE, 0, 1>, grid, block, s, q);
-  return b_kn ? launch(small_tile_kernel<BM, BN, 4, NST, T3_MODE, 1, 0>, grid, block, s, q)
-              : launch(small_tile_kernel<BM, BN, 4, NST, T3_MODE, 0, 0>, grid, block, s, q);
+  if (b_kn)
+    return a_km ? launch(small_tile_kernel<BM, BN, 4, NST, T3_MODE, 1, 1>, grid, block, s, q)
+                : launch(small_tile_kernel<BM, BN, 4, NST, T3_MODE, 1, 0>, grid, block, s, q);
+  if constexpr (NK)
+    return a_km ? launch(small_tile_kernel<BM, BN, 4, NST, T3_MODE, 0, 1>, grid, block, s, q)
+                : launch(small_tile_kernel<BM, BN, 4, NST, T3_MODE, 0, 0>, grid, block, s, q);
+  return T3_ERR_UNSUPPORTED;
 }
 
 }  // namespace
 
 t3_status T3_LAUNCHER(const Plan &q, int32_t tm, int32_t tn, bool b_kn, bool a_km, hipStream_t s) {
-  // 64 x 64: two 16-KiB stages per wavefront, one workgroup per compute unit; 32 x 64: three of 12 KiB;
-  // 32 x 32: two of 8 KiB, two workgroups
+  // 64 x 64: two 16-KiB stages per wavefront, one workgroup per compute unit; 32 x 64 (only
+  // chosen with B stored K x N): three of 12 KiB; 32 x 32: two of 8 KiB, two workgroups
   if (tm == 64) return launch_small<64, 64, 2>(q, b_kn, a_km, s);
-  return tn == 64 ? launch_small<32, 64, 3>(q, b_kn, a_km, s) : launch_small<32, 32, 2>(q, b_kn, a_km, s);
+  return tn == 64 ? launch_small<32, 64, 3, false>(q, b_kn, a_km, s) : launch_small<32, 32, 2>(q, b_kn, a_km, s);
 }
 
 }  // namespace t3k

@@ -56,6 +56,7 @@ def test_random_problems_are_covered_once():
                 assert (s.tile_m, s.tile_n) == t3.t3_default_tile(p) and (s.begin, s.limit) == (lo * tpc + 1, hi * tpc)
             else:
                 assert (s.begin, s.limit) == (lo * s.tpc, hi * s.tpc) and s.blocks == (hi - lo) * s.tpc
+            assert (s.kernel, s.tile_m, s.tile_n) != (SMALL, 32, 64) or layout.endswith("kn"), p
             if s.tail_r:
                 assert s.kernel == WIDE and s.tail_q * s.resident + s.tail_r == s.blocks and 2 * s.tail_r <= s.resident
 
@@ -70,6 +71,8 @@ def test_random_problems_are_covered_once():
     (64, 384, 128, 32, "nk", (SMALL, 64, 64)),
     (8, 384, 4096, 32, "kn", (SMALL, 32, 64)),
     (256, 256, 256, 4, "nk", (SMALL, 32, 32)),
+    (8, 384, 65536, 32, "nk", (SMALL, 32, 32)),      # (32 x 64 is not built for B stored N x K)
+    (8, 384, 65536, 32, "km", (SMALL, 32, 32)),
 ])
 def test_every_tile_has_a_problem(M, W, K, tp, layout, want):
     s = launch_shape(_problem(M, W, K, tp, layout))
