@@ -3,14 +3,17 @@ three or more tiles (LDS reused from tile to tile, the count of a tile deferred 
 tile's main loop), every element compared with the CPU oracle.
 
 Small-integer inputs make fp32 accumulation exact in any order, so R, the forward slots and C
-must equal the fp64 oracle bit for bit; the shapes have at least three tiles per resident
-workgroup for each of the four tile shapes (256 compute units hold 256 workgroups, 512 of the
-128 x 128 tile), a ragged last tile row and a K that ends in a partial slab."""
+must equal the fp64 oracle bit for bit; the shapes have at least three tracked tiles per resident
+workgroup for each of the four tracked tiles (256 compute units hold 256 workgroups, 512 of the
+128 x 128 tile), a ragged last tile row and a K that ends in a partial slab.  Over whole ring steps the
+workgroup tile is picked by size, whatever the tracked tile is: what the tracked tile changes there is what the
+counters end at.  The other workgroup tiles have tests of their own (test_gpu_workgroup_tiles.py)."""
 import numpy as np
 import pytest
 
 from paper_2401_16677_amd import binding as t3
 from paper_2401_16677_amd import workloads as wl
+from tests.launch_shape import GENERAL, WIDE, launch_shape
 
 pytestmark = pytest.mark.gpu
 
@@ -152,10 +155,9 @@ def test_three_tiles_per_workgroup_float_every_element(gpu, oracle, tile):
 @pytest.mark.parametrize("direct", [True, False])
 @pytest.mark.parametrize("rng_kind", ["all", "step1", "steps12", "cut"])
 def test_tracked_tiles_of_128_rows_computed_in_pairs(gpu, oracle, rng_kind, direct, unfused):
-    """128 x 256 tracked tiles: over ranges of whole ring steps the tile kernel computes two of
-    them as one 256 x 256 workgroup tile and counts both (the last tile row, here the 19th of a
-    column, stands alone); a range that cuts a step falls back to one workgroup per tracked
-    tile.  Counters, flags, queue and every element must not care."""
+    """128 x 256 tracked tiles, 19 rows of them: over ranges of whole ring steps the workgroup tile is another
+    one and its counts end at the tracked tiles all the same; a range that cuts a step runs one workgroup tile per tracked
+    tile.  Flags, queue and every element must not care."""
     M, N, K, tp, rank, tile = 2330, 3 * 1304, 200, 3, 1, (128, 256)
     tpc = oracle.tiles_per_chunk(M, N, tp, *tile)
     assert tpc == 19 * 6
@@ -173,18 +175,23 @@ def test_tracked_tiles_of_128_rows_computed_in_pairs(gpu, oracle, rng_kind, dire
     _check_ints(got, want, want["own"])
 
 
-def test_incoming_partial_survives_a_busy_lds_queue(gpu, oracle):
-    """The 128 x 128 tile runs two workgroups per compute unit, so the LDS unit is busy while a
+@pytest.mark.parametrize("begin", [0, 1])
+def test_incoming_partial_survives_a_busy_lds_queue(gpu, oracle, begin):
+    """The general kernel's 128 x 128 tile runs two workgroups per compute unit, so the LDS unit is busy while a
     workgroup turns its incoming partial into the accumulator layout in the stage that the main
-    loop refills next; those LDS accesses must be complete before the refill is requested.  The
+    loop refills next; those LDS accesses must be complete before the refill is requested.  (A range that cuts a
+    step is that kernel's; the whole problem runs the hand-ordered one.)  The
     launch is repeated: what is checked depends on timing."""
     tile, (M, N, K, tp, rank) = (128, 128), (2040, 9728, 520, 4, 3)
+    s = launch_shape(t3.problem(M, N, K, tp, rank, *tile, flags=t3.T3_FLAG_FWD_DIRECT, tile_begin=begin))
+    assert (s.kernel, s.resident) == ((GENERAL, 2 * CUS) if begin else (WIDE, CUS))
     a, b, inc = wl.make_integer_inputs(M, N, K, seed=77)
-    want = oracle.fused_path(a, b, inc, tp, rank, *tile, fwd_direct=True,
+    want = oracle.fused_path(a, b, inc, tp, rank, *tile, fwd_direct=True, tile_begin=begin,
                              fwd_init=np.full((tp - 1, M, N // tp), gpu.SENTINEL, np.float32))
     for rep in range(12):
         print(f"tile={tile} shape={(M, N, K, tp, rank)} repetition {rep}", flush=True)
-        got = gpu.run_gpu(a, b, inc, tp, rank, tile, flags=t3.T3_FLAG_FWD_DIRECT, ldr_pad=4, lda_pad=8)
+        got = gpu.run_gpu(a, b, inc, tp, rank, tile, flags=t3.T3_FLAG_FWD_DIRECT, ldr_pad=4, lda_pad=8,
+                          tile_begin=begin)
         assert np.array_equal(got["R"], want["R"]), _first_mismatch(got["R"], want["R"])
         assert np.array_equal(got["fwd"], want["fwd"]), _first_mismatch(got["fwd"], want["fwd"])
     _check_ints(got, want, want["own"])
@@ -193,11 +200,12 @@ def test_incoming_partial_survives_a_busy_lds_queue(gpu, oracle):
 # Balanced tail: the tiles do not fill a whole number of rounds of the resident workgroups and
 # the last round would fill at most half of them, so each of its tiles is computed as two
 # halves of K by two workgroups, the partial sums passing through the tile's destination.
-# M, N, K, tp, rank: tiles = q * resident + r, 0 < r <= resident / 2; K has a ragged last slab.
+# M, N, K, tp, rank: tiles = q * resident + r, 0 < r <= resident / 2; K has a ragged last slab.  By tracked tile; the
+# workgroup tile of all four is 256 x 256.
 TAIL = {
     (256, 256): (2040, 20480, 520, 5, 2),     # 8 x 16 x 5 = 640 = 2 x 256 + 128
     (256, 128): (2040, 10240, 584, 5, 4),     # 8 x 16 x 5 = 640
-    (128, 256): (2040, 20480, 520, 5, 0),     # computed in pairs: 8 x 16 x 5 = 640 workgroup tiles
+    (128, 256): (2040, 20480, 520, 5, 0),     # 8 x 16 x 5 = 640 tiles of 256 x 256
     (128, 128): (2040, 9728, 520, 4, 3),      # 16 x 19 x 4 = 1216 = 2 x 512 + 192
 }
 

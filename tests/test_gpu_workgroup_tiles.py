@@ -25,7 +25,7 @@ def gpu():
 def _check(gpu, oracle, M, W, K, tp, mode, layout="nk", unfused=False, tile=None, begin=0, limit=-1):
     N, rank = W * tp, (M + W) % tp
     print(f"M={M} W={W} K={K} tp={tp} rank={rank} mode={mode} layout={layout}", flush=True)
-    kn, km = layout != "nk", layout == "km_kn"
+    kn, km = layout.endswith("kn"), layout.startswith("km")
     direct, bf16, step0 = mode != "copy", mode == "bf16", mode == "step0"
     a, b, inc = wl.make_integer_inputs(M, N, K, seed=M + 3 * W + 7 * K)
     tile = tile or t3.t3_default_tile(t3.problem(M, N, K, tp, rank, 0, 0))
@@ -41,7 +41,7 @@ def _check(gpu, oracle, M, W, K, tp, mode, layout="nk", unfused=False, tile=None
         bad = np.argwhere(got[name] != want[name])
         assert bad.size == 0, f"{name}: {bad.shape[0]} mismatches, first at {tuple(bad[0])}"
     assert np.all(got["R_pad"] == 123.0)
-    if mode == "unfused":
+    if mode == "unfused" and (begin, limit) == (0, -1):      # (a range leaves the rest of C alone; its sums are in R)
         assert np.array_equal(got["C"], oracle.gemm_rows(a, b).astype(np.float32))
     assert np.array_equal(got["counter"], want["counter"]) and np.array_equal(got["ready"], want["ready"])
     n = want["queue_len"]
@@ -116,3 +116,60 @@ def test_reduction_of_a_cut_range(gpu, oracle, M, W, tp, tile, mode):
     tpc = t3.t3_tiles_per_chunk(t3.problem(M, W * tp, 64, tp, 0, *tile))
     for begin, limit in ((1, tpc * tp), (0, tpc * tp - 1)):
         _check(gpu, oracle, M, W, 64, tp, mode, unfused=True, tile=tile, begin=begin, limit=limit)
+
+
+# What the choice by size picks and nothing above reaches: the wide-tile kernel's 256 x 128 and 128 x 192 tiles (three LDS
+# stages), balanced tails on every tile that has them, and 32 x 64.  (Which tile each problem gets is checked
+# without a GPU as well.)  M, W, K, tp, layout, one ring step only, workgroup tile, tiles the tail splits.
+PICKED = [
+    # more tiles than workgroups; four to seven K-slabs, whole and ragged: a tile's count is put off into the next one's loop
+    (6432, 280, 200, 5, "nk", False, (128, 192), 0),
+    (533, 528, 264, 32, "nk", False, (128, 192), 0),
+    (522, 544, 320, 32, "nk", False, (128, 192), 0),
+    (4448, 136, 384, 16, "nk", False, (128, 192), 0),
+    (4344, 136, 392, 16, "nk", False, (128, 192), 0),
+    (8728, 144, 256, 8, "km", False, (128, 192), 0),
+    (544, 520, 320, 32, "km_kn", False, (128, 192), 0),
+    (8368, 136, 320, 8, "kn", False, (128, 192), 0),
+    (4096, 1536, 1536, 2, "nk", True, (128, 192), 0),       # one tile per compute unit
+    (6928, 40, 4104, 16, "nk", False, (256, 128), 0),
+    (3112, 56, 4096, 32, "nk", False, (256, 128), 0),
+    (7944, 8, 4096, 32, "km", False, (256, 128), 0),
+    (3352, 48, 4096, 32, "km_kn", False, (256, 128), 0),
+    (7432, 64, 4096, 16, "kn", False, (256, 128), 0),
+    # balanced tails: halves of four K-slabs, the second one with a ragged slab more
+    (4104, 136, 520, 16, "nk", False, (256, 192), 16),
+    (4128, 136, 512, 16, "km", False, (256, 192), 16),
+    (4488, 136, 512, 16, "kn", False, (256, 192), 32),
+    (4552, 136, 512, 16, "km_kn", False, (256, 192), 32),
+    (4200, 128, 520, 16, "nk", False, (256, 128), 16),
+    (4936, 8, 4096, 32, "km", False, (256, 128), 128),
+    (4704, 128, 1024, 16, "kn", False, (256, 128), 48),
+    (4104, 128, 512, 16, "km_kn", False, (256, 128), 16),
+    (4104, 136, 520, 8, "nk", False, (128, 192), 8),
+    (2088, 136, 512, 16, "km", False, (128, 192), 16),
+    (2080, 136, 512, 16, "kn", False, (128, 192), 16),
+    (2400, 136, 512, 16, "km_kn", False, (128, 192), 48),
+    # rows of a few tokens, the last columns ragged
+    (8, 392, 2816, 32, "kn", False, (32, 64), 0),
+    (24, 264, 1920, 32, "km_kn", False, (32, 64), 0),
+    (136, 40, 2048, 32, "km_kn", False, (32, 64), 0),
+]
+MODES = {"direct": t3.T3_FLAG_FWD_DIRECT, "copy": 0, "bf16": t3.T3_FLAG_FWD_DIRECT | t3.T3_FLAG_FWD_BF16,
+         "step0": t3.T3_FLAG_FWD_DIRECT | t3.T3_FLAG_STEP0_STORE_ONLY, "unfused": t3.T3_FLAG_FWD_DIRECT}
+# all modes where both operands are K-contiguous (no bfloat16 slots with a tail), the two kernels there are in every layout
+PICKED_MODES = [(case, mode) for case in PICKED for mode in MODES
+                if (case[4] == "nk" or case[6] == (32, 64) or mode in ("direct", "unfused")) and not (case[7] and mode == "bf16")]
+
+
+def picked_range(case):
+    M, W, K, tp, _, one_step, _, _ = case
+    tpc = t3.t3_tiles_per_chunk(t3.problem(M, W * tp, K, tp, 0, 0, 0))
+    return (tpc, 2 * tpc) if one_step else (0, -1)
+
+
+@pytest.mark.parametrize("case,mode", PICKED_MODES)
+def test_picked_tiles(gpu, oracle, case, mode):
+    M, W, K, tp, layout, _, _, _ = case
+    begin, limit = picked_range(case)
+    _check(gpu, oracle, M, W, K, tp, mode, layout, begin=begin, limit=limit)

@@ -79,6 +79,16 @@ def test_every_tile_has_a_problem(M, W, K, tp, layout, want):
     assert (s.kernel, s.tile_m, s.tile_n) == want
 
 
+def test_problems_of_the_gpu_tests_get_the_tiles_they_are_meant_for():
+    from tests.test_gpu_workgroup_tiles import MODES, PICKED_MODES, picked_range
+    for case, mode in PICKED_MODES:
+        M, W, K, tp, layout, _, tile, tail_r = case
+        begin, limit = picked_range(case)
+        p = _problem(M, W, K, tp, layout, tile_begin=begin, tile_limit=limit, flags=MODES[mode])
+        s = launch_shape(p, GEMM if mode == "unfused" else FUSED)
+        assert (s.kernel, s.tile_m, s.tile_n, s.tail_r) == (SMALL if tile == (32, 64) else WIDE, *tile, tail_r), (case, mode)
+
+
 def test_general_kernel():
     p = _problem(4096, 1536, 1536, 8, tile_m=256, tile_n=256, tile_begin=1)
     assert launch_shape(p).kernel == GENERAL                     # a range that cuts a step
