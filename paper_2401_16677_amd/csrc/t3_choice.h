@@ -28,12 +28,15 @@ struct Choice {
 };
 
 // For `steps` whole ring steps of a problem: the tile with the least time by rounds of workgroups x
-// time of a tile.  The times are fitted to 110 problems (8 to 16384 tokens, K 128 to 10240, all layouts,
-// TP 2 to 32), each run on every tile: what is picked is 0.4 % slower than the best of the eight on
-// average, 10 % at most.  They carry what the problems had in common (traffic past the L2s, clocks).
-// wide_ok: the wide-tile kernel may be used (sizes, see wide_fits).  Where it may not, or K has fewer slabs than its LDS stages, gemm_tile_kernel takes its place on the shapes it has: the
-// same main loop rate (12288 x 4096 x 6144, B stored K x N: 493 us, 495 wide), but the incoming partial
-// is waited for at the start of every tile (12288 x 4096 x 1536: 19 us per tile outside the main loop, 14 wide).
+// time of a tile.  The times are fitted to problems of 8 to 16384 tokens, K 128 to 10240, all layouts,
+// TP 2 to 32, run on every tile.  On 60 such problems (profiles/workgroup_tiles.txt) what is picked takes 1.013 of
+// the best tile's time on average and within 2 % on 51 of them; the worst, 2048 x 10240 x 512 with A transposed,
+// 59 us where the best takes 48.  The times carry what the problems had in common (traffic past the L2s, clocks); release
+// mode, incoming partial and the plain GEMM's shorter way out are not told apart.
+// wide_ok: the wide-tile kernel may be used (sizes, see wide_fits).  Where it may not, or K has fewer slabs than
+// its LDS stages, gemm_tile_kernel takes its place on the shapes it has: the same main loop rate (12288 x 4096 x 6144,
+// B stored K x N: 493 us, 495 wide), but the incoming partial is waited for at the start of every tile
+// (12288 x 4096 x 1536: 19 us per tile outside the main loop, 14 wide).
 inline Choice workgroup_tile(const t3_problem *p, int cus, int64_t steps, bool wide_ok) {
   struct Cand {
     TileShape t;
