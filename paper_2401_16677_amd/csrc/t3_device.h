@@ -67,6 +67,7 @@ struct Plan {
   int32_t stagger_blocks, stagger_groups, stagger_ticks;   // start-up phase offsets (see stagger_start)
   FastDiv by_groups;                   // by k_groups
   int32_t k_groups;                    // > 1: workgroup w starts its K loop (w % k_groups) / k_groups of the way in
+  int32_t col_align;                   // 15: tile columns start at 64-byte granules of R, 0: at multiples of the tile (wide-tile kernel)
   int32_t nt_out;                      // results leave with the streaming hint (wide-tile kernel: the plain GEMM's)
   // Timeline (a profiling aid, normally null): workgroup w < timeline_wgs writes, for its i-th
   // piece of work, i < kTimelineItems, four wall-clock readings (100 MHz) at

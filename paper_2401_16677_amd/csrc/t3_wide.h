@@ -181,6 +181,13 @@ void wide_tile_kernel(const Plan p) {
     const uint64_t a = (uint64_t)(uintptr_t)base;
     return u32x4{(uint32_t)a, (uint32_t)(a >> 32), (uint32_t)bytes, 0x00020000u};
   };
+  // A tile's first column in the chunk, and how many it has.  Where the grid has columns to spare, the chunk's tiles but the
+  // first start up to 15 columns early (p.col_align), at a 64-byte granule of R's rows (see column_align), and the
+  // first one has that many fewer.
+  auto col_at = [&](const Tile &t) { return t.nj * BN - (t.nj ? (t.c * p.W) & p.col_align : 0); };
+  auto cols_of = [&](const Tile &t, int at) {
+    return t.nj ? min(BN, p.W - at) : min(BN - ((t.c * p.W) & p.col_align), p.W);
+  };
   u32x4 descA, descB;
   // Which of a lane's copies lie outside in the piece's last slab (K-contiguous, ragged K) or throughout (transposed,
   // columns past the tile's end): their offsets get the top bit, the others lose it.
@@ -188,8 +195,8 @@ void wide_tile_kernel(const Plan p) {
   bool markedA = false, markedB = false;         // some have it
   int st_k0 = 0, st_nf = 0, st_koff = 0;         // the stream's piece: first slab, full slabs, where its walk starts
   auto stream_to = [&](const Piece &w) {
-    const int m0 = w.tl.mi * BM, n0 = w.tl.c * p.W + w.tl.nj * BN;
-    const int rows = min(BM, p.M - m0), cols = min(BN, p.W - w.tl.nj * BN);
+    const int m0 = w.tl.mi * BM, at = col_at(w.tl), n0 = w.tl.c * p.W + at;
+    const int rows = min(BM, p.M - m0), cols = cols_of(w.tl, at);
     descA = AKM ? descriptor(p.A + m0, (p.K * p.lda - m0) * 2) : descriptor(p.A + m0 * p.lda, rows * p.lda * 2);
     descB = BKN ? descriptor(p.B + n0, (p.K * p.ldb - n0) * 2) : descriptor(p.B + n0 * p.ldb, cols * p.ldb * 2);
     const bool cutA = AKM && rows < BM, cutB = BKN && cols < BN;
@@ -385,15 +392,15 @@ void wide_tile_kernel(const Plan p) {
   for (int it = 0;; ++it) {
     stamp(it, 0);
     const Tile tl = cur.tl;
-    const int m0 = tl.mi * BM, n0 = tl.c * p.W + tl.nj * BN;
+    const int m0 = tl.mi * BM, at = col_at(tl), n0 = tl.c * p.W + at;
     const uint32_t rows_in = (uint32_t)min(BM, p.M - m0);         // rows and columns of the tile inside the chunk
-    const int cols_in = min(BN, p.W - tl.nj * BN);
+    const int cols_in = cols_of(tl, at);
     const bool direct = (p.flags & kFlagFwdDirect) != 0, bf16 = (p.flags & kFlagFwdBf16) != 0;
     const bool to_slot = tracked && tl.c != p.own && cur.half != 1 && (direct || chunk_is_whole(p, tl.s));
     const bool to_r = !tracked || !direct || tl.c == p.own;
     // where a whole tile's fp32 sums go, or half a tile's (an fp32 slot if not R / C)
     const bool out_slot = tracked && direct && tl.c != p.own;
-    float *const slot_at0 = p.fwd + (((int64_t)tl.s * p.M + m0) * p.W + tl.nj * BN);      // the tile's first element in each
+    float *const slot_at0 = p.fwd + (((int64_t)tl.s * p.M + m0) * p.W + at);      // the tile's first element in each
     float *const r_at0 = p.R + (m0 * p.ldr + n0);
     float *const out_base = out_slot ? slot_at0 : r_at0;
     const uint32_t ld_out = out_slot ? (uint32_t)p.W : (uint32_t)p.ldr;

@@ -8,6 +8,11 @@ extern "C" void launch_shape(const t3_problem *p, int call, int tracked_m, int t
   for (int i = 0; i < 10; ++i) out[i] = v[i];
 }
 
+extern "C" int column_align(const t3_problem *p, int call, int tile_n, int64_t address, int64_t ld_out) {
+  return t3k::column_align(p, static_cast<t3k::Call>(call), {256, tile_n}, t3k::ceil_div(p->N / p->tp, tile_n),
+                           reinterpret_cast<const void *>(address), ld_out);
+}
+
 extern "C" void divide(const uint32_t *n, const uint32_t *d, uint32_t *out, int count) {
   for (int i = 0; i < count; ++i) out[i] = t3k::div_by(n[i], t3k::fast_div(d[i]));
 }

@@ -22,11 +22,11 @@ def gpu():
     return gpu_harness
 
 
-def _check(gpu, oracle, M, W, K, tp, mode, layout="nk", unfused=False, tile=None, begin=0, limit=-1):
+def _check(gpu, oracle, M, W, K, tp, mode, layout="nk", unfused=False, tile=None, begin=0, limit=-1, ldr_pad=4):
     N, rank = W * tp, (M + W) % tp
     print(f"M={M} W={W} K={K} tp={tp} rank={rank} mode={mode} layout={layout}", flush=True)
     kn, km = layout.endswith("kn"), layout.startswith("km")
-    direct, bf16, step0 = mode != "copy", mode == "bf16", mode == "step0"
+    direct, bf16, step0 = not mode.endswith("copy"), mode.startswith("bf16"), mode.startswith("step0")
     a, b, inc = wl.make_integer_inputs(M, N, K, seed=M + 3 * W + 7 * K)
     tile = tile or t3.t3_default_tile(t3.problem(M, N, K, tp, rank, 0, 0))
     init = np.full((tp - 1, M, W), gpu.SENTINEL_BF16 if bf16 else gpu.SENTINEL, np.uint16 if bf16 else np.float32)
@@ -35,7 +35,7 @@ def _check(gpu, oracle, M, W, K, tp, mode, layout="nk", unfused=False, tile=None
     flags = (t3.T3_FLAG_FWD_DIRECT if direct else 0) | (t3.T3_FLAG_FWD_BF16 if bf16 else 0) | \
             (t3.T3_FLAG_STEP0_STORE_ONLY if step0 else 0)
     # a launch before the one that is checked: the words its tiles are counted in must be back to zero
-    got = gpu.run_gpu(a, b, inc, tp, rank, tile, flags=flags, unfused=unfused or mode == "unfused", ldr_pad=4,
+    got = gpu.run_gpu(a, b, inc, tp, rank, tile, flags=flags, unfused=unfused or mode == "unfused", ldr_pad=ldr_pad,
                       lda_pad=8, b_kn=kn, a_km=km, launches_before=1, tile_begin=begin, tile_limit=limit)
     for name in ("R", "fwd"):
         bad = np.argwhere(got[name] != want[name])
@@ -173,3 +173,25 @@ def test_picked_tiles(gpu, oracle, case, mode):
     M, W, K, tp, layout, _, _, _ = case
     begin, limit = picked_range(case)
     _check(gpu, oracle, M, W, K, tp, mode, layout, begin=begin, limit=limit)
+
+
+# Rows of R and C that start at 64-byte granules, chunks that do not: tile columns start early, at granules, where the last
+# one has columns to spare.  Chunk widths of 4, 8 and 12 columns past a multiple of 16 (8 with k-rows of B), just enough to spare
+# and 4 or 8 columns too few, every tile with more than one column, tiles split by a balanced tail.
+@pytest.mark.parametrize("mode", ["copy", "bf16_copy", "unfused", "step0_copy"])
+@pytest.mark.parametrize("M,W,K,tp,layout", [
+    (4100, 532, 520, 8, "nk"),
+    (4100, 564, 328, 8, "nk"),           # 3 x 192 with 12 columns to spare
+    (4100, 568, 328, 8, "nk"),           # 8, and all chunks at multiples of 8
+    (4100, 572, 328, 8, "nk"),           # 4: too few
+    (2050, 1020, 200, 8, "nk"),
+    (2050, 500, 1536, 16, "nk"),
+    (4128, 200, 512, 12, "nk"),
+    (4096, 536, 384, 8, "kn"),
+    (2056, 1016, 576, 8, "kn"),
+    (4088, 568, 384, 6, "km_kn"),
+])
+def test_columns_start_at_granules(gpu, oracle, M, W, K, tp, layout, mode):
+    if "bf16" in mode and W % 8:
+        pytest.skip("bfloat16 slots hold multiples of 8 columns")
+    _check(gpu, oracle, M, W, K, tp, mode, layout, ldr_pad=16 + -W * tp % 16)

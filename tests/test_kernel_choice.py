@@ -123,3 +123,29 @@ def test_division_without_dividing():
     u32 = [np.ascontiguousarray(x, dtype=np.uint32) for x in (n, d, np.zeros(d.size))]
     choice_lib().divide(*[x.ctypes.data_as(ctypes.c_void_p) for x in u32], d.size)
     assert np.array_equal(u32[2], n // d)
+
+
+def test_columns_start_at_granules_where_the_grid_has_room():
+    """Every column of a chunk falls to one tile, no tile is wider than it is, and none but a chunk's first
+    starts inside a 64-byte granule."""
+    f = choice_lib().column_align
+    f.argtypes = [ctypes.c_void_p, ctypes.c_int, ctypes.c_int, ctypes.c_int64, ctypes.c_int64]
+    aligned = 0
+    for layout, step in (("nk", 4), ("kn", 8)):
+        for W in range(step, 1100, step):
+            p = _problem(512, W, 256, 8, layout)
+            for bn in (128, 192, 256):
+                mask = f(ctypes.addressof(p), FUSED, bn, 4096, 8 * W)
+                assert mask in (0, 15) and f(ctypes.addressof(p), GEMM, bn, 4096, 8 * W) == mask
+                assert f(ctypes.addressof(p), FUSED, bn, 4112, 8 * W) == 0 and f(ctypes.addressof(p), FUSED, bn, 4096, 8 * W + 4) == 0
+                direct = _problem(512, W, 256, 8, layout, flags=t3.T3_FLAG_FWD_DIRECT)
+                assert f(ctypes.addressof(direct), FUSED, bn, 4096, 8 * W) == 0
+                if not mask:
+                    continue
+                aligned += 1
+                for c in range(8):
+                    shift = c * W & mask
+                    starts = [j * bn - (shift if j else 0) for j in range(-(-W // bn))] + [W]
+                    assert all(0 < b - a <= bn for a, b in zip(starts, starts[1:])), (W, bn, c)
+                    assert all((c * W + a) % 16 == 0 and a % step == 0 for a in starts[1:-1]), (W, bn, c)
+    assert aligned > 100
