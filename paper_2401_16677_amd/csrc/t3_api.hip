@@ -738,10 +738,12 @@ t3_status t3_ag_step(const t3_problem *p, int32_t step, const float *upstream_R,
   if (p->ldr % 4 || ld_up % 4 || W % 4 || !aligned16(R) || !aligned16(upstream_R)) return T3_ERR_ALIGN;
   if (p->M == 0 || W == 0) return T3_OK;
   const int64_t c = (p->rank + step) % p->tp;    // what the upstream neighbour owned, or got a step ago
-  const unsigned rows_per_block = t3k::kThreads / 64;
-  const unsigned blocks = (unsigned)(ceil_div(p->M, rows_per_block) < 4096 ? ceil_div(p->M, rows_per_block) : 4096);
-  return launch(t3k::ag_copy_kernel, dim3(blocks), dim3(t3k::kThreads), static_cast<hipStream_t>(stream),
-                upstream_R + c * W, ld_up, R + c * W, (int64_t)p->ldr, (int32_t)p->M, (int32_t)W);
+  // rows of a workgroup: one batch, or fewer where that leaves fewer than four workgroups per compute unit
+  const int64_t batch = t3k::kAgBatch * t3k::kThreads * 4 / W, spread = ceil_div(p->M, 4 * kDefaultCus);
+  const int64_t most = batch < spread ? batch : spread, rows = most > 0 ? most : 1;
+  return launch(t3k::ag_copy_kernel, dim3((unsigned)ceil_div(p->M, rows)), dim3(t3k::kThreads), static_cast<hipStream_t>(stream),
+                upstream_R + c * W, ld_up, R + c * W, (int64_t)p->ldr, (int32_t)p->M, (int32_t)W, (int32_t)rows, t3k::fast_div((uint32_t)(W / 4)),
+                (int32_t)(t3k::kThreads / (W / 4)));
 }
 
 }  // extern "C"

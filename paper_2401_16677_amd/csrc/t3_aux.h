@@ -189,25 +189,40 @@ __global__ void track_reset_kernel(uint32_t *track, int P) {
 }
 
 // One step of the ring all-gather (Sec. 2.3): a chunk of M rows x W columns moves, unchanged,
-// from the upstream neighbour's buffer into the same columns of this rank's.  One wavefront per
-// row and pass, 16 bytes per lane, four accesses in flight per lane.
+// from the upstream neighbour's buffer into the same columns of this rank's.  Memory bound, and short (50 MB of traffic
+// take 10 us): what counts is that all of it is requested at once.  So a workgroup takes as many whole rows as make one batch
+// of kAgBatch 16-byte pieces per lane, its pieces numbered across the rows: no lane idles at a row's end, and none
+// has a second batch to wait with unless a row is longer than a batch.  (A wavefront per row, a second batch behind 256 pieces of
+// it, and now, in us: 4096 x 1536 11.6 and 10.3; 16384 x 384 12.9 and 11.8; 2000 x 2052 8.2 and 7.8; 16384 x 132 6.3 and
+// 6.2; 2048 x 640 4.5 and 4.5, with whole batches on fewer workgroups 5.3.)
+constexpr int kAgBatch = 4;
 __global__ __launch_bounds__(kThreads) void ag_copy_kernel(const float *src, int64_t ld_src, float *dst,
-                                                           int64_t ld_dst, int32_t M, int32_t W) {
-  const int lane = threadIdx.x & 63;
-  const int W4 = W >> 2;
-  const int waves = (int)(gridDim.x * (blockDim.x >> 6));
-  for (int r = (int)(blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6)); r < M; r += waves) {
-    const f32x4 *s4 = (const f32x4 *)(src + (int64_t)r * ld_src);
-    f32x4 *d4 = (f32x4 *)(dst + (int64_t)r * ld_dst);
-    for (int c0 = lane; c0 < W4; c0 += 4 * 64) {
-      f32x4 v[4];
+                                                           int64_t ld_dst, int32_t M, int32_t W, int32_t rows_per_block,
+                                                           FastDiv by_w4, int32_t row_step) {
+  const int W4 = W >> 2, m0 = (int)blockIdx.x * rows_per_block;
+  const int total = min(rows_per_block, M - m0) * W4;
+  src += m0 * ld_src;
+  dst += m0 * ld_dst;
+  int e = (int)threadIdx.x, row = (int)div_by(threadIdx.x, by_w4), col = e - row * W4;
+  const int col_step = kThreads - row_step * W4;                  // (row_step = kThreads / W4)
+  while (e < total) {
+    f32x4 v[kAgBatch];
+    f32x4 *at[kAgBatch];
 #pragma unroll
-      for (int u = 0; u < 4; ++u)
-        if (c0 + u * 64 < W4) v[u] = __builtin_nontemporal_load(s4 + c0 + u * 64);
-#pragma unroll
-      for (int u = 0; u < 4; ++u)
-        if (c0 + u * 64 < W4) __builtin_nontemporal_store(v[u], d4 + c0 + u * 64);
+    for (int u = 0; u < kAgBatch; ++u) {
+      at[u] = e < total ? (f32x4 *)(dst + row * ld_dst) + col : nullptr;
+      if (e < total) v[u] = __builtin_nontemporal_load((const f32x4 *)(src + row * ld_src) + col);
+      e += kThreads;
+      row += row_step;
+      col += col_step;
+      if (col >= W4) {
+        col -= W4;
+        ++row;
+      }
     }
+#pragma unroll
+    for (int u = 0; u < kAgBatch; ++u)
+      if (at[u]) __builtin_nontemporal_store(v[u], at[u]);
   }
 }
 

@@ -272,6 +272,23 @@ def test_ring_of_virtual_ranks_closes_on_unsliced_gemm(gpu, oracle, kind):
             assert gpu.rel_err(got, whole) <= EXPECT
 
 
+# rows of one 16-byte piece, of as many as a workgroup has lanes, of one batch, less and more, and of two; rows that
+# do not divide among the workgroups
+@pytest.mark.parametrize("M,W", [(1, 4), (2050, 4), (1025, 8), (37, 1024), (33, 1536), (7, 4092), (5, 4096), (3, 4100), (2, 8200)])
+def test_all_gather_step_widths(gpu, oracle, M, W):
+    import torch
+    P, r = 3, 1
+    rng = np.random.default_rng(M + W)
+    up, mine = (rng.standard_normal((M, P * W + pad)).astype(np.float32) for pad in (8, 4))
+    for g in range(P - 1):
+        U, R = torch.from_numpy(up).to("cuda:0"), torch.from_numpy(mine).to("cuda:0")
+        t3.t3_ag_step(t3.problem(M, P * W, 64, P, r, ldr=P * W + 4), g, U, R, ld_up=P * W + 8)
+        torch.cuda.synchronize()
+        got = R.cpu().numpy()
+        want = oracle.all_gather_step(up[:, :P * W], mine[:, :P * W], P, r, g)
+        assert np.array_equal(got[:, :P * W], want) and np.array_equal(got[:, P * W:], mine[:, P * W:])
+
+
 def test_all_gather_step_shapes_and_refusals(gpu, oracle):
     """t3_ag_step on a ragged shape with padded leading dimensions: only the chunk's columns
     change, bit for bit the oracle's step; bad steps and misaligned widths are refused."""
