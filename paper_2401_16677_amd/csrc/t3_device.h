@@ -92,19 +92,6 @@ struct Tile {
   int s, c, mi, nj;
 };
 
-// Requests every 64-byte line of the kernel's argument (the Plan) at once.  The compiler loads its fields where
-// they are needed, one group after the other, and each first touch of a line is a round trip past the scalar cache that a
-// new launch starts without: for a launch that is over in some microseconds.  (Small-tile kernel, 256 x 1024 x 256 on 4
-// chunks: 5.45 us without, 5.22 with; 24 x 12288 x 1536 on 8 10.90 and 10.83.  Not in the reduction, where it measured
-// slower, nor in the wide-tile kernel, which keeps more of them in registers than it has and waits for each on its way out.)
-__device__ inline void fetch_plan() {
-  typedef const __attribute__((address_space(4))) uint32_t *scalar_ptr;
-  const scalar_ptr a = (scalar_ptr)__builtin_amdgcn_kernarg_segment_ptr();
-  static_assert(sizeof(Plan) > 4 * 64 && sizeof(Plan) <= 5 * 64, "the lines below");
-  asm volatile("" : : "s"(a[0]), "s"(a[16]), "s"(a[32]), "s"(a[48]), "s"(a[64]), "s"(a[sizeof(Plan) / 4 - 1]));
-  __builtin_amdgcn_sched_barrier(0);             // (ahead of all of them)
-}
-
 // Tracker state (uint32 words): two banks of { counter[P] ready[P] queue[P] queue_len done },
 // then the globals { gen, error }.  A launch works in bank gen & 1; the last workgroup of the
 // launch to finish clears the other bank and increments gen, so the next launch starts from a

@@ -29,7 +29,6 @@ __global__ __launch_bounds__(64 * WK) void small_tile_kernel(const Plan p) {
   static_assert(NIN * 64 == kRowsPerWave * kChunks && (NST - 1) * NL < 64 && kLds <= 160 * 1024, "");
   __shared__ __attribute__((aligned(1024))) char lds[kLds];
 
-  fetch_plan();
   Tile tl;
   if (!decode_block(p, (int)blockIdx.x, tl)) return;
   // (the generation is needed only when the tile is counted: nothing waits for it here)
