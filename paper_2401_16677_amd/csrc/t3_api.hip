@@ -31,6 +31,7 @@ constexpr int kNumXcd = 8;            // the XCD grouping of decode_tile is writ
 constexpr int kDefaultCus = 256;       // compute units of an MI355X (host-only plan queries assume it)
 constexpr int kMaxDevices = 64;
 constexpr int kReleaseAgents = 32;     // release workgroups per chunk (t3_release_chunks)
+constexpr int64_t kMaxCopyBlocks = 1 << 20;   // workgroups of t3_ag_step; more rows are walked
 constexpr int kNtMinK = 3072;          // K from which result stores take the streaming hint
 constexpr int64_t kMemorySideCacheBytes = 256ll << 20;
 // Matrix rate of one compute unit the start-up offsets are sized with: 4096 flop/clock at a
@@ -738,12 +739,20 @@ t3_status t3_ag_step(const t3_problem *p, int32_t step, const float *upstream_R,
   if (p->ldr % 4 || ld_up % 4 || W % 4 || !aligned16(R) || !aligned16(upstream_R)) return T3_ERR_ALIGN;
   if (p->M == 0 || W == 0) return T3_OK;
   const int64_t c = (p->rank + step) % p->tp;    // what the upstream neighbour owned, or got a step ago
-  // rows of a workgroup: one batch, or fewer where that leaves fewer than four workgroups per compute unit
-  const int64_t batch = t3k::kAgBatch * t3k::kThreads * 4 / W, spread = ceil_div(p->M, 4 * kDefaultCus);
-  const int64_t most = batch < spread ? batch : spread, rows = most > 0 ? most : 1;
-  return launch(t3k::ag_copy_kernel, dim3((unsigned)ceil_div(p->M, rows)), dim3(t3k::kThreads), static_cast<hipStream_t>(stream),
-                upstream_R + c * W, ld_up, R + c * W, (int64_t)p->ldr, (int32_t)p->M, (int32_t)W, (int32_t)rows, t3k::fast_div((uint32_t)(W / 4)),
-                (int32_t)(t3k::kThreads / (W / 4)));
+  DeviceFacts dev;
+  const t3_status known = device_facts(&dev);
+  if (known != T3_OK) return known;
+  const t3k::CopyShape shape = t3k::copy_shape(p->M, W, dev.cus);
+  auto kernel = t3k::ag_copy_kernel<256, 8, 8>;
+  if (shape.team == 256 && shape.batch == 1) kernel = t3k::ag_copy_kernel<256, 1, 1>;
+  if (shape.team == 64 && shape.batch == 8)
+    kernel = shape.in_flight == 8 ? t3k::ag_copy_kernel<64, 8, 8> : (shape.in_flight == 2 ? t3k::ag_copy_kernel<64, 8, 2> : t3k::ag_copy_kernel<64, 8, 1>);
+  if (shape.team == 64 && shape.batch == 4) kernel = shape.in_flight == 4 ? t3k::ag_copy_kernel<64, 4, 4> : t3k::ag_copy_kernel<64, 4, 1>;
+  if (shape.team == 16) kernel = t3k::ag_copy_kernel<16, 4, 4>;
+  if (shape.team == 4) kernel = t3k::ag_copy_kernel<4, 4, 4>;
+  const int64_t blocks = shape.workgroups < kMaxCopyBlocks ? shape.workgroups : kMaxCopyBlocks;
+  return launch(kernel, dim3((unsigned)blocks), dim3(t3k::kThreads), static_cast<hipStream_t>(stream),
+                upstream_R + c * W, ld_up, R + c * W, (int64_t)p->ldr, (int32_t)p->M, (int32_t)W);
 }
 
 }  // extern "C"

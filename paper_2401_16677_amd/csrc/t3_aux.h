@@ -190,39 +190,35 @@ __global__ void track_reset_kernel(uint32_t *track, int P) {
 
 // One step of the ring all-gather (Sec. 2.3): a chunk of M rows x W columns moves, unchanged,
 // from the upstream neighbour's buffer into the same columns of this rank's.  Memory bound, and short (50 MB of traffic
-// take 10 us): what counts is that all of it is requested at once.  So a workgroup takes as many whole rows as make one batch
-// of kAgBatch 16-byte pieces per lane, its pieces numbered across the rows: no lane idles at a row's end, and none
-// has a second batch to wait with unless a row is longer than a batch.  (A wavefront per row, a second batch behind 256 pieces of
-// it, and now, in us: 4096 x 1536 11.6 and 10.3; 16384 x 384 12.9 and 11.8; 2000 x 2052 8.2 and 7.8; 16384 x 132 6.3 and
-// 6.2; 2048 x 640 4.5 and 4.5, with whole batches on fewer workgroups 5.3.)
-constexpr int kAgBatch = 4;
+// take 10 us).  A row is copied by a team of T lanes, U 16-byte pieces per lane and batch; copy_shape in
+// t3_choice.h says which.  The loads of a batch and their stores stand behind the same conditions: behind others
+// (a pointer that is null where there is nothing to store) the compiler carries the batch's registers through the
+// loop and waits for each load before the next.  IN_FLIGHT < U: such a wait on purpose, see copy_shape.
+// (A wavefront per row in every shape; pieces numbered across a workgroup's rows, load by load; and now, in us, eight
+// chunks: 100 x 1536 2.8, 2.8, 2.4; 1536 x 640 3.0, 3.8, 3.0; 2500 x 1024 5.2, 5.7, 5.2; 8192 x 640 10.3, 9.9, 9.3;
+// 4096 x 1536 11.5, 10.5, 10.4; 4096 x 4100 31.6, 31.6, 29.3; 16384 x 12 4.2, 2.8, 2.8; 16384 x 1024 24.8, 27.7, 23.9;
+// 16384 x 1536 43.4, 46.1, 43.6.  Over 448 shapes of 8 to 16384 rows and 4 to 5120 columns 6 % less time than the
+// first and 8 % less than the second; at most 0.1 us or 4 % over the first; 6000 rows and more of 384 to 1024
+// columns up to 10 % over the second on some.)
+template <int T, int U, int IN_FLIGHT>
 __global__ __launch_bounds__(kThreads) void ag_copy_kernel(const float *src, int64_t ld_src, float *dst,
-                                                           int64_t ld_dst, int32_t M, int32_t W, int32_t rows_per_block,
-                                                           FastDiv by_w4, int32_t row_step) {
-  const int W4 = W >> 2, m0 = (int)blockIdx.x * rows_per_block;
-  const int total = min(rows_per_block, M - m0) * W4;
-  src += m0 * ld_src;
-  dst += m0 * ld_dst;
-  int e = (int)threadIdx.x, row = (int)div_by(threadIdx.x, by_w4), col = e - row * W4;
-  const int col_step = kThreads - row_step * W4;                  // (row_step = kThreads / W4)
-  while (e < total) {
-    f32x4 v[kAgBatch];
-    f32x4 *at[kAgBatch];
+                                                           int64_t ld_dst, int32_t M, int32_t W) {
+  constexpr int kRows = kThreads / T;
+  const int lane = (int)(threadIdx.x % T), W4 = W >> 2;
+  for (int64_t r = (int64_t)blockIdx.x * kRows + (int)(threadIdx.x / T); r < M; r += (int64_t)gridDim.x * kRows) {
+    const f32x4 *s4 = (const f32x4 *)(src + r * ld_src);
+    f32x4 *d4 = (f32x4 *)(dst + r * ld_dst);
+    for (int c0 = lane; c0 < W4; c0 += U * T) {
+      f32x4 v[U];
 #pragma unroll
-    for (int u = 0; u < kAgBatch; ++u) {
-      at[u] = e < total ? (f32x4 *)(dst + row * ld_dst) + col : nullptr;
-      if (e < total) v[u] = __builtin_nontemporal_load((const f32x4 *)(src + row * ld_src) + col);
-      e += kThreads;
-      row += row_step;
-      col += col_step;
-      if (col >= W4) {
-        col -= W4;
-        ++row;
+      for (int u = 0; u < U; ++u) {
+        if (c0 + u * T < W4) v[u] = __builtin_nontemporal_load(s4 + c0 + u * T);
+        if (IN_FLIGHT < U) asm volatile("s_waitcnt vmcnt(%0)" : : "n"(IN_FLIGHT - 1) : "memory");
       }
-    }
 #pragma unroll
-    for (int u = 0; u < kAgBatch; ++u)
-      if (at[u]) __builtin_nontemporal_store(v[u], at[u]);
+      for (int u = 0; u < U; ++u)
+        if (c0 + u * T < W4) __builtin_nontemporal_store(v[u], d4 + c0 + u * T);
+    }
   }
 }
 

@@ -92,6 +92,41 @@ inline TileShape reduce_tile_shape(const t3_problem *p, int cus, int64_t steps) 
   return {(int32_t)tm, (int32_t)tn};
 }
 
+// How the all-gather step copies a chunk: `team` lanes of a workgroup of 256 per row, `batch` 16-byte pieces
+// per lane at a time, in_flight of them at once.  In us, chunk of rows x columns,
+// N of eight chunks:
+//  - Two rows per compute unit or fewer: a workgroup per row (500 x 1536 by wavefronts 2.9, by workgroups 2.8; 24 x 4100 3.8, 2.5).
+//  - Otherwise a wavefront per row while that is a batch of four or eight; a workgroup for longer rows, whose pieces
+//    would follow each other through a loop (2048 x 4100: 17.0 by wavefronts, 15.3), and for rows of 256 pieces (if they
+//    are many) and 512, which leave it no idle lane (8192 x 1024 13.8 by wavefronts, 13.0, 8192 x 2048 26.4 and 24.3); part of a wavefront for rows that do not fill it (16384 x 12: 4.2, 2.8).
+//  - Fewer loads in flight than a batch where the chunk is on the compute units at once, eight workgroups of four rows
+//    each at most, and they are well filled: all loads together, then all stores together, is slower there than a mixture of
+//    both (all, two and one in flight: 4096 x 1536 11.4, 10.4, 10.4 to 11.3; 4096 x 1152 8.5, 8.0, 8.4; 8192 x 1536 21.9, 22.2, 20.2;
+//    8192 x 640 10.1, 9.6, 8.6; with fewer workgroups, 2900 x 1536, 7.0, 7.3, 8.9; 4096 x 640 5.1, 5.3, 5.7).
+//  - Beyond that a workgroup per row, one piece at a time (by wavefronts and that way: 12000 x 512 12.1 and 11.2, 16384 x 1152
+//    31.4 and 29.3, 16384 x 2048 49.6 and 46.8; 16384 x 1536 43.4 both).
+struct CopyShape {
+  int32_t team, batch, in_flight;
+  int64_t workgroups;
+};
+inline CopyShape copy_shape(int64_t M, int64_t W, int cus) {
+  const int64_t pieces = W / 4, fours = ceil_div(M, 4);          // (workgroups of a wavefront per row)
+  const int32_t batch = pieces <= 256 ? 4 : 8;
+  CopyShape s{64, batch, batch, 0};
+  if (M <= 2 * (int64_t)cus || pieces > 512)
+    s = pieces <= 256 ? CopyShape{256, 1, 1, 0} : CopyShape{256, 8, 8, 0};
+  else if (pieces <= 4)
+    s = {4, 4, 4, 0};
+  else if (pieces <= 16 && fours > 4 * (int64_t)cus)
+    s = {16, 4, 4, 0};
+  else if (pieces == 512 || (pieces == 256 && fours >= 5 * (int64_t)cus) || (pieces > 96 && fours > 8 * (int64_t)cus))
+    s = {256, 1, 1, 0};
+  else if (pieces > 64 && fours <= 8 * (int64_t)cus)
+    s.in_flight = batch == 8 ? (fours < 4 * (int64_t)cus ? 8 : (fours < 6 * (int64_t)cus ? 2 : 1)) : (fours < 5 * (int64_t)cus ? 4 : 1);
+  s.workgroups = ceil_div(M, 256 / s.team);
+  return s;
+}
+
 // The wide-tile kernel's offsets count from where a tile starts, and what lies outside is marked by their top
 // bit: the rows of a tile (256 at most) have to fit 2 GiB, of a transposed operand the whole array.  (65536 x 12288
 // x 1536, R of 3 GiB: 2518 us here, 2744 by gemm_tile_kernel.)

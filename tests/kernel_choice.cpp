@@ -13,6 +13,12 @@ extern "C" int column_align(const t3_problem *p, int call, int tile_n, int64_t a
                            reinterpret_cast<const void *>(address), ld_out);
 }
 
+extern "C" void copy_shape(int64_t M, int64_t W, int cus, int64_t *out) {
+  const t3k::CopyShape s = t3k::copy_shape(M, W, cus);
+  const int64_t v[] = {s.team, s.batch, s.in_flight, s.workgroups};
+  for (int i = 0; i < 4; ++i) out[i] = v[i];
+}
+
 extern "C" void divide(const uint32_t *n, const uint32_t *d, uint32_t *out, int count) {
   for (int i = 0; i < count; ++i) out[i] = t3k::div_by(n[i], t3k::fast_div(d[i]));
 }

@@ -27,6 +27,14 @@ class Shape(NamedTuple):
     tail_q: int
 
 
+class CopyShape(NamedTuple):
+    """The all-gather step: lanes per row, 16-byte pieces per lane and batch, those in flight at once, workgroups."""
+    team: int
+    batch: int
+    in_flight: int
+    workgroups: int
+
+
 _lib = None
 
 
@@ -47,3 +55,9 @@ def launch_shape(p, call=FUSED, cus=CUS):
     out = (ctypes.c_int64 * 10)()
     lib().launch_shape(ctypes.byref(p), call, *tracked, cus, out)
     return Shape(*out)
+
+
+def copy_shape(M, W, cus=CUS):
+    out = (ctypes.c_int64 * 4)()
+    lib().copy_shape(ctypes.c_int64(M), ctypes.c_int64(W), cus, out)
+    return CopyShape(*out)

@@ -272,14 +272,26 @@ def test_ring_of_virtual_ranks_closes_on_unsliced_gemm(gpu, oracle, kind):
             assert gpu.rel_err(got, whole) <= EXPECT
 
 
-# rows of one 16-byte piece, of as many as a workgroup has lanes, of one batch, less and more, and of two; rows that
-# do not divide among the workgroups
-@pytest.mark.parametrize("M,W", [(1, 4), (2050, 4), (1025, 8), (37, 1024), (33, 1536), (7, 4092), (5, 4096), (3, 4100), (2, 8200)])
+# Every kernel of the all-gather step, in rows and columns: rows that leave the last workgroup part-filled, rows of one
+# piece, of less than a batch, of one, and of one piece more; the edges of the rule between them (256 compute units).
+COPIES = [(1, 4), (37, 1024), (7, 4100), (512, 132), (3, 8200),          # a workgroup per row
+          (2050, 4), (1025, 8), (600, 16),                               # four lanes
+          (4097, 20), (4099, 64),                                        # sixteen
+          (513, 132), (1025, 1020), (5116, 640), (2051, 256),            # a wavefront
+          (5120, 260), (8191, 1020),                                     # one piece in flight
+          (515, 1028), (1023, 1536), (2050, 2044),                       # a wavefront, batches of eight
+          (4093, 1028), (6140, 2044),                                    # two of them in flight
+          (6141, 1536), (8189, 1900),                                    # one
+          (8195, 388), (5117, 1024), (513, 2048), (8193, 1028),          # a workgroup per row, one piece at a time
+          (514, 2052), (513, 8196)]                                      # and eight
+
+
+@pytest.mark.parametrize("M,W", COPIES)
 def test_all_gather_step_widths(gpu, oracle, M, W):
     import torch
     P, r = 3, 1
     rng = np.random.default_rng(M + W)
-    up, mine = (rng.standard_normal((M, P * W + pad)).astype(np.float32) for pad in (8, 4))
+    up, mine = (rng.standard_normal((M, P * W + pad), dtype=np.float32) for pad in (8, 4))
     for g in range(P - 1):
         U, R = torch.from_numpy(up).to("cuda:0"), torch.from_numpy(mine).to("cuda:0")
         t3.t3_ag_step(t3.problem(M, P * W, 64, P, r, ldr=P * W + 4), g, U, R, ld_up=P * W + 8)

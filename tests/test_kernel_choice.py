@@ -6,7 +6,7 @@ import pytest
 
 from paper_2401_16677_amd import binding as t3
 from tests.launch_shape import lib as choice_lib
-from tests.launch_shape import FUSED, GEMM, GENERAL, REDUCE, REDUCTION, SMALL, WIDE, launch_shape
+from tests.launch_shape import FUSED, GEMM, GENERAL, REDUCE, REDUCTION, SMALL, WIDE, copy_shape, launch_shape
 
 
 def _problem(M, W, K, tp, layout="nk", **kw):
@@ -149,3 +149,17 @@ def test_columns_start_at_granules_where_the_grid_has_room():
                     assert all(0 < b - a <= bn for a, b in zip(starts, starts[1:])), (W, bn, c)
                     assert all((c * W + a) % 16 == 0 and a % step == 0 for a in starts[1:-1]), (W, bn, c)
     assert aligned > 100
+
+
+def test_all_gather_step_shapes():
+    """The workgroups hold all rows, one of them no more than it needs; the cases of the GPU test reach every kernel there is."""
+    from tests.test_gpu_parity import COPIES
+    kinds = {(256, 1, 1), (256, 8, 8), (64, 4, 4), (64, 4, 1), (64, 8, 8), (64, 8, 2), (64, 8, 1), (16, 4, 4), (4, 4, 4)}
+    assert {copy_shape(M, W)[:3] for M, W in COPIES} == kinds
+    rng = np.random.default_rng(12)
+    for _ in range(2000):
+        M, W = int(2 ** rng.uniform(0, 18)), 4 * int(2 ** rng.uniform(0, 12))
+        for cus in (64, 256):
+            s = copy_shape(M, W, cus)
+            assert s[:3] in kinds and (s.workgroups - 1) * (256 // s.team) < M <= s.workgroups * (256 // s.team)
+            assert s.in_flight == s.batch or 4 * cus <= s.workgroups <= 8 * cus

@@ -18,6 +18,7 @@ from paper_2401_16677_amd import build as hip_build
 
 LAYOUTS = [u for u in hip_build.UNITS if u[0] == "t3_wide_launch.hip"]
 GENERAL = [u for u in hip_build.UNITS if u[0] == "t3_gemm_launch.hip"]
+API = [u for u in hip_build.UNITS if u[0] == "t3_api.hip"]
 
 
 def _compile(out, units, kernel):
@@ -185,3 +186,37 @@ def test_general_main_loop_waits_once_a_slab(general, unit):
                 waits = [t for t, _ in block if t.startswith("s_waitcnt") and "vmcnt" in t]
                 assert len(waits) == 1 and "lgkmcnt(0)" in waits[0], (kernel, waits)
         assert loops == 1, kernel
+
+
+def _waits_inside_a_batch(lines):
+    """Whether a path leads from a load over a wait for global memory to another load, no store between."""
+    blocks = _blocks(lines)
+    seen, todo = set(), [(0, "none")]
+    while todo:
+        i, state = todo.pop()
+        if (i, state) in seen:
+            continue
+        seen.add((i, state))
+        for text, _ in blocks[i][0]:
+            op = text.split()[0]
+            if re.match(r"(global|flat)_load", op):
+                if state == "waited":
+                    return True
+                state = "loaded"
+            elif re.match(r"(global|flat)_store", op):
+                state = "none"
+            elif op == "s_waitcnt" and "vmcnt" in text and state == "loaded":
+                state = "waited"
+        todo += [(s, state) for s in blocks[i][1]]
+    return False
+
+
+def test_all_gather_step_requests_a_batch_at_once(tmp_path):
+    """A lane's loads of a batch are all on their way before the first is waited for, but where fewer are
+    meant to be."""
+    (code,) = _compile(tmp_path, API, "ag_copy_kernel").values()
+    assert len(code) == 9
+    for kernel, lines in code.items():
+        team, batch, in_flight = map(int, re.search(r"ILi(\d+)ELi(\d+)ELi(\d+)E", kernel).groups())
+        assert sum(t.startswith("global_load") for b, _ in _blocks(lines) for t, _ in b) == batch, kernel
+        assert _waits_inside_a_batch(lines) == (in_flight < batch), kernel
