@@ -138,9 +138,10 @@ typedef struct {
  * persistent workgroups, as many as the device holds at once; smaller ones have a workgroup
  * each.  The first wave of persistent workgroups starts in a few phase groups a few microseconds
  * apart, so that the compute units do not all reach their reduction traffic at the same
- * moment; the environment variable T3_STAGGER="groups,window_ns" (read once, at the first
- * launch of the process) overrides the default (4 groups over 12 us; 8 over 16 us in long
- * launches and none for K of 4096 and more, on tiles of 256 x 192 and up), T3_STAGGER=0 turns it
+ * moment; how many groups over how long goes by sizes (from two rounds of tiles on: 4 groups over half an
+ * estimated tile time, at most 12 us; on tiles of 256 x 192 and up over 4 to 12 us, 8 groups over 16 us in long launches of
+ * K >= 768, none for K >= 4096; the plain GEMM's windows widen only in launches of four rounds and more).  The
+ * environment variable T3_STAGGER="groups,window_ns" (read once, at the first launch of the process) overrides this, T3_STAGGER=0 turns it
  * off.  Results do not depend on it.  The XCD grouping is applied on devices with 8 XCDs.
  * Balanced tail: when the workgroup tiles of a launch over whole ring steps do not fill a whole
  * number of rounds of the persistent workgroups and the last round would occupy at most half of

@@ -34,10 +34,6 @@ constexpr int kReleaseAgents = 32;     // release workgroups per chunk (t3_relea
 constexpr int64_t kMaxCopyBlocks = 1 << 20;   // workgroups of t3_ag_step; more rows are walked
 constexpr int kNtMinK = 3072;          // K from which result stores take the streaming hint
 constexpr int64_t kMemorySideCacheBytes = 256ll << 20;
-// Matrix rate of one compute unit the start-up offsets are sized with: 4096 flop/clock at a
-// sustained ~1.5 GHz under load, in flop per nanosecond.
-constexpr double kCuFlopPerNs = 6.25e3;
-
 // What the launch plan needs to know of the device it launches on, read from the runtime once
 // per device (hardware attributes only; they never change while the process lives).
 struct DeviceFacts {
@@ -417,38 +413,15 @@ t3_status make_plan(const t3_problem *p, t3k::Call call, int need, const void *A
   const int64_t resident = shape.resident;
   q.stage0 = (int32_t)shape.stage0;
   q.total_blocks = (int32_t)shape.total_blocks;
-  // Start-up phase offsets (see stagger_start), from two rounds of tiles on (one round only ends later).
-  // The wide-tile kernel's tiles of 256 x 192 and up: four groups over 12 us; from six rounds on, and K of 12 slabs, eight
-  // over 16 us, whose later start is a smaller part of the launch; none where K has 64 slabs or more, whose way
-  // out is too small a part of a tile.  (No offsets, four groups over 12 us, eight over 16, in us: 4096 x 12288 x 384
-  // 101.4, 93.8, 96.6, x 1536 167.6, 160.3, 161.1, x 3840 304.0, 304.4, 305.3, x 6144 440.4, 447.5, 447.0; 4096 x 49152
-  // on 32 chunks, K of 384 343.8, 327.7, 330.1, of 768 416, 406, 397, of 1536 613, 611, 598; 8192 x 18432 x 1152
-  // on 16 398, 398, 391.  Half an estimated tile time as the limit: 97.2 on the first of them.)
-  // The others: four groups over 12 us, or half an estimated tile time if that is shorter.
-  // The environment variable T3_STAGGER="groups,window_ns" overrides this ("0" turns it off).
+  // Start-up phase offsets (see stagger_start); T3_STAGGER="groups,window_ns" overrides them ("0" turns them off).
   q.stagger_blocks = q.stagger_groups = q.stagger_ticks = 0;
   {
-    int g = 4;
-    double window_ns = 12000.0;
-    const double tile_ns = 2.0 * *tm * *tn * (double)p->K / kCuFlopPerNs;
-    if (shape.kernel == t3k::kWideTile && *tm == 256 && *tn >= 192) {
-      if (p->K >= 64 * 64) g = 0;
-      if (q.total_blocks >= 6 * resident && p->K >= 12 * 64) {
-        g = g ? 8 : 0;
-        window_ns = 16000.0;
-      }
-    } else if (window_ns > tile_ns / 2) {
-      window_ns = tile_ns / 2;
-    }
-    if (q.total_blocks < 2 * resident || *tm < 128) g = 0;
+    t3k::StartOffsets o = t3k::start_offsets(p, call, shape);
     const StaggerEnv &env = stagger_env();
-    if (env.set) {
-      g = env.off ? 0 : env.groups;
-      if (!env.off) window_ns = env.window_ns;
-    }
-    if (g > 1 && window_ns >= 100.0) {
-      q.stagger_groups = g;
-      q.stagger_ticks = (int32_t)(window_ns / 10.0 / g);   // 100 MHz ticks between consecutive groups
+    if (env.set) o = env.off ? t3k::StartOffsets{0, 0.0} : t3k::StartOffsets{env.groups, (double)env.window_ns};
+    if (o.groups > 1 && o.window_ns >= 100.0) {
+      q.stagger_groups = o.groups;
+      q.stagger_ticks = (int32_t)(o.window_ns / 10.0 / o.groups);   // 100 MHz ticks between consecutive groups
       q.stagger_blocks = (int32_t)resident;
     }
   }

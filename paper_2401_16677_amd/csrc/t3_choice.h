@@ -211,4 +211,44 @@ inline LaunchShape launch_shape(const t3_problem *p, Call call, TileShape tracke
   return s;
 }
 
+// Start-up offsets: the first wave of persistent workgroups starts in `groups` phase groups over window_ns (see
+// stagger_start; 0: all at once), from two rounds of tiles on.  The last group ends 3/4 of the window late; what is won is a
+// part of every round's way out.  So the window is half an estimated tile time, at most 12 us, and on the large tiles, their
+// columns and rows whole, what was measured to be better.  In us with half a tile time, 4 groups over 4 us, over 12 us,
+// 8 over 16 us (rounds in brackets):
+//   fused, 256 x 256   4096 x 12288 x 256     98.2  96.1  93.5  94.1  (3)    16384 x 8192 x 512, copy     331 336 314 301  (8)
+//                      8192 x 4096 x 192, copy 82.3 82.4  86.5  80.6  (2)    8192 x 4096 x 448           74.3  -  70.5  -  (2)
+//   fused, 256 x 192   4096 x 9216 x 256      74.6  72.2  74.0  75.2  (3)    8192 x 18432 x 1152         403 399 400 390  (12)
+//                      14748 x 2304 x 1152   114.1 110.8 116.9 115.0  (2.7; over 6 us 110.7)
+//                      4460 x 18432 x 1024   234.6 226.4 235.3 241.4  (6.8: not whole rounds)
+//   rows off 64-byte granules, copy   12288 x 3072 x 640, ldr 3076    149 147 160 149  (3; ldr 3072   115 114 111 108)
+//                                     4096 x 24576 x 512, ldr 24580   313  -  300  -   (6)
+//   plain GEMM         8192 x 4576 x 200      50.5  49.9  64.8  63.5  (3)    16384 x 9216 x 384          167 167 153 161  (12)
+//                      7144 x 6144 x 512      69.2  69.2  73.0  79.4  (3.5)  16384 x 6144 x 256           94  92  85  91  (6)
+//                      4096 x 20480 x 192     73.7   -    75.7   -    (5)    16384 x 8192 x 192          121   -  108   -  (8)
+// K of 4096 and more: none, four groups and eight differ by less than 1 % on eleven shapes of whole rounds; 9819 x 4608 x 4096
+// (3.7), copy: none 356, over 12 us 372.
+struct StartOffsets {
+  int32_t groups;
+  double window_ns;
+};
+// Matrix rate of one compute unit: 4096 flop/clock at a sustained ~1.5 GHz under load, in flop per nanosecond.
+constexpr double kCuFlopPerNs = 6.25e3;
+inline StartOffsets start_offsets(const t3_problem *p, Call call, const LaunchShape &s) {
+  if (s.tile.m < 128 || s.total_blocks < 2 * s.resident) return {0, 0.0};
+  const int64_t rounds = s.total_blocks / s.resident, slabs = p->K / 64, W = p->N / p->tp;
+  const double half_tile = (double)s.tile.m * s.tile.n * (double)p->K / kCuFlopPerNs;
+  const StartOffsets plain{4, half_tile < 12000.0 ? half_tile : 12000.0}, wide{4, 12000.0};
+  const bool fused = call != kCallGemm, direct = p->flags & T3_FLAG_FWD_DIRECT;
+  // (columns past the chunk's end, an eighth of a tile or more, have no way out)
+  if (s.kernel != kWideTile || s.tile.m < 256 || s.tile.n < 192 || 8 * W < 7 * s.Wt * s.tile.n) return plain;
+  if (slabs >= 64) return {0, 0.0};
+  if ((fused ? p->ldr : p->ldc) % 16 && rounds < (fused && direct ? 3 : 6)) return plain;
+  if (rounds >= 6 && slabs >= 12 && (s.total_blocks % s.resident == 0 || s.tail_r)) return {8, 16000.0};
+  if (!fused) return rounds >= (slabs >= 8 ? 4 : (slabs >= 4 ? 5 : 8)) ? wide : plain;
+  if (s.tile.n == 256) return slabs >= 8 || rounds >= 3 || direct ? wide : StartOffsets{4, 4000.0};
+  if (slabs >= 8) return rounds >= 3 ? wide : StartOffsets{4, 6000.0};
+  return rounds >= 6 && slabs >= 4 ? wide : StartOffsets{4, 4000.0};
+}
+
 }  // namespace t3k

@@ -8,6 +8,13 @@ extern "C" void launch_shape(const t3_problem *p, int call, int tracked_m, int t
   for (int i = 0; i < 10; ++i) out[i] = v[i];
 }
 
+extern "C" void start_offsets(const t3_problem *p, int call, int tracked_m, int tracked_n, int cus, double *out) {
+  const t3k::Call c = static_cast<t3k::Call>(call);
+  const t3k::StartOffsets o = t3k::start_offsets(p, c, t3k::launch_shape(p, c, {tracked_m, tracked_n}, cus));
+  out[0] = o.groups;
+  out[1] = o.window_ns;
+}
+
 extern "C" int column_align(const t3_problem *p, int call, int tile_n, int64_t address, int64_t ld_out) {
   return t3k::column_align(p, static_cast<t3k::Call>(call), {256, tile_n}, t3k::ceil_div(p->N / p->tp, tile_n),
                            reinterpret_cast<const void *>(address), ld_out);

@@ -61,3 +61,11 @@ def copy_shape(M, W, cus=CUS):
     out = (ctypes.c_int64 * 4)()
     lib().copy_shape(ctypes.c_int64(M), ctypes.c_int64(W), cus, out)
     return CopyShape(*out)
+
+
+def start_offsets(p, call=FUSED, cus=CUS):
+    """Phase groups and the window they start over, in ns."""
+    tracked = (p.tile_m, p.tile_n) if p.tile_m else t3.t3_default_tile(p)
+    out = (ctypes.c_double * 2)()
+    lib().start_offsets(ctypes.byref(p), call, *tracked, cus, out)
+    return tuple(out)

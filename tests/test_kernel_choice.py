@@ -6,7 +6,7 @@ import pytest
 
 from paper_2401_16677_amd import binding as t3
 from tests.launch_shape import lib as choice_lib
-from tests.launch_shape import FUSED, GEMM, GENERAL, REDUCE, REDUCTION, SMALL, WIDE, copy_shape, launch_shape
+from tests.launch_shape import FUSED, GEMM, GENERAL, REDUCE, REDUCTION, SMALL, WIDE, copy_shape, launch_shape, start_offsets
 
 
 def _problem(M, W, K, tp, layout="nk", **kw):
@@ -163,3 +163,48 @@ def test_all_gather_step_shapes():
             s = copy_shape(M, W, cus)
             assert s[:3] in kinds and (s.workgroups - 1) * (256 // s.team) < M <= s.workgroups * (256 // s.team)
             assert s.in_flight == s.batch or 4 * cus <= s.workgroups <= 8 * cus
+
+
+DIRECT = t3.T3_FLAG_FWD_DIRECT
+
+
+@pytest.mark.parametrize("M,W,K,tp,call,flags,tile,want", [
+    # 256 x 256 tiles: direct from two rounds on, by copy from three, or eight slabs
+    (8192, 1024, 192, 4, FUSED, DIRECT, (256, 256), (4, 12000)),
+    (8192, 1024, 192, 4, FUSED, 0, (256, 256), (4, 4000)),
+    (8192, 1024, 512, 4, FUSED, 0, (256, 256), (4, 12000)),
+    (4096, 1536, 192, 8, FUSED, 0, (256, 256), (4, 12000)),
+    (16384, 1024, 704, 8, FUSED, 0, (256, 256), (4, 12000)),            # eight rounds, 11 slabs
+    (16384, 1024, 768, 8, FUSED, 0, (256, 256), (8, 16000)),            # 12
+    (4096, 1536, 768, 8, FUSED, DIRECT, (256, 256), (4, 12000)),        # three rounds
+    (4096, 1536, 4032, 8, FUSED, DIRECT, (256, 256), (4, 12000)),
+    (4096, 1536, 4096, 8, FUSED, DIRECT, (256, 256), (0, 0)),
+    # 256 x 192
+    (8192, 576, 448, 8, FUSED, DIRECT, (256, 192), (4, 4000)),
+    (8192, 576, 512, 8, FUSED, DIRECT, (256, 192), (4, 12000)),
+    (14748, 576, 1152, 4, FUSED, DIRECT, (256, 192), (4, 6000)),        # less than three rounds
+    (16384, 576, 384, 8, FUSED, DIRECT, (256, 192), (4, 12000)),        # six
+    (8192, 1152, 1152, 16, FUSED, DIRECT, (256, 192), (8, 16000)),
+    (4460, 1152, 1024, 16, FUSED, DIRECT, (256, 192), (4, 12000)),      # 6.75
+    # the plain GEMM: half a tile time unless there are rounds enough
+    (8192, 572, 200, 8, GEMM, 0, (256, 192), (4, 256 * 192 * 200 / 6250)),
+    (4096, 1536, 192, 8, GEMM, 0, (256, 256), (4, 256 * 256 * 192 / 6250)),
+    (16384, 512, 512, 8, GEMM, 0, (256, 256), (4, 12000)),              # four
+    (16384, 512, 448, 8, GEMM, 0, (256, 256), (4, 256 * 256 * 448 / 6250)),
+    (16384, 1536, 256, 4, GEMM, 0, (256, 256), (4, 12000)),             # six
+    (16384, 1536, 192, 4, GEMM, 0, (256, 256), (4, 256 * 256 * 192 / 6250)),
+    (4096, 1536, 1536, 8, GEMM, 0, (256, 256), (4, 12000)),
+    # an eighth of the columns past the chunk's end; one round; smaller tiles
+    (8192, 388, 200, 8, FUSED, 0, (256, 256), (4, 256 * 256 * 200 / 6250)),
+    (4096, 512, 1536, 8, FUSED, 0, (256, 256), (0, 0)),
+    (8728, 144, 256, 8, FUSED, 0, (128, 192), (4, 128 * 192 * 256 / 6250)),
+])
+def test_start_up_offsets(M, W, K, tp, call, flags, tile, want):
+    p = _problem(M, W, K, tp, flags=flags)
+    assert launch_shape(p, call)[1:3] == tile
+    assert start_offsets(p, call) == pytest.approx(want)
+    off_granules = _problem(M, W, K, tp, flags=flags, ldr=W * tp + 4, ldc=W * tp + 4)
+    few = launch_shape(p, call).blocks // 256 < (3 if call == FUSED and flags & DIRECT else 6)
+    if few and want[0]:                          # (rows off 64-byte granules)
+        want = (4, min(12000, tile[0] * tile[1] * K / 6250))
+    assert start_offsets(off_granules, call) == pytest.approx(want)
