@@ -116,7 +116,7 @@ __global__ __launch_bounds__(kThreads) void reduce_tile_kernel(const Plan p) {
   } else {
     reduce_tile<1, true, false, ONE>(p, tl, store_only);
   }
-  track_tile(p, trk, tl);
+  track_tile(p, trk, tl, p.whole_chunks != 0);
 }
 
 // The upstream neighbour's updates (the DMA updates of Sec. 4.1), stood in for on one GPU:
@@ -158,7 +158,7 @@ __global__ __launch_bounds__(kThreads) void upstream_update_kernel(const Plan p)
         if (e0 + k * kThreads < total)
           __hip_atomic_fetch_add(p.R + at[k], v[k], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
-    track_tile(p, trk, tl);
+    track_tile(p, trk, tl, p.whole_chunks != 0);
   }
 }
 

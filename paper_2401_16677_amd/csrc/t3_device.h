@@ -123,7 +123,7 @@ __device__ inline Trk trk_at(const Plan &p, uint32_t gen_now) {
 __device__ inline uint32_t trk_gen(const Plan &p) { return p.track[2 * trk_bank_words(p.P)]; }
 __device__ inline Trk trk_open(const Plan &p) { return trk_at(p, trk_gen(p)); }
 // Who acts on the tracker's words: one thread, behind a branch of its own (an answer is waited for in there: where
-// the paths meet again there is none on its way) ...
+// the paths meet again there is none on its way; gemm_tile_kernel's, which clears a bank word by word) ...
 struct TrkThread {
   __device__ uint32_t add(uint32_t *w, uint32_t v) const {
     const uint32_t old = __hip_atomic_fetch_add(w, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -142,6 +142,7 @@ struct TrkThread {
   __device__ void put(uint32_t *w, uint32_t v) const {
     __hip_atomic_store(w, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   }
+  __device__ void wait() const { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
 };
 // ... or a wavefront as one: every lane issues the access, lane 0's address alone lies inside the array.  Without
 // a branch that differs between lanes the compiler keeps rare code out of the way of the loop it stands in (such
@@ -172,11 +173,12 @@ struct TrkWave {
   __device__ void put(uint32_t *w, uint32_t v) const {
     __builtin_amdgcn_raw_buffer_store_b32(v, words, (int)lane_at, (int)at(w), 16 /* sc1 */);
   }
+  __device__ void wait() const { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
   __device__ uint32_t at(uint32_t *w) const { return (uint32_t)(w - base) * 4u; }
 };
 // Called behind a workgroup's addition to `done`; d = what that made of it.
 template <typename Who>
-__device__ inline void trk_close_if_last(const Plan &p, const Trk &t, uint32_t d, const Who &who) {
+__host__ __device__ inline void trk_close_if_last(const Plan &p, const Trk &t, uint32_t d, const Who &who) {
   if (d == (uint32_t)p.expected_done) {
     who.clear_bank(t.other, p.P);
     who.add(t.gen, 1u);
@@ -400,14 +402,14 @@ __device__ inline void copy_chunk_rows(const Plan &p, int slot, int c, int r0, i
 // chunks, and the tiles of a chunk are counted in sub_groups groups first, each in a word of its
 // own, eight lines apart in turn; the tile that completes a group counts the group.  (The words are those of
 // the balanced tail, which such a launch does not have, and return to 0.)
-__device__ inline uint32_t *trk_group_word(const Plan &p, int s, int g) {
+__host__ __device__ inline uint32_t *trk_group_word(const Plan &p, int s, int g) {
   return p.tail_flags + (((g & 7) << 5) | ((s - p.stage0) << p.sub_shift) | (g >> 3));
 }
 // By thread 0, when the tile's results are visible: requests the count.
 struct TrkCount {
   uint32_t old, done;
 };
-__device__ inline uint32_t *track_word(const Plan &p, const Trk &t, const Tile &tl) {     // what counts this tile
+__host__ __device__ inline uint32_t *track_word(const Plan &p, const Trk &t, const Tile &tl) {     // what counts this tile
   return p.sub_groups > 1 ? trk_group_word(p, tl.s, (tl.nj * p.Mt + tl.mi) & (p.sub_groups - 1)) : &t.counter[tl.c];
 }
 __device__ inline TrkCount track_issue(const Plan &p, const Trk &t, const Tile &tl) {
@@ -417,9 +419,11 @@ __device__ inline TrkCount track_issue(const Plan &p, const Trk &t, const Tile &
   __builtin_amdgcn_s_waitcnt(kWaitVm0);          // (see TrkThread)
   return k;
 }
-// Acts on what the count returned.
+// Acts on what the count returned.  whole: the launch runs whole chunks (p.whole_chunks; kernels that serve no others say
+// so, and the chain at a launch's end has no more code than it needs: 64 x 18432 x 576 on 32 chunks 15.4 us asked, 14.9
+// known).  (On the host too: a test plays launches through it.)
 template <typename Who>
-__device__ inline void track_finish(const Plan &p, const Trk &t, const Tile &tl, TrkCount k, const Who &who) {
+__host__ __device__ inline void track_finish(const Plan &p, const Trk &t, const Tile &tl, TrkCount k, bool whole, const Who &who) {
   const int c = tl.c;
   uint32_t parts = (uint32_t)p.tpc;
   if (p.sub_groups > 1) {
@@ -432,41 +436,49 @@ __device__ inline void track_finish(const Plan &p, const Trk &t, const Tile &tl,
   // threshold = regions of the chunk x updates expected per element (Sec. 4.2.1)
   const uint32_t upd = (uint32_t)(c == p.rank ? p.upd_first : p.upd_rest);
   if (k.old + 1u == parts * upd) {                // the landing that reaches the threshold triggers
-    // `done` and the place in the queue are asked for together, and the other bank is cleared by a wavefront, not by
-    // a thread: each answer is a round trip to the memory side and back, each of one thread's stores an address of
-    // its own, at the end of the launch's last tile with nothing to cover them.  (One after the other, and now:
-    // 256 x 1024 x 256 on 4 chunks 6.38 us, 5.45; 24 x 12288 x 1536 on 8 12.34, 10.90; 2048 x 18432 x 576 on 32 75.6, 72.5.)
-    uint32_t done = p.whole_chunks ? (uint32_t)p.tpc : 0u, at = c != p.own ? 1u : 0u;
-    who.add_both(t.done, done, t.queue_len, at);
-    if (p.whole_chunks) k.done = done;
+    // Over whole chunks `done` and the place in the queue are asked for together: each answer is a round trip to the
+    // memory side and back, at the end of the launch's last tile with nothing to cover it.  (One after the other on
+    // one thread, which cleared the other bank as well, and this way, in us: 256 x 1024 x 256 on 4 chunks 6.7, 5.7;
+    // 24 x 12288 x 1536 on 8 13.0, 11.4; 2048 x 18432 x 576 on 32, without start-up offsets, 94.1, 90.6.)
+    // The kept chunk's addition of 0 to queue_len goes along.  Where every tile has asked for its part of `done` already,
+    // an addition of nothing to it delays the others (300 x 792 x 320 on 3 chunks from the second tile on 11.8 us,
+    // 12.4 with one).
+    const bool forwarded = c != p.own;
+    uint32_t at = forwarded ? 1u : 0u;
+    if (whole) {
+      k.done = (uint32_t)p.tpc;
+      who.add_both(t.done, k.done, t.queue_len, at);
+    } else if (forwarded) {
+      at = who.add(t.queue_len, at);
+    }
     if (p.tracked * upd != k.old + 1u)            // what the counter is read as: tracked tiles
       who.put(&t.counter[c], (uint32_t)p.tracked * upd);
-    if (c != p.own) who.put(&t.queue[at], (uint32_t)c);
+    if (forwarded) who.put(&t.queue[at], (uint32_t)c);
     // The flag is what publishes.  Everything it stands for was written through the caches and has
     // been acknowledged: the tiles before they were counted, the queue entry by the wait here.  (A
     // release store would write back the L2 on top, in which nothing of this is left.)
     // (queue_len alone publishes nothing: it may run ahead of the entry it reserves.)
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    who.wait();
     who.put(&t.ready[c], 1u);
-  } else if (p.whole_chunks) {
+  } else if (whole) {
     return;
   }
-  trk_close_if_last(p, t, k.done + (p.whole_chunks ? (uint32_t)p.tpc : 1u), who);
+  trk_close_if_last(p, t, k.done + (whole ? (uint32_t)p.tpc : 1u), who);
 }
 __device__ inline TrkWave trk_wave(const Plan &p) {
   return TrkWave{make_rsrc(p.track, (uint32_t)(2 * trk_bank_words(p.P) + 2 + kTailSlots) * 4u), p.track, threadIdx.x == 0 ? 0u : kOob};
 }
 // The whole of it, by all threads of a workgroup, after the tile's stores have been issued.
-__device__ inline void track_tile(const Plan &p, const Trk &t, const Tile &tl) {
+__device__ inline void track_tile(const Plan &p, const Trk &t, const Tile &tl, bool whole) {
   __builtin_amdgcn_s_waitcnt(kWaitAll);
   __syncthreads();
   if (threadIdx.x >= 64) return;
   const TrkWave who = trk_wave(p);
   TrkCount k{who.ask(track_word(p, t, tl), 1u), 0u};
-  if (!p.whole_chunks) k.done = who.ask(t.done, 1u);
+  if (!whole) k.done = who.ask(t.done, 1u);
   k.old = __builtin_amdgcn_readfirstlane(k.old);
   k.done = __builtin_amdgcn_readfirstlane(k.done);
-  track_finish(p, t, tl, k, who);
+  track_finish(p, t, tl, k, whole, who);
 }
 
 }  // namespace t3k

@@ -152,7 +152,7 @@ void gemm_tile_kernel(const Plan p) {
   // from the second tile on, tiles of 256 x 128: 191 us as two, 183 as one; of 128 x 256: 194 and 181.)
   auto settle_pending = [&]() {
     if (tracked && pending.c >= 0 && threadIdx.x == 0)
-      track_finish(p, trk, pending, track_issue(p, trk, pending), TrkThread{});
+      track_finish(p, trk, pending, track_issue(p, trk, pending), p.whole_chunks != 0, TrkThread{});
     pending.c = -1;
   };
   auto flush_pending = [&]() {

@@ -243,7 +243,7 @@ __global__ __launch_bounds__(64 * WK) void small_tile_kernel(const Plan p) {
         __builtin_amdgcn_raw_buffer_store_b64(pack_bf16(v), f_rsrc, (int)(at * 2u), 0, kAuxSc1);
     }
   }
-  if (MODE == kModeFused) track_tile(p, trk_at(p, gen), tl);
+  if (MODE == kModeFused) track_tile(p, trk_at(p, gen), tl, true);
 }
 
 }  // namespace t3k

@@ -133,7 +133,7 @@ void wide_tile_kernel(const Plan p) {
   };
   auto act_on_count = [&]() {
     if (pending.c >= 0 && wave == 0)
-      track_finish(p, trk, pending, TrkCount{(uint32_t)__builtin_amdgcn_readfirstlane(count_old), 0u}, who);
+      track_finish(p, trk, pending, TrkCount{(uint32_t)__builtin_amdgcn_readfirstlane(count_old), 0u}, true, who);
     pending.c = -1;
   };
   auto stamp = [&](int it, int k) {
