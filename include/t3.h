@@ -247,7 +247,9 @@ t3_status t3_track_reset(int32_t tp, uint32_t *track, void *stream);
  *                           the same array holds bfloat16: [tp-1][M][W] of 2 bytes.
  *   track                   tracker state (reset once; launches sharing it must be ordered
  *                           on one stream)
- * fp32 accumulation order is unspecified; integer outputs are exact.
+ * fp32 accumulation order is unspecified; integer outputs are exact.  The order follows from the problem and
+ * the device, not from where a buffer starts: but for two-writer mode the same problem gives the same bits on any
+ * buffers (t3_gemm: among calls under graph capture, and among the others).
  */
 t3_status t3_gemm_rs_fused(const t3_problem *p, const void *A, const void *B, float *R,
                            void *fwd, uint32_t *track, void *stream);

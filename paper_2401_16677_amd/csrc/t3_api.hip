@@ -455,8 +455,7 @@ t3_status make_plan(const t3_problem *p, t3k::Call call, int need, const void *A
     q.timeline_wgs = (int32_t)(wgs > (1ll << 30) ? (1ll << 30) : wgs);
   }
   q.wide = shape.kernel == t3k::kWideTile;
-  q.col_align = q.wide ? (call == t3k::kCallGemm ? t3k::column_align(p, call, shape.tile, Wt, C, p->ldc)
-                                                 : t3k::column_align(p, call, shape.tile, Wt, R, p->ldr)) : 0;
+  q.col_align = q.wide ? t3k::column_align(p, call, shape.tile, Wt) : 0;
   q.tail_r = (int32_t)shape.tail_r;
   q.tail_q = (int32_t)shape.tail_q;
   q.tail_flags = track ? tail_flags_in(track, p->tp) : nullptr;   // (t3_gemm brings its own)

@@ -15,9 +15,8 @@ extern "C" void start_offsets(const t3_problem *p, int call, int tracked_m, int 
   out[1] = o.window_ns;
 }
 
-extern "C" int column_align(const t3_problem *p, int call, int tile_n, int64_t address, int64_t ld_out) {
-  return t3k::column_align(p, static_cast<t3k::Call>(call), {256, tile_n}, t3k::ceil_div(p->N / p->tp, tile_n),
-                           reinterpret_cast<const void *>(address), ld_out);
+extern "C" int column_align(const t3_problem *p, int call, int tile_n) {
+  return t3k::column_align(p, static_cast<t3k::Call>(call), {256, tile_n}, t3k::ceil_div(p->N / p->tp, tile_n));
 }
 
 extern "C" void copy_shape(int64_t M, int64_t W, int cus, int64_t *out) {

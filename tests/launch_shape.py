@@ -69,3 +69,7 @@ def start_offsets(p, call=FUSED, cus=CUS):
     out = (ctypes.c_double * 2)()
     lib().start_offsets(ctypes.byref(p), call, *tracked, cus, out)
     return tuple(out)
+
+
+def column_align(p, tile_n, call=FUSED):
+    return lib().column_align(ctypes.byref(p), call, tile_n)

@@ -195,3 +195,31 @@ def test_columns_start_at_granules(gpu, oracle, M, W, K, tp, layout, mode):
     if "bf16" in mode and W % 8:
         pytest.skip("bfloat16 slots hold multiples of 8 columns")
     _check(gpu, oracle, M, W, K, tp, mode, layout, ldr_pad=16 + -W * tp % 16)
+
+
+@pytest.mark.parametrize("M,W,K,tp,layout", [(4100, 532, 520, 8, "nk"), (2050, 500, 1536, 16, "nk"), (2056, 1016, 576, 8, "kn")])
+def test_results_do_not_depend_on_where_the_buffers_start(gpu, M, W, K, tp, layout):
+    """Real-valued inputs: the sums of a call depend on its sizes alone, to the last bit, not on the address or the leading
+    dimension of C or R."""
+    import torch
+    N, kn = W * tp, layout.endswith("kn")
+    g = torch.Generator("cuda").manual_seed(W)
+    A = torch.randn(M, K, generator=g, device="cuda").to(torch.bfloat16)
+    B = torch.randn(*((K, N) if kn else (N, K)), generator=g, device="cuda").to(torch.bfloat16)
+    inc = torch.randn(M, N, generator=g, device="cuda")
+    track = torch.zeros(t3.t3_track_words(tp), dtype=torch.int32, device="cuda")
+    t3.t3_track_reset(tp, track)
+    first = None
+    for ld, off in ((N, 0), (N, 4), (N + 4, 0), (N + 16, 8)):
+        print(f"M={M} W={W} K={K} tp={tp} {layout} ld={ld} offset={off}", flush=True)
+        C, R = (torch.zeros(M * ld + off, device="cuda")[off:].view(M, ld) for _ in range(2))
+        R[:, :N] = inc
+        fwd = torch.zeros(tp - 1, M, W, device="cuda")
+        p = t3.problem(M, N, K, tp, 1, b_layout=t3.T3_B_KN if kn else t3.T3_B_NK, ldr=ld, ldc=ld)
+        t3.t3_gemm(p, A, B, C)
+        t3.t3_gemm_rs_fused(p, A, B, R, fwd, track)
+        torch.cuda.synchronize()
+        got = [t.cpu().numpy().view(np.uint32) for t in (C[:, :N].contiguous(), R[:, :N].contiguous(), fwd)]
+        first = first or got
+        for name, x, y in zip(("C", "R", "fwd"), got, first):
+            assert np.array_equal(x, y), (name, ld, off, int((x != y).sum()))
