@@ -175,25 +175,40 @@ def test_picked_tiles(gpu, oracle, case, mode):
     _check(gpu, oracle, M, W, K, tp, mode, layout, begin=begin, limit=limit)
 
 
-# Rows of R and C that start at 64-byte granules, chunks that do not: tile columns start early, at granules, where the last
-# one has columns to spare.  Chunk widths of 4, 8 and 12 columns past a multiple of 16 (8 with k-rows of B), just enough to spare
-# and 4 or 8 columns too few, every tile with more than one column, tiles split by a balanced tail.
-@pytest.mark.parametrize("mode", ["copy", "bf16_copy", "unfused", "step0_copy"])
-@pytest.mark.parametrize("M,W,K,tp,layout", [
-    (4100, 532, 520, 8, "nk"),
-    (4100, 564, 328, 8, "nk"),           # 3 x 192 with 12 columns to spare
-    (4100, 568, 328, 8, "nk"),           # 8, and all chunks at multiples of 8
-    (4100, 572, 328, 8, "nk"),           # 4: too few
-    (2050, 1020, 200, 8, "nk"),
-    (2050, 500, 1536, 16, "nk"),
-    (4128, 200, 512, 12, "nk"),
-    (4096, 536, 384, 8, "kn"),
-    (2056, 1016, 576, 8, "kn"),
-    (4088, 568, 384, 6, "km_kn"),
-])
-def test_columns_start_at_granules(gpu, oracle, M, W, K, tp, layout, mode):
-    if "bf16" in mode and W % 8:
-        pytest.skip("bfloat16 slots hold multiples of 8 columns")
+# Chunks that do not start at 64-byte granules of R and C: tile columns start early, at granules, where the last one has columns
+# to spare: 12 for chunk widths that are multiples of 4, 8 for multiples of 8.  M, W, K, tp, layout, workgroup tile, tiles a balanced
+# tail splits, whether they do.  (A test without a GPU checks the last three.)
+GRANULES = [
+    (1032, 564, 200, 12, "nk", (256, 192), 0, True),         # 12 to spare
+    (1032, 568, 200, 12, "nk", (256, 192), 0, True),         # 8, and a width that is a multiple of 8
+    (1032, 572, 200, 12, "nk", (256, 192), 0, False),        # 4
+    (4100, 532, 520, 8, "nk", (256, 192), 0, True),
+    (1304, 948, 520, 12, "nk", (256, 192), 104, True),
+    (520, 564, 200, 12, "nk", (128, 192), 0, True),
+    (1032, 568, 520, 12, "nk", (128, 192), 68, True),
+    (520, 372, 200, 5, "nk", (128, 128), 0, True),
+    (520, 500, 200, 32, "nk", (256, 256), 0, True),
+    (520, 508, 200, 32, "nk", (256, 256), 0, False),
+    (1304, 1012, 520, 12, "nk", (256, 256), 32, True),
+    (4104, 244, 2048, 8, "nk", (256, 128), 16, True),
+    (520, 952, 576, 16, "kn", (256, 192), 0, True),
+    (1032, 568, 576, 12, "kn", (128, 192), 68, True),
+    (4104, 248, 2048, 8, "kn", (256, 128), 16, True),
+    (520, 948, 576, 16, "km", (256, 192), 0, True),
+    (1304, 1012, 576, 12, "km", (256, 256), 32, True),
+    (1304, 244, 4096, 12, "km", (256, 128), 0, True),
+    (520, 952, 576, 16, "km_kn", (256, 192), 0, True),
+    (520, 504, 576, 32, "km_kn", (256, 256), 0, True),
+    (520, 376, 576, 5, "km_kn", (128, 128), 0, True),
+]
+# (bfloat16 slots hold multiples of 8 columns, and have no balanced tail)
+GRANULE_MODES = [(case, mode) for case in GRANULES for mode in ("copy", "bf16_copy", "unfused", "step0_copy")
+                 if mode != "bf16_copy" or (case[1] % 8 == 0 and not case[6])]
+
+
+@pytest.mark.parametrize("case,mode", GRANULE_MODES)
+def test_columns_start_at_granules(gpu, oracle, case, mode):
+    M, W, K, tp, layout, _, _, _ = case
     _check(gpu, oracle, M, W, K, tp, mode, layout, ldr_pad=16 + -W * tp % 16)
 
 

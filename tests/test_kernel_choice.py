@@ -89,6 +89,17 @@ def test_problems_of_the_gpu_tests_get_the_tiles_they_are_meant_for():
         assert (s.kernel, s.tile_m, s.tile_n, s.tail_r) == (SMALL if tile == (32, 64) else WIDE, *tile, tail_r), (case, mode)
 
 
+def test_granule_cases_of_the_gpu_tests_are_what_they_say():
+    from tests.test_gpu_workgroup_tiles import GRANULE_MODES
+    for case, mode in GRANULE_MODES:
+        M, W, K, tp, layout, tile, tail_r, early = case
+        p = _problem(M, W, K, tp, layout, flags=t3.T3_FLAG_FWD_BF16 if mode == "bf16_copy" else 0)
+        call = GEMM if mode == "unfused" else FUSED
+        s = launch_shape(p, call)
+        assert (s.kernel, s.tile_m, s.tile_n, s.tail_r) == (WIDE, *tile, tail_r), (case, mode)
+        assert column_align(p, s.tile_n, call) == (15 if early else 0), (case, mode)
+
+
 def test_general_kernel():
     p = _problem(4096, 1536, 1536, 8, tile_m=256, tile_n=256, tile_begin=1)
     assert launch_shape(p).kernel == GENERAL                     # a range that cuts a step
