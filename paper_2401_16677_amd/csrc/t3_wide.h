@@ -182,7 +182,7 @@ void wide_tile_kernel(const Plan p) {
     return u32x4{(uint32_t)a, (uint32_t)(a >> 32), (uint32_t)bytes, 0x00020000u};
   };
   // A tile's first column in the chunk, and how many it has.  Where the grid has columns to spare, the chunk's tiles but the
-  // first start up to 15 columns early (p.col_align), at a 64-byte granule of R's rows (see column_align), and the
+  // first start up to 12 columns early (p.col_align), at a 64-byte granule of R's rows (see column_align), and the
   // first one has that many fewer.
   auto col_at = [&](const Tile &t) { return t.nj * BN - (t.nj ? (t.c * p.W) & p.col_align : 0); };
   auto cols_of = [&](const Tile &t, int at) {
