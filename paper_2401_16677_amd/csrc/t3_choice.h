@@ -221,6 +221,7 @@ inline LaunchShape launch_shape(const t3_problem *p, Call call, TileShape tracke
 // 8 over 16 us (rounds in brackets):
 //   fused, 256 x 256   4096 x 12288 x 256     98.2  96.1  93.5  94.1  (3)    16384 x 8192 x 512, copy     331 336 314 301  (8)
 //                      8192 x 4096 x 192, copy 82.3 82.4  86.5  80.6  (2)    8192 x 4096 x 448           74.3  -  70.5  -  (2)
+//                      16384 x 4096 x 128, copy 155.6 153.9 163.1 -  (4)    eleven such with K of 128   1   .981 .987  -
 //   fused, 256 x 192   4096 x 9216 x 256      74.6  72.2  74.0  75.2  (3)    8192 x 18432 x 1152         403 399 400 390  (12)
 //                      14748 x 2304 x 1152   114.1 110.8 116.9 115.0  (2.7; over 6 us 110.7)
 //                      4460 x 18432 x 1024   234.6 226.4 235.3 241.4  (6.8: not whole rounds)
@@ -249,7 +250,7 @@ inline StartOffsets start_offsets(const t3_problem *p, Call call, const LaunchSh
   if ((fused ? p->ldr : p->ldc) % 16 && rounds < (fused && direct ? 3 : 6)) return plain;
   if (rounds >= 6 && slabs >= 12 && (s.total_blocks % s.resident == 0 || s.tail_r)) return {8, 16000.0};
   if (!fused) return rounds >= (slabs >= 8 ? 4 : (slabs >= 4 ? 5 : 8)) ? wide : plain;
-  if (s.tile.n == 256) return slabs >= 8 || rounds >= 3 || direct ? wide : StartOffsets{4, 4000.0};
+  if (s.tile.n == 256) return slabs >= 8 || (rounds >= 3 && slabs >= 3) || direct ? wide : StartOffsets{4, 4000.0};
   if (slabs >= 8) return rounds >= 3 ? wide : StartOffsets{4, 6000.0};
   return rounds >= 6 && slabs >= 4 ? wide : StartOffsets{4, 4000.0};
 }

@@ -184,6 +184,8 @@ DIRECT = t3.T3_FLAG_FWD_DIRECT
     (8192, 1024, 192, 4, FUSED, 0, (256, 256), (4, 4000)),
     (8192, 1024, 512, 4, FUSED, 0, (256, 256), (4, 12000)),
     (4096, 1536, 192, 8, FUSED, 0, (256, 256), (4, 12000)),
+    (4096, 1536, 128, 8, FUSED, 0, (256, 256), (4, 4000)),              # two slabs
+    (4096, 1536, 128, 8, FUSED, DIRECT, (256, 256), (4, 12000)),
     (16384, 1024, 704, 8, FUSED, 0, (256, 256), (4, 12000)),            # eight rounds, 11 slabs
     (16384, 1024, 768, 8, FUSED, 0, (256, 256), (8, 16000)),            # 12
     (4096, 1536, 768, 8, FUSED, DIRECT, (256, 256), (4, 12000)),        # three rounds
