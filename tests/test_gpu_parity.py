@@ -301,6 +301,17 @@ def test_all_gather_step_widths(gpu, oracle, M, W):
         assert np.array_equal(got[:, :P * W], want) and np.array_equal(got[:, P * W:], mine[:, P * W:])
 
 
+def test_all_gather_step_of_more_rows_than_the_grid_has(gpu):
+    """2^20 workgroups of 16 rows at most: the rest are walked."""
+    import torch
+    M, W, P = (1 << 24) + 21, 20, 2
+    U = torch.rand(M, P * W, device="cuda:0")
+    R = torch.full((M, P * W), 7.0, device="cuda:0")
+    t3.t3_ag_step(t3.problem(M, P * W, 64, P, 0), 0, U, R)
+    torch.cuda.synchronize()
+    assert torch.equal(R[:, :W], U[:, :W]) and bool((R[:, W:] == 7.0).all())
+
+
 def test_all_gather_step_shapes_and_refusals(gpu, oracle):
     """t3_ag_step on a ragged shape with padded leading dimensions: only the chunk's columns
     change, bit for bit the oracle's step; bad steps and misaligned widths are refused."""
