@@ -724,7 +724,7 @@ t3_status t3_ag_step(const t3_problem *p, int32_t step, const float *upstream_R,
   if (shape.team == 4) kernel = t3k::ag_copy_kernel<4, 4, 4>;
   const int64_t blocks = shape.workgroups < kMaxCopyBlocks ? shape.workgroups : kMaxCopyBlocks;
   return launch(kernel, dim3((unsigned)blocks), dim3(t3k::kThreads), static_cast<hipStream_t>(stream),
-                upstream_R + c * W, ld_up, R + c * W, (int64_t)p->ldr, (int32_t)p->M, (int32_t)W);
+                upstream_R + c * W, ld_up, R + c * W, (int64_t)p->ldr, (int32_t)p->M, (int32_t)W, blocks * (t3k::kThreads / shape.team));
 }
 
 }  // extern "C"

@@ -194,6 +194,7 @@ __global__ void track_reset_kernel(uint32_t *track, int P) {
 // t3_choice.h says which.  The loads of a batch and their stores stand behind the same conditions: behind others
 // (a pointer that is null where there is nothing to store) the compiler carries the batch's registers through the
 // loop and waits for each load before the next.  IN_FLIGHT < U: such a wait on purpose, see copy_shape.
+// grid_rows: rows of all workgroups (asked of the launch, as gridDim, it costs the host 0.5 us a call for hidden arguments).
 // (A wavefront per row in every shape; pieces numbered across a workgroup's rows, load by load; and now, in us, eight
 // chunks: 100 x 1536 2.8, 2.8, 2.4; 1536 x 640 3.0, 3.8, 3.0; 2500 x 1024 5.2, 5.7, 5.2; 8192 x 640 10.3, 9.9, 9.3;
 // 4096 x 1536 11.5, 10.5, 10.4; 4096 x 4100 31.6, 31.6, 29.3; 16384 x 12 4.2, 2.8, 2.8; 16384 x 1024 24.8, 27.7, 23.9;
@@ -202,10 +203,9 @@ __global__ void track_reset_kernel(uint32_t *track, int P) {
 // columns up to 10 % over the second on some.)
 template <int T, int U, int IN_FLIGHT>
 __global__ __launch_bounds__(kThreads) void ag_copy_kernel(const float *src, int64_t ld_src, float *dst,
-                                                           int64_t ld_dst, int32_t M, int32_t W) {
-  constexpr int kRows = kThreads / T;
+                                                           int64_t ld_dst, int32_t M, int32_t W, int64_t grid_rows) {
   const int lane = (int)(threadIdx.x % T), W4 = W >> 2;
-  for (int64_t r = (int64_t)blockIdx.x * kRows + (int)(threadIdx.x / T); r < M; r += (int64_t)gridDim.x * kRows) {
+  for (int64_t r = (int64_t)blockIdx.x * (kThreads / T) + (int)(threadIdx.x / T); r < M; r += grid_rows) {
     const f32x4 *s4 = (const f32x4 *)(src + r * ld_src);
     f32x4 *d4 = (f32x4 *)(dst + r * ld_dst);
     for (int c0 = lane; c0 < W4; c0 += U * T) {

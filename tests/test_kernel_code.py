@@ -220,3 +220,7 @@ def test_all_gather_step_requests_a_batch_at_once(tmp_path):
         team, batch, in_flight = map(int, re.search(r"ILi(\d+)ELi(\d+)ELi(\d+)E", kernel).groups())
         assert sum(t.startswith("global_load") for b, _ in _blocks(lines) for t, _ in b) == batch, kernel
         assert _waits_inside_a_batch(lines) == (in_flight < batch), kernel
+        # (nothing behind the call's own 48 bytes of arguments: a kernel that asks for the size of its grid has the host
+        # write as many again with every launch)
+        args = [int(m.group(1), 0) for line in lines for m in [re.match(r"\s*s_load_dword\S* \S+, s\[\d+:\d+\], (\w+)", line)] if m]
+        assert args and max(args) < 48, (kernel, args)
