@@ -92,6 +92,34 @@ struct Tile {
   int s, c, mi, nj;
 };
 
+// The plan in vector registers, a word per lane: one request for all of the kernel's argument, and a read of a lane
+// for each word where it is wanted.  As scalar loads the words come in batches, one behind the other, as the code needs
+// them: the wide-tile kernel's start was some twenty round trips, seven of them to lines nobody had touched yet, and a
+// compiler that runs out of scalar registers asks for the same words again at every tile.  One round of tiles, in us, that way and
+// this: 2136 x 384 x 1000 on 8 chunks 28.5, 28.1; 1697 x 72 x 1120 on 32 26.3, 25.1; 523 x 1004 x 752 on 16 42.2, 41.3;
+// a ring step of 4096 x 1536 x 1536 29.1, 28.4; long launches 0 to 1 % less.
+struct PlanWords {
+  static constexpr int kWords = sizeof(Plan) / 4;
+  static_assert(sizeof(Plan) % 4 == 0 && kWords > 64 && kWords <= 128, "two registers");
+  uint32_t lo, hi;
+  // (the plan is the kernel's only argument)
+  __device__ __forceinline__ void load(int lane) {
+    const __attribute__((address_space(4))) uint32_t *words = (const __attribute__((address_space(4))) uint32_t *)__builtin_amdgcn_kernarg_segment_ptr();
+    lo = words[lane];
+    hi = words[lane + 64 < kWords ? lane + 64 : kWords - 1];
+  }
+  // The plan, to be read here: what is used of it is read out of the lanes now, not kept from before.
+  __device__ __forceinline__ Plan now() {
+    struct {
+      uint32_t w[kWords];
+    } d;
+    asm volatile("" : "+v"(lo), "+v"(hi));
+#pragma unroll
+    for (int i = 0; i < kWords; ++i) d.w[i] = (uint32_t)__builtin_amdgcn_readlane((int)(i < 64 ? lo : hi), i & 63);
+    return __builtin_bit_cast(Plan, d);
+  }
+};
+
 // Tracker state (uint32 words): two banks of { counter[P] ready[P] queue[P] queue_len done },
 // then the globals { gen, error }.  A launch works in bank gen & 1; the last workgroup of the
 // launch to finish clears the other bank and increments gen, so the next launch starts from a
@@ -173,6 +201,10 @@ struct TrkWave {
   __device__ void put(uint32_t *w, uint32_t v) const {
     __builtin_amdgcn_raw_buffer_store_b32(v, words, (int)lane_at, (int)at(w), 16 /* sc1 */);
   }
+  __device__ uint32_t get(uint32_t *w) const {
+    asm volatile("" ::: "memory");               // (asked for anew every time)
+    return __builtin_amdgcn_readfirstlane((uint32_t)__builtin_amdgcn_raw_buffer_load_b32(words, (int)lane_at, (int)at(w), 16 /* sc1 */));
+  }
   __device__ void wait() const { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
   __device__ uint32_t at(uint32_t *w) const { return (uint32_t)(w - base) * 4u; }
 };
@@ -246,7 +278,8 @@ __device__ inline bool chunk_is_whole(const Plan &p, int s) {
 // spread of phases measures 5 % faster than whole XCDs running early or late.
 template <int TAIL>
 __device__ inline bool work_item(const Plan &p, int it, int &blk, int &part, int &nparts) {
-  const int G = (int)gridDim.x, w = (int)blockIdx.x;
+  // (workgroups of the grid, or more than there are positions: gridDim's hidden arguments cost the host 0.5 us a launch)
+  const int G = p.resident, w = (int)blockIdx.x;
   if (TAIL && p.tail_r) {
     nparts = 1;
     part = 0;

@@ -90,14 +90,14 @@ __device__ inline bool get_piece(const Plan &p, int it, Piece &w) {
   w.nf = part == nparts - 1 ? slabs - w.k0 : per;
   w.ns = w.nf + (part == nparts - 1 && p.K % kBK ? 1 : 0);
   w.half = nparts == 2 ? 1 + part : 0;
-  w.idx = blk - p.tail_q * (int)gridDim.x;
+  w.idx = blk - p.tail_q * p.resident;
   return true;
 }
 
 template <int FM, int FN, int NSTAGE, int NIMG, int PRE, int DEPTH, int MODE, int BKN, int AKM>
 __global__ __launch_bounds__(256)
 __attribute__((amdgpu_waves_per_eu((32 * (FM + FN) * 128 * NSTAGE + NIMG * 4096 * FN) <= 80 * 1024 ? 2 : 1)))
-void wide_tile_kernel(const Plan p) {
+void wide_tile_kernel(const Plan) {
   constexpr int BM = 32 * FM, BN = 32 * FN, WM = 16 * FM, WN = 16 * FN;
   constexpr int NA = BM / kRPC / 4, NB = BN / kRPC / 4, NL = NA + NB;   // 1-KiB copies per wavefront and slab
   constexpr int kStageBytes = (BM + BN) * kRowBytes, kBOff = BM * kRowBytes;
@@ -108,14 +108,22 @@ void wide_tile_kernel(const Plan p) {
   __shared__ __attribute__((aligned(1024))) char lds[kImgOff + NIMG * kImgBytes];
 
   constexpr bool tracked = MODE == kModeFused;
-  Trk trk;
-  if (tracked) trk = trk_open(p);
+  const int lane = threadIdx.x & 63;
+  PlanWords words;
+  words.load(lane);
+  Plan p = words.now();                          // (read anew where something rare begins)
+  // The tracker's generation, a scalar load nothing waits for until a tile is counted.  (Waited for here it puts a round trip
+  // to memory in front of the first slabs.)
+  uint32_t gen = 0u;
+  if (tracked) gen = *(const __attribute__((address_space(4))) uint32_t *)(p.track + 2 * trk_bank_words(p.P));
   if (p.stagger_groups > 1) stagger_start(p);
 
-  const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
   const int wm = wave >> 1, wn = wave & 1;
-  const int ktail = p.K % kBK;
+  const int ktail = __builtin_amdgcn_readfirstlane(p.K % kBK);
+  // bytes from one slab to the next in each operand
+  const uint32_t a_step = __builtin_amdgcn_readfirstlane(AKM ? (uint32_t)p.lda * (kBK * 2) : (uint32_t)kRowBytes);
+  const uint32_t b_step = __builtin_amdgcn_readfirstlane(BKN ? (uint32_t)p.ldb * (kBK * 2) : (uint32_t)kRowBytes);
   const uint32_t lds_base = (uint32_t)(uintptr_t)(lds_void_ptr)lds;
 
   // ---- tracking, deferred into the next piece's main loop
@@ -124,21 +132,32 @@ void wide_tile_kernel(const Plan p) {
   // The count is an atomic the compiler knows of: the register is its to keep, the wait its to make.  (Out of
   // inline assembly the value would be taken as there at once, and could be copied before it is.)
   const uint32_t lane_at = threadIdx.x == 0 ? 0u : kOob;
-  const TrkWave who{make_rsrc(p.track, tracked ? (uint32_t)(2 * trk_bank_words(p.P) + 2 + kTailSlots) * 4u : 0u), p.track, lane_at};
+  auto tracker = [&]() {
+    return TrkWave{make_rsrc(p.track, tracked ? (uint32_t)(2 * trk_bank_words(p.P) + 2 + kTailSlots) * 4u : 0u), p.track, lane_at};
+  };
   uint32_t count_old = 0u;
   auto ask_count = [&]() {                       // behind a barrier, stores acknowledged
+    p = words.now();
     if (pending_half >= 0) TrkWave{make_rsrc(p.tail_flags, kTailSlots * 4u), p.tail_flags, lane_at}.put(p.tail_flags + pending_half, 1u);
     pending_half = -1;
-    count_old = pending.c >= 0 ? who.ask(track_word(p, trk, pending), 1u) : 0u;
+    count_old = pending.c >= 0 ? tracker().ask(track_word(p, trk_at(p, gen), pending), 1u) : 0u;
   };
   auto act_on_count = [&]() {
-    if (pending.c >= 0 && wave == 0)
-      track_finish(p, trk, pending, TrkCount{(uint32_t)__builtin_amdgcn_readfirstlane(count_old), 0u}, true, who);
+    if (pending.c >= 0 && wave == 0) {
+      p = words.now();
+      track_finish(p, trk_at(p, gen), pending, TrkCount{(uint32_t)__builtin_amdgcn_readfirstlane(count_old), 0u}, true, tracker());
+    }
     pending.c = -1;
   };
+  const bool timeline = __builtin_amdgcn_readfirstlane(p.timeline != nullptr);
   auto stamp = [&](int it, int k) {
-    if (p.timeline && threadIdx.x == 0 && (int)blockIdx.x < p.timeline_wgs && it < kTimelineItems)
-      p.timeline[((size_t)blockIdx.x * kTimelineItems + it) * 4 + k] = wall_clock64();
+    if (!timeline) return;
+    p = words.now();
+    if (wave == 0 && (int)blockIdx.x < p.timeline_wgs && it < kTimelineItems) {
+      const uint64_t now = wall_clock64();
+      __builtin_amdgcn_raw_buffer_store_b64(u32x2{(uint32_t)now, (uint32_t)(now >> 32)},
+                                            make_rsrc(p.timeline + ((size_t)blockIdx.x * kTimelineItems + it) * 4 + k, 8u), (int)lane_at, 0, 0);
+    }
   };
 
   // ---- the copy stream.  Copy q of a wavefront and operand fills 1 KiB of the operand's region of a
@@ -177,9 +196,9 @@ void wide_tile_kernel(const Plan p) {
       offB[q] = (uint32_t)((wave * (BN / 4) + q * kRPC + lane / kCPR) * (int)p.ldb + k_chunk(q) * 8) * 2u;
     }
   }
-  auto descriptor = [](const void *base, int64_t bytes) {        // what make_rsrc makes, for inline assembly
+  auto descriptor = [](const void *base, uint32_t bytes) {       // what make_rsrc makes, for inline assembly
     const uint64_t a = (uint64_t)(uintptr_t)base;
-    return u32x4{(uint32_t)a, (uint32_t)(a >> 32), (uint32_t)bytes, 0x00020000u};
+    return u32x4{(uint32_t)a, (uint32_t)(a >> 32), bytes, 0x00020000u};
   };
   // A tile's first column in the chunk, and how many it has.  Where the grid has columns to spare, the chunk's tiles but the
   // first start up to 12 columns early (p.col_align), at a 64-byte granule of R's rows (see column_align), and the
@@ -193,12 +212,19 @@ void wide_tile_kernel(const Plan p) {
   // columns past the tile's end): their offsets get the top bit, the others lose it.
   auto mark = [](uint32_t off, bool outside) { return outside ? off | kOob : off & ~kOob; };
   bool markedA = false, markedB = false;         // some have it
-  int st_k0 = 0, st_nf = 0, st_koff = 0;         // the stream's piece: first slab, full slabs, where its walk starts
+  // The stream's piece in bytes from where the descriptors point, in A and in B (one value where both are K-contiguous): the next
+  // slab copied, the piece's first, and behind its last full one.
+  struct Walk {
+    uint32_t at, begin, end;
+  };
+  Walk walkA, walkB;
   auto stream_to = [&](const Piece &w) {
     const int m0 = w.tl.mi * BM, at = col_at(w.tl), n0 = w.tl.c * p.W + at;
     const int rows = min(BM, p.M - m0), cols = cols_of(w.tl, at);
-    descA = AKM ? descriptor(p.A + m0, (p.K * p.lda - m0) * 2) : descriptor(p.A + m0 * p.lda, rows * p.lda * 2);
-    descB = BKN ? descriptor(p.B + n0, (p.K * p.ldb - n0) * 2) : descriptor(p.B + n0 * p.ldb, cols * p.ldb * 2);
+    // (arrays of less than 2^31 elements: offsets in them are 32-bit products)
+    const uint32_t lda = (uint32_t)p.lda, ldb = (uint32_t)p.ldb;
+    descA = AKM ? descriptor(p.A + m0, ((uint32_t)p.K * lda - m0) * 2u) : descriptor(p.A + (uint32_t)m0 * lda, (uint32_t)rows * lda * 2u);
+    descB = BKN ? descriptor(p.B + n0, ((uint32_t)p.K * ldb - n0) * 2u) : descriptor(p.B + (uint32_t)n0 * ldb, (uint32_t)cols * ldb * 2u);
     const bool cutA = AKM && rows < BM, cutB = BKN && cols < BN;
     if (cutA || markedA) {
 #pragma unroll
@@ -218,16 +244,20 @@ void wide_tile_kernel(const Plan p) {
       }
       markedB = cutB;
     }
-    // (the same in every lane: said so, so that a slab's addresses are formed in scalar registers)
-    st_k0 = __builtin_amdgcn_readfirstlane(w.k0);
-    st_nf = __builtin_amdgcn_readfirstlane(w.nf);
     // K walks start at another slab on every XCD (p.k_groups of them) and wrap around: the chip reads as many
     // K ranges at a time instead of one, which spreads the traffic over the memory channels
-    st_koff = p.k_groups > 1 ? (int)div_by((blockIdx.x % (uint32_t)p.k_groups) * (uint32_t)w.nf, p.by_groups) : 0;
-    st_koff = __builtin_amdgcn_readfirstlane(st_koff);
+    const int off = p.k_groups > 1 ? (int)div_by((blockIdx.x - div_by(blockIdx.x, p.by_groups) * (uint32_t)p.k_groups) * (uint32_t)w.nf, p.by_groups) : 0;
+    // (the same in every lane: said so, so that a slab's addresses are formed in scalar registers)
+    auto walk = [&](uint32_t step) {
+      return Walk{(uint32_t)__builtin_amdgcn_readfirstlane((w.k0 + off) * step), (uint32_t)__builtin_amdgcn_readfirstlane(w.k0 * step),
+                  (uint32_t)__builtin_amdgcn_readfirstlane((w.k0 + w.nf) * step)};
+    };
+    walkA = walk(a_step);
+    if (AKM || BKN) walkB = walk(b_step);
   };
   auto stream_ragged = [&]() {                   // the stream's last slab ends with K: nothing behind it
     if constexpr (!AKM && !BKN) {
+      walkA.at = walkA.end;
 #pragma unroll
       for (int q = 0; q < NA; ++q) offA[q] = mark(offA[q], k_chunk(q) * 8 >= ktail);
 #pragma unroll
@@ -238,25 +268,25 @@ void wide_tile_kernel(const Plan p) {
   auto stream_end = [&]() { descA[2] = descB[2] = 0u; };          // (buffers of no bytes)
 #pragma clang diagnostic push
 #pragma clang diagnostic ignored "-Winline-asm"
-  auto copy_one = [&](auto Q, uint32_t so, uint32_t soffA, uint32_t soffB) {
+  auto copy_one = [&](auto Q, uint32_t so) {     // of the slab the walks are at
     constexpr int q = decltype(Q)::value;
     constexpr bool a = q < NA;
     const uint32_t dst = lds_base + so + (a ? wave * (NA * 1024) + q * 1024 : kBOff + wave * (NB * 1024) + (q - NA) * 1024);
-    const uint32_t off = a ? offA[a ? q : 0] : offB[a ? 0 : q - NA], soff = a ? soffA : soffB;
+    const uint32_t off = a ? offA[a ? q : 0] : offB[a ? 0 : q - NA], soff = a || !(AKM || BKN) ? walkA.at : walkB.at;
     const u32x4 desc = a ? descA : descB;
     asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds"
                  : : "s"(dst), "v"(off), "s"(desc), "s"(soff) : "memory", "m0");
   };
 #pragma clang diagnostic pop
-  auto slab_offs = [&](int j, uint32_t &a, uint32_t &b) {          // slab j of the stream's piece
-    int s = j;
-    if (j < st_nf) {
-      s = j + st_koff;
-      if (s >= st_nf) s -= st_nf;
-    }
-    s += st_k0;
-    a = (uint32_t)s * (AKM ? (uint32_t)p.lda * (kBK * 2) : (uint32_t)kRowBytes);
-    b = (uint32_t)s * (BKN ? (uint32_t)p.ldb * (kBK * 2) : (uint32_t)kRowBytes);
+  auto slab_next = [&]() {                       // on to the slab behind the one copied last
+    auto next = [](Walk &w, uint32_t step) {
+      uint32_t at = w.at + step;
+      if (at == w.end) at = w.begin;
+      asm volatile("" : "+s"(at));
+      w.at = at;
+    };
+    next(walkA, a_step);
+    if (AKM || BKN) next(walkB, b_step);
   };
 
   // ---- operand addresses (see gemm_tile_kernel)
@@ -314,9 +344,8 @@ void wide_tile_kernel(const Plan p) {
   };
   f32x4 acc[FM][FN];
   // One k-step: the products of operand set CS, (READS) k-step KK's operands of the stage at `sr` into the
-  // other set, and (COPIES) the stream's slab at (ca, cb) into the stage at `sc`.  `under`: what else is to
-  // be done under the products.
-  auto kstep = [&](auto FIRST, auto CS, auto KK, auto READS, auto COPIES, uint32_t sr, uint32_t sc, uint32_t ca, uint32_t cb, auto under) {
+  // other set, and (COPIES) the stream's slab into the stage at `sc`.  `under`: what else is to be done under the products.
+  auto kstep = [&](auto FIRST, auto CS, auto KK, auto READS, auto COPIES, uint32_t sr, uint32_t sc, auto under) {
     constexpr int cs = decltype(CS)::value, kk = decltype(KK)::value;
     uint32_t a_addr = 0, b_addr = 0;
     asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");            // this k-step's operands have landed
@@ -346,7 +375,7 @@ void wide_tile_kernel(const Plan p) {
         __builtin_amdgcn_sched_barrier(0);
       }
       if constexpr (decltype(COPIES)::value && m % kGapC == (kGapC > 1 ? 1 : 0) && m / kGapC < NL) {
-        copy_one(std::integral_constant<int, m / kGapC>{}, sc, ca, cb);
+        copy_one(std::integral_constant<int, m / kGapC>{}, sc);
         __builtin_amdgcn_sched_barrier(0);
       }
     });
@@ -369,10 +398,9 @@ void wide_tile_kernel(const Plan p) {
   stream_to(cur);
 #pragma unroll
   for (int j = 0; j < NSTAGE; ++j) {
-    uint32_t a, b;
-    slab_offs(j, a, b);
+    if (j) slab_next();
     if (ktail && j == cur.ns - 1 && cur.ns > cur.nf) stream_ragged();
-    static_for<NL>([&](auto Q) { copy_one(Q, (uint32_t)(j * kStageBytes), a, b); });
+    static_for<NL>([&](auto Q) { copy_one(Q, (uint32_t)(j * kStageBytes)); });
   }
   asm volatile("s_waitcnt vmcnt(%0)" : : "n"((NSTAGE - 1) * NL) : "memory");      // slab 0 landed
   uint32_t so = 0;                               // byte offset of the stage that holds the current slab
@@ -392,35 +420,20 @@ void wide_tile_kernel(const Plan p) {
   for (int it = 0;; ++it) {
     stamp(it, 0);
     const Tile tl = cur.tl;
-    const int m0 = tl.mi * BM, at = col_at(tl), n0 = tl.c * p.W + at;
-    const uint32_t rows_in = (uint32_t)min(BM, p.M - m0);         // rows and columns of the tile inside the chunk
-    const int cols_in = cols_of(tl, at);
-    const bool direct = (p.flags & kFlagFwdDirect) != 0, bf16 = (p.flags & kFlagFwdBf16) != 0;
-    const bool to_slot = tracked && tl.c != p.own && cur.half != 1 && (direct || chunk_is_whole(p, tl.s));
-    const bool to_r = !tracked || !direct || tl.c == p.own;
-    // where a whole tile's fp32 sums go, or half a tile's (an fp32 slot if not R / C)
-    const bool out_slot = tracked && direct && tl.c != p.own;
-    float *const slot_at0 = p.fwd + (((int64_t)tl.s * p.M + m0) * p.W + at);      // the tile's first element in each
-    float *const r_at0 = p.R + (m0 * p.ldr + n0);
-    float *const out_base = out_slot ? slot_at0 : r_at0;
-    const uint32_t ld_out = out_slot ? (uint32_t)p.W : (uint32_t)p.ldr;
+    p = words.now();
     const bool has_in = cur.half == 2 || (tracked && !((p.flags & kFlagStep0StoreOnly) && tl.s == 0));
-    // the incoming partial, or the first half's partial sums where the result will go
-    const float *const in_base = cur.half == 2 ? out_base : r_at0;
-    const uint32_t ld_in = cur.half == 2 ? ld_out : (uint32_t)p.ldr;
 
     if (cur.ns <= NSTAGE) flush();               // (too short a K loop to put the count off into)
-    if (cur.half == 2 && threadIdx.x == 0) {
+    if (cur.half == 2 && wave == 0) {
+      p = words.now();
       // The first half was computed by a workgroup with a lower index as its first piece of work and
       // waits for nothing, so this wait ends (normally at once).
+      const TrkWave flag{make_rsrc(p.tail_flags + cur.idx, 4u), p.tail_flags + cur.idx, lane_at};
       int spins = 0;
-      while (__hip_atomic_load(&p.tail_flags[cur.idx], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == 0u &&
-             ++spins < kSpinLimit)
-        __builtin_amdgcn_s_sleep(16);
-      if (tracked && spins >= kSpinLimit)
-        __hip_atomic_fetch_or(trk.error, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      while (flag.get(flag.base) == 0u && ++spins < kSpinLimit) __builtin_amdgcn_s_sleep(16);
+      if (tracked && spins >= kSpinLimit) tracker().put(trk_at(p, gen).error, 1u);
       // (this workgroup is the flag's only reader: cleared for the next launch)
-      __hip_atomic_store(&p.tail_flags[cur.idx], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      flag.put(flag.base, 0u);
       __builtin_amdgcn_s_waitcnt(kWaitVm0);
     }
     // slab 0 of this piece is in LDS (every wavefront has seen its own copies land); the images are free
@@ -431,8 +444,8 @@ void wide_tile_kernel(const Plan p) {
     static_for<NR>([&](auto R) { read_op(R, c0, c0, adA[0] + so, adB[0] + so); });
 
     f32x4 in[FM][FN];
-    const __amdgpu_buffer_rsrc_t in_rsrc = make_rsrc(in_base, rows_in * ld_in * 4u);
-    uint32_t in_at[UB];
+    __amdgpu_buffer_rsrc_t in_rsrc;
+    uint32_t in_at[UB], ld_in;
     auto load_in = [&](auto I) {                 // row block I of the incoming partial
       constexpr int i = decltype(I)::value;
       static_for<FN>([&](auto U) {
@@ -442,72 +455,99 @@ void wide_tile_kernel(const Plan p) {
                        in_rsrc, (int)(in_at[u % UB] + (uint32_t)(16 * i + (u / UB) * RS) * ld_in * 4u), 0, kAuxSc1 | kAuxNt));
       });
     };
-    auto in_here = [&]() {
+    // Where this piece's results go, worked out where it is wanted rather than kept through the main loop.
+    struct Place {
+      int cols_in;                               // rows and columns of the tile inside the chunk
+      uint32_t rows_in, ld_out;
+      float *slot_at0, *r_at0, *out_base;        // the tile's first element in the slot, in R or C, where its fp32 sums go
+      bool bf16, to_slot, to_r;
+    };
+    auto place = [&]() {
+      Place o;
+      const int m0 = tl.mi * BM, at = col_at(tl), n0 = tl.c * p.W + at;
+      o.rows_in = (uint32_t)min(BM, p.M - m0);
+      o.cols_in = cols_of(tl, at);
+      const bool direct = (p.flags & kFlagFwdDirect) != 0;
+      o.bf16 = (p.flags & kFlagFwdBf16) != 0;
+      o.to_slot = tracked && tl.c != p.own && cur.half != 1 && (direct || chunk_is_whole(p, tl.s));
+      o.to_r = !tracked || !direct || tl.c == p.own;
+      // where a whole tile's fp32 sums go, or half a tile's (an fp32 slot if not R / C)
+      const bool out_slot = tracked && direct && tl.c != p.own;
+      o.slot_at0 = p.fwd + (((int64_t)tl.s * p.M + m0) * p.W + at);
+      o.r_at0 = p.R + ((uint32_t)m0 * (uint32_t)p.ldr + (uint32_t)n0);
+      o.out_base = out_slot ? o.slot_at0 : o.r_at0;
+      o.ld_out = out_slot ? (uint32_t)p.W : (uint32_t)p.ldr;
+      return o;
+    };
+    auto in_here = [&](const Place &o) {
+      // the incoming partial, or the first half's partial sums where the result will go
+      ld_in = cur.half == 2 ? o.ld_out : (uint32_t)p.ldr;
+      in_rsrc = make_rsrc(cur.half == 2 ? o.out_base : o.r_at0, o.rows_in * ld_in * 4u);
 #pragma unroll
       for (int u = 0; u < UB; ++u) {
         const int L = u * 64 + lane, ir = wave * 8 + L / kRowCh, col = (L % kRowCh) * 4;
-        in_at[u] = col < cols_in ? ((uint32_t)strip_row(ir) * ld_in + (uint32_t)col) * 4u : kOob;
+        in_at[u] = col < o.cols_in ? ((uint32_t)strip_row(ir) * ld_in + (uint32_t)col) * 4u : kOob;
       }
     };
     Piece nxt;
     bool more = false;
     // The K loop.  A slab is two k-steps with a barrier between them, behind which the slab's stage is free and
     // the next slab visible; the loop runs from barrier to barrier and is left where something has to be done behind
-    // one (the count, the stream's last slab, its next piece).  One wavefront per SIMD: what stands between two
-    // products in the loop is time the matrix cores idle, so a barrier's wait is one test away, the addresses of the
-    // copies behind it are formed under the products before it, everything rare is outside, and the first k-step,
-    // ahead of the loop, starts the sums from a constant zero instead of 256 cleared registers.  (With all of it in the
+    // one (the count, the stream's last slab, its next piece) or a barrier waits for something else.  One wavefront per SIMD,
+    // and it issues an instruction every four clocks at best: what stands between two products in the loop is time the matrix
+    // cores idle, so a barrier is a wait and one test away from the last product, the next slab's place is worked out under the
+    // products before it, everything rare is outside, and the first k-step, ahead of the loop, starts the sums from a constant
+    // zero instead of 256 cleared registers.  (With all of it in the
     // loop, and one kernel for both modes: plain GEMM 4096 x 12288 x 1536 132.0 us, now 126.5; 16384 x 3072 x 1536
     // 141.6, 131.7; 4096 x 12288 x 6144 422.4, 415.1; fused 452.5, 444.6.)
-    int kt = 0, cj = NSTAGE;                     // slab multiplied, slab the stream copies next
-    const int k_switch = cur.ns - NSTAGE;        // the stream goes on to the next piece
+    int kt = 0;                                  // slab multiplied; slab kt + NSTAGE, or as many of the next piece, is copied next
+    const int last = cur.ns - 1, k_switch = cur.ns - NSTAGE;      // behind k_switch's barrier the stream goes on to the next piece
     const bool counting = pending.c >= 0 || pending_half >= 0;
-    uint32_t sn, ca, cb;                         // the next slab's stage, where the slab copied next lies
+    uint32_t sn;                                 // the next slab's stage
     auto first_half = [&](auto FIRST) {
-      kstep(FIRST, c0, c1, true_type{}, false_type{}, so, 0u, 0u, 0u, [&]() {
+      kstep(FIRST, c0, c1, true_type{}, false_type{}, so, 0u, [&]() {
         sn = next_stage(so);
-        slab_offs(cj, ca, cb);
-        asm volatile("" : "+s"(sn), "+s"(ca), "+s"(cb));
+        slab_next();
+        asm volatile("" : "+s"(sn));
       });
     };
-    // What the barrier waits for, beside this wavefront's own reads of the slab: kNext = the next slab's copies;
-    // kNextIn = the same with the incoming partial requested behind them; kLanded = nothing (the first slabs of every
-    // piece but the first landed during the way out, and behind the last slab nothing is needed).
-    enum { kNext, kNextIn, kLanded };
-    auto sync = [&](int kind) {
-      if (kind == kNext) asm volatile("s_waitcnt vmcnt(%0)" : : "n"((NSTAGE - 2) * NL) : "memory");
-      else if (NSTAGE > 2 && kind == kNextIn) asm volatile("s_waitcnt vmcnt(%0)" : : "n"((NSTAGE - 2) * NL + PRE * FN) : "memory");
+    auto barrier = [&]() {                       // this wavefront's own reads of the slab are done as well
       asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
       __builtin_amdgcn_s_barrier();
       asm volatile("" ::: "memory");
     };
+    // What it waits for beside them: the next slab's copies, with the incoming partial requested behind them or not; or nothing
+    // (the first slabs of every piece but the first landed during the way out, and behind the last slab nothing is needed).
+    auto next_landed = [&]() { asm volatile("s_waitcnt vmcnt(%0)" : : "n"((NSTAGE - 2) * NL) : "memory"); };
+    auto next_landed_in = [&]() { asm volatile("s_waitcnt vmcnt(%0)" : : "n"((NSTAGE - 2) * NL + PRE * FN) : "memory"); };
     first_half(true_type{});
-    sync(it > 0 || cur.ns == 1 ? kLanded : kNext);
-    for (;;) {                                   // behind the barrier of slab kt
-      if (kt == NSTAGE - 1 && counting && kt < cur.ns - 1) ask_count();          // (the previous piece's stores are older
-      if (kt == NSTAGE && counting) act_on_count();                              //   than copies that have been waited for)
+    if (it == 0 && last > 0) next_landed();
+    barrier();
+    for (;;) {                                   // behind the barrier of slab kt (left by equality: another test has the
+                                                 //   compiler keep two sets of accumulators)
+      if (counting && kt >= NSTAGE - 1) {        // (the previous piece's stores are older than copies that have been waited for)
+        if (kt == NSTAGE - 1 && kt < last) ask_count();
+        if (kt == NSTAGE) act_on_count();
+      }
       if (kt == k_switch) {
+        p = words.now();
         more = get_piece(p, it + 1, nxt);
         if (more) stream_to(nxt);
         else stream_end();
-        cj = 0;
-        slab_offs(cj, ca, cb);
         if (tracked && has_in) {
-          in_here();
+          in_here(place());
           static_for<PRE>([&](auto I) { load_in(I); });
         }
       }
       // the slab copied next is the last one of the stream's piece, and ragged
-      if (ktail && (kt == k_switch - 1 || (kt == cur.ns - 1 && more && nxt.ns == NSTAGE)) &&
-          (kt < k_switch ? cur.ns > cur.nf : nxt.ns > nxt.nf))
+      if (ktail && (kt == k_switch - 1 || (kt == last && more && nxt.ns == NSTAGE)) && (kt < k_switch ? cur.ns > cur.nf : nxt.ns > nxt.nf))
         stream_ragged();
       // the next barrier something is to be done behind, or whose wait is another one
-      int stop = kt < k_switch - 1 ? k_switch - 1 : (kt < k_switch ? k_switch : (kt < cur.ns - 2 ? cur.ns - 2 : cur.ns - 1));
-      if (kt < NSTAGE) stop = min(stop, kt + 1);
-      const int kind = kt + 1 == cur.ns - 1 || (it > 0 && kt + 1 < NSTAGE - 1) ? kLanded : (kt >= k_switch && tracked && has_in ? kNextIn : kNext);
+      int stop = kt < k_switch ? (ktail && kt < k_switch - 1 ? k_switch - 1 : k_switch) : (NSTAGE > 2 && kt < last - 1 ? kt + 1 : last);
+      if (kt < NSTAGE && (counting || (NSTAGE > 2 && it > 0))) stop = min(stop, kt + 1);
+      const int kind = kt + 1 == last || (it > 0 && kt + 1 < NSTAGE - 1) ? 2 : (NSTAGE > 2 && kt >= k_switch && tracked && has_in ? 1 : 0);
       do {
-        kstep(false_type{}, c1, c0, true_type{}, true_type{}, sn, so, ca, cb, []() {});     // (behind the last slab it reads what nobody uses)
-        ++cj;
+        kstep(false_type{}, c1, c0, true_type{}, true_type{}, sn, so, []() {});     // (behind the last slab it reads what nobody uses)
         so = sn;
         ++kt;
         // (the first k-step's wait, ahead of the branch: whatever the compiler keeps in registers along the way out of
@@ -517,12 +557,17 @@ void wide_tile_kernel(const Plan p) {
         xb[0].tie();
         if (kt == cur.ns) break;
         first_half(false_type{});
-        sync(kind);
+        if (kind == 0) next_landed();
+        else if (kind == 1) next_landed_in();
+        barrier();
       } while (kt < stop);
       if (kt == cur.ns) break;
     }
     stamp(it, 2);
 
+    p = words.now();
+    const Place to = place();
+    const bool nt_out = p.nt_out != 0;
     auto zero_in = [&](auto I) {
 #pragma unroll
       for (int u = 0; u < FN; ++u) in[decltype(I)::value][u] = f32x4{0.f, 0.f, 0.f, 0.f};
@@ -533,24 +578,26 @@ void wide_tile_kernel(const Plan p) {
     // TO: -1 = fp32 to C, kept in the caches; 0 = fp32 to R, C or a slot, streamed; 1 = R and the fp32 slot; 2 = the bfloat16 slot; 3 = R and the bfloat16 slot
     // ADD: there is something to add
     auto way_out = [&](auto TO, auto ADD) {
-      constexpr int to = decltype(TO)::value;
+      constexpr int kTo = decltype(TO)::value;
       constexpr bool add = decltype(ADD)::value;
+      const uint32_t ld_out = to.ld_out, W = (uint32_t)p.W;
       if constexpr (add && tracked) {
+        if (has_in && PRE == 0) in_here(to);
         if (has_in) static_for<DEPTH - PRE>([&](auto I) { load_in(std::integral_constant<int, decltype(I)::value + PRE>{}); });
         else static_for<DEPTH>(zero_in);
       } else if constexpr (add) {
-        in_here();
+        in_here(to);
         static_for<DEPTH>(load_in);
       }
-      const __amdgpu_buffer_rsrc_t out_rsrc = make_rsrc(out_base, rows_in * ld_out * 4u);
-      const void *slot = to >= 2 ? (const void *)((const uint16_t *)p.fwd + (slot_at0 - p.fwd)) : (const void *)slot_at0;
-      const __amdgpu_buffer_rsrc_t slot_rsrc = make_rsrc(slot, rows_in * (uint32_t)p.W * (to >= 2 ? 2u : 4u));
+      const __amdgpu_buffer_rsrc_t out_rsrc = make_rsrc(to.out_base, to.rows_in * ld_out * 4u);
+      const void *slot = kTo >= 2 ? (const void *)((const uint16_t *)p.fwd + (to.slot_at0 - p.fwd)) : (const void *)to.slot_at0;
+      const __amdgpu_buffer_rsrc_t slot_rsrc = make_rsrc(slot, to.rows_in * W * (kTo >= 2 ? 2u : 4u));
       uint32_t out_at[UB], slot_at[UB], img_at[FN];
 #pragma unroll
       for (int u = 0; u < UB; ++u) {
         const int L = u * 64 + lane_e, ir = wave * 8 + L / kRowCh, col = (L % kRowCh) * 4, row = strip_row(ir);
-        out_at[u] = col < cols_in ? ((uint32_t)row * ld_out + (uint32_t)col) * 4u : kOob;
-        slot_at[u] = col < cols_in ? ((uint32_t)row * (uint32_t)p.W + (uint32_t)col) * (to >= 2 ? 2u : 4u) : kOob;
+        out_at[u] = col < to.cols_in ? ((uint32_t)row * ld_out + (uint32_t)col) * 4u : kOob;
+        slot_at[u] = col < to.cols_in ? ((uint32_t)row * W + (uint32_t)col) * (kTo >= 2 ? 2u : 4u) : kOob;
       }
 #pragma unroll
       for (int u = 0; u < FN; ++u) {
@@ -577,10 +624,10 @@ void wide_tile_kernel(const Plan p) {
           f32x4 v = *(const f32x4 *)(lds + img + img_at[u]);
           if constexpr (add) v += in[i][u];
           const uint32_t rows = (uint32_t)(16 * i + (u / UB) * RS);
-          if constexpr (to != 2) store_agent_hint<(to >= 0)>(out_rsrc, out_at[u % UB] + rows * ld_out * 4u, 0u, v);
-          if constexpr (to == 1) store_agent_hint<true>(slot_rsrc, slot_at[u % UB] + rows * (uint32_t)p.W * 4u, 0u, v);
-          if constexpr (to >= 2)
-            __builtin_amdgcn_raw_buffer_store_b64(pack_bf16(v), slot_rsrc, (int)(slot_at[u % UB] + rows * (uint32_t)p.W * 2u), 0,
+          if constexpr (kTo != 2) store_agent_hint<(kTo >= 0)>(out_rsrc, out_at[u % UB] + rows * ld_out * 4u, 0u, v);
+          if constexpr (kTo == 1) store_agent_hint<true>(slot_rsrc, slot_at[u % UB] + rows * W * 4u, 0u, v);
+          if constexpr (kTo >= 2)
+            __builtin_amdgcn_raw_buffer_store_b64(pack_bf16(v), slot_rsrc, (int)(slot_at[u % UB] + rows * W * 2u), 0,
                                                   kAuxSc1 | kAuxNt);
         });
         if constexpr (add && i + DEPTH < FM) {
@@ -590,17 +637,17 @@ void wide_tile_kernel(const Plan p) {
         // The next piece's first NSTAGE slabs were requested before the last of the incoming partial,
         // so they have landed when that is used; where they were not, this wait makes sure of it.
         if constexpr (i == 1) {
-          if (!add || !has_in || (PRE == DEPTH && DEPTH == FM)) asm volatile("s_waitcnt vmcnt(%0)" : : "n"(2 * FN * (to <= 0 || to == 2 ? 1 : 2)) : "memory");
+          if (!add || !has_in || (PRE == DEPTH && DEPTH == FM)) asm volatile("s_waitcnt vmcnt(%0)" : : "n"(2 * FN * (kTo <= 0 || kTo == 2 ? 1 : 2)) : "memory");
         }
         __builtin_amdgcn_sched_barrier(0);
       });
     };
     constexpr std::integral_constant<int, -1> keep{};
     if constexpr (tracked) {
-      if (to_slot && bf16) {
-        if (to_r) way_out(std::integral_constant<int, 3>{}, true_type{});
+      if (to.to_slot && to.bf16) {
+        if (to.to_r) way_out(std::integral_constant<int, 3>{}, true_type{});
         else way_out(std::integral_constant<int, 2>{}, true_type{});
-      } else if (to_slot && to_r) {
+      } else if (to.to_slot && to.to_r) {
         way_out(c1, true_type{});
       } else {
         way_out(c0, true_type{});
@@ -608,7 +655,7 @@ void wide_tile_kernel(const Plan p) {
     } else if (cur.half == 2) {
       way_out(keep, true_type{});
     } else {
-      if (p.nt_out) way_out(c0, false_type{});
+      if (nt_out) way_out(c0, false_type{});
       else way_out(keep, false_type{});
     }
     stamp(it, 3);

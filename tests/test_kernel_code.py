@@ -173,6 +173,17 @@ def test_nothing_stands_between_the_products(code, unit):
         assert halves == 1, kernel
 
 
+@pytest.mark.parametrize("unit", [u[1] for u in LAYOUTS])
+def test_argument_is_requested_once(code, unit):
+    """The launch plan comes in two vector loads; the only scalar load is the tracker's generation.  Nothing goes through
+    a pointer whose address space the compiler does not know."""
+    for kernel, lines in code[unit].items():
+        text = [t for block, _ in _blocks(lines) for t, _ in block]
+        assert sum(t.startswith("global_load") for t in text) == 2, kernel
+        assert sum(t.startswith("s_load") for t in text) <= 1, kernel
+        assert not any(t.startswith("flat_") for t in text), kernel
+
+
 @pytest.mark.parametrize("unit", [u[1] for u in GENERAL])
 def test_general_main_loop_waits_once_a_slab(general, unit):
     """The loop over the slabs is one block that branches to itself.  Its copies stay in flight from one pass to the
