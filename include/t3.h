@@ -122,7 +122,8 @@ typedef struct {
  * stage s = t / tpc (the GEMM "stage" of Sec. 2.5, one per ring step), chunk
  * c = order[s], and inside the chunk q = t % tpc, tile row mi = q % Mt, tile column
  * nj = q / Mt.  Workgroups are launched in issue order up to a permutation inside a
- * stage that groups tiles sharing operands on one XCD.
+ * stage, or among the tiles the device works on at a time, that groups tiles sharing operands on
+ * one XCD.
  *
  * Supported (tile_m, tile_n): (256,256), (256,128), (128,256), (128,128).
  *

@@ -455,6 +455,7 @@ t3_status make_plan(const t3_problem *p, t3k::Call call, int need, const void *A
     q.timeline_wgs = (int32_t)(wgs > (1ll << 30) ? (1ll << 30) : wgs);
   }
   q.wide = shape.kernel == t3k::kWideTile;
+  if (q.wide) q.order = t3k::tile_order(p, call, shape, t3k::xcd_rows(shape, q.xcd_nbm ? q.xcd_bmk : 0, q.xcd_bnk));
   q.col_align = q.wide ? t3k::column_align(p, call, shape.tile, Wt) : 0;
   q.tail_r = (int32_t)shape.tail_r;
   q.tail_q = (int32_t)shape.tail_q;

@@ -5,6 +5,7 @@
 #include <stdint.h>
 
 #include "t3.h"
+#include "t3_div.h"
 
 namespace t3k {
 
@@ -212,6 +213,84 @@ inline LaunchShape launch_shape(const t3_problem *p, Call call, TileShape tracke
     }
   }
   return s;
+}
+
+// The rows of A and of B an XCD pulls at a time, stage by stage, in blocks of so many tiles (0: runs down the columns).
+inline double xcd_rows(const LaunchShape &s, int64_t block_rows, int64_t block_columns) {
+  const double round = (double)(s.total_blocks < s.resident ? s.total_blocks : s.resident), stages = round / (double)s.tpc;
+  double rows = (double)block_rows, columns = (double)block_columns;
+  if (!block_rows) {
+    const double run = (double)s.tpc / 8.0, all = (double)s.Mt;
+    rows = run < all ? (run < 1.0 ? 1.0 : run) : all;
+    columns = run / all + 0.5 > 1.0 ? run / all + 0.5 : 1.0;
+  }
+  return rows * s.tile.m + columns * (stages > 1.0 ? stages : 1.0) * s.tile.n;
+}
+
+// The order in which the persistent workgroups of the wide-tile kernel take the tiles of whole ring steps.  Workgroups are
+// dealt round-robin to the 8 XCDs, so of a round of grid positions every eighth runs on the same one and pulls its slabs
+// through the same L2.  Cutting every stage into 8 blocks (or runs down its columns) of its own is good where a round is about a stage;
+// where it is several, the stages' blocks lie on top of one another: 2048 x 20480 x 10240 on 8 chunks, 8 x 10 tiles a stage,
+// gives an XCD 2 rows and 16 columns at a time, 18 slabs to pull for 32 tiles, where 8 rows and 4 columns are 12.
+// So, here, the tiles are put in a line, an XCD takes a run of it in every round, and the line is laid so that a run is a compact
+// block: tile columns, counted through the stages, are taken `width` (a power of two) at a time, and such a band
+// is walked row by row, every other one from the bottom up, so that a run that goes on in the next band keeps its rows.
+// A round's tiles run at the same time whatever their order, so a band may hold columns of several stages as long as it is
+// no larger than a round; a larger one has to lie inside a stage.
+struct TileOrder {
+  uint32_t round, total, rows, bands, width_log2;    // positions of a round, of the launch; tile rows (0: not in a line); whole bands
+  FastDiv by_round, by_band, by_last, by_stage;      // by `round`; rows << width_log2; columns behind the bands; Wt
+};
+struct TilePlace {
+  int stage, row, col;                               // stage counted from the range's first
+};
+T3_HOST_DEVICE inline TilePlace tile_place(const TileOrder &o, uint32_t position) {
+  const uint32_t r = div_by(position, o.by_round), base = r * o.round, j = position - base, x = j & 7;
+  const uint32_t left = o.total - base, n = left < o.round ? left : o.round, odd = n & 7;
+  const uint32_t t = base + (n >> 3) * x + (odd < x ? odd : x) + (j >> 3);
+  const uint32_t band = div_by(t, o.by_band), in = t - ((band * o.rows) << o.width_log2);
+  const bool last = band == o.bands;
+  uint32_t row = last ? div_by(in, o.by_last) : in >> o.width_log2;
+  const uint32_t col = (band << o.width_log2) + in - (last ? row * o.by_last.d : row << o.width_log2);
+  if (band & 1) row = o.rows - 1 - row;
+  const uint32_t stage = div_by(col, o.by_stage);
+  return {(int)stage, (int)row, (int)(col - stage * o.by_stage.d)};
+}
+// now: xcd_rows of the blocks or runs stage by stage.  In us, stage by stage and in a line: 8689 x 840 x 1120 on 4 chunks, bfloat16 slots
+// 131.0, 113.1; 11434 x 820 x 7200 on 2, GEMM and reduction 353.5, 328.0; 700 x 128 x 392 on 16 11.8, 11.0; 2048 x 18432 x 576 on
+// 32 74.4, 71.2; 2048 x 20480 x 10240 on 8 657, 649; 2506 x 944 x 2064 on 2 45.4, 44.5.  Not taken
+//  - where it needs 85 % of the rows or more: the A rows of a stage's blocks are the same ones in every stage, and an
+//    XCD's L2 partly keeps them (4096 x 12288 x 1536 on 8, 12 bands either way: 160.8, 167.3);
+//  - with fewer than four K-slabs, where there is little to pull (534 x 1048 x 128 on 2: 9.8, 9.9);
+//  - with the release by copy of chunks whose rows start in the middle of a 128-byte line: the tiles either side of the line would
+//    write it at the same time (2131 x 464 x 640 on 16 71.9, 77.4; x 432 68.6, 75.5; x 448, whole lines, 69.3, 68.1).
+inline TileOrder tile_order(const t3_problem *p, Call call, const LaunchShape &s, double now) {
+  TileOrder o{};
+  if (s.total_blocks <= 0 || p->K < 256) return o;
+  if (call == kCallFused && !(p->flags & T3_FLAG_FWD_DIRECT) && (p->N / p->tp) % 32) return o;
+  const int64_t columns = s.total_blocks / s.Mt, round = s.total_blocks < s.resident ? s.total_blocks : s.resident;
+  const int64_t run = round < 8 ? 1 : round / 8;
+  int64_t best = -1;
+  for (uint32_t log2 = 0; log2 <= 5; ++log2) {
+    const int64_t width = 1ll << log2, in_rows = ceil_div(run, width), rows = in_rows < s.Mt ? in_rows : s.Mt;
+    if (log2 && (width > columns || (s.Mt * width > round && s.Wt % width))) continue;
+    const int64_t foot = rows * s.tile.m + ceil_div(in_rows, s.Mt) * width * s.tile.n;     // rows of A and of B an XCD pulls
+    if (best < 0 || foot < best) {
+      best = foot;
+      o.width_log2 = log2;
+    }
+  }
+  if ((double)best > 0.85 * now) return o;
+  o.round = (uint32_t)round;
+  o.total = (uint32_t)s.total_blocks;
+  o.rows = (uint32_t)s.Mt;
+  o.bands = (uint32_t)(columns >> o.width_log2);
+  const uint32_t rest = (uint32_t)columns & ((1u << o.width_log2) - 1);
+  o.by_round = fast_div(o.round);
+  o.by_band = fast_div(o.rows << o.width_log2);
+  o.by_last = fast_div(rest ? rest : 1);
+  o.by_stage = fast_div((uint32_t)s.Wt);
+  return o;
 }
 
 // Start-up offsets: the first wave of persistent workgroups starts in `groups` phase groups over window_ns (see

@@ -81,16 +81,28 @@ struct Piece {
   int k0, nf, ns;      // first K-slab, full slabs, slabs with a ragged last one
   int half, idx;       // 0: whole tile, 1 / 2: first / second half of split tile idx
 };
-__device__ inline bool get_piece(const Plan &p, int it, Piece &w) {
+// (each part of it reads of the plan what it needs: what is read is read, and kept, whether the branch is taken or not)
+__device__ __forceinline__ bool get_piece(PlanWords &words, int it, Piece &w) {
+  Plan p = words.now();
   int blk, part, nparts;
   if (!work_item<1>(p, it, blk, part, nparts)) return false;
-  decode_block(p, blk, w.tl);                    // (launches of whole ring steps: every position is a tile)
   const int slabs = p.K / kBK, per = nparts == 2 ? slabs >> 1 : slabs;
   w.k0 = part ? per : 0;
   w.nf = part == nparts - 1 ? slabs - w.k0 : per;
   w.ns = w.nf + (part == nparts - 1 && p.K % kBK ? 1 : 0);
   w.half = nparts == 2 ? 1 + part : 0;
   w.idx = blk - p.tail_q * p.resident;
+  if (p.order.rows) {
+    p = words.now();
+    const TilePlace at = tile_place(p.order, (uint32_t)blk);
+    w.tl.s = p.stage0 + at.stage;
+    w.tl.c = p.rank + w.tl.s >= p.P ? p.rank + w.tl.s - p.P : p.rank + w.tl.s;
+    w.tl.mi = at.row;
+    w.tl.nj = at.col;
+  } else {
+    p = words.now();
+    decode_block(p, blk, w.tl);                  // (launches of whole ring steps: every position is a tile)
+  }
   return true;
 }
 
@@ -394,7 +406,8 @@ void wide_tile_kernel(const Plan) {
   auto strip_row = [](int ir) { return (ir >> 4) * WM + (ir & 15); };   // image row -> tile row, row block 0
 
   Piece cur;
-  get_piece(p, 0, cur);                          // (the grid is no larger than the number of pieces)
+  get_piece(words, 0, cur);                      // (the grid is no larger than the number of pieces)
+  p = words.now();
   stream_to(cur);
 #pragma unroll
   for (int j = 0; j < NSTAGE; ++j) {
@@ -530,11 +543,12 @@ void wide_tile_kernel(const Plan) {
         if (kt == NSTAGE) act_on_count();
       }
       if (kt == k_switch) {
+        more = get_piece(words, it + 1, nxt);
         p = words.now();
-        more = get_piece(p, it + 1, nxt);
         if (more) stream_to(nxt);
         else stream_end();
         if (tracked && has_in) {
+          p = words.now();
           in_here(place());
           static_for<PRE>([&](auto I) { load_in(I); });
         }

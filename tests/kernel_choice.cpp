@@ -25,6 +25,20 @@ extern "C" void copy_shape(int64_t M, int64_t W, int cus, int64_t *out) {
   for (int i = 0; i < 4; ++i) out[i] = v[i];
 }
 
+// The order of a launch's tiles if they are put in a line (0 otherwise): position -> stage, row, column.
+extern "C" int tile_places(const t3_problem *p, int call, int tracked_m, int tracked_n, int cus, double now, int32_t *out) {
+  const t3k::Call c = static_cast<t3k::Call>(call);
+  const t3k::LaunchShape s = t3k::launch_shape(p, c, {tracked_m, tracked_n}, cus);
+  const t3k::TileOrder o = t3k::tile_order(p, c, s, now);
+  for (int64_t i = 0; o.rows && i < s.total_blocks; ++i) {
+    const t3k::TilePlace t = t3k::tile_place(o, (uint32_t)i);
+    out[3 * i] = t.stage;
+    out[3 * i + 1] = t.row;
+    out[3 * i + 2] = t.col;
+  }
+  return (int)o.width_log2 + (o.rows ? 1 : 0);
+}
+
 extern "C" void divide(const uint32_t *n, const uint32_t *d, uint32_t *out, int count) {
   for (int i = 0; i < count; ++i) out[i] = t3k::div_by(n[i], t3k::fast_div(d[i]));
 }

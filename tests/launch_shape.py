@@ -71,5 +71,15 @@ def start_offsets(p, call=FUSED, cus=CUS):
     return tuple(out)
 
 
+def tile_places(p, call=FUSED, cus=CUS, now=1e9):
+    """(stage, row, column) of every grid position where tiles are put in a line, else None; columns of a band."""
+    shape = launch_shape(p, call, cus)
+    tracked = (p.tile_m, p.tile_n) if p.tile_m else t3.t3_default_tile(p)
+    out = (ctypes.c_int32 * (3 * max(shape.blocks, 1)))()
+    lib().tile_places.argtypes = [ctypes.c_void_p] + [ctypes.c_int] * 4 + [ctypes.c_double, ctypes.c_void_p]
+    width = lib().tile_places(ctypes.byref(p), call, *tracked, cus, now, ctypes.byref(out))
+    return ([tuple(out[3 * i:3 * i + 3]) for i in range(shape.blocks)], 1 << (width - 1)) if width else (None, 0)
+
+
 def column_align(p, tile_n, call=FUSED):
     return lib().column_align(ctypes.byref(p), call, tile_n)

@@ -6,7 +6,7 @@ import pytest
 
 from paper_2401_16677_amd import binding as t3
 from tests.launch_shape import lib as choice_lib
-from tests.launch_shape import FUSED, GEMM, GENERAL, REDUCE, REDUCTION, SMALL, WIDE, column_align, copy_shape, launch_shape, start_offsets
+from tests.launch_shape import FUSED, GEMM, GENERAL, REDUCE, REDUCTION, SMALL, WIDE, column_align, copy_shape, launch_shape, start_offsets, tile_places
 
 
 def _problem(M, W, K, tp, layout="nk", **kw):
@@ -220,3 +220,39 @@ def test_start_up_offsets(M, W, K, tp, call, flags, tile, want):
     if few and want[0]:                          # (rows off 64-byte granules)
         want = (4, min(12000, tile[0] * tile[1] * K / 6250))
     assert start_offsets(off_granules, call) == pytest.approx(want)
+
+
+def test_tiles_in_a_line():
+    """Every tile once, its stage no further than two rounds from its place in the issue order; a band is no larger than a round or
+    lies inside a stage."""
+    rng = np.random.default_rng(11)
+    lines = 0
+    for _ in range(600):
+        col = 32
+        M, W, K = (int(round(np.exp(rng.uniform(np.log(a), np.log(b))))) for a, b in ((128, 16384), (32, 4096), (256, 4096)))
+        p = _problem(M, max(col, W // col * col), K // 8 * 8, int(rng.integers(1, 33)))
+        call, cus = int(rng.choice([FUSED, GEMM])), int(rng.choice([256, 256, 64, 20, 7]))
+        shape = launch_shape(p, call, cus)
+        if shape.kernel != WIDE or not 0 < shape.blocks <= 40000:
+            continue
+        places, width = tile_places(p, call, cus)
+        assert places is not None
+        lines += 1
+        Mt = -(-M // shape.tile_m)
+        Wt = shape.tpc // Mt
+        assert sorted(places) == [(s, r, c) for s in range(shape.blocks // shape.tpc) for r in range(Mt) for c in range(Wt)]
+        round_ = min(shape.blocks, shape.resident)
+        assert width == 1 or Mt * width <= round_ or Wt % width == 0
+        for i, (s, _, _) in enumerate(places):
+            assert s * shape.tpc - 2 * round_ <= i < (s + 1) * shape.tpc + 2 * round_
+    assert lines > 150
+
+
+def test_which_tiles_are_put_in_a_line():
+    in_line = lambda p, call=FUSED, now=1e9: tile_places(p, call, now=now)[0] is not None
+    wide = (2048, 2560, 10240, 8)                # 12 bands of 256 rows in a line
+    assert in_line(_problem(*wide, flags=DIRECT)) and in_line(_problem(*wide))
+    assert in_line(_problem(*wide), now=12 * 256 / 0.84) and not in_line(_problem(*wide), now=12 * 256 / 0.86)
+    assert not in_line(_problem(534, 1048, 192, 2, flags=DIRECT)) and in_line(_problem(534, 1048, 256, 2, flags=DIRECT))
+    assert not in_line(_problem(2131, 464, 640, 16)) and in_line(_problem(2131, 464, 640, 16, flags=DIRECT))
+    assert in_line(_problem(2131, 448, 640, 16)) and in_line(_problem(2131, 464, 640, 16), GEMM)
