@@ -32,6 +32,7 @@ constexpr int kDefaultCus = 256;       // compute units of an MI355X (host-only 
 constexpr int kMaxDevices = 64;
 constexpr int kReleaseAgents = 32;     // release workgroups per chunk (t3_release_chunks)
 constexpr int64_t kMaxCopyBlocks = 1 << 20;   // workgroups of t3_ag_step; more rows are walked
+constexpr int kReduceWordsBlocks = 1024;   // workgroups up to which the reduction takes its plan by a vector request
 constexpr int kNtMinK = 3072;          // K from which result stores take the streaming hint
 constexpr int64_t kMemorySideCacheBytes = 256ll << 20;
 // What the launch plan needs to know of the device it launches on, read from the runtime once
@@ -642,7 +643,9 @@ t3_status t3_rs_reduce(const t3_problem *p, const float *C, float *R, void *fwd,
   if (empty) return T3_OK;
   const int64_t W = p->N / p->tp, elements = (int64_t)(tm < p->M ? tm : p->M) * (tn < W ? tn : W);
   const bool one = elements <= 4 * t3k::kReduceBatch * t3k::kReduceThreads;
-  return launch(one ? t3k::reduce_tile_kernel<true> : t3k::reduce_tile_kernel<false>, dim3(grid_size(q)), dim3(t3k::kThreads),
+  auto kernel = q.total_blocks <= kReduceWordsBlocks ? (one ? t3k::reduce_tile_kernel<true, true> : t3k::reduce_tile_kernel<false, true>)
+                                                     : (one ? t3k::reduce_tile_kernel<true, false> : t3k::reduce_tile_kernel<false, false>);
+  return launch(kernel, dim3(grid_size(q)), dim3(t3k::kThreads),
                 static_cast<hipStream_t>(stream), q);
 }
 

@@ -99,11 +99,19 @@ __device__ inline void reduce_tile(const Plan &p, const Tile &tl, bool store_onl
   }
   finish(a);
 }
-template <bool ONE>
-__global__ __launch_bounds__(kThreads) void reduce_tile_kernel(const Plan p) {
+// WORDS: the plan by one vector request (PlanWords), for launches of a few workgroups per compute unit, all of which start on lines
+// nobody has touched; where thousands follow, the scalar cache has them (GEMM and reduction, scalar and by vector: 39 x 632 x 664
+// on 2 chunks 10.4 us, 10.1; 8 x 1124 x 3968 on 16 32.6, 32.1; 1000 x 1000 x 512 on 4, 976 workgroups, 24.3, 24.2; 2343 x 552 x 384 on 32,
+// 10000, 152.5, 154.7; 16384 x 384 x 1536 on 8 241.7, 243.1).
+template <bool ONE, bool WORDS>
+__global__ __launch_bounds__(kThreads) void reduce_tile_kernel(const Plan arg) {
+  PlanWords words;
+  if (WORDS) words.load((int)(threadIdx.x & 63));
+  Plan p = arg;
+  if (WORDS) p = words.now();
+  const uint32_t gen = *(const __attribute__((address_space(4))) uint32_t *)(p.track + 2 * trk_bank_words(p.P));
   Tile tl;
   if (!decode_block(p, blockIdx.x, tl)) return;
-  const Trk trk = trk_open(p);
   const bool store_only = (p.flags & kFlagStep0StoreOnly) && tl.s == 0;
   const bool direct = p.flags & kFlagFwdDirect, forwarded = tl.c != p.own, bf16 = p.flags & kFlagFwdBf16;
   const bool to_slot = forwarded && (direct || chunk_is_whole(p, tl.s)), to_r = !(forwarded && direct);
@@ -116,7 +124,8 @@ __global__ __launch_bounds__(kThreads) void reduce_tile_kernel(const Plan p) {
   } else {
     reduce_tile<1, true, false, ONE>(p, tl, store_only);
   }
-  track_tile(p, trk, tl, p.whole_chunks != 0);
+  if (WORDS) p = words.now();
+  track_tile(p, trk_at(p, gen), tl, p.whole_chunks != 0);
 }
 
 // The upstream neighbour's updates (the DMA updates of Sec. 4.1), stood in for on one GPU:

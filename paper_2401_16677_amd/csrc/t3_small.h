@@ -19,7 +19,7 @@
 namespace t3k {
 
 template <int BM, int BN, int WK, int NST, int MODE, int BKN, int AKM>
-__global__ __launch_bounds__(64 * WK) void small_tile_kernel(const Plan p) {
+__global__ __launch_bounds__(64 * WK) void small_tile_kernel(const Plan) {
   constexpr int FM = BM / 16, FN = BN / 16, KS = kBK / 32;
   constexpr int NA = BM / kRPC, NB = BN / kRPC, NL = NA + NB;     // 1-KiB copies per slab
   constexpr int kStageBytes = (BM + BN) * kRowBytes, kBOff = BM * kRowBytes;
@@ -29,14 +29,16 @@ __global__ __launch_bounds__(64 * WK) void small_tile_kernel(const Plan p) {
   static_assert(NIN * 64 == kRowsPerWave * kChunks && (NST - 1) * NL < 64 && kLds <= 160 * 1024, "");
   __shared__ __attribute__((aligned(1024))) char lds[kLds];
 
-  Tile tl;
-  if (!decode_block(p, (int)blockIdx.x, tl)) return;
+  const int lane = threadIdx.x & 63;
+  PlanWords words;
+  words.load(lane);
+  Plan p = words.now();
   // (the generation is needed only when the tile is counted: nothing waits for it here)
   uint32_t gen = 0;
-  if (MODE == kModeFused)
-    gen = trk_gen(p);
+  if (MODE == kModeFused) gen = *(const __attribute__((address_space(4))) uint32_t *)(p.track + 2 * trk_bank_words(p.P));
+  Tile tl;
+  if (!decode_block(p, (int)blockIdx.x, tl)) return;
 
-  const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
   const int m0 = tl.mi * BM, col_lo = tl.c * p.W, col_hi = col_lo + p.W, n0 = col_lo + tl.nj * BN;
   const int nkf = p.K / kBK, ktail = p.K - nkf * kBK;
@@ -200,10 +202,10 @@ __global__ __launch_bounds__(64 * WK) void small_tile_kernel(const Plan p) {
 #pragma unroll
       for (int q = 0; q < NL; ++q) {
         const int r = q < NA ? q : q - NA;
-        uint4 v = make_uint4(0, 0, 0, 0);
+        u32x4 v{0, 0, 0, 0};
         if (k_chunk(r) * 8 < ktail)
-          v = *(const uint4 *)((q < NA ? (const char *)p.A + offA[q < NA ? q : 0] : (const char *)p.B + offB[q < NA ? 0 : r]) + kb);
-        *(uint4 *)(st0 + q * 1024 + lane * 16) = v;
+          v = *(const __attribute__((address_space(1))) u32x4 *)((q < NA ? (const char *)p.A + offA[q < NA ? q : 0] : (const char *)p.B + offB[q < NA ? 0 : r]) + kb);
+        *(u32x4 *)(st0 + q * 1024 + lane * 16) = v;
       }
       asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
       read_slab(set0, st0);
@@ -243,7 +245,10 @@ __global__ __launch_bounds__(64 * WK) void small_tile_kernel(const Plan p) {
         __builtin_amdgcn_raw_buffer_store_b64(pack_bf16(v), f_rsrc, (int)(at * 2u), 0, kAuxSc1);
     }
   }
-  if (MODE == kModeFused) track_tile(p, trk_at(p, gen), tl, true);
+  if (MODE == kModeFused) {
+    p = words.now();
+    track_tile(p, trk_at(p, gen), tl, true);
+  }
 }
 
 }  // namespace t3k
