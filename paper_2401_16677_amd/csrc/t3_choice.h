@@ -215,9 +215,15 @@ inline LaunchShape launch_shape(const t3_problem *p, Call call, TileShape tracke
   return s;
 }
 
-// The rows of A and of B an XCD pulls at a time, stage by stage, in blocks of so many tiles (0: runs down the columns).
+// Tiles an XCD works on in step: an eighth of a round, or half of that with a balanced tail, whose two halves of the workgroups are
+// half a tile apart.
+inline int64_t xcd_run(const LaunchShape &s) {
+  const int64_t round = s.total_blocks < s.resident ? s.total_blocks : s.resident, run = s.tail_r ? round / 16 : round / 8;
+  return run < 1 ? 1 : run;
+}
+// The rows of A and of B it pulls for them stage by stage, in blocks of so many tiles (0: runs down the columns).
 inline double xcd_rows(const LaunchShape &s, int64_t block_rows, int64_t block_columns) {
-  const double round = (double)(s.total_blocks < s.resident ? s.total_blocks : s.resident), stages = round / (double)s.tpc;
+  const double stages = 8.0 * (double)xcd_run(s) / (double)s.tpc;
   double rows = (double)block_rows, columns = (double)block_columns;
   if (!block_rows) {
     const double run = (double)s.tpc / 8.0, all = (double)s.Mt;
@@ -258,7 +264,7 @@ T3_HOST_DEVICE inline TilePlace tile_place(const TileOrder &o, uint32_t position
 }
 // now: xcd_rows of the blocks or runs stage by stage.  In us, stage by stage and in a line: 8689 x 840 x 1120 on 4 chunks, bfloat16 slots
 // 131.0, 113.1; 11434 x 820 x 7200 on 2, GEMM and reduction 353.5, 328.0; 700 x 128 x 392 on 16 11.8, 11.0; 2048 x 18432 x 576 on
-// 32 74.4, 71.2; 2048 x 20480 x 10240 on 8 657, 649; 2506 x 944 x 2064 on 2 45.4, 44.5.  Not taken
+// 32 74.4, 71.2; 2048 x 20480 x 10240 on 8 663, 648; 2048 x 22528 x 4096 on 8 348, 325; 2506 x 944 x 2064 on 2 45.4, 44.5.  Not taken
 //  - where it needs 85 % of the rows or more: the A rows of a stage's blocks are the same ones in every stage, and an
 //    XCD's L2 partly keeps them (4096 x 12288 x 1536 on 8, 12 bands either way: 160.8, 167.3);
 //  - with fewer than four K-slabs, where there is little to pull (534 x 1048 x 128 on 2: 9.8, 9.9);
@@ -269,18 +275,24 @@ inline TileOrder tile_order(const t3_problem *p, Call call, const LaunchShape &s
   if (s.total_blocks <= 0 || p->K < 256) return o;
   if (call == kCallFused && !(p->flags & T3_FLAG_FWD_DIRECT) && (p->N / p->tp) % 32) return o;
   const int64_t columns = s.total_blocks / s.Mt, round = s.total_blocks < s.resident ? s.total_blocks : s.resident;
-  const int64_t run = round < 8 ? 1 : round / 8;
-  int64_t best = -1;
+  const int64_t run = xcd_run(s);
+  double best = -1.0, best_foot = 0.0;
+  auto foot = [&](int64_t tiles, int64_t width) {    // rows of A and of B of a run of so many tiles
+    const int64_t in_rows = ceil_div(tiles, width), rows = in_rows < s.Mt ? in_rows : s.Mt;
+    return (double)(rows * s.tile.m + ceil_div(in_rows, s.Mt) * width * s.tile.n);
+  };
   for (uint32_t log2 = 0; log2 <= 5; ++log2) {
-    const int64_t width = 1ll << log2, in_rows = ceil_div(run, width), rows = in_rows < s.Mt ? in_rows : s.Mt;
+    const int64_t width = 1ll << log2;
     if (log2 && (width > columns || (s.Mt * width > round && s.Wt % width))) continue;
-    const int64_t foot = rows * s.tile.m + ceil_div(in_rows, s.Mt) * width * s.tile.n;     // rows of A and of B an XCD pulls
-    if (best < 0 || foot < best) {
-      best = foot;
+    // (of equal ones the one whose halves are small too: workgroups drift)
+    const double cost = foot(run, width) + 0.25 * foot(ceil_div(run, 2), width);
+    if (best < 0 || cost < best) {
+      best = cost;
+      best_foot = foot(run, width);
       o.width_log2 = log2;
     }
   }
-  if ((double)best > 0.85 * now) return o;
+  if (best_foot > 0.85 * now) return TileOrder{};
   o.round = (uint32_t)round;
   o.total = (uint32_t)s.total_blocks;
   o.rows = (uint32_t)s.Mt;

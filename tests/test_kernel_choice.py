@@ -250,9 +250,12 @@ def test_tiles_in_a_line():
 
 def test_which_tiles_are_put_in_a_line():
     in_line = lambda p, call=FUSED, now=1e9: tile_places(p, call, now=now)[0] is not None
-    wide = (2048, 2560, 10240, 8)                # 12 bands of 256 rows in a line
+    wide = (2048, 2560, 10240, 8)                # a balanced tail: 8 bands of 256 rows in a line, in runs of 16
     assert in_line(_problem(*wide, flags=DIRECT)) and in_line(_problem(*wide))
-    assert in_line(_problem(*wide), now=12 * 256 / 0.84) and not in_line(_problem(*wide), now=12 * 256 / 0.86)
+    assert in_line(_problem(*wide), now=8 * 256 / 0.84) and not in_line(_problem(*wide), now=8 * 256 / 0.86)
+    assert tile_places(_problem(*wide))[1] == 4
+    whole = _problem(2048, 2048, 4096, 8)        # none: 12 in runs of 32
+    assert in_line(whole, now=12 * 256 / 0.84) and not in_line(whole, now=12 * 256 / 0.86)
     assert not in_line(_problem(534, 1048, 192, 2, flags=DIRECT)) and in_line(_problem(534, 1048, 256, 2, flags=DIRECT))
     assert not in_line(_problem(2131, 464, 640, 16)) and in_line(_problem(2131, 464, 640, 16, flags=DIRECT))
     assert in_line(_problem(2131, 448, 640, 16)) and in_line(_problem(2131, 464, 640, 16), GEMM)
