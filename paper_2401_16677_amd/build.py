@@ -21,12 +21,14 @@ UNITS = [("t3_api.hip", "t3_api.o", [])] + [
     ("t3_small_launch.hip", f"{fn}.o", [f"-DT3_LAUNCHER={fn}", f"-DT3_MODE={mode}"])
     for fn, mode in [("launch_small_fused", 1), ("launch_small_gemm", 0)]] + [
     ("t3_wide_launch.hip", f"{fn}.o",
-     [f"-DT3_LAUNCHER={fn}", f"-DT3_MODE={mode}", f"-DT3_BKN={kn}", f"-DT3_AKM={km}"])
-    for fn, mode, kn, km in [
-        ("launch_wide_fused", 1, 0, 0), ("launch_wide_fused_kn", 1, 1, 0),
-        ("launch_wide_fused_km", 1, 0, 1), ("launch_wide_fused_km_kn", 1, 1, 1),
-        ("launch_wide_gemm_nk", 0, 0, 0), ("launch_wide_gemm_kn", 0, 1, 0),
-        ("launch_wide_gemm_km", 0, 0, 1), ("launch_wide_gemm_km_kn", 0, 1, 1)]]
+     [f"-DT3_LAUNCHER={fn}", f"-DT3_MODE={mode}", f"-DT3_BKN={kn}", f"-DT3_AKM={km}", f"-DT3_OVERLAP={overlap}"])
+    for fn, mode, kn, km, overlap in [
+        ("launch_wide_fused", 1, 0, 0, 0), ("launch_wide_fused_kn", 1, 1, 0, 0),
+        ("launch_wide_fused_km", 1, 0, 1, 0), ("launch_wide_fused_km_kn", 1, 1, 1, 0),
+        ("launch_wide_overlap", 1, 0, 0, 1), ("launch_wide_overlap_kn", 1, 1, 0, 1),
+        ("launch_wide_overlap_km", 1, 0, 1, 1), ("launch_wide_overlap_km_kn", 1, 1, 1, 1),
+        ("launch_wide_gemm_nk", 0, 0, 0, 0), ("launch_wide_gemm_kn", 0, 1, 0, 0),
+        ("launch_wide_gemm_km", 0, 0, 1, 0), ("launch_wide_gemm_km_kn", 0, 1, 1, 0)]]
 DEPS = ["t3_api.hip", "t3_gemm_launch.hip", "t3_small_launch.hip", "t3_wide_launch.hip", "t3_choice.h", "t3_div.h", "t3_device.h", "t3_gemm.h",
         "t3_small.h", "t3_wide.h", "t3_aux.h", "t3_launch.h"]
 JOBS = 8

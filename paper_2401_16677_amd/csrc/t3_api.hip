@@ -457,6 +457,11 @@ t3_status make_plan(const t3_problem *p, t3k::Call call, int need, const void *A
   }
   q.wide = shape.kernel == t3k::kWideTile;
   if (q.wide) q.order = t3k::tile_order(p, call, shape, t3k::xcd_rows(shape, q.xcd_nbm ? q.xcd_bmk : 0, q.xcd_bnk));
+  q.overlap = q.granule = 0;
+  if (q.wide) {
+    q.granule = (p->flags & T3_FLAG_FWD_BF16) && fused_like ? 32 : 16;
+    q.overlap = t3k::column_overlap(p, call, shape.tile, Wt);
+  }
   q.col_align = q.wide ? t3k::column_align(p, call, shape.tile, Wt) : 0;
   q.tail_r = (int32_t)shape.tail_r;
   q.tail_q = (int32_t)shape.tail_q;
@@ -481,6 +486,9 @@ inline unsigned grid_size(const t3k::Plan &q) { return (unsigned)q.total_blocks;
 t3_status launch_gemm(int mode, const t3k::Plan &q, int32_t tm, int32_t tn, bool b_kn, bool a_km, hipStream_t s) {
   using namespace t3k;
   if (q.wide) {
+    if (mode == kModeFused && q.overlap)
+      return a_km ? (b_kn ? launch_wide_overlap_km_kn(q, tm, tn, s) : launch_wide_overlap_km(q, tm, tn, s))
+                  : (b_kn ? launch_wide_overlap_kn(q, tm, tn, s) : launch_wide_overlap(q, tm, tn, s));
     if (mode == kModeFused)
       return a_km ? (b_kn ? launch_wide_fused_km_kn(q, tm, tn, s) : launch_wide_fused_km(q, tm, tn, s))
                   : (b_kn ? launch_wide_fused_kn(q, tm, tn, s) : launch_wide_fused(q, tm, tn, s));

@@ -155,6 +155,21 @@ inline int32_t column_align(const t3_problem *p, Call call, TileShape tile, int6
   return Wt * tile.n - W >= most ? 15 : 0;
 }
 
+// With the direct release: by how many columns neighbouring tile columns of a chunk overlap, or 0.  A slot's rows are W elements apart, so where W is
+// no whole number of 64-byte granules, rows start at another place in one each, and no column is a granule's end in all of them.
+// Where the grid has the columns to spare, both neighbours compute the columns around the cut, and every row is cut
+// between them where its own granule ends; each element is still written once.  (What is left are the ends of the rows
+// themselves.)  By sizes alone, as column_align, and whatever R's leading dimension.  In us, cut at multiples of the tile and this way: 4293 x 1612 x
+// 208 on 4 chunks 70.0, 63.5; 8192 x 532 x 512 on 8 96.8, 91.2 (x 544, whole granules, 74.5); 6000 x 700 x 800 on 8 112.0, 106.8 (x 704 92.0);
+// 16384 x 396 x 256 on 8 121.0, 115.7; 1071 x 1460 x 640 on 8 41.1, 39.2; 2048 x 404 x 640 on 16 43.3, 41.3; long K hides it, 8192 x 532 x 2128 on 8
+// 189.5, 188.6.  Not with the release by copy, where R and the slot would want different cuts of the same sums.
+inline int32_t column_overlap(const t3_problem *p, Call call, TileShape tile, int64_t Wt) {
+  const int64_t W = p->N / p->tp, granule = p->flags & T3_FLAG_FWD_BF16 ? 32 : 16;
+  if (call != kCallFused || !(p->flags & T3_FLAG_FWD_DIRECT) || Wt < 2 || W % granule == 0) return 0;
+  const int64_t most = granule - (W & -W);       // (rows start at multiples of W's power of two)
+  return Wt * tile.n - W >= most * (Wt - 1) ? (int32_t)most : 0;
+}
+
 // What a call over a tile range launches.  `tracked`: the problem's tile, which the range is counted in.
 struct LaunchShape {
   Kernel kernel;

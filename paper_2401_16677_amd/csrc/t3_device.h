@@ -68,6 +68,7 @@ struct Plan {
   FastDiv by_groups;                   // by k_groups
   int32_t k_groups;                    // > 1: workgroup w starts its K loop (w % k_groups) / k_groups of the way in
   int32_t col_align;                   // 15: tile columns start at 64-byte granules of R, 0: at multiples of the tile (wide-tile kernel)
+  int32_t overlap, granule;            // columns by which a chunk's tile columns overlap, elements of a granule (wide-tile kernel, see column_overlap)
   int32_t nt_out;                      // results leave with the streaming hint (wide-tile kernel: the plain GEMM's)
   // Timeline (a profiling aid, normally null): workgroup w < timeline_wgs writes, for its i-th
   // piece of work, i < kTimelineItems, four wall-clock readings (100 MHz) at

@@ -38,6 +38,10 @@ t3_status launch_wide_fused(const Plan &q, int32_t tm, int32_t tn, hipStream_t s
 t3_status launch_wide_fused_kn(const Plan &q, int32_t tm, int32_t tn, hipStream_t s);
 t3_status launch_wide_fused_km(const Plan &q, int32_t tm, int32_t tn, hipStream_t s);
 t3_status launch_wide_fused_km_kn(const Plan &q, int32_t tm, int32_t tn, hipStream_t s);
+t3_status launch_wide_overlap(const Plan &q, int32_t tm, int32_t tn, hipStream_t s);      // (tile columns overlap, fused)
+t3_status launch_wide_overlap_kn(const Plan &q, int32_t tm, int32_t tn, hipStream_t s);
+t3_status launch_wide_overlap_km(const Plan &q, int32_t tm, int32_t tn, hipStream_t s);
+t3_status launch_wide_overlap_km_kn(const Plan &q, int32_t tm, int32_t tn, hipStream_t s);
 t3_status launch_wide_gemm_nk(const Plan &q, int32_t tm, int32_t tn, hipStream_t s);
 t3_status launch_wide_gemm_kn(const Plan &q, int32_t tm, int32_t tn, hipStream_t s);
 t3_status launch_wide_gemm_km(const Plan &q, int32_t tm, int32_t tn, hipStream_t s);

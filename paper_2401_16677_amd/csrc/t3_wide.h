@@ -106,7 +106,7 @@ __device__ __forceinline__ bool get_piece(PlanWords &words, int it, Piece &w) {
   return true;
 }
 
-template <int FM, int FN, int NSTAGE, int NIMG, int PRE, int DEPTH, int MODE, int BKN, int AKM>
+template <int FM, int FN, int NSTAGE, int NIMG, int PRE, int DEPTH, int MODE, int BKN, int AKM, int OVERLAP>
 __global__ __launch_bounds__(256)
 __attribute__((amdgpu_waves_per_eu((32 * (FM + FN) * 128 * NSTAGE + NIMG * 4096 * FN) <= 80 * 1024 ? 2 : 1)))
 void wide_tile_kernel(const Plan) {
@@ -215,9 +215,15 @@ void wide_tile_kernel(const Plan) {
   // A tile's first column in the chunk, and how many it has.  Where the grid has columns to spare, the chunk's tiles but the
   // first start up to 12 columns early (p.col_align), at a 64-byte granule of R's rows (see column_align), and the
   // first one has that many fewer.
-  auto col_at = [&](const Tile &t) { return t.nj * BN - (t.nj ? (t.c * p.W) & p.col_align : 0); };
+  // OVERLAP: all of them overlap by p.overlap columns, which both compute, and every row is cut between them where its granule ends (see
+  // column_overlap).  An instantiation of its own: in one with the others its arithmetic cost launches of one short tile 0.1 to 0.3 us.
+  auto col_at = [&](const Tile &t) {
+    if constexpr (OVERLAP) return t.nj * (BN - p.overlap);
+    else return t.nj * BN - (t.nj ? (t.c * p.W) & p.col_align : 0);
+  };
   auto cols_of = [&](const Tile &t, int at) {
-    return t.nj ? min(BN, p.W - at) : min(BN - ((t.c * p.W) & p.col_align), p.W);
+    if constexpr (OVERLAP) return min(BN, p.W - at);
+    else return t.nj ? min(BN, p.W - at) : min(BN - ((t.c * p.W) & p.col_align), p.W);
   };
   u32x4 descA, descB;
   // Which of a lane's copies lie outside in the piece's last slab (K-contiguous, ragged K) or throughout (transposed,
@@ -401,7 +407,8 @@ void wide_tile_kernel(const Plan) {
   // image row ir at k ^ (ir & 7) (both sides free of bank conflicts).  Wavefront w reads rows 8 w .. 8 w + 7
   // in FN accesses of 64 consecutive chunks; access u is at image row ir(u), column col(u) of the tile,
   // and the rows of access u + UB are those of access u plus RS.
-  constexpr int kRowCh = BN / 4, UB = BN == 192 ? 3 : 1, RS = UB * 64 / kRowCh;
+  // (OVERLAP: four rows, over which the place of the granules in a row repeats)
+  constexpr int kRowCh = BN / 4, UB = OVERLAP ? BN / 64 : (BN == 192 ? 3 : 1), RS = UB * 64 / kRowCh;
   static_assert(UB * 64 == RS * kRowCh && FN % UB == 0, "");
   auto strip_row = [](int ir) { return (ir >> 4) * WM + (ir & 15); };   // image row -> tile row, row block 0
 
@@ -471,7 +478,7 @@ void wide_tile_kernel(const Plan) {
     // Where this piece's results go, worked out where it is wanted rather than kept through the main loop.
     struct Place {
       int cols_in;                               // rows and columns of the tile inside the chunk
-      uint32_t rows_in, ld_out;
+      uint32_t rows_in, ld_out, first, row;      // first, row: where its rows start in a granule (in R as if R's started at one)
       float *slot_at0, *r_at0, *out_base;        // the tile's first element in the slot, in R or C, where its fp32 sums go
       bool bf16, to_slot, to_r;
     };
@@ -490,17 +497,44 @@ void wide_tile_kernel(const Plan) {
       o.r_at0 = p.R + ((uint32_t)m0 * (uint32_t)p.ldr + (uint32_t)n0);
       o.out_base = out_slot ? o.slot_at0 : o.r_at0;
       o.ld_out = out_slot ? (uint32_t)p.W : (uint32_t)p.ldr;
+      o.row = OVERLAP && out_slot ? (uint32_t)p.W : 0u;
+      o.first = out_slot ? (uint32_t)(tl.s * p.M + m0) * (uint32_t)p.W + (uint32_t)at : (uint32_t)n0;
       return o;
+    };
+    // This lane's row and column in access u, and which of the UB accesses' columns are this tile's to write
+    auto lane_row = [&](int l, int u) { return strip_row(wave * 8 + (u * 64 + l) / kRowCh); };
+    auto lane_col = [&](int l, int u) { return ((u * 64 + l) % kRowCh) * 4; };
+    auto inside = [&](const Place &o, int l, bool (&in)[UB]) {
+#pragma unroll
+      for (int u = 0; u < UB; ++u) in[u] = lane_col(l, u) < o.cols_in;
+      if constexpr (OVERLAP) {
+        const uint32_t next = (uint32_t)(BN - p.overlap), mask = (uint32_t)p.granule - 1u;
+#pragma unroll
+        for (int u = 0; u < UB; ++u) {
+          const uint32_t e = o.first + (uint32_t)lane_row(l, u) * o.row;
+          const int col = lane_col(l, u);
+          if (tl.nj && col < (int)(-e & mask)) in[u] = false;
+          if (tl.nj < p.Wt - 1 && col >= (int)(next + (-(e + next) & mask))) in[u] = false;
+        }
+      }
+    };
+    // Byte offsets of the UB accesses in rows of `ld` elements of `size` bytes (access u is rows_u rows on where a row is a part of one)
+    auto offsets = [&](int l, uint32_t ld, uint32_t size, const bool (&in)[UB], uint32_t (&at)[UB]) {
+      const uint32_t at0 = ((uint32_t)lane_row(l, 0) * ld + (uint32_t)lane_col(l, 0)) * size;
+#pragma unroll
+      for (int u = 0; u < UB; ++u) {
+        const uint32_t here = 64 % kRowCh == 0 ? at0 + (uint32_t)(u * 64 / kRowCh) * ld * size
+                                               : ((uint32_t)lane_row(l, u) * ld + (uint32_t)lane_col(l, u)) * size;
+        at[u] = in[u] ? here : kOob;
+      }
     };
     auto in_here = [&](const Place &o) {
       // the incoming partial, or the first half's partial sums where the result will go
       ld_in = cur.half == 2 ? o.ld_out : (uint32_t)p.ldr;
       in_rsrc = make_rsrc(cur.half == 2 ? o.out_base : o.r_at0, o.rows_in * ld_in * 4u);
-#pragma unroll
-      for (int u = 0; u < UB; ++u) {
-        const int L = u * 64 + lane, ir = wave * 8 + L / kRowCh, col = (L % kRowCh) * 4;
-        in_at[u] = col < o.cols_in ? ((uint32_t)strip_row(ir) * ld_in + (uint32_t)col) * 4u : kOob;
-      }
+      bool in[UB];
+      inside(o, lane, in);
+      offsets(lane, ld_in, 4u, in, in_at);
     };
     Piece nxt;
     bool more = false;
@@ -607,12 +641,10 @@ void wide_tile_kernel(const Plan) {
       const void *slot = kTo >= 2 ? (const void *)((const uint16_t *)p.fwd + (to.slot_at0 - p.fwd)) : (const void *)to.slot_at0;
       const __amdgpu_buffer_rsrc_t slot_rsrc = make_rsrc(slot, to.rows_in * W * (kTo >= 2 ? 2u : 4u));
       uint32_t out_at[UB], slot_at[UB], img_at[FN];
-#pragma unroll
-      for (int u = 0; u < UB; ++u) {
-        const int L = u * 64 + lane_e, ir = wave * 8 + L / kRowCh, col = (L % kRowCh) * 4, row = strip_row(ir);
-        out_at[u] = col < to.cols_in ? ((uint32_t)row * ld_out + (uint32_t)col) * 4u : kOob;
-        slot_at[u] = col < to.cols_in ? ((uint32_t)row * W + (uint32_t)col) * (kTo >= 2 ? 2u : 4u) : kOob;
-      }
+      bool in_tile[UB];
+      inside(to, lane_e, in_tile);
+      if (kTo != 2) offsets(lane_e, ld_out, 4u, in_tile, out_at);
+      if (kTo >= 1) offsets(lane_e, W, kTo >= 2 ? 2u : 4u, in_tile, slot_at);
 #pragma unroll
       for (int u = 0; u < FN; ++u) {
         const int L = u * 64 + lane_e, ir = wave * 8 + L / kRowCh;

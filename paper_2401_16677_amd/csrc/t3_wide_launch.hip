@@ -1,5 +1,5 @@
 // Launches of the wide-tile kernel for one mode and operand layout (T3_LAUNCHER names the function, T3_MODE,
-// T3_BKN and T3_AKM say which; compiled once for each).
+// T3_BKN, T3_AKM and T3_OVERLAP say which; compiled once for each).
 #include "t3_wide.h"
 #include "t3_launch.h"
 
@@ -7,7 +7,7 @@ namespace t3k {
 
 // FM, FN, LDS stages, images; row blocks of the incoming partial requested during the last slabs, and at
 // most in registers at a time (what the register file leaves)
-#define T3_WIDE(...) launch(wide_tile_kernel<__VA_ARGS__, T3_MODE, T3_BKN, T3_AKM>, grid, dim3(256), s, q)
+#define T3_WIDE(...) launch(wide_tile_kernel<__VA_ARGS__, T3_MODE, T3_BKN, T3_AKM, T3_OVERLAP>, grid, dim3(256), s, q)
 
 t3_status T3_LAUNCHER(const Plan &q, int32_t tm, int32_t tn, hipStream_t s) {
   // persistent workgroups: as many as the chip holds at once

@@ -19,6 +19,12 @@ extern "C" int column_align(const t3_problem *p, int call, int tile_n) {
   return t3k::column_align(p, static_cast<t3k::Call>(call), {256, tile_n}, t3k::ceil_div(p->N / p->tp, tile_n));
 }
 
+extern "C" int column_overlap(const t3_problem *p, int call, int tracked_m, int tracked_n, int cus) {
+  const t3k::Call c = static_cast<t3k::Call>(call);
+  const t3k::LaunchShape s = t3k::launch_shape(p, c, {tracked_m, tracked_n}, cus);
+  return s.kernel == t3k::kWideTile ? t3k::column_overlap(p, c, s.tile, s.Wt) : 0;
+}
+
 extern "C" void copy_shape(int64_t M, int64_t W, int cus, int64_t *out) {
   const t3k::CopyShape s = t3k::copy_shape(M, W, cus);
   const int64_t v[] = {s.team, s.batch, s.in_flight, s.workgroups};

@@ -81,5 +81,10 @@ def tile_places(p, call=FUSED, cus=CUS, now=1e9):
     return ([tuple(out[3 * i:3 * i + 3]) for i in range(shape.blocks)], 1 << (width - 1)) if width else (None, 0)
 
 
+def column_overlap(p, call=FUSED, cus=CUS):
+    tracked = (p.tile_m, p.tile_n) if p.tile_m else t3.t3_default_tile(p)
+    return lib().column_overlap(ctypes.byref(p), call, *tracked, cus)
+
+
 def column_align(p, tile_n, call=FUSED):
     return lib().column_align(ctypes.byref(p), call, tile_n)

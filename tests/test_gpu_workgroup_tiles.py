@@ -238,3 +238,59 @@ def test_results_do_not_depend_on_where_the_buffers_start(gpu, M, W, K, tp, layo
         first = first or got
         for name, x, y in zip(("C", "R", "fwd"), got, first):
             assert np.array_equal(x, y), (name, ld, off, int((x != y).sum()))
+
+
+# Direct release of chunks whose rows start inside a 64-byte granule of their slot: tile columns overlap where the grid has columns
+# to spare.  M, W, K, tp, layout, bfloat16 slots, workgroup tile, tiles a balanced tail splits, columns.  (A test without a GPU checks the last three.)
+OVERLAPS = [
+    (1032, 540, 200, 12, "nk", False, (256, 192), 0, 12),
+    (1032, 536, 200, 12, "nk", False, (256, 192), 0, 8),
+    (1030, 552, 200, 12, "nk", False, (256, 192), 0, 8),
+    (1032, 564, 200, 12, "nk", False, (256, 192), 0, 0),     # 12 columns to spare for two cuts
+    (1304, 908, 520, 12, "nk", False, (256, 192), 104, 12),
+    (520, 548, 200, 12, "nk", False, (128, 192), 0, 12),
+    (520, 372, 200, 5, "nk", False, (128, 128), 0, 0),
+    (520, 356, 200, 5, "nk", False, (128, 128), 0, 12),
+    (520, 500, 200, 32, "nk", False, (256, 256), 0, 12),
+    (1304, 976, 520, 12, "nk", False, (256, 256), 32, 0),    # whole granules
+    (1304, 980, 520, 12, "nk", False, (256, 256), 32, 12),
+    (4104, 244, 2048, 8, "nk", False, (256, 128), 16, 12),
+    (1032, 536, 200, 12, "nk", True, (256, 192), 0, 0),      # bfloat16: 24 columns a cut
+    (1032, 528, 200, 12, "nk", True, (256, 192), 0, 16),
+    (1032, 520, 200, 12, "nk", True, (256, 192), 0, 24),
+    (520, 952, 576, 16, "kn", False, (256, 192), 0, 0),
+    (520, 920, 576, 16, "kn", False, (256, 192), 0, 8),
+    (520, 504, 576, 32, "km_kn", False, (256, 256), 0, 8),
+]
+
+
+@pytest.mark.parametrize("case", OVERLAPS)
+def test_tile_columns_overlap(gpu, oracle, case):
+    M, W, K, tp, layout, bf16 = case[:6]
+    for mode in ("bf16",) if bf16 else ("direct", "step0"):
+        _check(gpu, oracle, M, W, K, tp, mode, layout)
+
+
+@pytest.mark.parametrize("M,W,K,tp,layout", [(1304, 908, 520, 12, "nk"), (2050, 500, 1536, 16, "nk"), (520, 920, 576, 16, "kn")])
+def test_direct_results_do_not_depend_on_where_the_buffers_start(gpu, M, W, K, tp, layout):
+    import torch
+    N, kn = W * tp, layout.endswith("kn")
+    g = torch.Generator("cuda").manual_seed(W)
+    A = torch.randn(M, K, generator=g, device="cuda").to(torch.bfloat16)
+    B = torch.randn(*((K, N) if kn else (N, K)), generator=g, device="cuda").to(torch.bfloat16)
+    inc = torch.randn(M, N, generator=g, device="cuda")
+    track = torch.zeros(t3.t3_track_words(tp), dtype=torch.int32, device="cuda")
+    t3.t3_track_reset(tp, track)
+    first = None
+    for ld, off in ((N, 0), (N, 4), (N + 4, 0), (N + 16, 8)):
+        print(f"M={M} W={W} K={K} tp={tp} {layout} ld={ld} offset={off}", flush=True)
+        R = torch.zeros(M * ld + off, device="cuda")[off:].view(M, ld)
+        R[:, :N] = inc
+        fwd = torch.zeros((tp - 1) * M * W + off, device="cuda")[off:]
+        p = t3.problem(M, N, K, tp, 1, b_layout=t3.T3_B_KN if kn else t3.T3_B_NK, ldr=ld, flags=t3.T3_FLAG_FWD_DIRECT)
+        t3.t3_gemm_rs_fused(p, A, B, R, fwd, track)
+        torch.cuda.synchronize()
+        got = [t.cpu().numpy().view(np.uint32) for t in (R[:, :N].contiguous(), fwd)]
+        first = first or got
+        for name, x, y in zip(("R", "fwd"), got, first):
+            assert np.array_equal(x, y), (name, ld, off, int((x != y).sum()))

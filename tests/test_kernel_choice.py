@@ -6,7 +6,7 @@ import pytest
 
 from paper_2401_16677_amd import binding as t3
 from tests.launch_shape import lib as choice_lib
-from tests.launch_shape import FUSED, GEMM, GENERAL, REDUCE, REDUCTION, SMALL, WIDE, column_align, copy_shape, launch_shape, start_offsets, tile_places
+from tests.launch_shape import FUSED, GEMM, GENERAL, REDUCE, REDUCTION, SMALL, WIDE, column_align, column_overlap, copy_shape, launch_shape, start_offsets, tile_places
 
 
 def _problem(M, W, K, tp, layout="nk", **kw):
@@ -259,3 +259,12 @@ def test_which_tiles_are_put_in_a_line():
     assert not in_line(_problem(534, 1048, 192, 2, flags=DIRECT)) and in_line(_problem(534, 1048, 256, 2, flags=DIRECT))
     assert not in_line(_problem(2131, 464, 640, 16)) and in_line(_problem(2131, 464, 640, 16, flags=DIRECT))
     assert in_line(_problem(2131, 448, 640, 16)) and in_line(_problem(2131, 464, 640, 16), GEMM)
+
+
+def test_overlap_cases_of_the_gpu_tests_are_what_they_say():
+    from tests.test_gpu_workgroup_tiles import OVERLAPS
+    for M, W, K, tp, layout, bf16, tile, tail, columns in OVERLAPS:
+        p = _problem(M, W, K, tp, layout, flags=DIRECT | (t3.T3_FLAG_FWD_BF16 if bf16 else 0), ldr=W * tp + 4)
+        s = launch_shape(p, FUSED)
+        assert (s.kernel, (s.tile_m, s.tile_n), s.tail_r, column_overlap(p)) == (WIDE, tile, tail, columns), (M, W, K, tp)
+        assert column_overlap(_problem(M, W, K, tp, layout)) == 0 and column_overlap(p, GEMM) == 0
