@@ -349,6 +349,7 @@ t3_status make_plan(const t3_problem *p, t3k::Call call, int need, const void *A
   *empty = shape.begin >= shape.limit;           // (no tiles, or an empty range of them)
 
   t3k::Plan &q = *plan;
+  q = t3k::Plan{};                               // (callers give memory with an earlier call's plan in it, and not every kernel has every field set)
   q.A = static_cast<const uint16_t *>(A);
   q.B = static_cast<const uint16_t *>(B);
   q.C = C;
@@ -382,8 +383,6 @@ t3_status make_plan(const t3_problem *p, t3k::Call call, int need, const void *A
   // if they stay in that L2 (half of its 4 MiB) they count once for all stages.  That is for small
   // tiles, which are in flight for several stages at a time: with large ones the slabs of B push A
   // out.  (A device with another number of XCDs takes the runs: order inside a stage is free.)
-  q.xcd_nbm = 0;
-  q.xcd_bmk = q.xcd_bnk = 0;
   const int64_t range_steps = tpc > 0 ? ceil_div(q.limit, tpc) - q.begin / tpc : 0;
   auto footprint = [&](double rows, double cols) {
     const bool stays = *tm < 128 && rows * (double)p->K * 2.0 <= 2.0 * (1 << 20);
@@ -410,12 +409,10 @@ t3_status make_plan(const t3_problem *p, t3k::Call call, int need, const void *A
   q.by_tpc = t3k::fast_div((uint32_t)(tpc > 0 ? tpc : 1));
   q.by_column = t3k::fast_div((uint32_t)(tpc == 0 ? 1 : (q.xcd_nbm ? q.xcd_bmk : Mt)));
 
-  q.agents = q.rows_per_agent = 0;
   const int64_t resident = shape.resident;
   q.stage0 = (int32_t)shape.stage0;
   q.total_blocks = (int32_t)shape.total_blocks;
   // Start-up phase offsets (see stagger_start); T3_STAGGER="groups,window_ns" overrides them ("0" turns them off).
-  q.stagger_blocks = q.stagger_groups = q.stagger_ticks = 0;
   {
     t3k::StartOffsets o = t3k::start_offsets(p, call, shape);
     const StaggerEnv &env = stagger_env();
@@ -457,7 +454,6 @@ t3_status make_plan(const t3_problem *p, t3k::Call call, int need, const void *A
   }
   q.wide = shape.kernel == t3k::kWideTile;
   if (q.wide) q.order = t3k::tile_order(p, call, shape, t3k::xcd_rows(shape, q.xcd_nbm ? q.xcd_bmk : 0, q.xcd_bnk));
-  q.overlap = q.granule = 0;
   if (q.wide) {
     q.granule = (p->flags & T3_FLAG_FWD_BF16) && fused_like ? 32 : 16;
     q.overlap = t3k::column_overlap(p, call, shape.tile, Wt);

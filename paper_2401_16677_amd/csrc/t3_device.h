@@ -87,7 +87,7 @@ struct Plan {
   int32_t sub_groups, sub_shift, whole_chunks;
   int32_t wide;                        // the wide-tile kernel serves the launch (host side only)
   uint32_t flags;
-  TileOrder order;                     // which tile a grid position is (wide-tile kernel; rows 0, and the other kernels: decode_block)
+  TileOrder order;                     // which tile a grid position is (wide-tile kernel; rows 0, as for all the other kernels: decode_block)
 };
 
 struct Tile {
