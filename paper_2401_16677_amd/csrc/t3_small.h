@@ -18,8 +18,12 @@
 
 namespace t3k {
 
-template <int BM, int BN, int WK, int NST, int MODE, int BKN, int AKM>
-__global__ __launch_bounds__(64 * WK) void small_tile_kernel(const Plan) {
+// WORDS: the plan by one vector request (PlanWords), where all workgroups of the launch start on argument lines nobody has touched.  Those that
+// take the place of finished ones find the lines in the scalar cache, and a request past it costs each of them 0.3 us (by scalar loads and
+// by vector: 24 x 12288 x 1536 on 8 chunks, 384 tiles of 32 x 32, 10.9 us, 10.8; 33 x 16000 x 256 on 2, 250 of 64 x 64,
+// 8.3, 8.1; 24 x 24576 x 1536 on 8, 768 of 32 x 32, 17.1, 17.7; 16 x 24576 x 4096 on 16 41.1, 42.4; 2097 x 1280 x 1472 on 32, 1056 of 64 x 64, 47.5, 48.1).
+template <int BM, int BN, int WK, int NST, int MODE, int BKN, int AKM, bool WORDS>
+__global__ __launch_bounds__(64 * WK) void small_tile_kernel(const Plan arg) {
   constexpr int FM = BM / 16, FN = BN / 16, KS = kBK / 32;
   constexpr int NA = BM / kRPC, NB = BN / kRPC, NL = NA + NB;     // 1-KiB copies per slab
   constexpr int kStageBytes = (BM + BN) * kRowBytes, kBOff = BM * kRowBytes;
@@ -31,13 +35,16 @@ __global__ __launch_bounds__(64 * WK) void small_tile_kernel(const Plan) {
 
   const int lane = threadIdx.x & 63;
   PlanWords words;
-  words.load(lane);
-  Plan p = words.now();
-  // (the generation is needed only when the tile is counted: nothing waits for it here)
-  uint32_t gen = 0;
-  if (MODE == kModeFused) gen = *(const __attribute__((address_space(4))) uint32_t *)(p.track + 2 * trk_bank_words(p.P));
+  if (WORDS) words.load(lane);
+  Plan p = arg;
+  if (WORDS) p = words.now();
   Tile tl;
   if (!decode_block(p, (int)blockIdx.x, tl)) return;
+  // The generation is needed only when the tile is counted: it is asked for behind the last wait for the argument, or the first
+  // copies would wait for its round trip to memory as well (9 x 16896 x 784 on 8 chunks 12.3 us, 12.7).  (Constant for as long as
+  // this kernel reads it: the launch's end, which changes it, waits for every workgroup's count.)
+  uint32_t gen = 0;
+  if (MODE == kModeFused) gen = *(const __attribute__((address_space(4))) uint32_t *)(p.track + 2 * trk_bank_words(p.P));
 
   const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
   const int m0 = tl.mi * BM, col_lo = tl.c * p.W, col_hi = col_lo + p.W, n0 = col_lo + tl.nj * BN;
@@ -246,7 +253,7 @@ __global__ __launch_bounds__(64 * WK) void small_tile_kernel(const Plan) {
     }
   }
   if (MODE == kModeFused) {
-    p = words.now();
+    if (WORDS) p = words.now();
     track_tile(p, trk_at(p, gen), tl, true);
   }
 }

@@ -6,16 +6,23 @@
 namespace t3k {
 namespace {
 
-template <int BM, int BN, int NST, bool NK = true>
+template <int BM, int BN, int NST, bool WORDS, bool NK>
 t3_status launch_small(const Plan &q, bool b_kn, bool a_km, hipStream_t s) {
   const dim3 grid((unsigned)q.total_blocks), block(256);
   if (b_kn)
-    return a_km ? launch(small_tile_kernel<BM, BN, 4, NST, T3_MODE, 1, 1>, grid, block, s, q)
-                : launch(small_tile_kernel<BM, BN, 4, NST, T3_MODE, 1, 0>, grid, block, s, q);
+    return a_km ? launch(small_tile_kernel<BM, BN, 4, NST, T3_MODE, 1, 1, WORDS>, grid, block, s, q)
+                : launch(small_tile_kernel<BM, BN, 4, NST, T3_MODE, 1, 0, WORDS>, grid, block, s, q);
   if constexpr (NK)
-    return a_km ? launch(small_tile_kernel<BM, BN, 4, NST, T3_MODE, 0, 1>, grid, block, s, q)
-                : launch(small_tile_kernel<BM, BN, 4, NST, T3_MODE, 0, 0>, grid, block, s, q);
+    return a_km ? launch(small_tile_kernel<BM, BN, 4, NST, T3_MODE, 0, 1, WORDS>, grid, block, s, q)
+                : launch(small_tile_kernel<BM, BN, 4, NST, T3_MODE, 0, 0, WORDS>, grid, block, s, q);
   return T3_ERR_UNSUPPORTED;
+}
+// (the plan by one vector request while all workgroups are on the chip at once: see small_tile_kernel)
+template <int BM, int BN, int NST, bool NK = true>
+t3_status launch_small(const Plan &q, bool b_kn, bool a_km, hipStream_t s) {
+  const int32_t at_once = q.resident * (BM == 32 && BN == 32 ? 2 : 1);
+  return q.total_blocks <= at_once ? launch_small<BM, BN, NST, true, NK>(q, b_kn, a_km, s)
+                                   : launch_small<BM, BN, NST, false, NK>(q, b_kn, a_km, s);
 }
 
 }  // namespace

@@ -68,6 +68,28 @@ def test_few_tokens_transposed(gpu, oracle, M, W, K, tp, layout):
     _check(gpu, oracle, M, W, K, tp, "direct", layout)
 
 
+# The small-tile kernel with exactly as many tiles as the chip holds at once, and with more: the latter take the argument another
+# way.  M, W, K, tp, layout, workgroup tile, tiles.  (A test without a GPU checks the last two.)
+ROUNDS = [
+    (8, 1000, 64, 16, "nk", (32, 32), 512),
+    (8, 1000, 64, 16, "km_kn", (32, 32), 512),
+    (8, 2072, 784, 8, "nk", (32, 32), 520),
+    (8, 2072, 1024, 8, "kn", (32, 32), 520),
+    (8, 2072, 1472, 8, "km_kn", (32, 32), 520),
+    (8, 2072, 2048, 8, "km_kn", (32, 64), 264),
+    (40, 968, 64, 16, "nk", (64, 64), 256),
+    (40, 2072, 1472, 8, "nk", (64, 64), 264),
+    (40, 2072, 1472, 8, "kn", (64, 64), 264),
+    (520, 8, 2048, 32, "km_kn", (64, 64), 288),
+]
+
+
+@pytest.mark.parametrize("mode", ["direct", "copy", "bf16", "unfused"])
+@pytest.mark.parametrize("M,W,K,tp,layout,tile,tiles", ROUNDS)
+def test_few_tokens_by_rounds(gpu, oracle, M, W, K, tp, layout, tile, tiles, mode):
+    _check(gpu, oracle, M, W, K, tp, mode, layout)
+
+
 # K: slabs of 64 from one to eight, whole and ragged.  Chunk widths: one 192 and one 256 column tile, the
 # same and 4 or 8 columns more or less.
 @pytest.mark.parametrize("K", [64, 128, 136, 192, 200, 256, 264, 328, 384, 392, 512])

@@ -89,6 +89,14 @@ def test_problems_of_the_gpu_tests_get_the_tiles_they_are_meant_for():
         assert (s.kernel, s.tile_m, s.tile_n, s.tail_r) == (SMALL if tile == (32, 64) else WIDE, *tile, tail_r), (case, mode)
 
 
+def test_cases_by_rounds_of_the_gpu_tests_are_what_they_say():
+    from tests.test_gpu_workgroup_tiles import ROUNDS
+    for M, W, K, tp, layout, tile, tiles in ROUNDS:
+        for call in (FUSED, GEMM):
+            s = launch_shape(_problem(M, W, K, tp, layout), call)
+            assert (s.kernel, s.tile_m, s.tile_n, s.blocks) == (SMALL, *tile, tiles), (M, W, K, tp)
+
+
 def test_granule_cases_of_the_gpu_tests_are_what_they_say():
     from tests.test_gpu_workgroup_tiles import GRANULE_MODES
     for case, mode in GRANULE_MODES:

@@ -16,6 +16,7 @@ import pytest
 
 from paper_2401_16677_amd import build as hip_build
 
+SMALL = [u for u in hip_build.UNITS if u[0] == "t3_small_launch.hip" and "-DT3_MODE=1" in u[2]]
 LAYOUTS = [u for u in hip_build.UNITS if u[0] == "t3_wide_launch.hip"]
 GENERAL = [u for u in hip_build.UNITS if u[0] == "t3_gemm_launch.hip"]
 API = [u for u in hip_build.UNITS if u[0] == "t3_api.hip"]
@@ -235,3 +236,20 @@ def test_all_gather_step_requests_a_batch_at_once(tmp_path):
         # write as many again with every launch)
         args = [int(m.group(1), 0) for line in lines for m in [re.match(r"\s*s_load_dword\S* \S+, s\[\d+:\d+\], (\w+)", line)] if m]
         assert args and max(args) < 48, (kernel, args)
+
+
+@pytest.mark.parametrize("unit", [u[1] for u in SMALL])
+def test_first_copies_do_not_wait_for_the_generation(unit, tmp_path):
+    """The small-tile kernel: one scalar load that is not of the argument, the tracker's generation, and no wait for scalar loads
+    between it and the first copies.  The instantiations that take the argument by vector have no other."""
+    kernels = _compile(str(tmp_path), [u for u in SMALL if u[1] == unit], "small_tile_kernel")[unit]
+    by_vector = 0
+    for kernel, lines in kernels.items():
+        text = [t for block, _ in _blocks(lines) for t, _ in block]
+        loads = [i for i, t in enumerate(text) if t.startswith("s_load")]
+        generation = [i for i in loads if ", s[0:1], " not in text[i]] or loads
+        by_vector += len(loads) == 1
+        copies = [i for i, t in enumerate(text) if t.startswith("global_load_lds")]
+        assert len(generation) == 1 and generation[0] < copies[0], kernel
+        assert not any(t.startswith("s_waitcnt") and "lgkmcnt" in t for t in text[generation[0]:copies[0]]), kernel
+    assert by_vector == len(kernels) // 2
