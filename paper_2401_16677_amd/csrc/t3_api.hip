@@ -27,7 +27,6 @@ using t3k::TileShape;
 // preference order of t3_default_tile
 constexpr TileShape kTileShapes[] = {{256, 256}, {256, 128}, {128, 256}, {128, 128}};
 constexpr int kNumTileShapes = sizeof(kTileShapes) / sizeof(kTileShapes[0]);
-constexpr int kNumXcd = 8;            // the XCD grouping of decode_tile is written for 8 XCDs
 constexpr int kDefaultCus = 256;       // compute units of an MI355X (host-only plan queries assume it)
 constexpr int kMaxDevices = 64;
 constexpr int kReleaseAgents = 32;     // release workgroups per chunk (t3_release_chunks)
@@ -337,7 +336,7 @@ t3_status make_plan(const t3_problem *p, t3k::Call call, int need, const void *A
   if (two_writers && T_t * split_k >= (1ll << 31)) return T3_ERR_UNSUPPORTED;
   if ((need & kNeedTwoWriters) && (need & kNeedC) && p->upstream_agents < 0) return T3_ERR_BAD_SHAPE;
 
-  DeviceFacts dev{kDefaultCus, kNumXcd};
+  DeviceFacts dev{kDefaultCus, t3k::kNumXcd};
   if (T_t) {                                     // (nothing is launched otherwise: no device needed)
     st = device_facts(&dev);
     if (st != T3_OK) return st;
@@ -377,33 +376,11 @@ t3_status make_plan(const t3_problem *p, t3k::Call call, int need, const void *A
   q.tracked = (int32_t)shape.tracked_tpc;
   q.flags = fused_like ? p->flags : 0u;
 
-  // XCD grouping: split a stage's Mt x Wt tiles into 8 equal blocks, one per XCD, or, where they do
-  // not split or that is better, into 8 runs down the tile columns (see decode_tile).  What counts is
-  // how many A rows and B columns an XCD's L2 pulls; the A rows are the same ones in every stage, so
-  // if they stay in that L2 (half of its 4 MiB) they count once for all stages.  That is for small
-  // tiles, which are in flight for several stages at a time: with large ones the slabs of B push A
-  // out.  (A device with another number of XCDs takes the runs: order inside a stage is free.)
+  const t3k::XcdBlocks blocks = t3k::xcd_blocks(p, shape, dev.xcds);
+  q.xcd_nbm = blocks.by_rows;
+  q.xcd_bmk = blocks.rows;
+  q.xcd_bnk = blocks.columns;
   const int64_t range_steps = tpc > 0 ? ceil_div(q.limit, tpc) - q.begin / tpc : 0;
-  auto footprint = [&](double rows, double cols) {
-    const bool stays = *tm < 128 && rows * (double)p->K * 2.0 <= 2.0 * (1 << 20);
-    return (stays && range_steps > 1 ? rows / (double)range_steps : rows) + cols;
-  };
-  double best = -1.0;
-  if (*tm < 128 && tpc > 0) {
-    const double run = (double)ceil_div(tpc, kNumXcd);
-    best = run >= (double)Mt ? footprint((double)p->M, (run / (double)Mt + 0.5) * *tn) : footprint(run * *tm, 1.5 * *tn);
-  }
-  for (int nbm = 1; nbm <= kNumXcd && dev.xcds == kNumXcd; nbm *= 2) {
-    const int nbn = kNumXcd / nbm;
-    if (Mt % nbm || Wt % nbn) continue;
-    const double foot = footprint((double)(Mt / nbm) * *tm, (double)(Wt / nbn) * *tn);
-    if (best < 0 || foot < best) {
-      best = foot;
-      q.xcd_nbm = nbm;
-      q.xcd_bmk = (int32_t)(Mt / nbm);
-      q.xcd_bnk = (int32_t)(Wt / nbn);
-    }
-  }
 
   // (an empty problem has no tiles to divide by)
   q.by_tpc = t3k::fast_div((uint32_t)(tpc > 0 ? tpc : 1));
@@ -453,8 +430,8 @@ t3_status make_plan(const t3_problem *p, t3k::Call call, int need, const void *A
     q.timeline_wgs = (int32_t)(wgs > (1ll << 30) ? (1ll << 30) : wgs);
   }
   q.wide = shape.kernel == t3k::kWideTile;
-  if (q.wide) q.order = t3k::tile_order(p, call, shape, t3k::xcd_rows(shape, q.xcd_nbm ? q.xcd_bmk : 0, q.xcd_bnk));
   if (q.wide) {
+    q.order = t3k::tile_order(p, call, shape, t3k::xcd_rows(shape, blocks));
     q.granule = (p->flags & T3_FLAG_FWD_BF16) && fused_like ? 32 : 16;
     q.overlap = t3k::column_overlap(p, call, shape.tile, Wt);
   }

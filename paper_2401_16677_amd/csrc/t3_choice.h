@@ -18,6 +18,7 @@ struct TileShape {
 enum Call { kCallFused, kCallGemm, kCallReduce, kCallOther };
 enum Kernel { kGeneralTile, kWideTile, kSmallTile, kReduction };   // t3_gemm.h, t3_wide.h, t3_small.h, t3_aux.h
 
+constexpr int kNumXcd = 8;            // the XCD grouping of decode_tile is written for 8 XCDs
 constexpr int kTailMinSlabs = 8;      // K-slabs of 64 a tile needs before a balanced tail splits it
 constexpr int kTailSlots = 256;       // tiles a balanced tail can split (flag words behind the tracker state)
 constexpr int kReduceThreads = 256;   // threads of a reduction workgroup
@@ -230,17 +231,51 @@ inline LaunchShape launch_shape(const t3_problem *p, Call call, TileShape tracke
   return s;
 }
 
+// XCD grouping: a stage's Mt x Wt tiles in 8 equal blocks, one per XCD, or, where they do
+// not split or that is better, in 8 runs down the tile columns (see decode_tile).  What counts is
+// how many A rows and B columns an XCD's L2 pulls; the A rows are the same ones in every stage, so
+// if they stay in that L2 (half of its 4 MiB) they count once for all stages.  That is for small
+// tiles, which are in flight for several stages at a time: with large ones the slabs of B push A
+// out.  (A device with another number of XCDs takes the runs: order inside a stage is free.)
+struct XcdBlocks {
+  int32_t by_rows, rows, columns;      // blocks a tile column is cut into (0: runs), tiles of a block
+};
+inline XcdBlocks xcd_blocks(const t3_problem *p, const LaunchShape &s, int xcds) {
+  XcdBlocks b{0, 0, 0};
+  if (s.tpc <= 0) return b;
+  const int64_t steps = ceil_div(s.limit, s.tpc) - s.begin / s.tpc;
+  auto footprint = [&](double rows, double cols) {
+    const bool stays = s.tile.m < 128 && rows * (double)p->K * 2.0 <= 2.0 * (1 << 20);
+    return (stays && steps > 1 ? rows / (double)steps : rows) + cols;
+  };
+  double best = -1.0;
+  if (s.tile.m < 128) {
+    const double run = (double)ceil_div(s.tpc, kNumXcd);
+    best = run >= (double)s.Mt ? footprint((double)p->M, (run / (double)s.Mt + 0.5) * s.tile.n) : footprint(run * s.tile.m, 1.5 * s.tile.n);
+  }
+  for (int nbm = 1; nbm <= kNumXcd && xcds == kNumXcd; nbm *= 2) {
+    const int nbn = kNumXcd / nbm;
+    if (s.Mt % nbm || s.Wt % nbn) continue;
+    const double foot = footprint((double)(s.Mt / nbm) * s.tile.m, (double)(s.Wt / nbn) * s.tile.n);
+    if (best < 0 || foot < best) {
+      best = foot;
+      b = {nbm, (int32_t)(s.Mt / nbm), (int32_t)(s.Wt / nbn)};
+    }
+  }
+  return b;
+}
+
 // Tiles an XCD works on in step: an eighth of a round, or half of that with a balanced tail, whose two halves of the workgroups are
 // half a tile apart.
 inline int64_t xcd_run(const LaunchShape &s) {
   const int64_t round = s.total_blocks < s.resident ? s.total_blocks : s.resident, run = s.tail_r ? round / 16 : round / 8;
   return run < 1 ? 1 : run;
 }
-// The rows of A and of B it pulls for them stage by stage, in blocks of so many tiles (0: runs down the columns).
-inline double xcd_rows(const LaunchShape &s, int64_t block_rows, int64_t block_columns) {
+// The rows of A and of B it pulls for them stage by stage.
+inline double xcd_rows(const LaunchShape &s, const XcdBlocks &blocks) {
   const double stages = 8.0 * (double)xcd_run(s) / (double)s.tpc;
-  double rows = (double)block_rows, columns = (double)block_columns;
-  if (!block_rows) {
+  double rows = (double)blocks.rows, columns = (double)blocks.columns;
+  if (!blocks.by_rows) {
     const double run = (double)s.tpc / 8.0, all = (double)s.Mt;
     rows = run < all ? (run < 1.0 ? 1.0 : run) : all;
     columns = run / all + 0.5 > 1.0 ? run / all + 0.5 : 1.0;

@@ -45,6 +45,19 @@ extern "C" int tile_places(const t3_problem *p, int call, int tracked_m, int tra
   return (int)o.width_log2 + (o.rows ? 1 : 0);
 }
 
+// The order the library takes: columns of a band, or 0 stage by stage; and of blocks (0: runs), tile rows and columns of one.
+extern "C" int tile_order(const t3_problem *p, int call, int tracked_m, int tracked_n, int cus, int xcds, int32_t *blocks) {
+  const t3k::Call c = static_cast<t3k::Call>(call);
+  const t3k::LaunchShape s = t3k::launch_shape(p, c, {tracked_m, tracked_n}, cus);
+  const t3k::XcdBlocks b = t3k::xcd_blocks(p, s, xcds);
+  blocks[0] = b.by_rows;
+  blocks[1] = b.rows;
+  blocks[2] = b.columns;
+  if (s.kernel != t3k::kWideTile) return 0;
+  const t3k::TileOrder o = t3k::tile_order(p, c, s, t3k::xcd_rows(s, b));
+  return o.rows ? 1 << o.width_log2 : 0;
+}
+
 extern "C" void divide(const uint32_t *n, const uint32_t *d, uint32_t *out, int count) {
   for (int i = 0; i < count; ++i) out[i] = t3k::div_by(n[i], t3k::fast_div(d[i]));
 }

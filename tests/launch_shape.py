@@ -81,6 +81,15 @@ def tile_places(p, call=FUSED, cus=CUS, now=1e9):
     return ([tuple(out[3 * i:3 * i + 3]) for i in range(shape.blocks)], 1 << (width - 1)) if width else (None, 0)
 
 
+def tile_order(p, call=FUSED, cus=CUS, xcds=8):
+    """What the library decides: columns of a band of tiles in a line, or 0 stage by stage; blocks a stage is cut into by rows (0: runs),
+    tile rows and columns of one."""
+    tracked = (p.tile_m, p.tile_n) if p.tile_m else t3.t3_default_tile(p)
+    blocks = (ctypes.c_int32 * 3)()
+    width = lib().tile_order(ctypes.byref(p), call, *tracked, cus, xcds, blocks)
+    return width, tuple(blocks)
+
+
 def column_overlap(p, call=FUSED, cus=CUS):
     tracked = (p.tile_m, p.tile_n) if p.tile_m else t3.t3_default_tile(p)
     return lib().column_overlap(ctypes.byref(p), call, *tracked, cus)

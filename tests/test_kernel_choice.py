@@ -6,7 +6,7 @@ import pytest
 
 from paper_2401_16677_amd import binding as t3
 from tests.launch_shape import lib as choice_lib
-from tests.launch_shape import FUSED, GEMM, GENERAL, REDUCE, REDUCTION, SMALL, WIDE, column_align, column_overlap, copy_shape, launch_shape, start_offsets, tile_places
+from tests.launch_shape import FUSED, GEMM, GENERAL, REDUCE, REDUCTION, SMALL, WIDE, column_align, column_overlap, copy_shape, launch_shape, start_offsets, tile_order, tile_places
 
 
 def _problem(M, W, K, tp, layout="nk", **kw):
@@ -276,3 +276,34 @@ def test_overlap_cases_of_the_gpu_tests_are_what_they_say():
         s = launch_shape(p, FUSED)
         assert (s.kernel, (s.tile_m, s.tile_n), s.tail_r, column_overlap(p)) == (WIDE, tile, tail, columns), (M, W, K, tp)
         assert column_overlap(_problem(M, W, K, tp, layout)) == 0 and column_overlap(p, GEMM) == 0
+
+
+@pytest.mark.parametrize("name,order,blocks", [
+    # tile columns of a band (0: stage by stage), blocks a stage is cut into by rows, tile rows and columns of one
+    ("gpt3_outproj", 0, (4, 4, 3)),
+    ("gpt3_fc2", 0, (4, 4, 3)),
+    ("wide_fc2", 4, (4, 2, 5)),
+    ("hightp_outproj", 0, (8, 4, 6)),
+    ("palm_outproj_tp32", 8, (8, 1, 3)),
+    ("tnlg_fc2_tp8", 0, (8, 4, 3)),
+    ("megagpt2_fc2_tp8", 0, (8, 8, 2)),
+])
+def test_order_of_the_named_workloads(name, order, blocks):
+    """As the library decides it: from the blocks a stage would be cut into otherwise, and what an XCD pulls for them."""
+    from paper_2401_16677_amd import workloads as wl
+    w = wl.WORKLOADS[name]
+    p = _problem(w.M, w.N // w.tp, w.K, w.tp, flags=DIRECT)
+    assert tile_order(p) == (order, blocks)
+    assert tile_order(p, xcds=4)[1] == (0, 0, 0)             # (runs on a device of other XCDs)
+
+
+@pytest.mark.parametrize("sizes,order,blocks", [
+    ((700, 128, 392, 16), 4, (0, 0, 0)),                     # runs, several stages a round
+    ((8689, 840, 1120, 4), 4, (0, 0, 0)),
+    ((841, 264, 5328, 32), 1, (4, 1, 1)),                    # blocks of one tile
+    ((2048, 640, 4096, 32), 4, (8, 1, 3)),                   # of one row
+    ((2048, 2816, 4096, 8), 4, (8, 1, 11)),
+    ((4096, 2048, 2048, 4), 0, (4, 4, 4)),                   # square ones
+])
+def test_order_by_what_an_xcd_pulls(sizes, order, blocks):
+    assert tile_order(_problem(*sizes, flags=DIRECT)) == (order, blocks)
