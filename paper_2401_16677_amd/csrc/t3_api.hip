@@ -431,7 +431,7 @@ t3_status make_plan(const t3_problem *p, t3k::Call call, int need, const void *A
   }
   q.wide = shape.kernel == t3k::kWideTile;
   if (q.wide) {
-    q.order = t3k::tile_order(p, call, shape, t3k::xcd_rows(shape, blocks));
+    q.order = t3k::tile_order(p, call, shape, t3k::xcd_rows(p, call, shape, blocks));
     q.granule = (p->flags & T3_FLAG_FWD_BF16) && fused_like ? 32 : 16;
     q.overlap = t3k::column_overlap(p, call, shape.tile, Wt);
   }

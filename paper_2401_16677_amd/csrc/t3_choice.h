@@ -271,14 +271,22 @@ inline int64_t xcd_run(const LaunchShape &s) {
   const int64_t round = s.total_blocks < s.resident ? s.total_blocks : s.resident, run = s.tail_r ? round / 16 : round / 8;
   return run < 1 ? 1 : run;
 }
-// The rows of A and of B it pulls for them stage by stage.
-inline double xcd_rows(const LaunchShape &s, const XcdBlocks &blocks) {
+// The rows of A and of B it pulls for them stage by stage.  An XCD's A rows are the same ones in every stage of blocks; the plain GEMM,
+// which pulls and stores little else, keeps them in its L2 of 4 MiB where they fit.  With a balanced tail, whose two halves of the
+// workgroups would each pull their own in a line, they are counted once for the launch: stage by stage and in a line, 2048 x 20480 x K on 8 chunks,
+// blocks of 2 x 5, K of 1536 134.7, 138.7; 3072 218.9, 225.7; 4096 273.6, 275.3; 10240, where they do not fit, 694, 681 (fused 144.6, 142.7;
+// 235.1, 231.7; 283.9, 287.1; 708, 694); 3920 x 13248 x 560 on 8 93.7, 103.3; 4096 x 10752 x 1168 on 4 135.0, 144.1; over 20 shapes 1.2 %,
+// with the reduction 0.8.  (Without a tail the line is 2.5 % ahead over 20 shapes, 0.4 behind with the reduction.)
+constexpr int64_t kXcdCacheBytes = 4ll << 20;
+inline double xcd_rows(const t3_problem *p, Call call, const LaunchShape &s, const XcdBlocks &blocks) {
   const double stages = 8.0 * (double)xcd_run(s) / (double)s.tpc;
   double rows = (double)blocks.rows, columns = (double)blocks.columns;
   if (!blocks.by_rows) {
     const double run = (double)s.tpc / 8.0, all = (double)s.Mt;
     rows = run < all ? (run < 1.0 ? 1.0 : run) : all;
     columns = run / all + 0.5 > 1.0 ? run / all + 0.5 : 1.0;
+  } else if (call == kCallGemm && s.tail_r && (int64_t)blocks.rows * s.tile.m * p->K * 2 <= kXcdCacheBytes) {
+    rows *= (double)s.resident / (double)s.total_blocks;
   }
   return rows * s.tile.m + columns * (stages > 1.0 ? stages : 1.0) * s.tile.n;
 }

@@ -54,7 +54,7 @@ extern "C" int tile_order(const t3_problem *p, int call, int tracked_m, int trac
   blocks[1] = b.rows;
   blocks[2] = b.columns;
   if (s.kernel != t3k::kWideTile) return 0;
-  const t3k::TileOrder o = t3k::tile_order(p, c, s, t3k::xcd_rows(s, b));
+  const t3k::TileOrder o = t3k::tile_order(p, c, s, t3k::xcd_rows(p, c, s, b));
   return o.rows ? 1 << o.width_log2 : 0;
 }
 

@@ -307,3 +307,12 @@ def test_order_of_the_named_workloads(name, order, blocks):
 ])
 def test_order_by_what_an_xcd_pulls(sizes, order, blocks):
     assert tile_order(_problem(*sizes, flags=DIRECT)) == (order, blocks)
+
+
+@pytest.mark.parametrize("K,fused,gemm", [(1536, 4, 0), (4096, 4, 0), (4160, 4, 4), (10240, 4, 4)])
+def test_plain_gemm_keeps_its_rows_of_a(K, fused, gemm):
+    """Blocks of 2 x 5 tiles over two and a half rounds, a balanced tail: A rows that fit an XCD's L2 are pulled once by the plain GEMM."""
+    p = _problem(2048, 2560, K, 8, flags=DIRECT)
+    assert (tile_order(p)[0], tile_order(p, GEMM)[0]) == (fused, gemm)
+    no_tail = _problem(2048, 2560, K, 8, tile_limit=3 * t3.t3_tiles_per_chunk(p))
+    assert tile_order(no_tail)[0] == tile_order(no_tail, GEMM)[0]
