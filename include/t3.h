@@ -121,9 +121,11 @@ typedef struct {
  * tpc = Mt*Wt tiles per chunk, T = tp*tpc tiles in all.  Issue index t in [0,T) names
  * stage s = t / tpc (the GEMM "stage" of Sec. 2.5, one per ring step), chunk
  * c = order[s], and inside the chunk q = t % tpc, tile row mi = q % Mt, tile column
- * nj = q / Mt.  Workgroups are launched in issue order up to a permutation inside a
- * stage, or among the tiles the device works on at a time, that groups tiles sharing operands on
- * one XCD.
+ * nj = q / Mt.  Workgroups are launched in issue order up to a permutation that groups tiles
+ * sharing operands on one XCD: inside a stage, or, where a launch over whole ring steps gains by
+ * it, among tiles up to one round (as many as the device holds workgroups) apart, of several
+ * stages.  A chunk is then complete in the round it would be in issue order or the one behind
+ * it, and tiles of later chunks may be done before.
  *
  * Supported (tile_m, tile_n): (256,256), (256,128), (128,256), (128,128).
  *

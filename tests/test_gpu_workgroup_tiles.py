@@ -316,3 +316,37 @@ def test_direct_results_do_not_depend_on_where_the_buffers_start(gpu, M, W, K, t
         first = first or got
         for name, x, y in zip(("R", "fwd"), got, first):
             assert np.array_equal(x, y), (name, ld, off, int((x != y).sum()))
+
+
+# Tiles in a line: bands of one to eight tile columns, a last band of fewer, in one round and in several, with a balanced tail, with
+# overlapping columns, bands larger than a round, ranges that begin at a later ring step.  M, W, K, tp, layout, first step, bfloat16 slots, workgroup
+# tile, tiles the tail splits, columns of overlap, columns of a band, of the last one if it has fewer.  (A test without a GPU checks the last five.)
+LINES = [
+    (523, 16, 272, 32, "nk", 0, False, (128, 128), 0, 0, 1, 0),
+    (712, 68, 296, 11, "nk", 0, False, (128, 128), 0, 0, 2, 1),
+    (561, 160, 256, 11, "nk", 0, False, (128, 128), 0, 0, 4, 2),
+    (2555, 16, 264, 15, "nk", 0, False, (128, 128), 0, 0, 8, 7),
+    (4429, 16, 256, 15, "kn", 0, False, (128, 128), 0, 0, 8, 7),
+    (4429, 16, 256, 18, "nk", 3, False, (128, 128), 0, 0, 8, 7),
+    (2246, 160, 664, 15, "nk", 0, False, (128, 192), 14, 0, 4, 3),
+    (2246, 160, 664, 18, "nk", 3, False, (128, 192), 14, 0, 4, 3),
+    (2945, 208, 264, 11, "nk", 0, True, (256, 256), 0, 0, 4, 3),
+    (535, 136, 256, 11, "nk", 0, True, (128, 128), 0, 24, 4, 2),
+    (7464, 264, 512, 3, "km_kn", 0, False, (128, 192), 98, 8, 4, 2),
+    (2208, 16, 512, 32, "km_kn", 1, False, (256, 128), 23, 0, 4, 3),
+    (11112, 688, 512, 1, "km_kn", 0, False, (128, 192), 92, 0, 4, 0),
+    (22752, 280, 320, 2, "km_kn", 0, False, (128, 192), 0, 8, 2, 0),
+]
+LINE_MODES = [(case, mode) for case in LINES for mode in ("direct", "copy", "unfused", "bf16")
+              if (mode == "bf16") == case[6] and (mode != "copy" or case[1] % 32 == 0) and (mode != "unfused" or case[4] == "nk")]
+
+
+def line_range(case):
+    M, W, K, tp = case[:4]
+    return case[5] * t3.t3_tiles_per_chunk(t3.problem(M, W * tp, K, tp, 0, 0, 0))
+
+
+@pytest.mark.parametrize("case,mode", LINE_MODES)
+def test_tiles_in_a_line(gpu, oracle, case, mode):
+    M, W, K, tp, layout = case[:5]
+    _check(gpu, oracle, M, W, K, tp, mode, layout, begin=line_range(case))

@@ -256,6 +256,29 @@ def test_tiles_in_a_line():
     assert lines > 150
 
 
+def test_chunks_in_a_line_are_complete_no_more_than_a_round_later():
+    """As the header has it: a tile is worked on in its stage, or a round from where it would be in issue order, and so is a chunk's last."""
+    rng = np.random.default_rng(12)
+    later, chunks = 0, 0
+    for _ in range(400):
+        M, W, K = (int(round(np.exp(rng.uniform(np.log(a), np.log(b))))) for a, b in ((128, 16384), (32, 4096), (256, 4096)))
+        p = _problem(M, max(4, W // 4 * 4), K // 8 * 8, int(rng.integers(1, 33)), flags=DIRECT)
+        shape = launch_shape(p)
+        if shape.kernel != WIDE or not 0 < shape.blocks <= 40000 or not tile_order(p)[0]:
+            continue
+        places, _ = tile_places(p)
+        Mt = -(-M // shape.tile_m)
+        index = np.array([s * shape.tpc + c * Mt + r for s, r, c in places])         # issue index of every position
+        here, there = np.arange(index.size) // shape.resident, index // shape.resident
+        inside = np.arange(index.size) // shape.tpc == index // shape.tpc
+        assert np.all(inside | (abs(here - there) <= 1)), p
+        ends = np.array([here[index // shape.tpc == s].max() for s in range(index.size // shape.tpc)])
+        due = (np.arange(1, ends.size + 1) * shape.tpc - 1) // shape.resident
+        assert np.all(ends <= due + 1), p
+        later, chunks = later + int((ends > due).sum()), chunks + ends.size
+    assert 0 < later < 0.05 * chunks
+
+
 def test_which_tiles_are_put_in_a_line():
     in_line = lambda p, call=FUSED, now=1e9: tile_places(p, call, now=now)[0] is not None
     wide = (2048, 2560, 10240, 8)                # a balanced tail: 8 bands of 256 rows in a line, in runs of 16
@@ -316,3 +339,18 @@ def test_plain_gemm_keeps_its_rows_of_a(K, fused, gemm):
     assert (tile_order(p)[0], tile_order(p, GEMM)[0]) == (fused, gemm)
     no_tail = _problem(2048, 2560, K, 8, tile_limit=3 * t3.t3_tiles_per_chunk(p))
     assert tile_order(no_tail)[0] == tile_order(no_tail, GEMM)[0]
+
+
+def test_line_cases_of_the_gpu_tests_are_what_they_say():
+    from tests.test_gpu_workgroup_tiles import LINE_MODES, MODES, line_range
+    larger = 0
+    for case, mode in LINE_MODES:
+        M, W, K, tp, layout, first, _, tile, tail, overlap, width, rest = case
+        p = _problem(M, W, K, tp, layout, flags=MODES[mode], tile_begin=line_range(case))
+        call = GEMM if mode == "unfused" else FUSED
+        s = launch_shape(p, call)
+        assert (s.kernel, (s.tile_m, s.tile_n), s.tail_r, s.begin) == (WIDE, tile, tail, first * s.tpc), (case, mode)
+        assert tile_order(p, call)[0] == width and s.blocks // -(-M // s.tile_m) % width == rest, (case, mode)
+        assert column_overlap(p, call) == (overlap if mode in ("direct", "bf16") else 0), (case, mode)
+        larger += -(-M // s.tile_m) * width > s.resident
+    assert larger >= 2
