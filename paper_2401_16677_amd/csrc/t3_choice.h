@@ -339,7 +339,7 @@ inline TileOrder tile_order(const t3_problem *p, Call call, const LaunchShape &s
     const int64_t in_rows = ceil_div(tiles, width), rows = in_rows < s.Mt ? in_rows : s.Mt;
     return (double)(rows * s.tile.m + ceil_div(in_rows, s.Mt) * width * s.tile.n);
   };
-  for (uint32_t log2 = 0; log2 <= 5; ++log2) {
+  for (uint32_t log2 = 0; log2 <= 3; ++log2) {       // (runs are of 64 tiles at most: no wider band needs fewer rows)
     const int64_t width = 1ll << log2;
     if (log2 && (width > columns || (s.Mt * width > round && s.Wt % width))) continue;
     // (of equal ones the one whose halves are small too: workgroups drift)
