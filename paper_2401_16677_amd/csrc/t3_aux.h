@@ -109,7 +109,7 @@ __global__ __launch_bounds__(kThreads) void reduce_tile_kernel(const Plan arg) {
   if (WORDS) words.load((int)(threadIdx.x & 63));
   Plan p = arg;
   if (WORDS) p = words.now();
-  const uint32_t gen = *(const __attribute__((address_space(4))) uint32_t *)(p.track + 2 * trk_bank_words(p.P));
+  uint32_t gen = *(const __attribute__((address_space(4))) uint32_t *)(p.track + 2 * trk_bank_words(p.P));
   Tile tl;
   if (!decode_block(p, blockIdx.x, tl)) return;
   const bool store_only = (p.flags & kFlagStep0StoreOnly) && tl.s == 0;
@@ -125,6 +125,9 @@ __global__ __launch_bounds__(kThreads) void reduce_tile_kernel(const Plan arg) {
     reduce_tile<1, true, false, ONE>(p, tl, store_only);
   }
   if (WORDS) p = words.now();
+  // (Read as constant memory, which it is until this workgroup's tile is counted.  Behind that another workgroup may end the launch and
+  // change it, in a range that cuts a ring step while this one still has a chunk to publish: the compiler may not read it again there.)
+  asm volatile("" : "+s"(gen));
   track_tile(p, trk_at(p, gen), tl, p.whole_chunks != 0);
 }
 

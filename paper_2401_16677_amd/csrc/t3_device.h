@@ -332,8 +332,9 @@ __device__ inline bool work_item(const Plan &p, int it, int &blk, int &part, int
 __device__ inline void stagger_start(const Plan &p) {
   const int b = blockIdx.x;
   if (b >= p.stagger_blocks) return;
-  // (workgroups of an XCD that share a row of tiles are in one group, in a line as in blocks: 8689 x 840 x 1120 on 4 chunks
-  // 115.3 us with a band's columns in groups, 113.1 with its rows)
+  // (In a line, workgroups of an XCD that share a row of tiles are in one group: 8689 x 840 x 1120 on 4 chunks 115.3 us with a
+  // band's columns in groups, 113.1 with its rows.  In blocks, tiles down the columns, a row's are in one group where the groups divide the
+  // block's rows, four groups on blocks of 4 x 3; eight groups on blocks of 4 x 6 have a row in two.)
   const int grp = (((b >> 3) >> p.order.width_log2) + (b >> 8)) % p.stagger_groups;
   if (!grp) return;
   const uint64_t t0 = wall_clock64(), wait = (uint64_t)grp * (uint64_t)p.stagger_ticks;

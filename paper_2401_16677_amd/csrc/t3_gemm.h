@@ -132,7 +132,7 @@ void gemm_tile_kernel(const Plan p) {
 
   __shared__ __attribute__((aligned(1024))) char lds[NSTAGE * kStageBytes];
 
-  // Persistent workgroups: workgroup w takes grid positions w, w + gridDim.x, ... in order.  The tracking of a finished tile is
+  // Persistent workgroups: workgroup w takes grid positions w, w + p.resident, ... in order (see work_item).  The tracking of a finished tile is
   // deferred into the next tile: by the first barrier of that tile's main loop every
   // wavefront has waited for its stores (they are older than the slab copies waited for
   // there), so the acknowledgement wait costs nothing.

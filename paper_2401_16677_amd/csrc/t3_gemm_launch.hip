@@ -9,7 +9,8 @@ namespace {
 
 template <int MODE, int BKN, int AKM>
 t3_status launch_gemm_layout(const Plan &q, int32_t tm, int32_t tn, hipStream_t s) {
-  // Persistent workgroups: as many as the chip holds at once, each walking the grid positions.
+  // Persistent workgroups: as many as the chip holds at once, each walking the grid positions.  (work_item strides by
+  // q.resident: a smaller grid would leave positions out)
   const int64_t positions = (int64_t)q.total_blocks * (MODE == kModeFused ? q.split_k : 1);
   const dim3 grid((unsigned)(positions > q.resident ? q.resident : positions));
   // K-slabs of 64 everywhere.  256 x 256: 8 wavefronts of 128 x 64, two 64-KiB stages; 256 x 128 and

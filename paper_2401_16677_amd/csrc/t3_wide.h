@@ -116,7 +116,7 @@ void wide_tile_kernel(const Plan) {
   constexpr int kImgBytes = 2 * 16 * BN * 4, kImgOff = NSTAGE * kStageBytes;
   static_assert(kImgOff + NIMG * kImgBytes <= 160 * 1024 && (NSTAGE == 2 || NSTAGE == 3), "LDS");
   constexpr bool kOneWave = kImgOff + NIMG * kImgBytes > 80 * 1024;     // per SIMD: 512 registers
-  static_assert(PRE <= DEPTH && DEPTH <= FM && NL + PRE * FN < 64, "");
+  static_assert(PRE > 0 && PRE <= DEPTH && DEPTH <= FM && NL + PRE * FN < 64, "");
   __shared__ __attribute__((aligned(1024))) char lds[kImgOff + NIMG * kImgBytes];
 
   constexpr bool tracked = MODE == kModeFused;
@@ -125,7 +125,8 @@ void wide_tile_kernel(const Plan) {
   words.load(lane);
   Plan p = words.now();                          // (read anew where something rare begins)
   // The tracker's generation, a scalar load nothing waits for until a tile is counted.  (Waited for here it puts a round trip
-  // to memory in front of the first slabs.)
+  // to memory in front of the first slabs.)  It is read as constant memory, which it is while this workgroup reads it: the launch's
+  // end, which changes it, waits for every workgroup's last count.
   uint32_t gen = 0u;
   if (tracked) gen = *(const __attribute__((address_space(4))) uint32_t *)(p.track + 2 * trk_bank_words(p.P));
   if (p.stagger_groups > 1) stagger_start(p);
@@ -176,8 +177,8 @@ void wide_tile_kernel(const Plan) {
   // stage: eight rows of 64 K-contiguous bf16, or k-rows of a transposed operand (layouts and
   // swizzles as in gemm_tile_kernel).  off*: this lane's byte offsets from where the tile starts in the
   // operand, which is where the piece's descriptor points: from one piece to the next only the descriptors
-  // change, in scalar registers (and, transposed, which columns lie outside), and a K-contiguous operand may be of
-  // any size.
+  // change, in scalar registers (and, transposed, which columns lie outside), and a K-contiguous operand may be as large as the
+  // host takes one: fewer than 2^31 elements, so that a tile's start is a 32-bit product.
   uint32_t offA[NA], offB[NB];
   constexpr int kARow = BM * 2, kBRow = BN * 2;  // bytes of a k-row of a transposed operand's region
   auto sw_mask = [](int blocks) { return (blocks % 8 == 0 ? 8 : 4) - 1; };
@@ -518,7 +519,7 @@ void wide_tile_kernel(const Plan) {
         }
       }
     };
-    // Byte offsets of the UB accesses in rows of `ld` elements of `size` bytes (access u is rows_u rows on where a row is a part of one)
+    // Byte offsets of the UB accesses in rows of `ld` elements of `size` bytes (where 64 lanes are whole rows, access u is u * 64 / kRowCh rows behind access 0)
     auto offsets = [&](int l, uint32_t ld, uint32_t size, const bool (&in)[UB], uint32_t (&at)[UB]) {
       const uint32_t at0 = ((uint32_t)lane_row(l, 0) * ld + (uint32_t)lane_col(l, 0)) * size;
 #pragma unroll
@@ -630,7 +631,6 @@ void wide_tile_kernel(const Plan) {
       constexpr bool add = decltype(ADD)::value;
       const uint32_t ld_out = to.ld_out, W = (uint32_t)p.W;
       if constexpr (add && tracked) {
-        if (has_in && PRE == 0) in_here(to);
         if (has_in) static_for<DEPTH - PRE>([&](auto I) { load_in(std::integral_constant<int, decltype(I)::value + PRE>{}); });
         else static_for<DEPTH>(zero_in);
       } else if constexpr (add) {

@@ -10,7 +10,8 @@ namespace t3k {
 #define T3_WIDE(...) launch(wide_tile_kernel<__VA_ARGS__, T3_MODE, T3_BKN, T3_AKM, T3_OVERLAP>, grid, dim3(256), s, q)
 
 t3_status T3_LAUNCHER(const Plan &q, int32_t tm, int32_t tn, hipStream_t s) {
-  // persistent workgroups: as many as the chip holds at once
+  // persistent workgroups: as many as the chip holds at once (work_item strides by q.resident: a smaller grid would leave
+  // positions out, and with a balanced tail the halves of its tiles)
   const dim3 grid((unsigned)(q.total_blocks > q.resident ? q.resident : q.total_blocks));
   if (tm == 256 && tn == 256) return T3_WIDE(8, 8, 2, 1, 1, 2);
   if (tm == 256 && tn == 192) return T3_WIDE(8, 6, 2, 2, 2, 5);
