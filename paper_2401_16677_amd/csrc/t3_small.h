@@ -38,13 +38,18 @@ __global__ __launch_bounds__(64 * WK) void small_tile_kernel(const Plan arg) {
   if (WORDS) words.load(lane);
   Plan p = arg;
   if (WORDS) p = words.now();
+  // The generation is needed only when the tile is counted.  By scalar loads it is asked for behind the last wait for the argument, or the
+  // first copies would wait for its round trip to memory as well (9 x 16896 x 784 on 8 chunks 12.3 us, 12.7); with the argument by vector nothing
+  // waits, and its address is out of the way.  (Constant for as long as this kernel reads it: the launch's end, which changes it, waits
+  // for every workgroup's count.)
+  uint32_t gen = 0;
+  auto ask_generation = [&]() {
+    if (MODE == kModeFused) gen = *(const __attribute__((address_space(4))) uint32_t *)(p.track + 2 * trk_bank_words(p.P));
+  };
+  if (WORDS) ask_generation();
   Tile tl;
   if (!decode_block(p, (int)blockIdx.x, tl)) return;
-  // The generation is needed only when the tile is counted: it is asked for behind the last wait for the argument, or the first
-  // copies would wait for its round trip to memory as well (9 x 16896 x 784 on 8 chunks 12.3 us, 12.7).  (Constant for as long as
-  // this kernel reads it: the launch's end, which changes it, waits for every workgroup's count.)
-  uint32_t gen = 0;
-  if (MODE == kModeFused) gen = *(const __attribute__((address_space(4))) uint32_t *)(p.track + 2 * trk_bank_words(p.P));
+  if (!WORDS) ask_generation();
 
   const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
   const int m0 = tl.mi * BM, col_lo = tl.c * p.W, col_hi = col_lo + p.W, n0 = col_lo + tl.nj * BN;
