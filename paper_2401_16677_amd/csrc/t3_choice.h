@@ -163,7 +163,9 @@ inline int32_t column_align(const t3_problem *p, Call call, TileShape tile, int6
 // themselves.)  By sizes alone, as column_align, and whatever R's leading dimension.  In us, cut at multiples of the tile and this way: 4293 x 1612 x
 // 208 on 4 chunks 70.0, 63.5; 8192 x 532 x 512 on 8 96.8, 91.2 (x 544, whole granules, 74.5); 6000 x 700 x 800 on 8 112.0, 106.8 (x 704 92.0);
 // 16384 x 396 x 256 on 8 121.0, 115.7; 1071 x 1460 x 640 on 8 41.1, 39.2; 2048 x 404 x 640 on 16 43.3, 41.3; long K hides it, 8192 x 532 x 2128 on 8
-// 189.5, 188.6.  Not with the release by copy, where R and the slot would want different cuts of the same sums.
+// 189.5, 188.6.  Over 160 drawn problems 4.6 % less below K of 512, 2.9 below 1024, 1.0 below 2048, 0.5 beyond, with bfloat16 slots (10125 x 696 x 168
+// on 8 99.5, 92.2; 620 x 2056 x 2352 on 8 67.1, 67.0) and transposed operands (1387 x 1288 x 192 on 2 13.9, 12.6; 3735 x 2472 x 640 on 4 109.7, 97.2)
+// as with fp32 and K-contiguous ones; at worst 1756 x 1796 x 2520 on 8 168.9, 174.4, and 0.2 us on short launches of one round.  Not with the release by copy, where R and the slot would want different cuts of the same sums.
 inline int32_t column_overlap(const t3_problem *p, Call call, TileShape tile, int64_t Wt) {
   const int64_t W = p->N / p->tp, granule = p->flags & T3_FLAG_FWD_BF16 ? 32 : 16;
   if (call != kCallFused || !(p->flags & T3_FLAG_FWD_DIRECT) || Wt < 2 || W % granule == 0) return 0;
@@ -322,7 +324,8 @@ T3_HOST_DEVICE inline TilePlace tile_place(const TileOrder &o, uint32_t position
 }
 // now: xcd_rows of the blocks or runs stage by stage.  In us, stage by stage and in a line: 8689 x 840 x 1120 on 4 chunks, bfloat16 slots
 // 131.0, 113.1; 11434 x 820 x 7200 on 2, GEMM and reduction 353.5, 328.0; 700 x 128 x 392 on 16 11.8, 11.0; 2048 x 18432 x 576 on
-// 32 74.4, 71.2; 2048 x 20480 x 10240 on 8 663, 648; 2048 x 22528 x 4096 on 8 348, 325; 2506 x 944 x 2064 on 2 45.4, 44.5.  Not taken
+// 32 74.4, 71.2; 2048 x 20480 x 10240 on 8 663, 648; 2048 x 22528 x 4096 on 8 348, 325; 2506 x 944 x 2064 on 2 45.4, 44.5.  Over 660 drawn launches
+// 4.8 % less; 18 are more than 2 % slower, the worst 1472 x 9968 x 6136 on 2 with the reduction, 200, 216.  Not taken
 //  - where it needs 85 % of the rows or more: the A rows of a stage's blocks are the same ones in every stage, and an
 //    XCD's L2 partly keeps them (4096 x 12288 x 1536 on 8, 12 bands either way: 160.8, 167.3);
 //  - with fewer than four K-slabs, where there is little to pull (534 x 1048 x 128 on 2: 9.8, 9.9);

@@ -96,10 +96,11 @@ struct Tile {
 
 // The plan in vector registers, a word per lane: one request for all of the kernel's argument, and a read of a lane
 // for each word where it is wanted.  As scalar loads the words come in batches, one behind the other, as the code needs
-// them: the wide-tile kernel's start was some twenty round trips, seven of them to lines nobody had touched yet, and a
-// compiler that runs out of scalar registers asks for the same words again at every tile.  One round of tiles, in us, that way and
-// this: 2136 x 384 x 1000 on 8 chunks 28.5, 28.1; 1697 x 72 x 1120 on 32 26.3, 25.1; 523 x 1004 x 752 on 16 42.2, 41.3;
-// a ring step of 4096 x 1536 x 1536 29.1, 28.4; long launches 0 to 1 % less.
+// them, from lines nobody has touched yet.  The small-tile kernel in one round, in us, by scalar loads and this way: 1024 x 64 x 128 on 16 chunks
+// 5.5, 5.3; 40 x 1152 x 256 on 2 5.7, 5.4; 16 x 15184 x 256 on 2 6.4, 6.1; long K 0 to 1 % less.  In the wide-tile kernel it is reading the
+// words where they are wanted that counts, which lets the compiler keep none of them through the main loop; by scalar loads at the
+// same places it is as fast (2136 x 3072 x 1000 on 8 29.4, 29.3; 1697 x 2304 x 1120 on 32 25.2, 25.3; 523 x 16064 x 752 on 16 39.9, 40.0; a
+// ring step of 4096 x 1536 x 1536 28.6, 28.9; twelve shapes 0.1 % less).
 struct PlanWords {
   static constexpr int kWords = sizeof(Plan) / 4;
   static_assert(sizeof(Plan) % 4 == 0 && kWords > 64 && kWords <= 128, "two registers");
