@@ -330,13 +330,14 @@ __device__ inline bool work_item(const Plan &p, int it, int &blk, int &part, int
 // `stagger_groups` phase groups; group g starts g * stagger_ticks (100 MHz ticks) late.  A
 // persistent workgroup keeps its offset through all its tiles (every tile takes the same time);
 // with one workgroup per grid position, later ones are dispatched as earlier ones retire.
-__device__ inline void stagger_start(const Plan &p) {
+// width_log2: that of the bands of tiles in a line (wide-tile kernel).
+__device__ inline void stagger_start(const Plan &p, uint32_t width_log2) {
   const int b = blockIdx.x;
   if (b >= p.stagger_blocks) return;
   // (In a line, workgroups of an XCD that share a row of tiles are in one group: 8689 x 840 x 1120 on 4 chunks 115.3 us with a
   // band's columns in groups, 113.1 with its rows.  In blocks, tiles down the columns, a row's are in one group where the groups divide the
   // block's rows, four groups on blocks of 4 x 3; eight groups on blocks of 4 x 6 have a row in two.)
-  const int grp = (((b >> 3) >> p.order.width_log2) + (b >> 8)) % p.stagger_groups;
+  const int grp = (((b >> 3) >> width_log2) + (b >> 8)) % p.stagger_groups;
   if (!grp) return;
   const uint64_t t0 = wall_clock64(), wait = (uint64_t)grp * (uint64_t)p.stagger_ticks;
   while (wall_clock64() - t0 < wait) __builtin_amdgcn_s_sleep(8);

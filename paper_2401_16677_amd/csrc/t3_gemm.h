@@ -139,7 +139,7 @@ void gemm_tile_kernel(const Plan p) {
   constexpr bool tracked = MODE == kModeFused;
   Trk trk;
   if (tracked) trk = trk_open(p);              // reads gen now; used when tiles are done
-  if (p.stagger_groups > 1) stagger_start(p);
+  if (p.stagger_groups > 1) stagger_start(p, 0u);
 
   const int tid = threadIdx.x;
   const int lane = tid & 63;

@@ -129,7 +129,7 @@ void wide_tile_kernel(const Plan) {
   // end, which changes it, waits for every workgroup's last count.
   uint32_t gen = 0u;
   if (tracked) gen = *(const __attribute__((address_space(4))) uint32_t *)(p.track + 2 * trk_bank_words(p.P));
-  if (p.stagger_groups > 1) stagger_start(p);
+  if (p.stagger_groups > 1) stagger_start(p, p.order.width_log2);
 
   const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
   const int wm = wave >> 1, wn = wave & 1;
